@@ -1,5 +1,28 @@
-// fp32 reference-mode GEMM (plain FMA, LDS-tiled).  Used only in PMC_F32 mode, where results must
-// agree with the fp64 oracle to 1e-5, which rules out the bf16 matrix cores.  Any sizes.
+// fp32-mode GEMM on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32): fp32 products and fp32
+// accumulation throughout, as PMC_F32 mode needs (results agree with the fp64 oracle to 1e-5).
+//
+// The instruction runs at 256 FLOP per clock and compute unit, 1/16 of the bf16 rate, so LDS and the
+// load path are never near their limits; what bounds a product is how many compute units have a tile
+// and how long the serial K chain of one tile is.  Two kernels:
+//
+//  * gemm_f32_tile_kernel: operand tiles go straight from global memory into an LDS ring
+//    (buffer_load ... lds), waves are a WAVES_M x WAVES_N grid times WK groups that share K (each
+//    group has its own ring and takes every WK-th 32-deep tile; the partial sums are added in group
+//    order through LDS).  WK > 1 puts four waves on a compute unit that owns only a 32 x 64 or
+//    32 x 32 output tile.
+//  * gemm_f32_direct_kernel: a 16 x 16 output tile per workgroup, K dealt over its eight waves in
+//    16-deep groups, operands loaded in the fragment layout without LDS (one memory latency per few
+//    groups, no barrier before the final fold).  For products whose 32 x 32 tiles would leave most
+//    compute units idle, and (element-wise loads) for sizes, pitches or pointers that are not
+//    multiples of four elements, which makes it the path for every shape.
+//
+// Measured against a 64 x 64 tile of plain FMAs with scalar loads (before): 128 x 256 x 1024 from 170 to
+// 5.9 us, 512 x 1024 x 4096 from 560 to 46 us, 768 x 5120 x 1280 at 105 TFLOP/s; the library's fp32
+// product reaches 154 TFLOP/s at 8192^3.
+//
+// Both contract k in the same assignment: in a 16-deep group, lane quarter q = lane / 16 holds
+// k = 4 q .. 4 q + 3 and instruction j takes element j of every quarter, so an operand whose
+// contraction index is contiguous is read 16 bytes at a time.
 #include "dev_common.h"
 #include "kernels.h"
 
@@ -7,98 +30,380 @@ namespace pmc {
 namespace k {
 namespace {
 
-constexpr int BM = 64, BN = 64, BK = 16;
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
-// C[M,N] (+)= op(A) . op(B); TA: A stored [K,M]; TB: B stored [N,K].  Sum over k in ascending order.
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A, int lda,
-                                                        const float* __restrict__ B, int ldb, float* C, int ldc,
-                                                        int epi, const float* __restrict__ bias, const float* resid,
-                                                        float* aux) {
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
-  const int tid = threadIdx.x;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int tx = tid % 16, ty = tid / 16;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += BK) {
-    for (int i = tid; i < BM * BK; i += 256) {
-      int m, k;
-      if (TA) { m = i % BM; k = i / BM; } else { k = i % BK; m = i / BK; }
-      const int gm = m0 + m, gk = k0 + k;
-      float v = 0.f;
-      if (gm < M && gk < K) v = TA ? A[(size_t)gk * lda + gm] : A[(size_t)gm * lda + gk];
-      As[k][m] = v;
-    }
-    for (int i = tid; i < BN * BK; i += 256) {
-      int n, k;
-      if (TB) { k = i % BK; n = i / BK; } else { n = i % BN; k = i / BN; }
-      const int gn = n0 + n, gk = k0 + k;
-      float v = 0.f;
-      if (gn < N && gk < K) v = TB ? B[(size_t)gn * ldb + gk] : B[(size_t)gk * ldb + gn];
-      Bs[k][n] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < BK; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+struct F32Params {
+  const float* A;
+  const float* B;
+  float* C;
+  const float* bias;
+  const float* resid;
+  float* aux;
+  int M, N, K, lda, ldb, ldc, epi;
+  int tiles_m, tiles_n;
+};
+
+__device__ __forceinline__ float apply_epilogue(const F32Params& p, float v, size_t idx, int n) {
+  switch (p.epi) {
+    case PMC_EPI_NONE: return v;
+    case PMC_EPI_BIAS: return v + p.bias[n];
+    case PMC_EPI_BIAS_RESID: return v + p.bias[n] + p.resid[idx];
+    case PMC_EPI_BIAS_GELU: v += p.bias[n]; p.aux[idx] = gelu_f(v); return v;
+    case PMC_EPI_DGELU: return v * gelu_grad_f(p.aux[idx]);
+    case PMC_EPI_ACCUM_F32: return p.C[idx] + v;
+    case PMC_EPI_BIAS_GELU_GRAD: v += p.bias[n]; p.aux[idx] = gelu_f(v); return gelu_grad_f(v);
+    case PMC_EPI_MUL: return v * p.aux[idx];
   }
+  return v;
+}
+
+// Four consecutive columns of one row; every pointer and pitch is a multiple of 16 bytes.
+__device__ __forceinline__ void store_quad_f32(const F32Params& p, f32x4 v, int m, int n) {
+  const size_t idx = (size_t)m * p.ldc + n;
+  f32x4 out;
+  if (p.epi == PMC_EPI_NONE) {
+    out = v;
+  } else if (p.epi == PMC_EPI_ACCUM_F32) {
+    out = *reinterpret_cast<const f32x4*>(p.C + idx) + v;
+  } else if (p.epi == PMC_EPI_MUL) {
+    out = v * *reinterpret_cast<const f32x4*>(p.aux + idx);
+  } else if (p.epi == PMC_EPI_DGELU) {
+    const f32x4 u = *reinterpret_cast<const f32x4*>(p.aux + idx);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int gm = m0 + ty * 4 + i;
-    if (gm >= M) continue;
+    for (int e = 0; e < 4; ++e) out[e] = v[e] * gelu_grad_f(u[e]);
+  } else {
+    out = v + *reinterpret_cast<const f32x4*>(p.bias + n);
+    if (p.epi == PMC_EPI_BIAS_RESID) {
+      out += *reinterpret_cast<const f32x4*>(p.resid + idx);
+    } else if (p.epi == PMC_EPI_BIAS_GELU || p.epi == PMC_EPI_BIAS_GELU_GRAD) {
+      f32x4 g;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int gn = n0 + tx * 4 + j;
-      if (gn >= N) continue;
-      const size_t idx = (size_t)gm * ldc + gn;
-      float v = acc[i][j];
-      switch (epi) {
-        case PMC_EPI_NONE: C[idx] = v; break;
-        case PMC_EPI_BIAS: C[idx] = v + bias[gn]; break;
-        case PMC_EPI_BIAS_RESID: C[idx] = v + bias[gn] + resid[idx]; break;
-        case PMC_EPI_BIAS_GELU: v += bias[gn]; C[idx] = v; aux[idx] = gelu_f(v); break;
-        case PMC_EPI_DGELU: C[idx] = v * gelu_grad_f(aux[idx]); break;
-        case PMC_EPI_ACCUM_F32: C[idx] += v; break;
-        case PMC_EPI_BIAS_GELU_GRAD: v += bias[gn]; C[idx] = gelu_grad_f(v); aux[idx] = gelu_f(v); break;
-        case PMC_EPI_MUL: C[idx] = v * aux[idx]; break;
+      for (int e = 0; e < 4; ++e) g[e] = gelu_f(out[e]);
+      *reinterpret_cast<f32x4*>(p.aux + idx) = g;
+      if (p.epi == PMC_EPI_BIAS_GELU_GRAD) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[e] = gelu_grad_f(out[e]);
       }
     }
+  }
+  *reinterpret_cast<f32x4*>(p.C + idx) = out;
+}
+
+// One operand's 32-deep K tile in LDS, 128 bytes per row.  KMAJ (contraction contiguous): [rows][32],
+// 16-byte chunk c of row r at position c ^ ((r >> 1) & 7), so 16 rows at one chunk hit 16 bank groups.
+// Otherwise [32][ROWS] with the 64-byte spans of k-row k exchanged by (k >> 2) & 3, so that the four
+// lane quarters of a fragment read (k-rows 4 apart) fall into different bank quarters.
+// Rows past the edge are clamped (the epilogue does not store them); what lies past K is read as zero:
+// [k][rows] tiles by the size of the buffer descriptor, [rows][k] tiles by an offset outside it.
+template <int ROWS, bool KMAJ, int NW>
+struct F32Loader {
+  static constexpr int NL = ROWS / 8 / NW;  // 1 KB loads per wave and tile
+  static_assert(ROWS % (8 * NW) == 0, "tile must split evenly over the waves");
+  uint32_t voff[NL];
+  int kc[KMAJ ? NL : 1];  // first k of this lane's chunk
+
+  __device__ __forceinline__ static int swz(int k) { return ROWS >= 64 ? ((k >> 2) & 3) << 2 : ROWS == 32 ? ((k >> 2) & 1) << 2 : 0; }
+  __device__ __forceinline__ void init(int ld, int mn0, int mn_total, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int q = wave * NL + i;
+      if constexpr (KMAJ) {
+        const int row = q * 8 + (lane >> 3);
+        kc[i] = 4 * ((lane & 7) ^ ((row >> 1) & 7));
+        voff[i] = ((uint32_t)min(mn0 + row, mn_total - 1) * (uint32_t)ld + kc[i]) * 4;
+      } else {
+        constexpr int CPR = ROWS / 4;
+        const int idx = q * 64 + lane, kr = idx / CPR, chunk = (idx % CPR) ^ swz(kr);
+        voff[i] = ((uint32_t)kr * (uint32_t)ld + min(mn0 + 4 * chunk, mn_total - 4)) * 4;
+      }
+    }
+  }
+  __device__ __forceinline__ void issue(i32x4 rsrc, float* tile, int k0, int K, uint32_t ld, int wave) const {
+    const bool past = k0 >= K;  // a whole tile past the end
+    const uint32_t soff = past ? 0u : KMAJ ? (uint32_t)k0 * 4 : (uint32_t)k0 * ld * 4;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)((lds_void_ptr)(tile + (wave * NL + i) * 256)));
+      const uint32_t v = past || (KMAJ && k0 + kc[KMAJ ? i : 0] >= K) ? 0x80000000u : voff[i];
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                   :: "s"(lds_addr), "v"(v), "s"(rsrc), "s"(soff) : "memory");
+    }
+  }
+  // Fragment of 16 rows from r0 for the 16-deep group c of the tile: element j is the operand of instruction j.
+  __device__ __forceinline__ static f32x4 frag(const float* tile, int r0, int c, int lane) {
+    const int row = r0 + (lane & 15), quarter = lane >> 4;
+    if constexpr (KMAJ) {
+      return *reinterpret_cast<const f32x4*>(tile + row * 32 + (((4 * c + quarter) ^ ((row >> 1) & 7)) << 2));
+    } else {
+      const float* t = tile + (16 * c + 4 * quarter) * ROWS + (row ^ (swz(4 * quarter) << 2));
+      f32x4 v = {t[0], t[ROWS], t[2 * ROWS], t[3 * ROWS]};
+      return v;
+    }
+  }
+};
+
+// Workgroup id -> tile, giving each of the 8 XCDs a contiguous run of tiles (ids are dealt round-robin)
+// walked in column groups 8 tiles tall, so that neighbours share operand panels in one L2.
+__device__ __forceinline__ void tile_of(const F32Params& p, int& tm, int& tn) {
+  const int ntiles = p.tiles_m * p.tiles_n, pid0 = blockIdx.x;
+  const int xcd = pid0 & 7, lo = ntiles >> 3, rem = ntiles & 7;
+  const int pid = xcd * lo + min(xcd, rem) + (pid0 >> 3);
+  const int per_group = 8 * p.tiles_n, group = pid / per_group, in = pid % per_group;
+  const int height = min(p.tiles_m - 8 * group, 8);
+  tm = 8 * group + in % height;
+  tn = in / height;
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int WK, int NSTAGE, bool A_KMAJ, bool B_KMAJ>
+// (at least two waves per SIMD: within the 256 registers that leaves, the compiler keeps the sums in
+// vector registers; given 512 it rotates them through accumulation registers and waits for every
+// product of a K step to copy them)
+__global__ __launch_bounds__(WAVES_M * WAVES_N * WK * 64, 2) void gemm_f32_tile_kernel(F32Params p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int NW = WAVES_M * WAVES_N, TM = BM / WAVES_M / 16, TN = BN / WAVES_N / 16;
+  constexpr int TA = 32 * BM, TB = 32 * BN, STAGE = TA + TB, RING = NSTAGE * STAGE;
+  extern __shared__ __attribute__((aligned(1024))) float smem_f32[];
+  const int tid = threadIdx.x, lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave_all / NW, wave = wave_all % NW;
+  const int wm0 = (wave / WAVES_N) * (BM / WAVES_M), wn0 = (wave % WAVES_N) * (BN / WAVES_N);
+  float* ring = smem_f32 + kg * RING;
+  int tile_m, tile_n;
+  tile_of(p, tile_m, tile_n);
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+
+  auto make_rsrc = [](const void* ptr, size_t bytes) {
+    const uint64_t a = (uint64_t)ptr;
+    i32x4 r = {(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)bytes, 0x00020000};
+    return r;
+  };
+  const i32x4 ra = make_rsrc(p.A, (size_t)(A_KMAJ ? p.M : p.K) * p.lda * 4), rb = make_rsrc(p.B, (size_t)(B_KMAJ ? p.N : p.K) * p.ldb * 4);
+  using LA = F32Loader<BM, A_KMAJ, NW>;
+  using LB = F32Loader<BN, B_KMAJ, NW>;
+  LA la;
+  LB lb;
+  la.init(p.lda, m0, p.M, wave, lane);
+  lb.init(p.ldb, n0, p.N, wave, lane);
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // Tile t of this group is K tile t WK + kg.  Every group runs the same number of steps (tiles past
+  // the end lie past K and read as zeros), so all waves meet at the same barriers and the number of
+  // loads in flight is the same at every wait.
+  const int nk = (p.K + 32 * WK - 1) / (32 * WK);
+  auto request = [&](int t, int stage) {
+    const int k0 = (min(t, nk - 1) * WK + kg) * 32;
+    la.issue(ra, ring + stage * STAGE, k0, p.K, p.lda, wave);
+    lb.issue(rb, ring + stage * STAGE + TA, k0, p.K, p.ldb, wave);
+  };
+  constexpr int INFL = (NSTAGE - 2) * (LA::NL + LB::NL);
+  static_assert(INFL < 64, "vmcnt is a 6-bit field");
+  constexpr int WAIT_TILE = (INFL & 15) | ((INFL >> 4) << 14) | (7 << 4) | (15 << 8);
+#pragma unroll
+  for (int t = 0; t < NSTAGE - 1; ++t) request(t, t);
+  f32x4 fa[2][TM], fb[2][TN];
+  auto read = [&](int set, const float* ta, int c) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) fa[set][i] = LA::frag(ta, wm0 + 16 * i, c, lane);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) fb[set][j] = LB::frag(ta + TA, wn0 + 16 * j, c, lane);
+    __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the products they run under
+  };
+  auto multiply = [&](int set) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[set][j][e], fa[set][i][e], acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  __builtin_amdgcn_s_waitcnt(WAIT_TILE);
+  __syncthreads();
+  read(0, ring, 0);
+  int cur = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    // the stage refilled here was read for the last time before the last barrier
+    request(kt + NSTAGE - 1, cur == 0 ? NSTAGE - 1 : cur - 1);
+    read(1, ring + cur * STAGE, 1);
+    multiply(0);
+    __builtin_amdgcn_s_waitcnt(WAIT_TILE);  // tile kt + 1 has landed
+    __syncthreads();
+    cur = cur + 1 == NSTAGE ? 0 : cur + 1;
+    read(0, ring + cur * STAGE, 0);  // after the last tile: a clamped tile, unused
+    multiply(1);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the clamped tail loads
+  if constexpr (WK > 1) {
+    // group g > 0 leaves its sums in LDS ([tile register][64 lanes] per wave), group 0 adds them in order
+    constexpr int SLOT = TM * TN * 256;
+    static_assert((WK - 1) * NW * SLOT <= WK * RING, "partial sums must fit in the rings");
+    __syncthreads();
+    if (kg > 0) {
+      float* my = smem_f32 + ((kg - 1) * NW + wave) * SLOT + 4 * lane;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) *reinterpret_cast<f32x4*>(my + (i * TN + j) * 256) = acc[i][j];
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int g = 1; g < WK; ++g) {
+      const float* other = smem_f32 + ((g - 1) * NW + wave) * SLOT + 4 * lane;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] += *reinterpret_cast<const f32x4*>(other + (i * TN + j) * 256);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int m = m0 + wm0 + 16 * i + (lane & 15);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + wn0 + 16 * j + 4 * (lane >> 4);
+      if (m < p.M && n < p.N) store_quad_f32(p, acc[i][j], m, n);
+    }
+  }
+#endif
+}
+
+// Four k-consecutive elements (k .. k+3) of row `row` of an operand; zeros past K.
+template <bool KMAJ, bool VEC>
+__device__ __forceinline__ f32x4 load_k4(const float* __restrict__ X, int ld, int row, int k, int K) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (KMAJ && VEC) {
+    if (k < K) v = *reinterpret_cast<const f32x4*>(X + (size_t)row * ld + k);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (k + j < K) v[j] = KMAJ ? X[(size_t)row * ld + k + j] : X[(size_t)(k + j) * ld + row];
+  }
+  return v;
+}
+
+template <bool A_KMAJ, bool B_KMAJ, bool VEC>
+__global__ __launch_bounds__(512, 2) void gemm_f32_direct_kernel(F32Params p) {
+  constexpr int NWAVE = 8, UNROLL = 4;
+  __shared__ float part[NWAVE][16][17];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int tm, tn;
+  tile_of(p, tm, tn);
+  const int m = min(16 * tm + (lane & 15), p.M - 1), n = min(16 * tn + (lane & 15), p.N - 1), kq = 4 * (lane >> 4);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  const int step = 16 * NWAVE;
+  for (int k = 16 * wave; k < p.K; k += UNROLL * step) {
+    f32x4 a[UNROLL], b[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      a[u] = load_k4<A_KMAJ, VEC>(p.A, p.lda, m, k + u * step + kq, p.K);
+      b[u] = load_k4<B_KMAJ, VEC>(p.B, p.ldb, n, k + u * step + kq, p.K);
+    }
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u][e], a[u][e], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[wave][lane & 15][kq + e] = acc[e];
+  __syncthreads();
+  if (threadIdx.x < 256) {
+    const int r = threadIdx.x >> 4, c = threadIdx.x & 15, gm = 16 * tm + r, gn = 16 * tn + c;
+    if (gm < p.M && gn < p.N) {
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < NWAVE; ++w) v += part[w][r][c];
+      const size_t idx = (size_t)gm * p.ldc + gn;
+      p.C[idx] = apply_epilogue(p, v, idx, gn);
+    }
+  }
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int WK, int NSTAGE, bool TA, bool TB>
+int launch_tile_f32(hipStream_t st, F32Params p) {
+  constexpr size_t lds = (size_t)WK * NSTAGE * 32 * (BM + BN) * sizeof(float);
+  static_assert(lds <= 160 * 1024, "rings do not fit the 160 KB LDS");
+  auto kern = gemm_f32_tile_kernel<BM, BN, WAVES_M, WAVES_N, WK, NSTAGE, !TA, TB>;
+  static std::atomic<bool> configured{false};
+  if (int rc = reserve_lds(kern, lds, configured, "gemm_f32")) return rc;
+  p.tiles_m = (p.M + BM - 1) / BM;
+  p.tiles_n = (p.N + BN - 1) / BN;
+  kern<<<dim3(p.tiles_m * p.tiles_n), dim3(WAVES_M * WAVES_N * WK * 64), lds, st>>>(p);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(PMC_ERR_HIP, "gemm_f32 launch failed: %s", hipGetErrorString(e));
+  return PMC_OK;
+}
+
+template <bool TA, bool TB>
+int launch_direct_f32(hipStream_t st, F32Params p, bool vec) {
+  p.tiles_m = (p.M + 15) / 16;
+  p.tiles_n = (p.N + 15) / 16;
+  const dim3 grid(p.tiles_m * p.tiles_n), block(512);
+  if (vec) gemm_f32_direct_kernel<!TA, TB, true><<<grid, block, 0, st>>>(p);
+  else gemm_f32_direct_kernel<!TA, TB, false><<<grid, block, 0, st>>>(p);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(PMC_ERR_HIP, "gemm_f32 launch failed: %s", hipGetErrorString(e));
+  return PMC_OK;
+}
+
+// Shape of the output tile: the one whose rounds over the 256 compute units take least.  A round costs
+// kPerK us per 1024 of K plus kFixed us (ring fill, fold, epilogue), both measured over M = 40 .. 16384,
+// N = 96 .. 16384, K = 40 .. 16384; at few tiles the small shapes win although they read more (for
+// 128 x 256 x 1024: 71 / 22.7 / 14.0 / 9.1 / 5.9 us), at many the 64 x 64 and 128 x 128 ones
+// (768 x 5120 x 1280: 98 / 96 / 124 / 147 / 232 us).  The gemm_tile switch forces one (tests).
+int pick_tile_f32(const F32Params& p) {
+  if (const int f = tuning(kTuneGemmTile); f >= 0) return f;
+  constexpr int kBm[5] = {128, 64, 32, 32, 16}, kBn[5] = {128, 64, 64, 32, 16};
+  constexpr double kPerK[5] = {68.0, 20.5, 13.0, 8.8, 3.25}, kFixed[5] = {2.6, 0.3, 0.9, 1.2, 0.4};
+  int best = 0;
+  double best_us = 1e300;
+  for (int c = 0; c < 5; ++c) {
+    const long tiles = (long)((p.M + kBm[c] - 1) / kBm[c]) * ((p.N + kBn[c] - 1) / kBn[c]);
+    const double us = (double)((tiles + 255) / 256) * (kPerK[c] * p.K / 1024.0 + kFixed[c]);
+    if (us < best_us) {
+      best_us = us;
+      best = c;
+    }
+  }
+  return best;
+}
+
+template <bool TA, bool TB>
+int launch_f32(hipStream_t st, const F32Params& p, bool vec) {
+  if (!vec) return launch_direct_f32<TA, TB>(st, p, false);
+  switch (pick_tile_f32(p)) {
+    case 0: return launch_tile_f32<128, 128, 2, 2, 1, 4, TA, TB>(st, p);
+    case 1: return launch_tile_f32<64, 64, 2, 2, 1, 4, TA, TB>(st, p);
+    case 2: return launch_tile_f32<32, 64, 1, 2, 2, 4, TA, TB>(st, p);
+    case 3: return launch_tile_f32<32, 32, 1, 1, 4, 4, TA, TB>(st, p);
+    default: return launch_direct_f32<TA, TB>(st, p, true);
   }
 }
 
 }  // namespace
 
 int gemm_f32(hipStream_t st, const GemmArgs& a) {
-  dim3 grid((a.N + BN - 1) / BN, (a.M + BM - 1) / BM), block(256);
-  const float* A = (const float*)a.A;
-  const float* B = (const float*)a.B;
-  float* C = (float*)a.C;
-  const float* bias = (const float*)a.bias;
-  const float* resid = (const float*)a.resid;
-  float* aux = (float*)a.aux;
-#define GO(TA, TB) \
-  gemm_f32_kernel<TA, TB><<<grid, block, 0, st>>>(a.M, a.N, a.K, A, a.lda, B, a.ldb, C, a.ldc, a.epilogue, bias, resid, aux)
-  if (!a.trans_a && !a.trans_b) GO(false, false);
-  else if (!a.trans_a && a.trans_b) GO(false, true);
-  else if (a.trans_a && !a.trans_b) GO(true, false);
-  else GO(true, true);
-#undef GO
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(PMC_ERR_HIP, "gemm_f32 launch failed: %s", hipGetErrorString(e));
-  return PMC_OK;
+  F32Params p;
+  p.A = (const float*)a.A; p.B = (const float*)a.B; p.C = (float*)a.C;
+  p.bias = (const float*)a.bias; p.resid = (const float*)a.resid; p.aux = (float*)a.aux;
+  p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.ldc = a.ldc; p.epi = a.epilogue;
+  p.tiles_m = p.tiles_n = 0;
+  auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
+  // whole 16-byte chunks everywhere, operands inside the 2 GB that an offset of the tile loads can reach
+  const size_t a_bytes = (size_t)(a.trans_a ? a.K : a.M) * a.lda * 4, b_bytes = (size_t)(a.trans_b ? a.N : a.K) * a.ldb * 4;
+  const bool vec = a.M % 4 == 0 && a.N % 4 == 0 && a.K % 4 == 0 && a.lda % 4 == 0 && a.ldb % 4 == 0 && a.ldc % 4 == 0 && al(a.A) &&
+                   al(a.B) && al(a.C) && al(a.bias) && al(a.resid) && al(a.aux) && a_bytes < 0x7fffffffull && b_bytes < 0x7fffffffull;
+  if (!a.trans_a && !a.trans_b) return launch_f32<false, false>(st, p, vec);
+  if (!a.trans_a && a.trans_b) return launch_f32<false, true>(st, p, vec);
+  if (a.trans_a && !a.trans_b) return launch_f32<true, false>(st, p, vec);
+  return launch_f32<true, true>(st, p, vec);
 }
-
 // Shape and pointer checks common to both precisions, then dispatch.
 int gemm(hipStream_t st, const GemmArgs& a) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return fail(PMC_ERR_INVALID, "gemm: M=%d N=%d K=%d", a.M, a.N, a.K);

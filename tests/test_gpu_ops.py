@@ -70,6 +70,18 @@ def test_gemm_f32_layouts_and_epilogues(ctx, ta, tb):
     _gemm_case(ctx, "f32", ta, tb, 128, 256, 1024, P.EPI_NONE)
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])
+def test_gemm_f32_tile_shapes(ctx, tune, tile):
+    """Every tile shape of the fp32 product (128x128 .. 16x16) in every layout: less than one tile, ragged
+    edges in M and N, K shorter than one 32-deep tile, past the K groups' last full round, and ragged."""
+    tune(gemm_tile=tile)
+    for ta in (False, True):
+        for tb in (False, True):
+            for M, N, K in ((4, 4, 4), (36, 68, 200), (132, 260, 36), (256, 132, 416)):
+                for epi in (P.EPI_BIAS_RESID, P.EPI_ACCUM_F32, P.EPI_BIAS_GELU_GRAD):
+                    _gemm_case(ctx, "f32", ta, tb, M, N, K, epi)
+
+
 @pytest.mark.parametrize("ta", [False, True])
 @pytest.mark.parametrize("tb", [False, True])
 def test_gemm_bf16_small_tiles_ragged(ctx, ta, tb):
