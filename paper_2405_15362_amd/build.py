@@ -19,7 +19,7 @@ BUILD = os.path.join(ROOT, "_build")
 
 SOURCES = [
     "error.cpp", "tuning.cpp", "schedule.cpp", "api.cpp", "replay.cpp", "attention.cpp",
-    "norm_act.hip", "gemm_f32.hip", "gemm_bf16.hip", "attn_simple.hip", "attn_mfma.hip",
+    "norm_act.hip", "gemm_f32.hip", "gemm_bf16.hip", "attn_f32.hip", "attn_mfma.hip",
 ]
 # hipcc would by itself turn fp32 pairs into packed-fp32 instructions; they are kept off.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

@@ -4,9 +4,9 @@
 namespace pmc {
 namespace k {
 
-int attention_forward_simple(hipStream_t st, int dtype, int batch, int seq, int heads, int dh, int causal,
+int attention_forward_f32(hipStream_t st, int dtype, int batch, int seq, int heads, int dh, int causal,
                              const void* qkv, void* o, float* lse);
-int attention_backward_simple(hipStream_t st, int dtype, int batch, int seq, int heads, int dh, int causal,
+int attention_backward_f32(hipStream_t st, int dtype, int batch, int seq, int heads, int dh, int causal,
                               const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv,
                               void* dq_stage, float* delta);
 
@@ -17,7 +17,7 @@ int attention_backward_mfma(hipStream_t st, int batch, int seq, int heads, int d
 
 namespace {
 // bf16 storage with a head size that is a multiple of 8 (up to 128) runs on the matrix cores;
-// everything else (fp32 mode, other head sizes) on the plain-arithmetic kernels.
+// everything else (fp32 mode, other head sizes) on the kernels of the fp32 matrix instruction.
 bool use_mfma(int dtype, int head_dim) { return dtype == PMC_BF16 && head_dim >= 8 && head_dim <= 128 && head_dim % 8 == 0; }
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 size_t elem(int dtype) { return dtype == PMC_F32 ? 4 : 2; }
@@ -28,7 +28,7 @@ int attention_forward(hipStream_t st, int dtype, int batch, int seq, int heads, 
   if (!qkv || !o || !lse) return fail(PMC_ERR_INVALID, "attention_forward: NULL pointer");
   if (dtype != PMC_F32 && dtype != PMC_BF16) return fail(PMC_ERR_INVALID, "attention_forward: bad dtype %d", dtype);
   if (use_mfma(dtype, head_dim)) return attention_forward_mfma(st, batch, seq, heads, head_dim, causal, qkv, o, lse);
-  return attention_forward_simple(st, dtype, batch, seq, heads, head_dim, causal, qkv, o, lse);
+  return attention_forward_f32(st, dtype, batch, seq, heads, head_dim, causal, qkv, o, lse);
 }
 
 size_t attention_backward_scratch_bytes(int dtype, int batch, int seq, int heads, int head_dim) {
@@ -51,7 +51,7 @@ int attention_backward(hipStream_t st, int dtype, int batch, int seq, int heads,
   // read only by the workgroup that later overwrites it).
   const int rc = use_mfma(dtype, head_dim)
                      ? attention_backward_mfma(st, batch, seq, heads, head_dim, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta)
-                     : attention_backward_simple(st, dtype, batch, seq, heads, head_dim, causal, qkv, o, lse, d_o, dqkv,
+                     : attention_backward_f32(st, dtype, batch, seq, heads, head_dim, causal, qkv, o, lse, d_o, dqkv,
                                                  dq_stage, delta);
   if (rc) return rc;
   return copy_rows(st, dtype, (int)tokens, h, dq_stage, h, dqkv, 3 * h);

@@ -16,9 +16,9 @@
 //    compute units idle, and (element-wise loads) for sizes, pitches or pointers that are not
 //    multiples of four elements, which makes it the path for every shape.
 //
-// Measured against a 64 x 64 tile of plain FMAs with scalar loads (before): 128 x 256 x 1024 from 170 to
-// 5.9 us, 512 x 1024 x 4096 from 560 to 46 us, 768 x 5120 x 1280 at 105 TFLOP/s; the library's fp32
-// product reaches 154 TFLOP/s at 8192^3.
+// Measured against a 64 x 64 tile of plain FMAs with scalar loads (before), mean over the products of a
+// pass, F / B / W: hidden 256, 128 tokens 65 / 74 / 23 -> 5.2 / 5.2 / 5.1 us; hidden 1024, 512 tokens
+// 308 / 322 / 107 -> 41 / 37 / 40 us (about 90 TFLOP/s; the library's fp32 product reaches 154 at 8192^3).
 //
 // Both contract k in the same assignment: in a 16-deep group, lane quarter q = lane / 16 holds
 // k = 4 q .. 4 q + 3 and instruction j takes element j of every quarter, so an operand whose

@@ -391,6 +391,34 @@ def test_attention_forward_backward(ctx, dtype, dh, causal):
     assert torch.equal(inplace, dq)
 
 
+@pytest.mark.parametrize("dtype,heads,dh", [("f32", 4, 3), ("f32", 2, 66), ("f32", 2, 64), ("bf16", 4, 6), ("bf16", 2, 20),
+                                            ("bf16", 8, 101)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_attention_fp32_matrix_path(ctx, dtype, heads, dh, causal):
+    """The kernels of the fp32 matrix instruction: head sizes with and without whole aligned groups of four
+    columns, on both sides of the 64-column tile; one row, one row past a 16-row block, and more 16-row
+    groups than the eight waves of a workgroup."""
+    for seq in (1, 17, 145):
+        batch, h = (8 if dtype == "bf16" else 4), heads * dh
+        key = ("attn-f32path", dtype, heads, dh, causal, seq)
+        print("attention case", key, flush=True)
+        qkv = mat(key + ("qkv",), (batch * seq, 3 * h), dtype)
+        d_o = mat(key + ("do",), (batch * seq, h), dtype)
+        q64 = qkv.astype(np.float64)
+        o_ref, probs, lse_ref = OL.attention(q64, heads, causal, batch)
+        dqkv_ref = OL.attention_input_grad(d_o.astype(np.float64), q64, probs, heads, batch)
+        qd = dev(qkv, dtype)
+        o = dev(np.zeros((batch * seq, h)), dtype)
+        lse = torch.zeros(batch * heads * seq, device="cuda")
+        P.pmc_attention_forward(ctx, qd, o, lse, batch, seq, heads, dh, causal)
+        P.pmc_attention_backward(ctx, qd, o, lse, dev(d_o, dtype), qd, batch, seq, heads, dh, causal)
+        torch.cuda.synchronize()
+        assert_close(host(o), o_ref, dtype, str(key))
+        assert np.abs(host(lse) - lse_ref.reshape(-1)).max() <= (2e-2 if dtype == "bf16" else 2e-5)
+        for name, cols in (("dq", slice(0, h)), ("dk", slice(h, 2 * h)), ("dv", slice(2 * h, 3 * h))):
+            assert_close(host(qd)[:, cols], dqkv_ref[:, cols], dtype, name, scale=np.sqrt(np.mean(dqkv_ref ** 2)))
+
+
 def test_attention_random_shapes(ctx):
     """Seeded random batch, sequence length, head count and head size (every multiple of 8 up to 128),
     causal or not, in the library's own choice of launch shape: ragged last blocks, sequences shorter
