@@ -729,9 +729,10 @@ int stage_backward_weight(pmc_chunk* ch, const int32_t* mbs, int32_t count) {
     for (int32_t j = 0; j < i; ++j)
       if (mbs[j] == mbs[i]) return fail(PMC_ERR_INVALID, "stage_backward_weight: microbatch %d listed twice", mbs[i]);
   }
-  // bf16 chunks whose token count fills whole 64-wide K tiles: groups of queued microbatches go
-  // through one product per weight; everything else one microbatch at a time
-  const bool group = ch->cfg.dtype == PMC_BF16 && ch->tokens % 64 == 0;
+  // bf16 chunks: groups of queued microbatches go through one product per weight; fp32 ones (and
+  // tensors that one buffer descriptor does not span) one microbatch at a time
+  const bool group = ch->cfg.dtype == PMC_BF16 &&
+                     (size_t)ch->tokens * std::max(3 * (size_t)ch->cfg.hidden, (size_t)ch->cfg.ffn) * 2 < 0x7fffffffull;
   for (int32_t i = 0; i < count;) {
     const int32_t n = group ? (count - i < PMC_MAX_QUEUED_W ? count - i : PMC_MAX_QUEUED_W) : 1;
     if (n > 1) PMC_TRY(chunk_backward_weight_group(ch, mbs + i, n));
@@ -793,6 +794,7 @@ int pmc_gemm_grouped_wgrad(pmc_ctx* ctx, int32_t M, int32_t N, int32_t K, int32_
                            const void* const* b, int32_t ldb, float* C, int32_t ldc) {
   if (!ctx || !a || !b || !C) return fail(PMC_ERR_INVALID, "pmc_gemm_grouped_wgrad: NULL argument");
   if (count < 1 || count > PMC_MAX_QUEUED_W) return fail(PMC_ERR_INVALID, "pmc_gemm_grouped_wgrad: count %d (1..%d)", count, PMC_MAX_QUEUED_W);
+  if (K % 64) return fail(PMC_ERR_INVALID, "pmc_gemm_grouped_wgrad: K=%d must be a multiple of 64", K);
   k::GroupedWgradArgs g;
   g.M = M; g.N = N; g.K = K; g.count = count; g.lda = lda; g.ldb = ldb; g.C = C; g.ldc = ldc;
   for (int i = 0; i < count; ++i) {

@@ -5,9 +5,10 @@
 //   W: dW += X^T . dY  (fp32 accumulate)           A stored [K,M], B stored [K,N]
 // Two kernels share the fragment layouts and the epilogue:
 //
-//  * gemm_bf16_dma_kernel, the fast path (K a multiple of 64).  Operand tiles go straight from
+//  * gemm_bf16_dma_kernel, the fast path.  Operand tiles go straight from
 //    global memory into LDS (buffer_load ... lds, no registers in between) into a ring of 2 or 3
-//    stages; rows past the edge are clamped, never branched on.  LDS tiles are unpadded and
+//    stages; rows past the edge are clamped, never branched on; what lies past K in the last K tile
+//    arrives as zeros, because its addresses are outside the buffer descriptor.  LDS tiles are unpadded and
 //    XOR-swizzled in 16-byte chunks so that both the DMA writes and the fragment reads are free of
 //    bank conflicts.  The K loop is software pipelined by hand: while the MFMAs of one 16-wide K
 //    step run, the fragments of the next step are read from LDS into a second register set, in a
@@ -16,7 +17,7 @@
 //    exposed at tile boundaries.  The DMA loads are issued as inline assembly and waited for with
 //    explicit vmcnt values, because the compiler would otherwise drain every outstanding load
 //    before each LDS read.
-//  * gemm_bf16_kernel, the general path (any K multiple of 8, all layout/epilogue combinations):
+//  * gemm_bf16_kernel, the general path (operands of 2 GB and more, all layout/epilogue combinations):
 //    global -> registers -> padded LDS tiles, double buffered.
 //
 // An operand whose contraction index is contiguous in memory is read from LDS with 16-byte loads;
@@ -48,14 +49,21 @@ struct GemmParams {
   int M, N, K, lda, ldb, ldc;
   int tiles_m, tiles_n;
   int group_m;            // height, in tiles, of the column groups the tiles are walked in (see tile_of_pid)
-  int k_tiles_per_split;  // fast path: 64-wide K tiles each blockIdx.y handles (all of K when not split)
+  int splits, k_tiles_per_split;  // fast path: 64-wide K tiles each blockIdx.y handles (all of K when not split)
   // Segmented contraction (weight gradients of several queued microbatches in one product): the K
-  // axis is the concatenation of nseg pieces of seg_tiles 64-wide tiles each, piece i living at
-  // (Aseg[i], Bseg[i]) with the pitches lda, ldb.  nseg = 0: one piece at (A, B).
+  // axis is the concatenation of nseg pieces of seg_k rows each (every piece fills whole K tiles of its
+  // own, the last one with zeros), piece i living at (Aseg[i], Bseg[i]) with the pitches lda, ldb.
+  // nseg = 0: one piece at (A, B).
   const bf16_t* Aseg[kMaxSegments];
   const bf16_t* Bseg[kMaxSegments];
-  int nseg, seg_tiles;
+  int nseg, seg_k;
 };
+
+// K tiles of depth BK of the whole (possibly segmented) contraction.
+template <bool SEG, int BK>
+__host__ __device__ inline int k_tiles(const GemmParams& p) {
+  return SEG ? p.nseg * ((p.seg_k + BK - 1) / BK) : (p.K + BK - 1) / BK;
+}
 
 constexpr int kEpiPartial = 100;  // fast path, split K: store the fp32 partial product of split blockIdx.y
 
@@ -469,6 +477,15 @@ struct DmaLoader {
       }
     }
   }
+  // Last K tile of a contraction-contiguous operand, of which only `valid` (a multiple of 8) columns
+  // exist: the chunks past them get an offset outside the descriptor, which reads as zero.
+  __device__ __forceinline__ void cut(int valid, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int row = (wave * NL + i) * 8 + (lane >> 3);
+      if ((((lane & 7) ^ ((row >> 1) & 7)) << 3) >= valid) voff[i] = 0x80000000u;
+    }
+  }
   __device__ __forceinline__ void issue(i32x4 rsrc, bf16_t* tile, uint32_t soff, int wave) const {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
@@ -503,7 +520,9 @@ __device__ __forceinline__ bf16x8 read_frag_swz(const bf16_t* tile, int r0, int 
 // staged epilogue.  All waves of the workgroup call it together; on return the LDS ring holds
 // epilogue slabs that other waves may still be reading (barrier before the ring is filled again).
 // BK = 32 (both operands [k][rows] only): kt0 and nk count 32-wide K tiles, two 16-wide steps per tile.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64>
+// CUT: the last K tile of a contraction-contiguous operand is partial.  (A kernel of its own: the test for
+// that tile in the K loop cost the steps whose K is whole 0.3 to 1 %.)
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64, bool CUT = false>
 __device__ __forceinline__ void dma_tile(const GemmParams& p, bf16_t* smem, int tile_m, int tile_n, int kt0, int nk) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int NW = WAVES_M * WAVES_N, WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
@@ -512,12 +531,17 @@ __device__ __forceinline__ void dma_tile(const GemmParams& p, bf16_t* smem, int 
   const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
-  auto make_rsrc = [](const void* ptr) {  // raw buffer descriptor: base, no stride, 2 GB window
+  // Raw buffer descriptor: base, no stride, size.  A [k][rows] operand's size ends with its last k-row,
+  // so the k-rows of the last K tile that do not exist read as zeros; a [rows][k] operand has a 2 GB
+  // window and its last K tile is cut (see request).
+  auto make_rsrc = [](const void* ptr, uint32_t bytes) {
     const uint64_t a = (uint64_t)ptr;
-    i32x4 r = {(int)(uint32_t)a, (int)(uint32_t)(a >> 32), 0x7fffffff, 0x00020000};
+    i32x4 r = {(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)bytes, 0x00020000};
     return r;
   };
-  i32x4 ra = make_rsrc(p.A), rb = make_rsrc(p.B);
+  const uint32_t k_rows = SEG ? p.seg_k : p.K;
+  const uint32_t size_a = A_KMAJ ? 0x7fffffffu : k_rows * (uint32_t)p.lda * 2, size_b = B_KMAJ ? 0x7fffffffu : k_rows * (uint32_t)p.ldb * 2;
+  i32x4 ra = make_rsrc(p.A, size_a), rb = make_rsrc(p.B, size_b);
   DmaLoader<BM, A_KMAJ, NW, BK> la;
   DmaLoader<BN, B_KMAJ, NW, BK> lb;
   la.init(p.lda, m0, p.M, wave, lane);
@@ -562,23 +586,29 @@ __device__ __forceinline__ void dma_tile(const GemmParams& p, bf16_t* smem, int 
   // is tile `local` of piece `seg`; the two are stepped along with the requests (which come in
   // ascending t), so no division sits in the loop.
   int seg = 0, local = 0;
-  const int seg_tiles = SEG ? p.seg_tiles * (64 / BK) : 0;  // K tiles of this depth per piece
+  const int seg_tiles = SEG ? (p.seg_k + BK - 1) / BK : 0;  // K tiles of this depth per piece
   if (SEG) {
     seg = kt0 / seg_tiles;
     local = kt0 - seg * seg_tiles;
-    ra = make_rsrc(p.Aseg[seg]);
-    rb = make_rsrc(p.Bseg[seg]);
+    ra = make_rsrc(p.Aseg[seg], size_a);
+    rb = make_rsrc(p.Bseg[seg], size_b);
   }
   auto request = [&](int t, int stage) {
     const int kt = SEG ? local : tile_k(t);
+    if constexpr (CUT) {
+      if (kt == p.K >> 6) {  // requests come in ascending order, and past the end this tile is requested again
+        if constexpr (A_KMAJ) la.cut(p.K & 63, wave, lane);
+        if constexpr (B_KMAJ) lb.cut(p.K & 63, wave, lane);
+      }
+    }
     la.issue(ra, smem + stage * STAGE, kt * stepa, wave);
     lb.issue(rb, smem + stage * STAGE + TA, kt * stepb, wave);
     if (SEG && t + 1 < nk) {  // past the end the last tile is requested again
       if (++local == seg_tiles) {
         local = 0;
         ++seg;
-        ra = make_rsrc(p.Aseg[seg]);
-        rb = make_rsrc(p.Bseg[seg]);
+        ra = make_rsrc(p.Aseg[seg], size_a);
+        rb = make_rsrc(p.Bseg[seg], size_b);
       }
     }
   };
@@ -621,14 +651,16 @@ __device__ __forceinline__ void dma_tile(const GemmParams& p, bf16_t* smem, int 
 #endif
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64,
+          bool CUT = false>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void gemm_bf16_dma_kernel(GemmParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   int tile_m, tile_n;
   tile_of_block(p, tile_m, tile_n);
-  const int nk = p.k_tiles_per_split * (64 / BK);
-  dma_tile<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK>(p, smem, tile_m, tile_n, (int)blockIdx.y * nk, nk);
+  const int per = p.k_tiles_per_split * (64 / BK), kt0 = (int)blockIdx.y * per;
+  dma_tile<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT>(p, smem, tile_m, tile_n, kt0,
+                                                                           min(per, k_tiles<SEG, BK>(p) - kt0));
 #endif
 }
 
@@ -645,7 +677,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void gemm_bf16_wgrad_persis
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   const int ntiles = p.tiles_m * p.tiles_n, G = gridDim.x, b = blockIdx.x;
-  const int nk = p.k_tiles_per_split * (64 / BK);  // all of K, in tiles of this depth
+  const int nk = k_tiles<SEG, BK>(p);
   const int group = (b >> 3) % GROUPS;  // neighbours on one XCD fall into different groups
   const int head = (nk * group) / GROUPS;  // K tiles of the first tile left for the end
   bool first = true;
@@ -681,7 +713,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_wgrad_pair_kernel(GemmParams
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   int tile_m, tile_n;
   tile_of_block(p, tile_m, tile_n);
-  dma_tile<256, 128, 2, 2, false, false, 3, PMC_EPI_ACCUM_F32, SEG, 32>(p, smem, tile_m, tile_n, 0, 2 * p.k_tiles_per_split);
+  dma_tile<256, 128, 2, 2, false, false, 3, PMC_EPI_ACCUM_F32, SEG, 32>(p, smem, tile_m, tile_n, 0, k_tiles<SEG, 32>(p));
 #endif
 }
 
@@ -790,12 +822,15 @@ int launch_tile(hipStream_t st, const GemmParams& p, int epi) {
   return launch_epi<128, 128, 64, 64, 64, A_KMAJ, B_KMAJ>(st, p, epi);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64,
+          bool CUT = false>
 int launch_dma(hipStream_t st, GemmParams p) {
+  if constexpr ((A_KMAJ || B_KMAJ) && !CUT)
+    if (p.K & 63) return launch_dma<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, true>(st, p);
   constexpr int NT = WAVES_M * WAVES_N * 64;
   constexpr size_t lds = (size_t)NSTAGE * (BM + BN) * BK * sizeof(bf16_t);
   static_assert(lds <= 160 * 1024, "stages do not fit the 160 KB LDS");
-  auto kern = gemm_bf16_dma_kernel<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK>;
+  auto kern = gemm_bf16_dma_kernel<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT>;
   static std::atomic<bool> configured{false};  // per instantiation
   if (int rc = reserve_lds(kern, lds, configured, "gemm_bf16")) return rc;
   p.tiles_m = (p.M + BM - 1) / BM;
@@ -804,8 +839,7 @@ int launch_dma(hipStream_t st, GemmParams p) {
     const int forced = tuning(kTuneGemmGroup);
     p.group_m = forced > 0 ? forced : (BM >= 256 ? 4 : 8);
   }
-  const int splits = (p.K / 64) / p.k_tiles_per_split;
-  kern<<<dim3(p.tiles_m * p.tiles_n, splits), dim3(NT), lds, st>>>(p);
+  kern<<<dim3(p.tiles_m * p.tiles_n, p.splits), dim3(NT), lds, st>>>(p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(PMC_ERR_HIP, "gemm_bf16 launch failed: %s", hipGetErrorString(e));
   return PMC_OK;
@@ -945,7 +979,7 @@ int pick_splits(int M, int N, int K, size_t ws_bytes) {
   // up to K = 6144 the 64x128 tiles (no partials, no second kernel) are faster once there are
   // enough of them (measured at M = 1024, N = 2048: 15 / 38 us against 27 / 41 us at K = 2048 / 6144)
   if (K < 8192 && (long)((M + 63) / 64) * ((N + 127) / 128) >= 192) return 1;
-  const int nkt = K / 64;
+  const int nkt = (K + 63) / 64;
   int best = 1;
   for (int s : {2, 4, 8}) {
     if (nkt % s || nkt / s < 4) continue;                          // whole tiles, at least 256 of K per split
@@ -959,7 +993,8 @@ int pick_splits(int M, int N, int K, size_t ws_bytes) {
 template <bool A_KMAJ, bool B_KMAJ>
 int launch_partial(hipStream_t st, GemmParams p, void* ws, int splits) {
   p.C = ws;
-  p.k_tiles_per_split = (p.K / 64) / splits;
+  p.splits = splits;
+  p.k_tiles_per_split = k_tiles<false, 64>(p) / splits;
   return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 2, kEpiPartial>(st, p);
 }
 
@@ -1029,14 +1064,15 @@ int gemm_bf16(hipStream_t st, const GemmArgs& a) {
   p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.ldc = a.ldc;
   p.tiles_m = p.tiles_n = 0;
   p.group_m = 8;
-  p.k_tiles_per_split = 0;
-  p.nseg = p.seg_tiles = 0;
+  p.splits = 1;
+  p.k_tiles_per_split = k_tiles<false, 64>(p);
+  p.nseg = p.seg_k = 0;
   for (int i = 0; i < kMaxSegments; ++i) p.Aseg[i] = p.Bseg[i] = nullptr;
   const bool a_kmaj = !a.trans_a, b_kmaj = a.trans_b;
-  // Fast path: K in whole 64-wide tiles, operands inside the 2 GB window of a buffer descriptor.
-  const size_t a_bytes = (size_t)(a.trans_a ? a.K : a.M) * a.lda * 2, b_bytes = (size_t)(a.trans_b ? a.N : a.K) * a.ldb * 2;
-  if (a.K % 64 == 0 && a_bytes < 0x7fffffffull && b_bytes < 0x7fffffffull) {
-    p.k_tiles_per_split = a.K / 64;
+  // Fast path: operands inside the 2 GB window of a buffer descriptor.  A K that is no multiple of 64 only
+  // costs it a partly empty last tile.  (Two layers of hidden 2048: 1208 us a step at 1024 tokens; at 1000
+  // tokens 1379 us with the weight gradients on the general kernel, 1237 us here.)
+  if (a_bytes < 0x7fffffffull && b_bytes < 0x7fffffffull) {
     const int splits = (a.ws && !(a_kmaj == false && b_kmaj == true)) ? pick_splits(a.M, a.N, a.K, a.ws_bytes) : 1;
     if (splits > 1) {
       int rc = a_kmaj ? (b_kmaj ? launch_partial<true, true>(st, p, a.ws, splits) : launch_partial<true, false>(st, p, a.ws, splits))
@@ -1059,7 +1095,7 @@ int gemm_bf16(hipStream_t st, const GemmArgs& a) {
 // whose contraction runs through the pieces one after the other, one read-modify-write of C.
 int gemm_bf16_grouped_wgrad(hipStream_t st, const GroupedWgradArgs& a) {
   if (a.count < 1 || a.count > kMaxSegments) return fail(PMC_ERR_INVALID, "grouped weight gradient: %d pieces (1..%d)", a.count, kMaxSegments);
-  if (a.M % 8 || a.N % 8 || a.K % 64) return fail(PMC_ERR_INVALID, "grouped weight gradient: M=%d N=%d must be multiples of 8, K=%d of 64", a.M, a.N, a.K);
+  if (a.M % 8 || a.N % 8 || a.K % 8) return fail(PMC_ERR_INVALID, "grouped weight gradient: M=%d N=%d K=%d must be multiples of 8", a.M, a.N, a.K);
   if (a.lda % 8 || a.ldb % 8 || a.ldc % 4 || a.lda < a.M || a.ldb < a.N || a.ldc < a.N)
     return fail(PMC_ERR_INVALID, "grouped weight gradient: bad pitches (lda=%d ldb=%d ldc=%d)", a.lda, a.ldb, a.ldc);
   if ((size_t)a.K * a.lda * 2 >= 0x7fffffffull || (size_t)a.K * a.ldb * 2 >= 0x7fffffffull)
@@ -1071,9 +1107,10 @@ int gemm_bf16_grouped_wgrad(hipStream_t st, const GroupedWgradArgs& a) {
   p.M = a.M; p.N = a.N; p.K = a.K * a.count; p.lda = a.lda; p.ldb = a.ldb; p.ldc = a.ldc;
   p.tiles_m = p.tiles_n = 0;
   p.group_m = 8;
-  p.k_tiles_per_split = p.K / 64;
   p.nseg = a.count;
-  p.seg_tiles = a.K / 64;
+  p.seg_k = a.K;
+  p.splits = 1;
+  p.k_tiles_per_split = k_tiles<true, 64>(p);
   for (int i = 0; i < kMaxSegments; ++i) {
     const int j = i < a.count ? i : a.count - 1;
     if (!a.A[j] || !a.B[j] || !aligned(a.A[j], 16) || !aligned(a.B[j], 16))

@@ -6,7 +6,7 @@ import torch
 import paper_2405_15362_amd as P
 import synth
 from oracle import layer as OL
-from gpu_util import assert_close, dev, host, mat, rel_l2, tol
+from gpu_util import assert_close, dev, host, mat, rel_l2, tol, tuned
 
 pytestmark = pytest.mark.gpu
 
@@ -280,6 +280,39 @@ def test_gemm_bf16_random_shapes(ctx, ta, tb, epis):
         M, N = (int(8 * rng.integers(1, 190)) for _ in range(2))
         K = int(64 * rng.integers(1, 40)) if i % 3 else int(8 * rng.integers(1, 90))
         _gemm_case(ctx, "bf16", ta, tb, M, N, K, epis[int(rng.integers(0, len(epis)))])
+
+
+@pytest.mark.parametrize("ta,tb,epi", [(False, False, P.EPI_NONE), (False, True, P.EPI_NONE), (True, False, P.EPI_ACCUM_F32)])
+@pytest.mark.parametrize("K", [8, 40, 56, 104, 968, 1000])
+def test_gemm_bf16_partial_last_k_tile(ctx, tune, ta, tb, epi, K):
+    """A K that is no multiple of the K tile's depth (64, or 32 in the ring kernels of the weight gradient): every tile
+    shape and weight-gradient kernel, on operands that are views of buffers holding NaN everywhere past K, so a value
+    read from there cannot go unnoticed."""
+    M, N = 328, 200
+    key = ("k tail", ta, tb, K)
+
+    def view(name, rows, k_fast, scale):
+        m = mat(key + (name,), (rows, K) if k_fast else (K, rows), "bf16", scale)
+        big = torch.full((rows, K + 64) if k_fast else (K + 64, rows), float("nan"), dtype=torch.bfloat16, device="cuda")
+        v = big[:, :K] if k_fast else big[:K]
+        v.copy_(dev(m, "bf16"))
+        return v, (m if k_fast else m.T).astype(np.float64)
+
+    a, A = view("a", M, not ta, 1.0)
+    b, B = view("b", N, tb, 0.05)
+    c0 = mat(key + ("c0",), (M, N), "f32")
+    accum = epi == P.EPI_ACCUM_F32
+    ref = A @ B.T + (c0 if accum else 0.0)
+    for switches in [{"gemm_tile": t} for t in range(5)] + ([{"gemm_wgrad": w} for w in range(3)] if accum else [{}]):
+        print("k tail", key, switches, flush=True)
+        tune(**switches)
+        c = dev(c0, "f32" if accum else "bf16")
+        rc = P.lib.pmc_gemm(ctx, P.PMC_BF16, int(ta), int(tb), M, N, K, a.data_ptr(), a.stride(0), b.data_ptr(), b.stride(0),
+                            c.data_ptr(), N, epi, None, None, None)
+        torch.cuda.synchronize()
+        tuned.reset()
+        assert rc == 0
+        assert_close(host(c), ref, "bf16", f"{key} {switches}")
 
 
 def test_gemm_grouped_weight_gradient_rejects_bad_arguments(ctx):

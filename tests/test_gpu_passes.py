@@ -128,8 +128,8 @@ def test_deferred_w_accumulates_over_microbatches(name):
 
 
 def test_queued_w_groups_larger_than_the_maximum():
-    """More queued microbatches than one grouped product takes (8): the list is cut into groups; ragged
-    token count (not a multiple of 64) falls back to one microbatch at a time.  Both against the oracle."""
+    """More queued microbatches than one grouped product takes (8): the list is cut into groups; with a
+    ragged token count (not a multiple of 64) every piece ends in a partial K tile.  Both against the oracle."""
     for name, n_mb in (("dh128_bf16", 10), ("dh64_ragged_bf16", 3)):
         cfg = CASES[name]
         params, xs, dys, (ys, dxs, grads) = _run_fbw(cfg, name + "_q", n_mb, defer=True)
