@@ -587,7 +587,7 @@ __device__ __forceinline__ void dma_tile(const GemmParams& p, bf16_t* smem, int 
   // ascending t), so no division sits in the loop.
   int seg = 0, local = 0;
   const int seg_tiles = SEG ? (p.seg_k + BK - 1) / BK : 0;  // K tiles of this depth per piece
-  if (SEG) {
+  if constexpr (SEG) {
     seg = kt0 / seg_tiles;
     local = kt0 - seg * seg_tiles;
     ra = make_rsrc(p.Aseg[seg], size_a);
@@ -1072,6 +1072,7 @@ int gemm_bf16(hipStream_t st, const GemmArgs& a) {
   // Fast path: operands inside the 2 GB window of a buffer descriptor.  A K that is no multiple of 64 only
   // costs it a partly empty last tile.  (Two layers of hidden 2048: 1208 us a step at 1024 tokens; at 1000
   // tokens 1379 us with the weight gradients on the general kernel, 1237 us here.)
+  const size_t a_bytes = (size_t)(a.trans_a ? a.K : a.M) * a.lda * 2, b_bytes = (size_t)(a.trans_b ? a.N : a.K) * a.ldb * 2;
   if (a_bytes < 0x7fffffffull && b_bytes < 0x7fffffffull) {
     const int splits = (a.ws && !(a_kmaj == false && b_kmaj == true)) ? pick_splits(a.M, a.N, a.K, a.ws_bytes) : 1;
     if (splits > 1) {
