@@ -378,6 +378,47 @@ __device__ __forceinline__ void epilogue_staged(const GemmParams& p, f32x16 (&ac
   }
 }
 
+// Epilogue of the K-split kernels: every wave holds a partial sum of the whole BM x BN tile.  Each leaves its
+// sums in an LDS slab of its own; after the barrier the workgroup's threads add the slabs in wave order, eight
+// columns per thread, and store whole row segments.
+template <int BM, int BN, int NW, int EPI>
+__device__ __forceinline__ void epilogue_ksplit(const GemmParams& p, f32x16 (&acc)[BM / 32][BN / 32], float* slabs, int m0, int n0,
+                                                int wave, int lane) {
+  constexpr int PITCH = BN + 4, SLAB = BM * PITCH, LPR = BN / 8, RPP = 64 * NW / LPR, NPASS = (BM + RPP - 1) / RPP;
+  const int tid = wave * 64 + lane, orow = tid / LPR, ocol = 8 * (tid % LPR), n = n0 + ocol;
+  OctOperand<EPI> ahead[NPASS];
+#pragma unroll
+  for (int pass = 0; pass < NPASS; ++pass) {
+    const int row = pass * RPP + orow;
+    if (OctOperand<EPI>::used && row < BM && m0 + row < p.M && n < p.N) ahead[pass].load(p, m0 + row, n);
+  }
+  float* my = slabs + wave * SLAB + (lane & 31) * PITCH + 4 * (lane >> 5);
+#pragma unroll
+  for (int i = 0; i < BM / 32; ++i)
+#pragma unroll
+    for (int j = 0; j < BN / 32; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        f32x4 t = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+        *reinterpret_cast<f32x4*>(my + 32 * i * PITCH + 32 * j + 8 * q) = t;
+      }
+  __syncthreads();
+#pragma unroll
+  for (int pass = 0; pass < NPASS; ++pass) {
+    const int row = pass * RPP + orow;
+    if (row >= BM || m0 + row >= p.M || n >= p.N) continue;
+    const float* from = slabs + row * PITCH + ocol;
+    f32x4 lo = *reinterpret_cast<const f32x4*>(from), hi = *reinterpret_cast<const f32x4*>(from + 4);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      lo += *reinterpret_cast<const f32x4*>(from + w * SLAB);
+      hi += *reinterpret_cast<const f32x4*>(from + w * SLAB + 4);
+    }
+    float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    store_oct<EPI>(p, v, m0 + row, n, ahead[pass]);
+  }
+}
+
 // Second half of a split-K product: adds the fp32 partials of the splits in ascending order (a
 // fixed order, so the result does not depend on scheduling) and applies the epilogue.
 template <int EPI>
@@ -441,7 +482,7 @@ typedef __attribute__((address_space(3))) void* lds_void_ptr;
 // chunks per k-row is not a multiple of 16).
 template <int ROWS>
 __device__ __forceinline__ constexpr int kswz(int kr) {
-  return ROWS % 128 == 0 ? ((kr & 3) << 2) : (((kr >> 1) & 1) << 2);
+  return ROWS % 128 == 0 ? ((kr & 3) << 2) : ROWS == 32 ? 0 : (((kr >> 1) & 1) << 2);
 }
 
 // BK: K rows of the tile; 64 everywhere except the [32 k][ROWS] tiles of the two-workgroup weight-gradient kernel
@@ -451,7 +492,7 @@ struct DmaLoader {
   static constexpr int NL = ROWS * BK * 2 / 1024 / NW;  // 1 KB loads per wave per tile
   static_assert(ROWS * BK * 2 / 1024 % NW == 0, "tile must split evenly over the waves");
   static_assert(BK == 64 || (!KMAJ && BK == 32), "K depth of a tile");
-  static_assert(KMAJ || ROWS % 128 == 0 || ROWS == 320, "the [64 k][rows] swizzle is defined for whole 128-row groups and for 320 rows");
+  static_assert(KMAJ || ROWS % 128 == 0 || ROWS == 320 || ROWS == 64 || ROWS == 32, "the [64 k][rows] swizzle is not defined for this width");
   uint32_t voff[NL];  // byte offset of this lane's chunk at K offset 0
 
   // Wave w issues loads w*NL .. w*NL+NL-1; load q fills tile bytes [1024 q, 1024 q + 1024).
@@ -520,15 +561,23 @@ __device__ __forceinline__ bf16x8 read_frag_swz(const bf16_t* tile, int r0, int 
 // staged epilogue.  All waves of the workgroup call it together; on return the LDS ring holds
 // epilogue slabs that other waves may still be reading (barrier before the ring is filled again).
 // BK = 32 (both operands [k][rows] only): kt0 and nk count 32-wide K tiles, two 16-wide steps per tile.
+// KSPLIT: for tiles of 64 x 64 and less, which are bound by the serial chain of a K tile (LDS latency, then
+// matrix instructions, four times per tile) rather than by any rate.  Every wave owns the whole output tile and
+// one of the four 16-wide steps of each K tile, so a K tile is one such link instead of four and each LDS byte
+// is read once; the four partial tiles are added at the end.  Kernel times, 128x128 / 64x128 tiles (before)
+// against these: 192 x 256 x 1024 (F) 13.7 / 8.3 -> 5.7 us, 496 x 832 x 3328 (F) 39 / 18.6 -> 10.3,
+// 1024 x 1024 x 4096 (W) 46.7 -> 17.1, 256 x 256 x 2048 (W) 25.6 -> 7.0.
 // CUT: the last K tile of a contraction-contiguous operand is partial.  (A kernel of its own: the test for
 // that tile in the K loop cost the steps whose K is whole 0.3 to 1 %.)
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64, bool CUT = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64, bool CUT = false,
+          bool KSPLIT = false>
 __device__ __forceinline__ void dma_tile(const GemmParams& p, bf16_t* smem, int tile_m, int tile_n, int kt0, int nk) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  constexpr int NW = WAVES_M * WAVES_N, WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
+  constexpr int NW = WAVES_M * WAVES_N, WM = KSPLIT ? BM : BM / WAVES_M, WN = KSPLIT ? BN : BN / WAVES_N, TM = WM / 32, TN = WN / 32;
   constexpr int TA = BM * BK, TB = BN * BK, STAGE = TA + TB;
+  static_assert(!KSPLIT || BK == 16 * NW, "K split over the waves: one 16-wide step of a K tile each");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
+  const int wm0 = KSPLIT ? 0 : (wave / WAVES_N) * WM, wn0 = KSPLIT ? 0 : (wave % WAVES_N) * WN;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
   // Raw buffer descriptor: base, no stride, size.  A [k][rows] operand's size ends with its last k-row,
@@ -617,10 +666,28 @@ __device__ __forceinline__ void dma_tile(const GemmParams& p, bf16_t* smem, int 
   __builtin_amdgcn_s_waitcnt(WAIT_TILE);
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < TM; ++i) fa[0][i] = read_frag_swz<BM, A_KMAJ>(smem, wm0 + 32 * i, 0, lane);
+  for (int i = 0; i < TM; ++i) fa[0][i] = read_frag_swz<BM, A_KMAJ>(smem, wm0 + 32 * i, KSPLIT ? 16 * wave : 0, lane);
 #pragma unroll
-  for (int j = 0; j < TN; ++j) fb[0][j] = read_frag_swz<BN, B_KMAJ>(smem + TA, wn0 + 32 * j, 0, lane);
+  for (int j = 0; j < TN; ++j) fb[0][j] = read_frag_swz<BN, B_KMAJ>(smem + TA, wn0 + 32 * j, KSPLIT ? 16 * wave : 0, lane);
   int cur = 0;
+  if constexpr (KSPLIT) {
+    auto k_tile = [&](int c, int kt) {
+      request(kt + NSTAGE - 1, cur == 0 ? NSTAGE - 1 : cur - 1);  // all its readers passed the last barrier
+      __builtin_amdgcn_s_waitcnt(WAIT_TILE);
+      __syncthreads();
+      cur = cur + 1 == NSTAGE ? 0 : cur + 1;
+      step(c, smem + cur * STAGE, smem + cur * STAGE + TA, 16 * wave);  // after the last tile: reads a clamped tile, unused
+    };
+    for (int kt = 0; kt < nk; kt += 2) {
+      k_tile(0, kt);
+      if (kt + 1 < nk) k_tile(1, kt + 1);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+    epilogue_ksplit<BM, BN, NW, EPI>(p, acc, reinterpret_cast<float*>(smem), m0, n0, wave, lane);
+    static_assert(!KSPLIT || NW * BM * (BN + 4) * 4 <= NSTAGE * STAGE * 2, "partial tiles must fit in the stage ring");
+    return;
+  }
   for (int kt = 0; kt < nk; ++kt) {
     const bf16_t* cur_a = smem + cur * STAGE;
     const bf16_t* cur_b = cur_a + TA;
@@ -652,15 +719,15 @@ __device__ __forceinline__ void dma_tile(const GemmParams& p, bf16_t* smem, int 
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64,
-          bool CUT = false>
+          bool CUT = false, bool KSPLIT = false>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void gemm_bf16_dma_kernel(GemmParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   int tile_m, tile_n;
   tile_of_block(p, tile_m, tile_n);
   const int per = p.k_tiles_per_split * (64 / BK), kt0 = (int)blockIdx.y * per;
-  dma_tile<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT>(p, smem, tile_m, tile_n, kt0,
-                                                                           min(per, k_tiles<SEG, BK>(p) - kt0));
+  dma_tile<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT, KSPLIT>(p, smem, tile_m, tile_n, kt0,
+                                                                                   min(per, k_tiles<SEG, BK>(p) - kt0));
 #endif
 }
 
@@ -823,14 +890,14 @@ int launch_tile(hipStream_t st, const GemmParams& p, int epi) {
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64,
-          bool CUT = false>
+          bool CUT = false, bool KSPLIT = false>
 int launch_dma(hipStream_t st, GemmParams p) {
   if constexpr ((A_KMAJ || B_KMAJ) && !CUT)
-    if (p.K & 63) return launch_dma<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, true>(st, p);
+    if (p.K & 63) return launch_dma<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, true, KSPLIT>(st, p);
   constexpr int NT = WAVES_M * WAVES_N * 64;
   constexpr size_t lds = (size_t)NSTAGE * (BM + BN) * BK * sizeof(bf16_t);
   static_assert(lds <= 160 * 1024, "stages do not fit the 160 KB LDS");
-  auto kern = gemm_bf16_dma_kernel<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT>;
+  auto kern = gemm_bf16_dma_kernel<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT, KSPLIT>;
   static std::atomic<bool> configured{false};  // per instantiation
   if (int rc = reserve_lds(kern, lds, configured, "gemm_bf16")) return rc;
   p.tiles_m = (p.M + BM - 1) / BM;
@@ -845,28 +912,57 @@ int launch_dma(hipStream_t st, GemmParams p) {
   return PMC_OK;
 }
 
-// Tile shape for the fast path.  Tiles are dealt over the 256 compute units, so the time is
-// (tiles per unit, rounded up) x (work of a tile) / (throughput of that shape on a busy unit); the
-// largest tile wins once there are enough tiles, smaller ones when units would otherwise idle.
-//   0: 256x256, 8 waves, 2 stages    1: 256x128, 8 waves, 3 stages    2: 128x128, 4 waves, 2 stages
-//   3: 64x128, 4 waves, 3 stages (skinny outputs: twice the tiles of shape 2)
-//   4: 256x320, 8 waves, 2 stages (N a multiple of 320 whose 256-wide tiles would leave a ragged last
-//      round, e.g. 4096 x 5120 = exactly 256 tiles)
+// Layout of a product, by what its operands' contraction index is in memory; index into the times below.
+enum Layout { kLayoutF = 0, kLayoutB = 1, kLayoutW = 2 };
+constexpr Layout layout_of(bool a_kmaj, bool b_kmaj) { return !a_kmaj ? kLayoutW : b_kmaj ? kLayoutB : kLayoutF; }
+
+// Tile shapes of the fast path.
+//   0: 256x256, 8 waves, 2 stages    1: 256x128, 8 waves, 3 stages
+//   2: 128x128, 4 waves: 4 stages as long as a compute unit gets one tile at most, otherwise 2 stages, so that
+//      two workgroups fit a unit.  With one workgroup per unit nothing else covers the latency of a tile's
+//      loads: 4096 x 1024 x 4096, F / B / W layout, 2 stages 52.1 / 47.2 / 52.8 us, 4 stages 39.8 / 36.4 / 43.0
+//   3: 64x128, 4 waves, 3 stages (skinny outputs; only where A is contraction-contiguous)
+//   4: 256x320, 8 waves, 2 stages (not with the fp32 read-modify-write epilogue: registers)
+//   5: 64x64, 5 stages   6: 32x64, 6 stages   7: 32x32, 8 stages; 4 waves that split K (see dma_tile)
+//   8: 64x128, 6 stages, K split likewise, in the B layout: at long K the reads from LDS, 6 KB per 16 of K instead of
+//      shape 3's 12, are what counts (1024 x 2048 x 8192 41.1 us against 44.0, x 2048 14.1 against 13.6; in the F
+//      layout 43.2 against 43.8 alone and 68 against 69 inside a step, not worth a kernel)
 // The gemm_tile tuning switch (0..4) forces a shape (for tests and tuning).
-int pick_tile(int M, int N, bool wide_ok) {
+constexpr int kShapes = 9;
+constexpr int kBm[kShapes] = {256, 256, 128, 64, 256, 64, 32, 32, 64}, kBn[kShapes] = {256, 128, 128, 128, 320, 64, 64, 32, 128};
+
+long tiles_of(int shape, int M, int N) {
+  return (long)((M + kBm[shape] - 1) / kBm[shape]) * ((N + kBn[shape] - 1) / kBn[shape]);
+}
+
+// Time of a product in us: fixed + rounds of tiles over the 256 compute units x (per_k for every 1024 of K +
+// per_round).  Fitted to every shape's time at the products of layers of hidden 64 .. 7168 with 16 .. 4096
+// tokens (308 products, kernel durations with operands that rotate through several buffers; the fit is within
+// 6 to 20 % of a time, and the shape it picks is on average 0.5 % slower than the best one).
+double shape_us(Layout layout, int shape, long tiles, double K) {
+  struct T { double fixed, per_k, per_round; };
+  static constexpr T kTimes[3][kShapes] = {
+      {{0., 19.5, 6.1}, {0., 11.4, 4.9}, {0., 8.1, 4.8}, {2.5, 4.9, 1.1}, {0., 23.1, 8.2}, {2.75, 3.1, 0.93}, {2.5, 2.2, 0.78}, {2.5, 1.8, 0.64}, {1e9, 0., 0.}},
+      {{0., 18.3, 4.7}, {0., 10.6, 3.7}, {0., 7.5, 3.7}, {2.5, 5.0, 0.5}, {0., 21.5, 5.9}, {2.2, 2.8, 1.05}, {2.3, 2.0, 0.74}, {2.3, 1.3, 0.68}, {0.3, 4.7, 4.0}},
+      {{0., 21.0, 8.6}, {0., 13.0, 6.6}, {0., 8.3, 5.9}, {0., 8.3, 5.9}, {0., 23.1, 8.2}, {1.8, 2.7, 2.2}, {2.1, 2.3, 1.2}, {2.2, 2.1, 0.96}, {1e9, 0., 0.}}};
+  static constexpr T kShallow[3] = {{4.5, 9.4, 0.}, {3.3, 9.2, 0.}, {0., 9.6, 5.3}};  // shape 2, two workgroups per unit
+  const T& t = shape == 2 && tiles > 256 ? kShallow[layout] : kTimes[layout][shape];
+  return t.fixed + (double)((tiles + 255) / 256) * (t.per_k * K / 1024. + t.per_round);
+}
+
+int pick_tile(Layout layout, int M, int N, long K, bool wide_ok, double* us = nullptr) {
   if (const int f = tuning(kTuneGemmTile); f >= 0) return (f == 4 && !wide_ok) ? 0 : f;
-  const int bm[5] = {256, 256, 128, 64, 256}, bn[5] = {256, 128, 128, 128, 320};
-  const double rate[5] = {1.0, 0.95, 0.75, 0.6, 1.02};  // on a tie in rounds x area the 320-wide tile wins (fewer rounds)
   int best = 0;
-  double best_t = 1e300;
-  for (int c = 0; c < (wide_ok ? 5 : 4); ++c) {
-    const long n = (long)((M + bm[c] - 1) / bm[c]) * ((N + bn[c] - 1) / bn[c]);
-    const double t = (double)((n + 255) / 256) * bm[c] * bn[c] / rate[c];
-    if (t < best_t) {
-      best_t = t;
+  double best_us = 1e300;
+  for (int c = 0; c < kShapes; ++c) {
+    if ((c == 3 && layout == kLayoutW) || (c == 4 && !wide_ok)) continue;
+    const double t = shape_us(layout, c, tiles_of(c, M, N), (double)K);
+    if (t < best_us) {
+      best_us = t;
       best = c;
     }
   }
+  if (us) *us = best_us;
   return best;
 }
 
@@ -875,7 +971,7 @@ int launch_dma_tile(hipStream_t st, const GemmParams& p) {
   // the 320-wide tile holds 10 accumulator tiles per wave; with the fp32 read-modify-write epilogue on
   // top it would spill registers, so weight-gradient products do not use it
   constexpr bool kWideOk = EPI != PMC_EPI_ACCUM_F32;
-  switch (pick_tile(p.M, p.N, kWideOk)) {
+  switch (pick_tile(layout_of(A_KMAJ, B_KMAJ), p.M, p.N, SEG ? (long)p.nseg * p.seg_k : p.K, kWideOk)) {
     case 0:
       // both operands stored [k][rows] (weight gradients): four 32-deep stages instead of two 64-deep ones, see
       // launch_wgrad_persistent
@@ -885,11 +981,19 @@ int launch_dma_tile(hipStream_t st, const GemmParams& p) {
     case 4:
       if constexpr (kWideOk) return launch_dma<256, 320, 4, 2, A_KMAJ, B_KMAJ, 2, EPI, SEG>(st, p);
       else return launch_dma<256, 256, 2, 4, A_KMAJ, B_KMAJ, 2, EPI, SEG>(st, p);
-    case 3:  // the [64 k][rows] swizzle needs 128 rows: a 64-row A tile only when A is contraction-contiguous
+    case 3:
       if constexpr (A_KMAJ) return launch_dma<64, 128, 1, 4, A_KMAJ, B_KMAJ, 3, EPI, SEG>(st, p);
-      else return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 2, EPI, SEG>(st, p);
-    default: return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 2, EPI, SEG>(st, p);
+      else break;
+    case 5: return launch_dma<64, 64, 2, 2, A_KMAJ, B_KMAJ, 5, EPI, SEG, 64, false, true>(st, p);
+    case 6: return launch_dma<32, 64, 2, 2, A_KMAJ, B_KMAJ, 6, EPI, SEG, 64, false, true>(st, p);
+    case 7: return launch_dma<32, 32, 2, 2, A_KMAJ, B_KMAJ, 8, EPI, SEG, 64, false, true>(st, p);
+    case 8:
+      if constexpr (A_KMAJ && B_KMAJ) return launch_dma<64, 128, 2, 2, A_KMAJ, B_KMAJ, 6, EPI, SEG, 64, false, true>(st, p);
+      else break;
+    default: break;
   }
+  if (tiles_of(2, p.M, p.N) <= 256) return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 4, EPI, SEG>(st, p);
+  return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 2, EPI, SEG>(st, p);
 }
 
 // Compute units of the current device, asked once (0 if the query fails).
@@ -942,12 +1046,13 @@ int launch_wgrad_persistent(hipStream_t st, GemmParams p) {
 // The two-workgroup kernel pays 1.5x the operand traffic of 256x256 tiles and a barrier every 16 matrix
 // instructions; it wins where the K loop is short, so that a tile's ring fill and read-modify-write
 // epilogue weigh as much as its K loop (measured on whole steps: -5 % of the W pass at 1024 tokens,
-// +6 % at 2048, +26 % at 4096).  Taking it for some of a layer's products only (those with 256 tiles
-// or more) was slower than taking it for none, so the bar on the tile count is low.  gemm_wgrad = 2 forces it.
+// +6 % at 2048, +26 % at 4096), and where the layer's other products take it too: alone, 8192 x 2048 at K = 1024
+// takes 49.7 us (the best other shape 52.2), but 2048 x 2048 (128 tiles) 25.4 against 18.1.  With fewer tiles
+// the smaller shapes win: the W pass of hidden 832, 496 tokens, 41 % less time.  gemm_wgrad = 2 forces it.
 bool use_wgrad_pair(const GemmParams& p) {
   if (const int f = tuning(kTuneGemmWgrad); f >= 0) return f == 2;
   if (tuning(kTuneGemmTile) >= 0) return false;
-  return p.K <= 1024 && (long)((p.M + 255) / 256) * ((p.N + 127) / 128) >= 64;
+  return p.K <= 1024 && (long)((p.M + 255) / 256) * ((p.N + 127) / 128) >= 128;
 }
 
 template <bool SEG>
@@ -968,33 +1073,61 @@ int launch_wgrad_pair(hipStream_t st, GemmParams p) {
   return PMC_OK;
 }
 
-// Split K: when even 128x128 tiles leave most compute units idle (skinny products such as the
-// [tokens, hidden] outputs at short sequence length), K is cut into `splits` ranges, each range
-// writes an fp32 partial product to the workspace and a second kernel adds them and applies the
-// epilogue.  Returns 1 when splitting does not pay or does not fit.
-int pick_splits(int M, int N, int K, size_t ws_bytes) {
+// Split K: when the output has too few tiles for the compute units and K is long, K is cut into ranges, each
+// range writes an fp32 partial product to the workspace and a second kernel adds them and applies the epilogue.
+// The partial products run in 128x128 tiles (2 stages, two workgroups per unit) or 64x64 ones.
+struct SplitPlan {
+  int splits, tiles_per_split, shape;  // splits = 1: no split
+};
+
+// Largest number of ranges the workspace of a pass has room for.
+int scratch_splits(int M, int N, int K) {
   if (tuning(kTuneGemmTile) >= 0) return 1;
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
-  if (tiles >= 192) return 1;
-  // up to K = 6144 the 64x128 tiles (no partials, no second kernel) are faster once there are
-  // enough of them (measured at M = 1024, N = 2048: 15 / 38 us against 27 / 41 us at K = 2048 / 6144)
-  if (K < 8192 && (long)((M + 63) / 64) * ((N + 127) / 128) >= 192) return 1;
+  if (tiles >= 192 || (K < 8192 && (long)((M + 63) / 64) * ((N + 127) / 128) >= 192)) return 1;
   const int nkt = (K + 63) / 64;
   int best = 1;
   for (int s : {2, 4, 8}) {
-    if (nkt % s || nkt / s < 4) continue;                          // whole tiles, at least 256 of K per split
-    if ((size_t)s * M * N * sizeof(float) > ws_bytes) break;
+    if (nkt % s || nkt / s < 4) continue;
     best = s;
     if (tiles * s >= 384) break;
   }
   return best;
 }
 
+// The split with the least time, if it beats the product in one piece.  Partial sums and the second launch cost
+// 4.5 us and 1.6 us per million partial sums (9.1 us with the larger tiles).  Past K = 8192 the products in one piece
+// are slower inside a step, where the weights come from HBM, than their fitted times: 512 x 4096 x 16384 121 / 110 us in
+// one piece (F / B layout), 94 / 92 split; 1024 x 2048 x 8192 inside a step F 69 in one piece, 64 in four ranges, B 55 and 55.
+SplitPlan pick_splits(Layout layout, int M, int N, int K, size_t ws_bytes) {
+  SplitPlan best = {1, 0, 0};
+  if (tuning(kTuneGemmTile) >= 0 || K < 2048) return best;
+  double limit;
+  (void)pick_tile(layout, M, N, K, true, &limit);
+  limit *= K < 8192 ? 0.9 : layout == kLayoutF ? 1.25 : 1.15;
+  const int nkt = (K + 63) / 64;
+  for (int shape : {2, 5})
+    for (int s : {2, 4, 8}) {
+      const int per = (nkt + s - 1) / s, n = (nkt + per - 1) / per;
+      if (per < 4 || (size_t)n * M * N * sizeof(float) > ws_bytes) continue;
+      const long tiles = tiles_of(shape, M, N) * n;
+      const double sums = 1.6e-6 * (double)M * N * n;
+      const double us = shape == 2 ? 9.1 + (tiles <= 256 ? 14. : 7.6 * (double)((tiles + 255) / 256)) * per / 16. + sums
+                                   : 4.5 + shape_us(layout, 5, tiles, per * 64.) + sums;
+      if (us < limit) {
+        limit = us;
+        best = {n, per, shape};
+      }
+    }
+  return best;
+}
+
 template <bool A_KMAJ, bool B_KMAJ>
-int launch_partial(hipStream_t st, GemmParams p, void* ws, int splits) {
+int launch_partial(hipStream_t st, GemmParams p, void* ws, const SplitPlan& plan) {
   p.C = ws;
-  p.splits = splits;
-  p.k_tiles_per_split = k_tiles<false, 64>(p) / splits;
+  p.splits = plan.splits;
+  p.k_tiles_per_split = plan.tiles_per_split;
+  if (plan.shape == 5) return launch_dma<64, 64, 2, 2, A_KMAJ, B_KMAJ, 5, kEpiPartial, false, 64, false, true>(st, p);
   return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 2, kEpiPartial>(st, p);
 }
 
@@ -1074,12 +1207,13 @@ int gemm_bf16(hipStream_t st, const GemmArgs& a) {
   // tokens 1379 us with the weight gradients on the general kernel, 1237 us here.)
   const size_t a_bytes = (size_t)(a.trans_a ? a.K : a.M) * a.lda * 2, b_bytes = (size_t)(a.trans_b ? a.N : a.K) * a.ldb * 2;
   if (a_bytes < 0x7fffffffull && b_bytes < 0x7fffffffull) {
-    const int splits = (a.ws && !(a_kmaj == false && b_kmaj == true)) ? pick_splits(a.M, a.N, a.K, a.ws_bytes) : 1;
-    if (splits > 1) {
-      int rc = a_kmaj ? (b_kmaj ? launch_partial<true, true>(st, p, a.ws, splits) : launch_partial<true, false>(st, p, a.ws, splits))
-                      : launch_partial<false, false>(st, p, a.ws, splits);
+    const bool split_ok = a.ws && !(a_kmaj == false && b_kmaj == true);
+    const SplitPlan plan = split_ok ? pick_splits(layout_of(a_kmaj, b_kmaj), a.M, a.N, a.K, a.ws_bytes) : SplitPlan{1, 0, 0};
+    if (plan.splits > 1) {
+      int rc = a_kmaj ? (b_kmaj ? launch_partial<true, true>(st, p, a.ws, plan) : launch_partial<true, false>(st, p, a.ws, plan))
+                      : launch_partial<false, false>(st, p, a.ws, plan);
       if (rc != PMC_OK) return rc;
-      return launch_reduce(st, p, (const float*)a.ws, splits, a.epilogue);
+      return launch_reduce(st, p, (const float*)a.ws, plan.splits, a.epilogue);
     }
     if (!a_kmaj && !b_kmaj && a.epilogue == PMC_EPI_ACCUM_F32 && use_wgrad_pair(p)) return launch_wgrad_pair<false>(st, p);
     if (!a_kmaj && !b_kmaj && a.epilogue == PMC_EPI_ACCUM_F32 && use_wgrad_persistent(p)) return launch_wgrad_persistent<false>(st, p);
@@ -1126,7 +1260,7 @@ int gemm_bf16_grouped_wgrad(hipStream_t st, const GroupedWgradArgs& a) {
 
 size_t gemm_scratch_bytes(int dtype, int M, int N, int K) {
   if (dtype != PMC_BF16 || K % 64 || M <= 0 || N <= 0) return 0;
-  const int splits = pick_splits(M, N, K, (size_t)-1);
+  const int splits = scratch_splits(M, N, K);
   return splits > 1 ? (size_t)splits * M * N * sizeof(float) : 0;
 }
 

@@ -315,6 +315,19 @@ def test_gemm_bf16_partial_last_k_tile(ctx, tune, ta, tb, epi, K):
         assert_close(host(c), ref, "bf16", f"{key} {switches}")
 
 
+@pytest.mark.parametrize("ta,tb,epis", [(False, False, (P.EPI_BIAS, P.EPI_BIAS_RESID, P.EPI_BIAS_GELU_GRAD)),
+                                        (False, True, (P.EPI_NONE, P.EPI_DGELU, P.EPI_MUL)),
+                                        (True, False, (P.EPI_NONE, P.EPI_ACCUM_F32))])
+# M, N, K: one tile, shorter than a 16-wide step, fewer K tiles than ring stages, odd and even numbers of K tiles with a
+# partial last one (32x32, 32x64 and 64x64 tiles whose waves split K); 128x128 tiles with a four-stage ring; K ranges
+# of unequal length (partial sums of 64x64 and 128x128 tiles, the last range ending in a partial K tile)
+@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (40, 24, 104), (72, 200, 1000), (192, 256, 1088), (264, 520, 584), (488, 840, 840),
+                                   (1032, 1000, 392), (1000, 3080, 456), (72, 136, 16392), (264, 1032, 9160)])
+def test_gemm_bf16_library_choice_of_small_tiles(ctx, ta, tb, epis, M, N, K):
+    for epi in epis:
+        _gemm_case(ctx, "bf16", ta, tb, M, N, K, epi)
+
+
 def test_gemm_grouped_weight_gradient_rejects_bad_arguments(ctx):
     a = [torch.zeros(64, 128, device="cuda", dtype=torch.bfloat16)]
     b = [torch.zeros(64, 128, device="cuda", dtype=torch.bfloat16)]
