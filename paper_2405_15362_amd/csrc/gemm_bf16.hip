@@ -6,7 +6,7 @@
 // Two kernels share the fragment layouts and the epilogue:
 //
 //  * gemm_bf16_dma_kernel, the fast path.  Operand tiles go straight from
-//    global memory into LDS (buffer_load ... lds, no registers in between) into a ring of 2 or 3
+//    global memory into LDS (buffer_load ... lds, no registers in between) into a ring of 2 to 8
 //    stages; rows past the edge are clamped, never branched on; what lies past K in the last K tile
 //    arrives as zeros, because its addresses are outside the buffer descriptor.  LDS tiles are unpadded and
 //    XOR-swizzled in 16-byte chunks so that both the DMA writes and the fragment reads are free of
@@ -479,7 +479,8 @@ typedef __attribute__((address_space(3))) void* lds_void_ptr;
 // four different 64-byte quarters by their two low bits.  In a 320-row tile (640 bytes per k-row)
 // consecutive k-rows already sit 128 bytes apart; bit 1 of kr supplies the other 64 bytes, and
 // flipping only bit 2 of the chunk index keeps every chunk inside its own group of 8 (320 / 8 = 40
-// chunks per k-row is not a multiple of 16).
+// chunks per k-row is not a multiple of 16).  The 128-byte k-rows of a 64-row tile are the same case; the 64-byte ones
+// of a 32-row tile fall into four quarters as they are.
 template <int ROWS>
 __device__ __forceinline__ constexpr int kswz(int kr) {
   return ROWS % 128 == 0 ? ((kr & 3) << 2) : ROWS == 32 ? 0 : (((kr >> 1) & 1) << 2);
