@@ -1049,7 +1049,7 @@ int launch_wgrad_persistent(hipStream_t st, GemmParams p) {
 // epilogue weigh as much as its K loop (measured on whole steps: -5 % of the W pass at 1024 tokens,
 // +6 % at 2048, +26 % at 4096), and where the layer's other products take it too: alone, 8192 x 2048 at K = 1024
 // takes 49.7 us (the best other shape 52.2), but 2048 x 2048 (128 tiles) 25.4 against 18.1.  With fewer tiles
-// the smaller shapes win: the W pass of hidden 832, 496 tokens, 41 % less time.  gemm_wgrad = 2 forces it.
+// the smaller shapes win: the products of the W pass of hidden 832, 496 tokens, 38 % less kernel time.  gemm_wgrad = 2 forces it.
 bool use_wgrad_pair(const GemmParams& p) {
   if (const int f = tuning(kTuneGemmWgrad); f >= 0) return f == 2;
   if (tuning(kTuneGemmTile) >= 0) return false;
