@@ -790,6 +790,23 @@ int pmc_gemm(pmc_ctx* ctx, int32_t dtype, int32_t trans_a, int32_t trans_b, int3
   return k::gemm(ctx->stream, g);
 }
 
+// For the library's own tests (not in pmc.h): the plan of a product whose first operand starts `offset` bytes past
+// a 16-byte boundary.
+int pmc_test_gemm_plan(int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t M, int32_t N, int32_t K, int32_t lda, int32_t ldb,
+                       int32_t ldc, int32_t epilogue, int32_t offset, size_t ws_bytes, int32_t* out) {
+  k::GemmArgs g;
+  g.dtype = dtype; g.trans_a = trans_a != 0; g.trans_b = trans_b != 0;
+  g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldb; g.ldc = ldc; g.epilogue = epilogue;
+  g.A = (const char*)nullptr + offset;
+  g.ws_bytes = ws_bytes;
+  if (dtype != PMC_F32) return fail(PMC_ERR_INVALID, "gemm plan: dtype %d", dtype);
+  const k::GemmPlan plan = k::gemm_f32_plan(g);
+  out[0] = plan.kernel;
+  out[1] = plan.splits;
+  out[2] = plan.k_tiles_per_split;
+  return PMC_OK;
+}
+
 int pmc_gemm_grouped_wgrad(pmc_ctx* ctx, int32_t M, int32_t N, int32_t K, int32_t count, const void* const* a, int32_t lda,
                            const void* const* b, int32_t ldb, float* C, int32_t ldc) {
   if (!ctx || !a || !b || !C) return fail(PMC_ERR_INVALID, "pmc_gemm_grouped_wgrad: NULL argument");

@@ -3,7 +3,7 @@
 //
 // The instruction runs at 256 FLOP per clock and compute unit, 1/16 of the bf16 rate, so LDS and the
 // load path are never near their limits; what bounds a product is how many compute units have a tile
-// and how long the serial K chain of one tile is.  Two kernels:
+// and how long the serial K chain of one tile is.  Three kernels:
 //
 //  * gemm_f32_tile_kernel: operand tiles go straight from global memory into an LDS ring
 //    (buffer_load ... lds), waves are a WAVES_M x WAVES_N grid times WK groups that share K (each
@@ -13,8 +13,11 @@
 //  * gemm_f32_direct_kernel: a 16 x 16 output tile per workgroup, K dealt over its eight waves in
 //    16-deep groups, operands loaded in the fragment layout without LDS (one memory latency per few
 //    groups, no barrier before the final fold).  For products whose 32 x 32 tiles would leave most
-//    compute units idle, and (element-wise loads) for sizes, pitches or pointers that are not
-//    multiples of four elements, which makes it the path for every shape.
+//    compute units idle and, with element-wise loads, for small products of sizes, pitches or pointers
+//    that are not multiples of four elements.
+//  * gemm_f32_fma_kernel: 64 x 64 tiles of plain FMAs staged element by element through LDS, for the
+//    larger products of such sizes: it reads an operand element once per 64 outputs, the direct kernel
+//    once per 16, one 4-byte load at a time.
 //
 // Measured against a 64 x 64 tile of plain FMAs with scalar loads (before), mean over the products of a
 // pass, F / B / W: hidden 256, 128 tokens 65 / 74 / 23 -> 5.2 / 5.2 / 5.1 us; hidden 1024, 512 tokens
@@ -325,6 +328,53 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_direct_kernel(F32Params p) {
   }
 }
 
+// Sum over k in ascending order, any sizes, pitches and alignments.
+template <bool A_KMAJ, bool B_KMAJ>
+__global__ __launch_bounds__(256) void gemm_f32_fma_kernel(F32Params p) {
+  constexpr int BM = 64, BN = 64, BK = 16;
+  __shared__ float As[BK][BM + 4];
+  __shared__ float Bs[BK][BN + 4];
+  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+  float acc[4][4] = {};
+  for (int k0 = 0; k0 < p.K; k0 += BK) {
+    for (int i = tid; i < BM * BK; i += 256) {
+      const int k = A_KMAJ ? i % BK : i / BM, m = A_KMAJ ? i / BK : i % BM, gm = m0 + m, gk = k0 + k;
+      As[k][m] = gm < p.M && gk < p.K ? (A_KMAJ ? p.A[(size_t)gm * p.lda + gk] : p.A[(size_t)gk * p.lda + gm]) : 0.f;
+    }
+    for (int i = tid; i < BN * BK; i += 256) {
+      const int k = B_KMAJ ? i % BK : i / BN, n = B_KMAJ ? i / BK : i % BN, gn = n0 + n, gk = k0 + k;
+      Bs[k][n] = gn < p.N && gk < p.K ? (B_KMAJ ? p.B[(size_t)gn * p.ldb + gk] : p.B[(size_t)gk * p.ldb + gn]) : 0.f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < BK; ++k) {
+      float a[4], b[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = m0 + ty * 4 + i;
+    if (m >= p.M) continue;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int n = n0 + tx * 4 + j;
+      if (n >= p.N) continue;
+      const size_t idx = (size_t)m * p.ldc + n;
+      p.C[idx] = apply_epilogue(p, acc[i][j], idx, n);
+    }
+  }
+}
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int WK, int NSTAGE, bool TA, bool TB>
 int launch_tile_f32(hipStream_t st, F32Params p) {
   constexpr size_t lds = (size_t)WK * NSTAGE * 32 * (BM + BN) * sizeof(float);
@@ -352,38 +402,79 @@ int launch_direct_f32(hipStream_t st, F32Params p, bool vec) {
   return PMC_OK;
 }
 
-// Shape of the output tile: the one whose rounds over the 256 compute units take least.  A round costs
+template <bool TA, bool TB>
+int launch_fma_f32(hipStream_t st, const F32Params& p) {
+  gemm_f32_fma_kernel<!TA, TB><<<dim3((p.N + 63) / 64, (p.M + 63) / 64), dim3(256), 0, st>>>(p);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(PMC_ERR_HIP, "gemm_f32 launch failed: %s", hipGetErrorString(e));
+  return PMC_OK;
+}
+
+// Kernel and output tile of a product: 128 x 128, 64 x 64, 32 x 64 and 32 x 32 tiles staged in LDS, 16 x 16
+// ones in the direct kernel with 16-byte loads, and, with element-wise loads, 16 x 16 ones in the direct
+// kernel or 64 x 64 ones in the FMA kernel.
+enum F32Shape { kTile128, kTile64, kTile32x64, kTile32, kDirect, kDirectElements, kFmaElements };
+
+// With 16-byte loads: the tile whose rounds over the 256 compute units take least.  A round costs
 // kPerK us per 1024 of K plus kFixed us (ring fill, fold, epilogue), both measured over M = 40 .. 16384,
 // N = 96 .. 16384, K = 40 .. 16384; at few tiles the small shapes win although they read more (for
 // 128 x 256 x 1024: 71 / 22.7 / 14.0 / 9.1 / 5.9 us), at many the 64 x 64 and 128 x 128 ones
 // (768 x 5120 x 1280: 98 / 96 / 124 / 147 / 232 us).  The gemm_tile switch forces one (tests).
-int pick_tile_f32(const F32Params& p) {
-  if (const int f = tuning(kTuneGemmTile); f >= 0) return f;
+F32Shape pick_tile_f32(int M, int N, int K) {
   constexpr int kBm[5] = {128, 64, 32, 32, 16}, kBn[5] = {128, 64, 64, 32, 16};
   constexpr double kPerK[5] = {68.0, 20.5, 13.0, 8.8, 3.25}, kFixed[5] = {2.6, 0.3, 0.9, 1.2, 0.4};
   int best = 0;
   double best_us = 1e300;
   for (int c = 0; c < 5; ++c) {
-    const long tiles = (long)((p.M + kBm[c] - 1) / kBm[c]) * ((p.N + kBn[c] - 1) / kBn[c]);
-    const double us = (double)((tiles + 255) / 256) * (kPerK[c] * p.K / 1024.0 + kFixed[c]);
+    const long tiles = (long)((M + kBm[c] - 1) / kBm[c]) * ((N + kBn[c] - 1) / kBn[c]);
+    const double us = (double)((tiles + 255) / 256) * (kPerK[c] * K / 1024.0 + kFixed[c]);
     if (us < best_us) {
       best_us = us;
       best = c;
     }
   }
-  return best;
+  if (const int f = tuning(kTuneGemmTile); f >= 0) best = f;
+  // one dimension of a launch holds fewer than 2^32 threads, 512 to a 16 x 16 tile
+  if (best == kDirect && (long)((M + 15) / 16) * ((N + 15) / 16) >= 1L << 23) best = kTile64;
+  return (F32Shape)best;
+}
+
+// With element-wise loads: the kernel with the smaller fitted time in us, u = 16 x 16 tiles per compute unit.
+// The direct kernel's grows with the tiles, by what a quarter-wave's loads of the layout cost; the FMA kernel's
+// is the chain of one workgroup until about five of its tiles share a unit.  Fitted to 260 products of odd
+// sizes, M, N = 129 .. 3073, K = 37 .. 2051, where the kernel picked is at most 14 % slower than the other, 0.2 %
+// on average; direct / FMA kernel: A [M,K] B [K,N] 255 x 513 x 517 11.3 / 60.8 us, 2049 x 3073 x 517 292 / 130;
+// A [M,K] B [N,K] 17.3 / 61.5 and 493 / 131; A [K,M] B [K,N] 8.5 / 60.3 and 223 / 136; 1025 x 2049 x 37 32 / 11.8.
+F32Shape pick_elements_f32(bool ta, bool tb, int M, int N, int K) {
+  const double u = (double)((M + 15) / 16) * ((N + 15) / 16) / 256.0;
+  const double per_tile = ta == tb ? 0.85 : tb ? 0.5 : 1.03, per_k = ta == tb ? 0.0046 : tb ? 0.0084 : 0.0029;
+  double chain = 0.12 + 0.0027 * u;
+  if (chain > 0.195) chain = 0.195;
+  if (chain < 0.0025 * u) chain = 0.0025 * u;
+  return u * (per_tile + per_k * K) < 0.15 * u + chain * K ? kDirectElements : kFmaElements;
+}
+
+F32Shape shape_of(const GemmArgs& a) {
+  auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
+  // whole 16-byte chunks everywhere, operands inside the 2 GB that an offset of the tile loads can reach
+  const size_t a_bytes = (size_t)(a.trans_a ? a.K : a.M) * a.lda * 4, b_bytes = (size_t)(a.trans_b ? a.N : a.K) * a.ldb * 4;
+  const bool vec = a.M % 4 == 0 && a.N % 4 == 0 && a.K % 4 == 0 && a.lda % 4 == 0 && a.ldb % 4 == 0 && a.ldc % 4 == 0 && al(a.A) &&
+                   al(a.B) && al(a.C) && al(a.bias) && al(a.resid) && al(a.aux) && a_bytes < 0x7fffffffull && b_bytes < 0x7fffffffull;
+  return vec ? pick_tile_f32(a.M, a.N, a.K) : pick_elements_f32(a.trans_a, a.trans_b, a.M, a.N, a.K);
 }
 
 template <bool TA, bool TB>
-int launch_f32(hipStream_t st, const F32Params& p, bool vec) {
-  if (!vec) return launch_direct_f32<TA, TB>(st, p, false);
-  switch (pick_tile_f32(p)) {
-    case 0: return launch_tile_f32<128, 128, 2, 2, 1, 4, TA, TB>(st, p);
-    case 1: return launch_tile_f32<64, 64, 2, 2, 1, 4, TA, TB>(st, p);
-    case 2: return launch_tile_f32<32, 64, 1, 2, 2, 4, TA, TB>(st, p);
-    case 3: return launch_tile_f32<32, 32, 1, 1, 4, 4, TA, TB>(st, p);
-    default: return launch_direct_f32<TA, TB>(st, p, true);
+int launch_f32(hipStream_t st, const F32Params& p, F32Shape shape) {
+  switch (shape) {
+    case kTile128: return launch_tile_f32<128, 128, 2, 2, 1, 4, TA, TB>(st, p);
+    case kTile64: return launch_tile_f32<64, 64, 2, 2, 1, 4, TA, TB>(st, p);
+    case kTile32x64: return launch_tile_f32<32, 64, 1, 2, 2, 4, TA, TB>(st, p);
+    case kTile32: return launch_tile_f32<32, 32, 1, 1, 4, 4, TA, TB>(st, p);
+    case kDirect: return launch_direct_f32<TA, TB>(st, p, true);
+    case kDirectElements: return launch_direct_f32<TA, TB>(st, p, false);
+    case kFmaElements: return launch_fma_f32<TA, TB>(st, p);
   }
+  return fail(PMC_ERR_INVALID, "gemm_f32: unknown shape %d", (int)shape);
 }
 
 }  // namespace
@@ -394,16 +485,15 @@ int gemm_f32(hipStream_t st, const GemmArgs& a) {
   p.bias = (const float*)a.bias; p.resid = (const float*)a.resid; p.aux = (float*)a.aux;
   p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.ldc = a.ldc; p.epi = a.epilogue;
   p.tiles_m = p.tiles_n = 0;
-  auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
-  // whole 16-byte chunks everywhere, operands inside the 2 GB that an offset of the tile loads can reach
-  const size_t a_bytes = (size_t)(a.trans_a ? a.K : a.M) * a.lda * 4, b_bytes = (size_t)(a.trans_b ? a.N : a.K) * a.ldb * 4;
-  const bool vec = a.M % 4 == 0 && a.N % 4 == 0 && a.K % 4 == 0 && a.lda % 4 == 0 && a.ldb % 4 == 0 && a.ldc % 4 == 0 && al(a.A) &&
-                   al(a.B) && al(a.C) && al(a.bias) && al(a.resid) && al(a.aux) && a_bytes < 0x7fffffffull && b_bytes < 0x7fffffffull;
-  if (!a.trans_a && !a.trans_b) return launch_f32<false, false>(st, p, vec);
-  if (!a.trans_a && a.trans_b) return launch_f32<false, true>(st, p, vec);
-  if (a.trans_a && !a.trans_b) return launch_f32<true, false>(st, p, vec);
-  return launch_f32<true, true>(st, p, vec);
+  const F32Shape shape = shape_of(a);
+  if (!a.trans_a && !a.trans_b) return launch_f32<false, false>(st, p, shape);
+  if (!a.trans_a && a.trans_b) return launch_f32<false, true>(st, p, shape);
+  if (a.trans_a && !a.trans_b) return launch_f32<true, false>(st, p, shape);
+  return launch_f32<true, true>(st, p, shape);
 }
+
+GemmPlan gemm_f32_plan(const GemmArgs& a) { return {kPlanF32 + (int)shape_of(a), 1, 0}; }
+
 // Shape and pointer checks common to both precisions, then dispatch.
 int gemm(hipStream_t st, const GemmArgs& a) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return fail(PMC_ERR_INVALID, "gemm: M=%d N=%d K=%d", a.M, a.N, a.K);

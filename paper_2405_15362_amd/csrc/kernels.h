@@ -55,6 +55,14 @@ int gemm_bf16_grouped_wgrad(hipStream_t stream, const GroupedWgradArgs& a);
 // Scratch a product of this shape can use (0: none).
 size_t gemm_scratch_bytes(int dtype, int M, int N, int K);
 
+// What gemm() launches for a product: host arithmetic only, so that the rules can be tested without a GPU.
+// kernel: kPlanF32 + F32Shape in fp32.
+enum { kPlanF32 = 100 };
+struct GemmPlan {
+  int kernel, splits, k_tiles_per_split;
+};
+GemmPlan gemm_f32_plan(const GemmArgs& a);
+
 int gemm(hipStream_t stream, const GemmArgs& a);
 int gemm_f32(hipStream_t stream, const GemmArgs& a);
 int gemm_bf16(hipStream_t stream, const GemmArgs& a);

@@ -110,6 +110,23 @@ def oracle_chunk(cfg, params, x, dy):
     return y, dx, ln, wg
 
 
+# what the library would launch for a product (host arithmetic, no GPU needed)
+F32_TILE128, F32_TILE64, F32_TILE32X64, F32_TILE32, F32_DIRECT, F32_DIRECT_ELEMENTS, F32_FMA_ELEMENTS = range(100, 107)
+
+
+def gemm_plan(dtype, ta, tb, M, N, K, epi=0, lda=None, ldb=None, ldc=None, offset=0, ws_bytes=0):
+    """(kernel, K ranges, 64-wide K tiles per range) that the library picks; `offset`: bytes by which A misses a
+    16-byte boundary."""
+    import ctypes
+
+    import paper_2405_15362_amd as P
+    out = (ctypes.c_int32 * 3)()
+    rc = P.lib.pmc_test_gemm_plan(P.PMC_F32 if dtype == "f32" else P.PMC_BF16, int(ta), int(tb), M, N, K, lda or (M if ta else K),
+                                  ldb or (K if tb else N), ldc or N, epi, offset, ctypes.c_size_t(ws_bytes), out)
+    assert rc == 0, rc
+    return tuple(out)
+
+
 class tuned:
     """Sets process-wide tuning switches of the library for a with-block (or until reset()) and hands
     the choice back to the library afterwards."""

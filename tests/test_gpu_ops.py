@@ -6,6 +6,7 @@ import torch
 import paper_2405_15362_amd as P
 import synth
 from oracle import layer as OL
+import gpu_util as U
 from gpu_util import assert_close, dev, host, mat, rel_l2, tol, tuned
 
 pytestmark = pytest.mark.gpu
@@ -80,6 +81,42 @@ def test_gemm_f32_tile_shapes(ctx, tune, tile):
             for M, N, K in ((4, 4, 4), (36, 68, 200), (132, 260, 36), (256, 132, 416)):
                 for epi in (P.EPI_BIAS_RESID, P.EPI_ACCUM_F32, P.EPI_BIAS_GELU_GRAD):
                     _gemm_case(ctx, "f32", ta, tb, M, N, K, epi)
+
+
+@pytest.mark.parametrize("ta", [False, True])
+@pytest.mark.parametrize("tb", [False, True])
+def test_gemm_f32_element_loads(ctx, ta, tb):
+    """Odd sizes: the 64x64 tiles of plain FMAs (every epilogue; one row, one column, one k past whole tiles, and less
+    than a 16-deep step) and the 16x16 tiles on the other side of the rule."""
+    for epi in range(8):
+        assert U.gemm_plan("f32", ta, tb, 1025, 2113, 33, epi)[0] == U.F32_FMA_ELEMENTS
+        _gemm_case(ctx, "f32", ta, tb, 1025, 2113, 33, epi)
+    assert U.gemm_plan("f32", ta, tb, 3001, 1031, 7)[0] == U.F32_FMA_ELEMENTS
+    _gemm_case(ctx, "f32", ta, tb, 3001, 1031, 7, P.EPI_BIAS_RESID)
+    assert U.gemm_plan("f32", ta, tb, 257, 255, 517)[0] == U.F32_DIRECT_ELEMENTS
+    _gemm_case(ctx, "f32", ta, tb, 257, 255, 517, P.EPI_BIAS_RESID)
+
+
+@pytest.mark.parametrize("ta", [False, True])
+@pytest.mark.parametrize("tb", [False, True])
+def test_gemm_f32_output_of_2_to_the_31_elements(ctx, ta, tb):
+    """More output elements than 2^31 (8.6 GB) of odd sizes: 2^23 and more 16x16 tiles of 512 threads would not fit one
+    launch dimension.  Every element against the same three products in float64, a band of rows at a time."""
+    M, N, K = 46343, 46351, 3
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    a = torch.randn((K, M) if ta else (M, K), device="cuda", generator=gen)
+    b = torch.randn((N, K) if tb else (K, N), device="cuda", generator=gen)
+    c = torch.empty(M, N, device="cuda")
+    print("fp32 output of 2^31 elements", ta, tb, flush=True)
+    P.pmc_gemm(ctx, a, b, c, ta, tb)
+    torch.cuda.synchronize()
+    A, B = (a.T if ta else a).double(), (b.T if tb else b).double()
+    for r in range(0, M, 4096):
+        want = sum(A[r:r + 4096, k, None] * B[None, k] for k in range(K))
+        # three products and two sums, each rounded to 2^-24 relative
+        bound = 4 * 2.0 ** -24 * sum((A[r:r + 4096, k, None] * B[None, k]).abs() for k in range(K))
+        assert bool(((c[r:r + 4096].double() - want).abs() <= bound).all()), (r, ta, tb)
+    del c
 
 
 @pytest.mark.parametrize("ta", [False, True])

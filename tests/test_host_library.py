@@ -6,6 +6,7 @@ import re
 import pytest
 
 import paper_2405_15362_amd as P
+import gpu_util as U
 from oracle import layer as OL
 from oracle import schedule as S
 
@@ -232,3 +233,29 @@ def test_header_is_plain_c():
     r = subprocess.run([gcc, "-std=c99", "-Wall", "-Wextra", "-pedantic", "-fsyntax-only", "-x", "c",
                         os.path.join(ROOT, "include", "pmc.h")], capture_output=True, text=True)
     assert r.returncode == 0 and not r.stderr.strip(), r.stderr
+
+
+LAYOUTS = [(False, False), (False, True), (True, False), (True, True)]
+
+
+@pytest.mark.parametrize("ta,tb", LAYOUTS)
+def test_fp32_products_of_odd_sizes_pick_the_faster_kernel(ta, tb):
+    """Element-wise loads: 16x16 tiles without LDS while a compute unit gets few of them, 64x64 tiles through LDS
+    beyond that (measured: 2049 x 3073 x 517 takes 1.6 to 3.8 times as long in 16x16 tiles, 255 x 513 x 517 a sixth),
+    whether it is the sizes, a pitch or a pointer that rules 16-byte loads out."""
+    for M, N, K in ((33, 65, 31), (77, 130, 45), (255, 513, 517), (511, 1025, 513)):
+        assert U.gemm_plan("f32", ta, tb, M, N, K)[0] == U.F32_DIRECT_ELEMENTS, (M, N, K)
+    for M, N, K in ((1025, 2049, 37), (2049, 3073, 517), (4097, 4099, 4101), (46343, 46351, 3), (131073, 16385, 4097)):
+        assert U.gemm_plan("f32", ta, tb, M, N, K)[0] == U.F32_FMA_ELEMENTS, (M, N, K)
+    for kw in ({"offset": 4}, {"ldc": 4097}):
+        assert U.gemm_plan("f32", ta, tb, 4096, 4096, 4096, **kw)[0] == U.F32_FMA_ELEMENTS, kw
+        assert U.gemm_plan("f32", ta, tb, 128, 128, 256, **kw)[0] == U.F32_DIRECT_ELEMENTS, kw
+
+
+@pytest.mark.parametrize("ta,tb", LAYOUTS)
+def test_fp32_16x16_tiles_fit_one_launch(ta, tb):
+    """A launch dimension holds fewer than 2^32 threads: no choice, forced ones included, asks for 2^23 or more
+    workgroups of 512."""
+    with U.tuned(gemm_tile=4):
+        assert U.gemm_plan("f32", ta, tb, 16384, 16384, 64)[0] == U.F32_DIRECT
+        assert U.gemm_plan("f32", ta, tb, 65536, 32768, 64)[0] == U.F32_TILE64
