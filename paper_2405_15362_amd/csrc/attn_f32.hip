@@ -32,6 +32,7 @@ namespace {
 constexpr int kMaxDh = 128;
 constexpr int kWavesF = 8;
 constexpr int kRows = 16;  // rows a workgroup owns
+constexpr int kMaxGrid = 65535;  // workgroups in the second and third dimension of a launch
 
 // Four consecutive columns of a row, zeros past dh.  VEC: dh is a multiple of 4 and the four are one aligned load.
 template <typename T, bool VEC>
@@ -144,24 +145,24 @@ __device__ __forceinline__ float quarters_sum(float v) {
   return v + __shfl_xor(v, 32, 64);
 }
 
-// Workgroup -> (row block, head, sequence).  Under a causal mask late query blocks and early key blocks
-// see the most of the other side: they are dealt out first and the short ones fill the tail.
+// Workgroup -> (row block, head, sequence); the grid is (heads, sequences, row blocks from `block0` on), see
+// for_row_blocks.  Under a causal mask late query blocks and early key blocks see the most of the other side:
+// they are dealt out first and the short ones fill the tail.
 struct Place {
   int row0, head, b;
 };
-__device__ __forceinline__ Place place(int seq, int heads, bool late_first) {
-  const int blocks = (seq + kRows - 1) / kRows, pairs = (int)(gridDim.x / blocks);
-  const int block = blockIdx.x / pairs, pair = blockIdx.x % pairs;
-  return {(late_first ? blocks - 1 - block : block) * kRows, pair % heads, pair / heads};
+__device__ __forceinline__ Place place(int seq, int block0, bool late_first) {
+  const int blocks = (seq + kRows - 1) / kRows, block = block0 + (int)blockIdx.z;
+  return {(late_first ? blocks - 1 - block : block) * kRows, (int)blockIdx.x, (int)blockIdx.y};
 }
 
 template <typename T, int DH, bool VEC>
-__global__ __launch_bounds__(kWavesF * 64, 2) void attn_fwd_f32(int seq, int heads, int dh, int causal, const T* __restrict__ qkv,
+__global__ __launch_bounds__(kWavesF * 64, 2) void attn_fwd_f32(int block0, int seq, int heads, int dh, int causal, const T* __restrict__ qkv,
                                                              T* __restrict__ o, float* __restrict__ lse) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(16))) float fold_f32[];  // [8 waves][16][DH + 4], then [8][16] weights
   __shared__ float stat_m[kWavesF][kRows], stat_l[kWavesF][kRows];
-  const Place at = place(seq, heads, causal != 0);
+  const Place at = place(seq, block0, causal != 0);
   const int h = heads * dh, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, quarter = lane >> 4;
   const size_t pitch = (size_t)3 * h;
   const T* base = qkv + (size_t)at.b * seq * pitch + (size_t)at.head * dh;
@@ -235,13 +236,13 @@ __global__ __launch_bounds__(kWavesF * 64, 2) void attn_fwd_f32(int seq, int hea
 // dq[i] = sigma * sum_j dS[i][j] k[j],  dS = P * (dP - delta),  P = exp(S - lse),  dP = dO . V^T; also
 // emits delta = rowsum(dO * O).
 template <typename T, int DH, bool VEC>
-__global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dq_f32(int seq, int heads, int dh, int causal, const T* __restrict__ qkv,
+__global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dq_f32(int block0, int seq, int heads, int dh, int causal, const T* __restrict__ qkv,
                                                                 const T* __restrict__ o, const float* __restrict__ lse,
                                                                 const T* __restrict__ d_o, T* __restrict__ dq,
                                                                 float* __restrict__ delta) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(16))) float fold_f32[];
-  const Place at = place(seq, heads, causal != 0);
+  const Place at = place(seq, block0, causal != 0);
   const int h = heads * dh, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, quarter = lane >> 4;
   const size_t pitch = (size_t)3 * h, own = (size_t)at.b * seq * h + (size_t)at.head * dh;
   const T* base = qkv + (size_t)at.b * seq * pitch + (size_t)at.head * dh;
@@ -294,12 +295,12 @@ __global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dq_f32(int seq, int 
 // For 16 keys: dv[j] = sum_i P[i][j] dO[i],  dk[j] = sigma * sum_i dS[i][j] q[i]; written over v[j] and
 // k[j] inside the packed buffer (a key block is read only by the workgroup that owns it, before its fold).
 template <typename T, int DH, bool VEC>
-__global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dkv_f32(int seq, int heads, int dh, int causal, const T* qkv,
+__global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dkv_f32(int block0, int seq, int heads, int dh, int causal, const T* qkv,
                                                                  const float* __restrict__ lse, const float* __restrict__ delta,
                                                                  const T* __restrict__ d_o, T* dqkv) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(16))) float fold_f32[];
-  const Place at = place(seq, heads, false);
+  const Place at = place(seq, block0, false);
   const int h = heads * dh, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, quarter = lane >> 4;
   const size_t pitch = (size_t)3 * h;
   const T* base = qkv + (size_t)at.b * seq * pitch + (size_t)at.head * dh;
@@ -353,8 +354,21 @@ __global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dkv_f32(int seq, int
 int check(const char* what, int batch, int seq, int heads, int dh) {
   if (batch <= 0 || seq <= 0 || heads <= 0) return fail(PMC_ERR_INVALID, "%s: batch=%d seq=%d heads=%d", what, batch, seq, heads);
   if (dh <= 0 || dh > kMaxDh) return fail(PMC_ERR_INVALID, "%s: head size %d not in 1..%d", what, dh, kMaxDh);
-  if (heads > 65535 || batch > 65535 || (int64_t)((seq + kRows - 1) / kRows) * heads * batch > 0x7fffffffLL)
-    return fail(PMC_ERR_INVALID, "%s: seq, heads and batch exceed the grid limit", what);
+  if (heads > kMaxGrid || batch > kMaxGrid) return fail(PMC_ERR_INVALID, "%s: heads/batch exceed the grid limit", what);
+  return PMC_OK;
+}
+
+// Calls launch(first row block, grid) for the row blocks of every (head, sequence) pair, in as many launches as the
+// grid's third dimension needs.  (One dimension for all three holds fewer than 2^32 threads, 2^23 of these workgroups;
+// a launch past that is not refused but leaves workgroups out.)
+template <typename Launch>
+int for_row_blocks(const char* what, int batch, int seq, int heads, Launch launch) {
+  const int blocks = (int)(((int64_t)seq + kRows - 1) / kRows);
+  for (int b0 = 0; b0 < blocks; b0 += kMaxGrid) {
+    launch(b0, dim3(heads, batch, blocks - b0 < kMaxGrid ? blocks - b0 : kMaxGrid));
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(PMC_ERR_HIP, "%s launch failed: %s", what, hipGetErrorString(e));
+  }
   return PMC_OK;
 }
 
@@ -374,11 +388,9 @@ template <typename T, int DH, bool VEC>
 int fwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, void* o, float* lse) {
   static std::atomic<bool> done{false};
   if (int rc = reserve_lds(attn_fwd_f32<T, DH, VEC>, fold_bytes<DH>(), done, "attention_forward")) return rc;
-  attn_fwd_f32<T, DH, VEC><<<dim3((seq + kRows - 1) / kRows * heads * batch), dim3(kWavesF * 64), fold_bytes<DH>(), st>>>(
-      seq, heads, dh, causal, (const T*)qkv, (T*)o, lse);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(PMC_ERR_HIP, "attention_forward launch failed: %s", hipGetErrorString(e));
-  return PMC_OK;
+  return for_row_blocks("attention_forward", batch, seq, heads, [&](int block0, dim3 grid) {
+    attn_fwd_f32<T, DH, VEC><<<grid, dim3(kWavesF * 64), fold_bytes<DH>(), st>>>(block0, seq, heads, dh, causal, (const T*)qkv, (T*)o, lse);
+  });
 }
 
 template <typename T, int DH, bool VEC>
@@ -387,14 +399,15 @@ int bwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal
   static std::atomic<bool> done_dq{false}, done_dkv{false};
   if (int rc = reserve_lds(attn_bwd_dq_f32<T, DH, VEC>, fold_bytes<DH>(), done_dq, "attention_backward")) return rc;
   if (int rc = reserve_lds(attn_bwd_dkv_f32<T, DH, VEC>, fold_bytes<DH>(), done_dkv, "attention_backward")) return rc;
-  const dim3 grid((seq + kRows - 1) / kRows * heads * batch), block(kWavesF * 64);
-  attn_bwd_dq_f32<T, DH, VEC><<<grid, block, fold_bytes<DH>(), st>>>(seq, heads, dh, causal, (const T*)qkv, (const T*)o, lse,
-                                                                      (const T*)d_o, (T*)dq_stage, delta);
-  attn_bwd_dkv_f32<T, DH, VEC><<<grid, block, fold_bytes<DH>(), st>>>(seq, heads, dh, causal, (const T*)qkv, lse, delta,
-                                                                       (const T*)d_o, (T*)dqkv);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(PMC_ERR_HIP, "attention_backward launch failed: %s", hipGetErrorString(e));
-  return PMC_OK;
+  int rc = for_row_blocks("attention_backward", batch, seq, heads, [&](int block0, dim3 grid) {
+    attn_bwd_dq_f32<T, DH, VEC><<<grid, dim3(kWavesF * 64), fold_bytes<DH>(), st>>>(block0, seq, heads, dh, causal, (const T*)qkv,
+                                                                                     (const T*)o, lse, (const T*)d_o, (T*)dq_stage, delta);
+  });
+  if (rc) return rc;
+  return for_row_blocks("attention_backward", batch, seq, heads, [&](int block0, dim3 grid) {
+    attn_bwd_dkv_f32<T, DH, VEC><<<grid, dim3(kWavesF * 64), fold_bytes<DH>(), st>>>(block0, seq, heads, dh, causal, (const T*)qkv, lse,
+                                                                                      delta, (const T*)d_o, (T*)dqkv);
+  });
 }
 
 template <typename T>

@@ -502,6 +502,64 @@ def test_attention_fp32_matrix_path(ctx, dtype, heads, dh, causal):
             assert_close(host(qd)[:, cols], dqkv_ref[:, cols], dtype, name, scale=np.sqrt(np.mean(dqkv_ref ** 2)))
 
 
+def test_attention_fp32_more_workgroups_than_one_dimension_holds(ctx):
+    """2^23 (row block, head, sequence) triples and more, 512 threads each, would be 2^32 threads in one launch
+    dimension.  One-token sequences: o = v, lse = q k / sqrt(dh), dv = dO, no gradient in q and k, element by element."""
+    batch, heads, dh = 65535, 132, 1
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    qkv = torch.randn(batch, 3 * heads, device="cuda", generator=gen)
+    d_o = torch.randn(batch, heads, device="cuda", generator=gen)
+    o, lse = torch.full_like(d_o, float("nan")), torch.full((batch * heads,), float("nan"), device="cuda")
+    print("fp32 attention, one-token sequences", batch, heads, flush=True)
+    P.pmc_attention_forward(ctx, qkv, o, lse, batch, 1, heads, dh, True)
+    torch.cuda.synchronize()
+    q, k, v = qkv.view(batch, 3, heads).unbind(1)
+    assert torch.equal(o, v)
+    # one product, and the product with sqrt(1)
+    assert bool(((lse.view(batch, heads).double() - q.double() * k.double()).abs() <= 2.0 ** -22 * (q * k).abs().double() + 1e-30).all())
+    dqkv = torch.full_like(qkv, float("nan"))
+    P.pmc_attention_backward(ctx, qkv, o, lse, d_o, dqkv, batch, 1, heads, dh, True)
+    torch.cuda.synchronize()
+    dq, dk, dv = dqkv.view(batch, 3, heads).unbind(1)
+    # P = exp(s - lse) is 1 up to the rounding of its argument, |s| <= 30 here: 30 * 2^-23
+    assert bool(((dv - d_o).abs() <= 4e-6 * d_o.abs()).all())
+    assert float(dq.abs().max()) <= 1e-5 and float(dk.abs().max()) <= 1e-5
+
+
+@pytest.mark.timeout(300)
+def test_attention_fp32_more_row_blocks_than_one_launch_takes(ctx):
+    """A sequence of more than 65535 blocks of 16 rows goes out in several launches.  With q = 0 the causal
+    probabilities of row i are all 1 / (i + 1), so outputs and gradients are running sums (float64)."""
+    seq, dh = 65535 * 16 + 21, 4
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    qkv = torch.randn(seq, 3 * dh, device="cuda", generator=gen)
+    qkv[:, :dh] = 0
+    qkv[:, 2 * dh:] += 0.5
+    d_o = torch.randn(seq, dh, device="cuda", generator=gen)
+    o, lse = torch.zeros_like(d_o), torch.zeros(seq, device="cuda")
+    print("fp32 attention, one sequence of", seq, flush=True)
+    P.pmc_attention_forward(ctx, qkv, o, lse, 1, seq, 1, dh, True)
+    torch.cuda.synchronize()
+    print("forward done", flush=True)
+    P.pmc_attention_backward(ctx, qkv, o, lse, d_o, dqkv := torch.zeros_like(qkv), 1, seq, 1, dh, True)
+    torch.cuda.synchronize()
+    k, v, g = qkv[:, dh:2 * dh].double(), qkv[:, 2 * dh:].double(), d_o.double()
+    n = torch.arange(1, seq + 1, device="cuda", dtype=torch.float64)[:, None]
+    want_o = v.cumsum(0) / n
+    delta = (g * want_o).sum(1, keepdim=True)
+    pairs = (v[:, :, None] * k[:, None, :]).cumsum(0)
+    want_dq = ((g[:, :, None] * pairs).sum(1) - delta * k.cumsum(0)) / n / dh ** 0.5
+    want_dv = (g / n).flip(0).cumsum(0).flip(0)
+    assert float((lse.double() - n[:, 0].log()).abs().max()) <= 2e-5
+    assert_close(host(o), want_o.cpu().numpy(), "f32", "o")
+    assert_close(host(dqkv)[:, :dh], want_dq.cpu().numpy(), "f32", "dq")
+    # a wave adds up to seq / 8 terms one after the other, each time rounded by up to 2^-24 of a partial sum that the
+    # terms' absolute values bound: independent roundings grow with the root of their number
+    bound = (seq / 8) ** 0.5 * 2.0 ** -24 * (g / n).abs().flip(0).cumsum(0).flip(0)
+    assert bool(((dqkv[:, 2 * dh:].double() - want_dv).abs() <= bound).all())
+    assert float(dqkv[:, dh:2 * dh].abs().max()) == 0.0
+
+
 def test_attention_random_shapes(ctx):
     """Seeded random batch, sequence length, head count and head size (every multiple of 8 up to 128),
     causal or not, in the library's own choice of launch shape: ragged last blocks, sequences shorter
