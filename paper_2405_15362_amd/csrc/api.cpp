@@ -798,9 +798,10 @@ int pmc_test_gemm_plan(int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t 
   g.dtype = dtype; g.trans_a = trans_a != 0; g.trans_b = trans_b != 0;
   g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldb; g.ldc = ldc; g.epilogue = epilogue;
   g.A = (const char*)nullptr + offset;
+  g.ws = ws_bytes ? out : nullptr;
   g.ws_bytes = ws_bytes;
-  if (dtype != PMC_F32) return fail(PMC_ERR_INVALID, "gemm plan: dtype %d", dtype);
-  const k::GemmPlan plan = k::gemm_f32_plan(g);
+  if (dtype != PMC_F32 && dtype != PMC_BF16) return fail(PMC_ERR_INVALID, "gemm plan: dtype %d", dtype);
+  const k::GemmPlan plan = dtype == PMC_F32 ? k::gemm_f32_plan(g) : k::gemm_bf16_plan(g);
   out[0] = plan.kernel;
   out[1] = plan.splits;
   out[2] = plan.k_tiles_per_split;

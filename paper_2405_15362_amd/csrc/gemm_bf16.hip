@@ -967,12 +967,13 @@ int pick_tile(Layout layout, int M, int N, long K, bool wide_ok, double* us = nu
   return best;
 }
 
+// the 320-wide tile holds 10 accumulator tiles per wave; with the fp32 read-modify-write epilogue on
+// top it would spill registers, so weight-gradient products do not use it
+constexpr bool wide_ok(int epi) { return epi != PMC_EPI_ACCUM_F32; }
+
 template <bool A_KMAJ, bool B_KMAJ, int EPI, bool SEG = false>
-int launch_dma_tile(hipStream_t st, const GemmParams& p) {
-  // the 320-wide tile holds 10 accumulator tiles per wave; with the fp32 read-modify-write epilogue on
-  // top it would spill registers, so weight-gradient products do not use it
-  constexpr bool kWideOk = EPI != PMC_EPI_ACCUM_F32;
-  switch (pick_tile(layout_of(A_KMAJ, B_KMAJ), p.M, p.N, SEG ? (long)p.nseg * p.seg_k : p.K, kWideOk)) {
+int launch_dma_tile(hipStream_t st, const GemmParams& p, int shape) {
+  switch (shape) {
     case 0:
       // both operands stored [k][rows] (weight gradients): four 32-deep stages instead of two 64-deep ones, see
       // launch_wgrad_persistent
@@ -980,8 +981,8 @@ int launch_dma_tile(hipStream_t st, const GemmParams& p) {
       else return launch_dma<256, 256, 2, 4, A_KMAJ, B_KMAJ, 2, EPI, SEG>(st, p);
     case 1: return launch_dma<256, 128, 4, 2, A_KMAJ, B_KMAJ, 3, EPI, SEG>(st, p);
     case 4:
-      if constexpr (kWideOk) return launch_dma<256, 320, 4, 2, A_KMAJ, B_KMAJ, 2, EPI, SEG>(st, p);
-      else return launch_dma<256, 256, 2, 4, A_KMAJ, B_KMAJ, 2, EPI, SEG>(st, p);
+      if constexpr (wide_ok(EPI)) return launch_dma<256, 320, 4, 2, A_KMAJ, B_KMAJ, 2, EPI, SEG>(st, p);
+      else break;
     case 3:
       if constexpr (A_KMAJ) return launch_dma<64, 128, 1, 4, A_KMAJ, B_KMAJ, 3, EPI, SEG>(st, p);
       else break;
@@ -1011,11 +1012,11 @@ int compute_units() {
 
 // Persistent, phase-shifted weight-gradient kernel: when every compute unit gets at least two
 // 256x256 tiles.  The gemm_wgrad tuning switch (0|1) forces the choice (tests, tuning).
-bool use_wgrad_persistent(const GemmParams& p) {
-  if (p.K < 4 * 64) return false;
+bool use_wgrad_persistent(int M, int N, long K) {
+  if (K < 4 * 64) return false;
   if (const int f = tuning(kTuneGemmWgrad); f >= 0) return f == 1;
   if (tuning(kTuneGemmTile) >= 0) return false;
-  return (long)((p.M + 255) / 256) * ((p.N + 255) / 256) >= 2 * 256;
+  return (long)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256;
 }
 
 template <bool SEG>
@@ -1050,10 +1051,10 @@ int launch_wgrad_persistent(hipStream_t st, GemmParams p) {
 // +6 % at 2048, +26 % at 4096), and where the layer's other products take it too: alone, 8192 x 2048 at K = 1024
 // takes 49.7 us (the best other shape 52.2), but 2048 x 2048 (128 tiles) 25.4 against 18.1.  With fewer tiles
 // the smaller shapes win: the products of the W pass of hidden 832, 496 tokens, 38 % less kernel time.  gemm_wgrad = 2 forces it.
-bool use_wgrad_pair(const GemmParams& p) {
+bool use_wgrad_pair(int M, int N, long K) {
   if (const int f = tuning(kTuneGemmWgrad); f >= 0) return f == 2;
   if (tuning(kTuneGemmTile) >= 0) return false;
-  return p.K <= 1024 && (long)((p.M + 255) / 256) * ((p.N + 127) / 128) >= 128;
+  return K <= 1024 && (long)((M + 255) / 256) * ((N + 127) / 128) >= 128;
 }
 
 template <bool SEG>
@@ -1097,15 +1098,24 @@ int scratch_splits(int M, int N, int K) {
 }
 
 // The split with the least time, if it beats the product in one piece.  Partial sums and the second launch cost
-// 4.5 us and 1.6 us per million partial sums (9.1 us with the larger tiles).  Past K = 8192 the products in one piece
-// are slower inside a step, where the weights come from HBM, than their fitted times: 512 x 4096 x 16384 121 / 110 us in
-// one piece (F / B layout), 94 / 92 split; 1024 x 2048 x 8192 inside a step F 69 in one piece, 64 in four ranges, B 55 and 55.
-SplitPlan pick_splits(Layout layout, int M, int N, int K, size_t ws_bytes) {
+// 4.5 us and 1.6 us per million partial sums (9.1 us with the larger tiles).
+//  * Where the product in one piece fills the units (256-row tiles, or more than one round of 128x128 ones) a split
+//    does not pay, whatever the fitted times say: W 3912 x 4104 x 16168 584 us in one piece, 655 in two ranges, F
+//    2176 x 2560 x 10240 140 / 175, W 1408 x 5632 x 13440 224 / 248.
+//  * The fitted times are those of operands in the caches.  Inside a step they come from HBM, and then few workgroups
+//    with a long K loop take 1.3 to 1.5 times as long (shapes 3 and 5 .. 8), 128x128 tiles 1.1 to 1.25 times, partial
+//    products, whose ranges load side by side, about what the fit says: hence the two factors (where the fit puts a
+//    split beyond them it is slower).  With cold operands, one piece / the split picked: F 56 x 4000 x 16000
+//    49.1 / 31.6 us, W 96 x 288 x 12376 50.3 / 16.9, B 632 x 2592 x 10368 70.7 / 62.2.  Over 422 products of layers
+//    with K from 1024 the rule is 1.3 % slower than the best of one piece and six splits.
+SplitPlan pick_splits(Layout layout, int M, int N, int K, int epi, size_t ws_bytes) {
   SplitPlan best = {1, 0, 0};
   if (tuning(kTuneGemmTile) >= 0 || K < 2048) return best;
   double limit;
-  (void)pick_tile(layout, M, N, K, true, &limit);
-  limit *= K < 8192 ? 0.9 : layout == kLayoutF ? 1.25 : 1.15;
+  const int whole = pick_tile(layout, M, N, K, wide_ok(epi), &limit);
+  if (whole == 2 && tiles_of(2, M, N) <= 256) limit *= 0.95;
+  else if (whole == 3 || whole >= 5) limit *= 1.25;
+  else return best;
   const int nkt = (K + 63) / 64;
   for (int shape : {2, 5})
     for (int s : {2, 4, 8}) {
@@ -1124,11 +1134,11 @@ SplitPlan pick_splits(Layout layout, int M, int N, int K, size_t ws_bytes) {
 }
 
 template <bool A_KMAJ, bool B_KMAJ>
-int launch_partial(hipStream_t st, GemmParams p, void* ws, const SplitPlan& plan) {
+int launch_partial(hipStream_t st, GemmParams p, void* ws, const GemmPlan& plan) {
   p.C = ws;
   p.splits = plan.splits;
-  p.k_tiles_per_split = plan.tiles_per_split;
-  if (plan.shape == 5) return launch_dma<64, 64, 2, 2, A_KMAJ, B_KMAJ, 5, kEpiPartial, false, 64, false, true>(st, p);
+  p.k_tiles_per_split = plan.k_tiles_per_split;
+  if (plan.kernel == kPlanSplit + 5) return launch_dma<64, 64, 2, 2, A_KMAJ, B_KMAJ, 5, kEpiPartial, false, 64, false, true>(st, p);
   return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 2, kEpiPartial>(st, p);
 }
 
@@ -1156,35 +1166,66 @@ int launch_reduce(hipStream_t st, const GemmParams& p, const float* ws, int spli
 }
 
 // The layout/epilogue combinations the passes use (and the plain product of each layout) have a
-// fast-path instantiation; returns -100 if this combination has none.
-constexpr int kNoFastPath = -100;
-int launch_fast(hipStream_t st, const GemmParams& p, bool a_kmaj, bool b_kmaj, int epi) {
+// fast-path instantiation.
+bool has_fast_path(bool a_kmaj, bool b_kmaj, int epi) {
+  if (a_kmaj && !b_kmaj)
+    return epi == PMC_EPI_NONE || epi == PMC_EPI_BIAS || epi == PMC_EPI_BIAS_RESID || epi == PMC_EPI_BIAS_GELU || epi == PMC_EPI_BIAS_GELU_GRAD;
+  if (a_kmaj && b_kmaj) return epi == PMC_EPI_NONE || epi == PMC_EPI_DGELU || epi == PMC_EPI_MUL;
+  return !a_kmaj && !b_kmaj && (epi == PMC_EPI_NONE || epi == PMC_EPI_ACCUM_F32);
+}
+
+int launch_fast(hipStream_t st, const GemmParams& p, bool a_kmaj, bool b_kmaj, int epi, int shape) {
   if (a_kmaj && !b_kmaj) {  // F: Y = X . W
     switch (epi) {
-      case PMC_EPI_NONE: return launch_dma_tile<true, false, PMC_EPI_NONE>(st, p);
-      case PMC_EPI_BIAS: return launch_dma_tile<true, false, PMC_EPI_BIAS>(st, p);
-      case PMC_EPI_BIAS_RESID: return launch_dma_tile<true, false, PMC_EPI_BIAS_RESID>(st, p);
-      case PMC_EPI_BIAS_GELU: return launch_dma_tile<true, false, PMC_EPI_BIAS_GELU>(st, p);
-      case PMC_EPI_BIAS_GELU_GRAD: return launch_dma_tile<true, false, PMC_EPI_BIAS_GELU_GRAD>(st, p);
+      case PMC_EPI_NONE: return launch_dma_tile<true, false, PMC_EPI_NONE>(st, p, shape);
+      case PMC_EPI_BIAS: return launch_dma_tile<true, false, PMC_EPI_BIAS>(st, p, shape);
+      case PMC_EPI_BIAS_RESID: return launch_dma_tile<true, false, PMC_EPI_BIAS_RESID>(st, p, shape);
+      case PMC_EPI_BIAS_GELU: return launch_dma_tile<true, false, PMC_EPI_BIAS_GELU>(st, p, shape);
+      case PMC_EPI_BIAS_GELU_GRAD: return launch_dma_tile<true, false, PMC_EPI_BIAS_GELU_GRAD>(st, p, shape);
     }
   } else if (a_kmaj && b_kmaj) {  // B: dX = dY . W^T
     switch (epi) {
-      case PMC_EPI_NONE: return launch_dma_tile<true, true, PMC_EPI_NONE>(st, p);
-      case PMC_EPI_DGELU: return launch_dma_tile<true, true, PMC_EPI_DGELU>(st, p);
-      case PMC_EPI_MUL: return launch_dma_tile<true, true, PMC_EPI_MUL>(st, p);
+      case PMC_EPI_NONE: return launch_dma_tile<true, true, PMC_EPI_NONE>(st, p, shape);
+      case PMC_EPI_DGELU: return launch_dma_tile<true, true, PMC_EPI_DGELU>(st, p, shape);
+      case PMC_EPI_MUL: return launch_dma_tile<true, true, PMC_EPI_MUL>(st, p, shape);
     }
   } else if (!a_kmaj && !b_kmaj) {  // W: dW += X^T . dY
     switch (epi) {
-      case PMC_EPI_NONE: return launch_dma_tile<false, false, PMC_EPI_NONE>(st, p);
-      case PMC_EPI_ACCUM_F32: return launch_dma_tile<false, false, PMC_EPI_ACCUM_F32>(st, p);
+      case PMC_EPI_NONE: return launch_dma_tile<false, false, PMC_EPI_NONE>(st, p, shape);
+      case PMC_EPI_ACCUM_F32: return launch_dma_tile<false, false, PMC_EPI_ACCUM_F32>(st, p, shape);
     }
   }
-  return kNoFastPath;
+  return fail(PMC_ERR_INVALID, "gemm_bf16: no direct-to-LDS kernel for epilogue %d in this layout", epi);
+}
+
+// Kernel of an fp32 read-modify-write product of stored-[k][rows] operands (K: all pieces).
+int wgrad_kernel(int M, int N, long K) {
+  if (use_wgrad_pair(M, N, K)) return kPlanPair;
+  if (use_wgrad_persistent(M, N, K)) return kPlanPersistent;
+  return kPlanTile + pick_tile(kLayoutW, M, N, K, false);
 }
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
 }  // namespace
+
+// Fast path: operands inside the 2 GB window of a buffer descriptor.  A K that is no multiple of 64 only
+// costs it a partly empty last tile.  (Two layers of hidden 2048: 1208 us a step at 1024 tokens; at 1000
+// tokens 1379 us with the weight gradients on the general kernel, 1237 us here.)
+GemmPlan gemm_bf16_plan(const GemmArgs& a) {
+  const bool a_kmaj = !a.trans_a, b_kmaj = a.trans_b;
+  const size_t a_bytes = (size_t)(a.trans_a ? a.K : a.M) * a.lda * 2, b_bytes = (size_t)(a.trans_b ? a.N : a.K) * a.ldb * 2;
+  const GemmPlan general = {kPlanGeneral, 1, 0};
+  if ((!a_kmaj && b_kmaj) || a_bytes >= 0x7fffffffull || b_bytes >= 0x7fffffffull) return general;
+  const Layout layout = layout_of(a_kmaj, b_kmaj);
+  if (a.ws) {
+    const SplitPlan split = pick_splits(layout, a.M, a.N, a.K, a.epilogue, a.ws_bytes);
+    if (split.splits > 1) return {kPlanSplit + split.shape, split.splits, split.tiles_per_split};
+  }
+  if (!has_fast_path(a_kmaj, b_kmaj, a.epilogue)) return general;
+  if (a.epilogue == PMC_EPI_ACCUM_F32) return {wgrad_kernel(a.M, a.N, a.K), 1, 0};
+  return {kPlanTile + pick_tile(layout, a.M, a.N, a.K, true), 1, 0};
+}
 
 int gemm_bf16(hipStream_t st, const GemmArgs& a) {
   if (a.M % 8 || a.N % 8 || a.K % 8) return fail(PMC_ERR_INVALID, "gemm_bf16: M=%d N=%d K=%d must be multiples of 8", a.M, a.N, a.K);
@@ -1203,24 +1244,16 @@ int gemm_bf16(hipStream_t st, const GemmArgs& a) {
   p.nseg = p.seg_k = 0;
   for (int i = 0; i < kMaxSegments; ++i) p.Aseg[i] = p.Bseg[i] = nullptr;
   const bool a_kmaj = !a.trans_a, b_kmaj = a.trans_b;
-  // Fast path: operands inside the 2 GB window of a buffer descriptor.  A K that is no multiple of 64 only
-  // costs it a partly empty last tile.  (Two layers of hidden 2048: 1208 us a step at 1024 tokens; at 1000
-  // tokens 1379 us with the weight gradients on the general kernel, 1237 us here.)
-  const size_t a_bytes = (size_t)(a.trans_a ? a.K : a.M) * a.lda * 2, b_bytes = (size_t)(a.trans_b ? a.N : a.K) * a.ldb * 2;
-  if (a_bytes < 0x7fffffffull && b_bytes < 0x7fffffffull) {
-    const bool split_ok = a.ws && !(a_kmaj == false && b_kmaj == true);
-    const SplitPlan plan = split_ok ? pick_splits(layout_of(a_kmaj, b_kmaj), a.M, a.N, a.K, a.ws_bytes) : SplitPlan{1, 0, 0};
-    if (plan.splits > 1) {
-      int rc = a_kmaj ? (b_kmaj ? launch_partial<true, true>(st, p, a.ws, plan) : launch_partial<true, false>(st, p, a.ws, plan))
-                      : launch_partial<false, false>(st, p, a.ws, plan);
-      if (rc != PMC_OK) return rc;
-      return launch_reduce(st, p, (const float*)a.ws, plan.splits, a.epilogue);
-    }
-    if (!a_kmaj && !b_kmaj && a.epilogue == PMC_EPI_ACCUM_F32 && use_wgrad_pair(p)) return launch_wgrad_pair<false>(st, p);
-    if (!a_kmaj && !b_kmaj && a.epilogue == PMC_EPI_ACCUM_F32 && use_wgrad_persistent(p)) return launch_wgrad_persistent<false>(st, p);
-    const int rc = launch_fast(st, p, a_kmaj, b_kmaj, a.epilogue);
-    if (rc != kNoFastPath) return rc;
+  const GemmPlan plan = gemm_bf16_plan(a);
+  if (plan.splits > 1) {
+    int rc = a_kmaj ? (b_kmaj ? launch_partial<true, true>(st, p, a.ws, plan) : launch_partial<true, false>(st, p, a.ws, plan))
+                    : launch_partial<false, false>(st, p, a.ws, plan);
+    if (rc != PMC_OK) return rc;
+    return launch_reduce(st, p, (const float*)a.ws, plan.splits, a.epilogue);
   }
+  if (plan.kernel == kPlanPair) return launch_wgrad_pair<false>(st, p);
+  if (plan.kernel == kPlanPersistent) return launch_wgrad_persistent<false>(st, p);
+  if (plan.kernel != kPlanGeneral) return launch_fast(st, p, a_kmaj, b_kmaj, a.epilogue, plan.kernel - kPlanTile);
   if (a_kmaj && b_kmaj) return launch_tile<true, true>(st, p, a.epilogue);
   if (a_kmaj && !b_kmaj) return launch_tile<true, false>(st, p, a.epilogue);
   if (!a_kmaj && b_kmaj) return launch_tile<false, true>(st, p, a.epilogue);
@@ -1254,9 +1287,10 @@ int gemm_bf16_grouped_wgrad(hipStream_t st, const GroupedWgradArgs& a) {
     p.Aseg[i] = (const bf16_t*)a.A[j];
     p.Bseg[i] = (const bf16_t*)a.B[j];
   }
-  if (use_wgrad_pair(p)) return launch_wgrad_pair<true>(st, p);
-  if (use_wgrad_persistent(p)) return launch_wgrad_persistent<true>(st, p);
-  return launch_dma_tile<false, false, PMC_EPI_ACCUM_F32, true>(st, p);
+  const int kernel = wgrad_kernel(p.M, p.N, p.K);
+  if (kernel == kPlanPair) return launch_wgrad_pair<true>(st, p);
+  if (kernel == kPlanPersistent) return launch_wgrad_persistent<true>(st, p);
+  return launch_dma_tile<false, false, PMC_EPI_ACCUM_F32, true>(st, p, kernel - kPlanTile);
 }
 
 size_t gemm_scratch_bytes(int dtype, int M, int N, int K) {

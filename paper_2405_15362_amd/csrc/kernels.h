@@ -56,12 +56,14 @@ int gemm_bf16_grouped_wgrad(hipStream_t stream, const GroupedWgradArgs& a);
 size_t gemm_scratch_bytes(int dtype, int M, int N, int K);
 
 // What gemm() launches for a product: host arithmetic only, so that the rules can be tested without a GPU.
-// kernel: kPlanF32 + F32Shape in fp32.
-enum { kPlanF32 = 100 };
+// kernel: in bf16 tiles of a shape (see gemm_bf16.hip), the two weight-gradient kernels, the general kernel, or partial
+// products in tiles of a shape over `splits` ranges of K; kPlanF32 + F32Shape in fp32.
+enum { kPlanTile = 0, kPlanPersistent = 20, kPlanPair = 21, kPlanGeneral = 22, kPlanSplit = 30, kPlanF32 = 100 };
 struct GemmPlan {
   int kernel, splits, k_tiles_per_split;
 };
 GemmPlan gemm_f32_plan(const GemmArgs& a);
+GemmPlan gemm_bf16_plan(const GemmArgs& a);
 
 int gemm(hipStream_t stream, const GemmArgs& a);
 int gemm_f32(hipStream_t stream, const GemmArgs& a);

@@ -259,3 +259,25 @@ def test_fp32_16x16_tiles_fit_one_launch(ta, tb):
     with U.tuned(gemm_tile=4):
         assert U.gemm_plan("f32", ta, tb, 16384, 16384, 64)[0] == U.F32_DIRECT
         assert U.gemm_plan("f32", ta, tb, 65536, 32768, 64)[0] == U.F32_TILE64
+
+
+# (layout, M, N, K), us in one piece and in the split that was picked there (operands from HBM)
+ONE_PIECE = [("W", 1088, 4352, 8464, 115, 149), ("F", 2176, 2560, 10240, 140, 175), ("F", 1432, 3744, 14976, 191, 238),
+             ("W", 1408, 4224, 13440, 185, 223), ("W", 3912, 4104, 16168, 584, 655), ("W", 1024, 3072, 10816, 100, 115),
+             ("B", 824, 3024, 12096, 99, 110), ("B", 1024, 2048, 8192, 55, 55)]
+SPLIT = [("W", 96, 288, 12376, 50.3, 16.9), ("F", 56, 4000, 16000, 49.1, 31.6), ("F", 1024, 2048, 8192, 69, 64),
+         ("F", 512, 4096, 16384, 121, 94), ("W", 256, 768, 8048, 35.8, 17.6), ("B", 384, 5504, 16512, 151, 125)]
+
+
+@pytest.mark.parametrize("layout,M,N,K,whole_us,split_us", ONE_PIECE + SPLIT)
+def test_bf16_products_are_split_along_k_where_that_is_faster(layout, M, N, K, whole_us, split_us):
+    ta, tb, epi = {"F": (False, False, P.EPI_BIAS), "B": (False, True, P.EPI_NONE), "W": (True, False, P.EPI_ACCUM_F32)}[layout]
+    plan = U.gemm_plan("bf16", ta, tb, M, N, K, epi, ws_bytes=1 << 40)
+    assert (plan[1] > 1) == (split_us < whole_us), plan
+
+
+def test_bf16_plan_of_layouts_without_a_direct_path():
+    assert U.gemm_plan("bf16", True, True, 512, 512, 512)[0] == U.PLAN_GENERAL
+    assert U.gemm_plan("bf16", False, False, 512, 512, 512, P.EPI_MUL)[0] == U.PLAN_GENERAL
+    assert U.gemm_plan("bf16", False, False, 1 << 20, 512, 1024)[0] == U.PLAN_GENERAL       # 2 GB of A
+    assert U.gemm_plan("bf16", False, False, (1 << 20) - 8, 512, 1024)[0] < 9
