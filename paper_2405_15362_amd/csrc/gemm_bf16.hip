@@ -28,6 +28,7 @@
 // epilogue use 8/16-byte accesses.  Workgroup ids are remapped so that the ids resident on one XCD
 // (they are dealt round-robin over the 8 XCDs) cover a compact group of tiles and share operand
 // panels in that XCD's L2.
+#include <algorithm>
 #include <cstdlib>
 
 #include "dev_common.h"
@@ -1102,20 +1103,23 @@ int scratch_splits(int M, int N, int K) {
 //  * Where the product in one piece fills the units (256-row tiles, or more than one round of 128x128 ones) a split
 //    does not pay, whatever the fitted times say: W 3912 x 4104 x 16168 584 us in one piece, 655 in two ranges, F
 //    2176 x 2560 x 10240 140 / 175, W 1408 x 5632 x 13440 224 / 248.
-//  * The fitted times are those of operands in the caches.  Inside a step they come from HBM, and then few workgroups
-//    with a long K loop take 1.3 to 1.5 times as long (shapes 3 and 5 .. 8), 128x128 tiles 1.1 to 1.25 times, partial
-//    products, whose ranges load side by side, about what the fit says: hence the two factors (where the fit puts a
-//    split beyond them it is slower).  With cold operands, one piece / the split picked: F 56 x 4000 x 16000
-//    49.1 / 31.6 us, W 96 x 288 x 12376 50.3 / 16.9, B 632 x 2592 x 10368 70.7 / 62.2.  Over 422 products of layers
-//    with K from 1024 the rule is 1.3 % slower than the best of one piece and six splits.
+//  * The fitted times are those of operands in the caches.  From HBM, few workgroups with a long K loop take 1.3 to 1.5
+//    times as long (shapes 3 and 5 .. 8), 128x128 tiles 1.1 to 1.25 times, partial products, whose ranges load side by
+//    side, about what the fit says.  Inside a step an operand comes from HBM where it is large against the 256 MB
+//    memory-side cache (its layer has ten times these bytes with the other weights and the gradients): from 32 MB on the
+//    small shapes give way to a split of up to 1.25 times their fitted time.  Below that the operands may be cached, where
+//    a split has to be clearly better.  Time in the split picked / in one piece over 422 products of layers, K from 1024:
+//    32 MB and more, from HBM: F 0.90, B 0.93, W 0.59, worst 1.10 (40 x 16680 x 5560: 54 -> 60 us); smaller ones,
+//    cached: 0.98, 1.00, 0.90, worst 1.07.  From HBM, one piece / split: F 56 x 4000 x 16000 49.1 / 31.6 us,
+//    W 96 x 288 x 12376 50.3 / 16.9; inside a step F 1024 x 2048 x 8192 69 / 64, F 512 x 4096 x 16384 121 / 94.
 SplitPlan pick_splits(Layout layout, int M, int N, int K, int epi, size_t ws_bytes) {
   SplitPlan best = {1, 0, 0};
   if (tuning(kTuneGemmTile) >= 0 || K < 2048) return best;
   double limit;
   const int whole = pick_tile(layout, M, N, K, wide_ok(epi), &limit);
-  if (whole == 2 && tiles_of(2, M, N) <= 256) limit *= 0.95;
-  else if (whole == 3 || whole >= 5) limit *= 1.25;
-  else return best;
+  const bool small = whole == 3 || whole >= 5;
+  if (!small && (whole != 2 || tiles_of(2, M, N) > 256)) return best;
+  limit *= small && (double)std::max(M, N) * K * sizeof(bf16_t) >= 32e6 ? 1.25 : 0.85;
   const int nkt = (K + 63) / 64;
   for (int shape : {2, 5})
     for (int s : {2, 4, 8}) {

@@ -261,12 +261,14 @@ def test_fp32_16x16_tiles_fit_one_launch(ta, tb):
         assert U.gemm_plan("f32", ta, tb, 65536, 32768, 64)[0] == U.F32_TILE64
 
 
-# (layout, M, N, K), us in one piece and in the split that was picked there (operands from HBM)
+# (layout, M, N, K), us in one piece and in the split that was picked there (operands from HBM; cached where the larger is below 32 MB)
 ONE_PIECE = [("W", 1088, 4352, 8464, 115, 149), ("F", 2176, 2560, 10240, 140, 175), ("F", 1432, 3744, 14976, 191, 238),
              ("W", 1408, 4224, 13440, 185, 223), ("W", 3912, 4104, 16168, 584, 655), ("W", 1024, 3072, 10816, 100, 115),
-             ("B", 824, 3024, 12096, 99, 110), ("B", 1024, 2048, 8192, 55, 55)]
+             ("B", 824, 3024, 12096, 99, 110), ("B", 1024, 2048, 8192, 55, 55), ("F", 672, 3080, 12320, 92, 98),
+             ("F", 376, 1792, 8064, 26.0, 26.5), ("B", 376, 1792, 8064, 23.9, 25.9), ("F", 40, 1088, 4352, 9.3, 10.1),
+             ("W", 128, 512, 3432, 8.1, 10.6)]
 SPLIT = [("W", 96, 288, 12376, 50.3, 16.9), ("F", 56, 4000, 16000, 49.1, 31.6), ("F", 1024, 2048, 8192, 69, 64),
-         ("F", 512, 4096, 16384, 121, 94), ("W", 256, 768, 8048, 35.8, 17.6), ("B", 384, 5504, 16512, 151, 125)]
+         ("F", 512, 4096, 16384, 121, 94), ("F", 256, 2048, 8192, 39, 36), ("W", 256, 768, 8048, 35.8, 17.6), ("B", 40, 5560, 16680, 69.7, 57.9)]
 
 
 @pytest.mark.parametrize("layout,M,N,K,whole_us,split_us", ONE_PIECE + SPLIT)
