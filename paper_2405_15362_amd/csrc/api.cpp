@@ -185,11 +185,28 @@ WorkspaceLayout workspace_of(const pmc_chunk_cfg& c) {
   const size_t pf = k::layernorm_backward_scratch_floats(t, c.hidden);
   w.partial_stride = align256(pf * sizeof(float));
   at += w.partial_stride * (size_t)std::min(2 * c.layers, (int)k::LnPartialJobs::kMax);
-  // split-K partial products of the skinny projections (F and B write [tokens, hidden] outputs)
+  // split-K partial products: room for the plan of every product of the three passes (the queued weight gradients
+  // and those on the second stream are not split)
   size_t g = 0;
   const int h = c.hidden, f = c.ffn;
-  const int shapes[7][3] = {{t, 3 * h, h}, {t, h, h}, {t, f, h}, {t, h, f}, {t, h, 3 * h}, {f, h, t}, {h, 3 * h, t}};
-  for (const auto& sh : shapes) g = std::max(g, k::gemm_scratch_bytes(c.dtype, sh[0], sh[1], sh[2]));
+  auto product = [&](bool ta, bool tb, int M, int N, int K, int epi) {
+    k::GemmArgs p;
+    p.dtype = c.dtype; p.trans_a = ta; p.trans_b = tb;
+    p.M = M; p.N = N; p.K = K; p.lda = ta ? M : K; p.ldb = tb ? K : N; p.ldc = N; p.epilogue = epi;
+    g = std::max(g, k::gemm_scratch_bytes(p));
+  };
+  product(false, false, t, 3 * h, h, PMC_EPI_BIAS);
+  product(false, false, t, h, h, PMC_EPI_BIAS_RESID);
+  product(false, false, t, f, h, PMC_EPI_BIAS_GELU_GRAD);
+  product(false, false, t, h, f, PMC_EPI_BIAS_RESID);
+  product(false, true, t, f, h, PMC_EPI_MUL);
+  product(false, true, t, h, f, PMC_EPI_NONE);
+  product(false, true, t, h, h, PMC_EPI_NONE);
+  product(false, true, t, h, 3 * h, PMC_EPI_NONE);
+  product(true, false, f, h, t, PMC_EPI_ACCUM_F32);
+  product(true, false, h, f, t, PMC_EPI_ACCUM_F32);
+  product(true, false, h, h, t, PMC_EPI_ACCUM_F32);
+  product(true, false, h, 3 * h, t, PMC_EPI_ACCUM_F32);
   w.gemm = at;
   w.gemm_bytes = g;
   at += align256(g);
@@ -807,6 +824,9 @@ int pmc_test_gemm_plan(int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t 
   out[2] = plan.k_tiles_per_split;
   return PMC_OK;
 }
+
+// For the library's own tests (not in pmc.h): the part of a pass's workspace that its split products use.
+size_t pmc_test_pass_gemm_scratch(const pmc_chunk_cfg* cfg) { return check_cfg(cfg) == PMC_OK ? workspace_of(*cfg).gemm_bytes : 0; }
 
 int pmc_gemm_grouped_wgrad(pmc_ctx* ctx, int32_t M, int32_t N, int32_t K, int32_t count, const void* const* a, int32_t lda,
                            const void* const* b, int32_t ldb, float* C, int32_t ldc) {

@@ -1083,21 +1083,6 @@ struct SplitPlan {
   int splits, tiles_per_split, shape;  // splits = 1: no split
 };
 
-// Largest number of ranges the workspace of a pass has room for.
-int scratch_splits(int M, int N, int K) {
-  if (tuning(kTuneGemmTile) >= 0) return 1;
-  const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
-  if (tiles >= 192 || (K < 8192 && (long)((M + 63) / 64) * ((N + 127) / 128) >= 192)) return 1;
-  const int nkt = (K + 63) / 64;
-  int best = 1;
-  for (int s : {2, 4, 8}) {
-    if (nkt % s || nkt / s < 4) continue;
-    best = s;
-    if (tiles * s >= 384) break;
-  }
-  return best;
-}
-
 // The split with the least time, if it beats the product in one piece.  Partial sums and the second launch cost
 // 4.5 us and 1.6 us per million partial sums (9.1 us with the larger tiles).
 //  * Where the product in one piece fills the units (256-row tiles, or more than one round of 128x128 ones) a split
@@ -1297,10 +1282,12 @@ int gemm_bf16_grouped_wgrad(hipStream_t st, const GroupedWgradArgs& a) {
   return launch_dma_tile<false, false, PMC_EPI_ACCUM_F32, true>(st, p, kernel - kPlanTile);
 }
 
-size_t gemm_scratch_bytes(int dtype, int M, int N, int K) {
-  if (dtype != PMC_BF16 || K % 64 || M <= 0 || N <= 0) return 0;
-  const int splits = scratch_splits(M, N, K);
-  return splits > 1 ? (size_t)splits * M * N * sizeof(float) : 0;
+size_t gemm_scratch_bytes(GemmArgs a) {
+  if (a.dtype != PMC_BF16) return 0;
+  a.ws = &a;  // any non-NULL pointer: nothing is launched
+  a.ws_bytes = (size_t)-1;
+  const GemmPlan plan = gemm_bf16_plan(a);
+  return plan.splits > 1 ? (size_t)plan.splits * a.M * a.N * sizeof(float) : 0;
 }
 
 }  // namespace k

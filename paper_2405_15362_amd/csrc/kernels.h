@@ -52,8 +52,8 @@ struct GroupedWgradArgs {
 };
 int gemm_bf16_grouped_wgrad(hipStream_t stream, const GroupedWgradArgs& a);
 
-// Scratch a product of this shape can use (0: none).
-size_t gemm_scratch_bytes(int dtype, int M, int N, int K);
+// Scratch for the plan that this product gets where there is room for any (0: it is not split).
+size_t gemm_scratch_bytes(GemmArgs a);
 
 // What gemm() launches for a product: host arithmetic only, so that the rules can be tested without a GPU.
 // kernel: in bf16 tiles of a shape (see gemm_bf16.hip), the two weight-gradient kernels, the general kernel, or partial

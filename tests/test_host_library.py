@@ -278,6 +278,39 @@ def test_bf16_products_are_split_along_k_where_that_is_faster(layout, M, N, K, w
     assert (plan[1] > 1) == (split_us < whole_us), plan
 
 
+def test_the_workspace_of_a_pass_holds_the_plan_of_each_of_its_products():
+    """Every product of a pass gets, with the scratch that the pass's workspace has, the plan it gets with unlimited
+    scratch, whatever the sizes (token counts that are no multiple of 64, ranges of unequal length), and the scratch is
+    no larger than the largest plan needs."""
+    import ctypes
+    import random
+    P.lib.pmc_test_pass_gemm_scratch.restype = ctypes.c_size_t
+    rng = random.Random(2405)
+    sizes = [(16, 2880, 12480), (288, 6640, 26560), (512, 4096, 16392), (512, 4096, 16384), (1024, 2048, 8192)]
+    sizes += [(8 * round(2 ** rng.uniform(1, 9)), 8 * round(2 ** rng.uniform(3, 10.4)), 8 * round(2 ** rng.uniform(4, 11.8)))
+              for _ in range(400)]
+    split = 0
+    for t, h, f in sizes:
+        cfg = P.make_cfg(1, h, max(1, h // 8), f, t)
+        assert P.pmc_pass_workspace_bytes(cfg) > 0
+        room = P.lib.pmc_test_pass_gemm_scratch(ctypes.byref(cfg))
+        most = 0
+        for ta, tb, M, N, K, epi in [(0, 0, t, 3 * h, h, P.EPI_BIAS), (0, 0, t, h, h, P.EPI_BIAS_RESID),
+                                     (0, 0, t, f, h, P.EPI_BIAS_GELU_GRAD), (0, 0, t, h, f, P.EPI_BIAS_RESID),
+                                     (0, 1, t, f, h, P.EPI_MUL), (0, 1, t, h, f, P.EPI_NONE), (0, 1, t, h, h, P.EPI_NONE),
+                                     (0, 1, t, h, 3 * h, P.EPI_NONE), (1, 0, f, h, t, P.EPI_ACCUM_F32),
+                                     (1, 0, h, f, t, P.EPI_ACCUM_F32), (1, 0, h, h, t, P.EPI_ACCUM_F32),
+                                     (1, 0, h, 3 * h, t, P.EPI_ACCUM_F32)]:
+            free = U.gemm_plan("bf16", ta, tb, M, N, K, epi, ws_bytes=1 << 62)
+            assert U.gemm_plan("bf16", ta, tb, M, N, K, epi, ws_bytes=room) == free, (t, h, f, M, N, K)
+            if free[1] > 1:
+                split += 1
+                most = max(most, free[1] * M * N * 4)
+                assert (free[1] - 1) * free[2] < (K + 63) // 64 <= free[1] * free[2]      # no empty range, nothing left over
+        assert room == most
+    assert split > 100
+
+
 def test_bf16_plan_of_layouts_without_a_direct_path():
     assert U.gemm_plan("bf16", True, True, 512, 512, 512)[0] == U.PLAN_GENERAL
     assert U.gemm_plan("bf16", False, False, 512, 512, 512, P.EPI_MUL)[0] == U.PLAN_GENERAL
