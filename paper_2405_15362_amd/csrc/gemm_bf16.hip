@@ -1049,13 +1049,16 @@ int launch_wgrad_persistent(hipStream_t st, GemmParams p) {
 // The two-workgroup kernel pays 1.5x the operand traffic of 256x256 tiles and a barrier every 16 matrix
 // instructions; it wins where the K loop is short, so that a tile's ring fill and read-modify-write
 // epilogue weigh as much as its K loop (measured on whole steps: -5 % of the W pass at 1024 tokens,
-// +6 % at 2048, +26 % at 4096), and where the layer's other products take it too: alone, 8192 x 2048 at K = 1024
-// takes 49.7 us (the best other shape 52.2), but 2048 x 2048 (128 tiles) 25.4 against 18.1.  With fewer tiles
-// the smaller shapes win: the products of the W pass of hidden 832, 496 tokens, 38 % less kernel time.  gemm_wgrad = 2 forces it.
+// +6 % at 2048, +26 % at 4096).  It does not win alone (2048 x 2048 at K = 1024 takes 27.4 us, 18.3 in 128x128
+// tiles; 8192 x 2048 48.4 against 51.2) but beside its own kind on the second stream, so all four products of a layer
+// take it or none.  What they share is the smaller side, hidden: steps of two layers at 512 / 1000 / 1024 tokens with it
+// everywhere against nowhere, hidden 1024 +5 / +4 / +5 %, 1152 +1 / +3 / +3 %, 1280 0 / +2 / +2 %, 1408 -1 / -1 / -1 %,
+// 1664 -2 / -2 / -2 %, 2560 -2 / -1 / -2 %; a bar on the tile count, which some of the products of hidden 1024 .. 1920
+// passed, cost 1 to 3 %.  gemm_wgrad = 2 forces it.
 bool use_wgrad_pair(int M, int N, long K) {
   if (const int f = tuning(kTuneGemmWgrad); f >= 0) return f == 2;
   if (tuning(kTuneGemmTile) >= 0) return false;
-  return K <= 1024 && (long)((M + 255) / 256) * ((N + 127) / 128) >= 128;
+  return K <= 1024 && std::min(M, N) > 1280;
 }
 
 template <bool SEG>
