@@ -22,6 +22,22 @@ def ctx():
     P.pmc_destroy(c)
 
 
+def _nan_past_k(key, rows, K, k_fast, scale):
+    """A bf16 operand stored [rows, K] (k_fast) or [K, rows] as a view of a buffer that holds NaN everywhere past K, so that
+    a value read from there cannot go unnoticed; and its values as [rows, K] in float64."""
+    m = mat(key, (rows, K) if k_fast else (K, rows), "bf16", scale)
+    big = torch.full((rows, K + 64) if k_fast else (K + 64, rows), float("nan"), dtype=torch.bfloat16, device="cuda")
+    v = big[:, :K] if k_fast else big[:K]
+    v.copy_(dev(m, "bf16"))
+    return v, (m if k_fast else m.T).astype(np.float64)
+
+
+def _gemm_views(ctx, ta, tb, M, N, K, a, b, c, epi):
+    rc = P.lib.pmc_gemm(ctx, P.PMC_BF16, int(ta), int(tb), M, N, K, a.data_ptr(), a.stride(0), b.data_ptr(), b.stride(0),
+                        c.data_ptr(), c.stride(0), epi, None, None, None)
+    assert rc == 0
+
+
 def _gemm_case(ctx, dtype, ta, tb, M, N, K, epi):
     key = (dtype, ta, tb, M, N, K, epi)
     print("gemm case", key, flush=True)
@@ -152,20 +168,36 @@ def test_gemm_bf16_direct_to_lds_path(ctx, ta, tb, epis):
                                         (False, True, (P.EPI_NONE, P.EPI_DGELU, P.EPI_MUL)),
                                         (True, False, (P.EPI_ACCUM_F32,))])
 def test_gemm_bf16_split_k(ctx, ta, tb, epis):
-    """Skinny products are cut along K into fp32 partials that a second kernel adds in a fixed
-    order; the result must also be identical from run to run."""
+    """Long K and few tiles: K is cut into ranges whose fp32 partial products (in 128x128 or 64x64 tiles) a second kernel
+    adds in a fixed order; the result must also be identical from run to run, and close to the product in one piece.
+    Equal and unequal ranges, the last one ending in a whole or a partial K tile, on operands with NaN past K."""
     for epi in epis:
-        _gemm_case(ctx, "bf16", ta, tb, 512, 1024, 1024, epi)      # 4 splits
-        _gemm_case(ctx, "bf16", ta, tb, 136, 264, 4096, epi)       # 8 splits, ragged tiles
-    a = dev(mat(("sk", "a"), (1024, 256) if ta else (256, 1024), "bf16"), "bf16")
-    b = dev(mat(("sk", "b"), (512, 1024) if tb else (1024, 512), "bf16", 0.05), "bf16")
-    outs = []
-    for _ in range(3):
-        c = torch.zeros(256, 512, device="cuda", dtype=torch.bfloat16)
-        P.pmc_gemm(ctx, a, b, c, ta, tb)
-        outs.append(c)
-    torch.cuda.synchronize()
-    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+        _gemm_case(ctx, "bf16", ta, tb, 512, 1024, 1024, epi)      # K too short for a split
+        _gemm_case(ctx, "bf16", ta, tb, 136, 264, 4096, epi)       # cut only where both operands are stored [k][rows]
+    layout_epi = P.EPI_ACCUM_F32 if ta else epis[0]
+    # M, N, K, tile of the partial products, ranges
+    for M, N, K, shape, ranges in ((304, 3272, 6816, 2, 4), (392, 2544, 6384, 2, 4), (144, 3272, 11576, 2, 8), (144, 3272, 11584, 2, 8),
+                                   (72, 3256, 5328, 5, 2), (72, 2992, 5792, 5, 2), (16, 8, 7880, 5, 8), (64, 8, 8704, 5, 8)):
+        for epi in epis:
+            plan = U.gemm_plan("bf16", ta, tb, M, N, K, epi, ws_bytes=256 << 20)
+            assert plan[:2] == (U.PLAN_SPLIT + shape, ranges), (M, N, K, plan)
+        for epi in epis if M * N * K < 3e9 else epis[-1:]:
+            _gemm_case(ctx, "bf16", ta, tb, M, N, K, epi)
+        key = ("split k", ta, tb, M, N, K)
+        a, A = _nan_past_k(key + ("a",), M, K, not ta, 1.0)
+        b, B = _nan_past_k(key + ("b",), N, K, tb, 0.05)
+        accum = layout_epi == P.EPI_ACCUM_F32
+        c0 = mat(key + ("c0",), (M, N), "f32")
+        outs = []
+        for tile in (None, None, 2):                               # a forced tile is never split
+            with tuned(gemm_tile=tile):
+                c = dev(c0 if accum else np.zeros((M, N)), "f32" if accum else "bf16")
+                _gemm_views(ctx, ta, tb, M, N, K, a, b, c, P.EPI_ACCUM_F32 if accum else P.EPI_NONE)
+                outs.append(c)
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], outs[1]), key
+        assert_close(host(outs[0]), A @ B.T + (c0 if accum else 0.0), "f32" if accum else "bf16", str(key))
+        assert rel_l2(host(outs[0]), host(outs[2])) <= (1e-6 if accum else 3e-3), key   # fp32 sums in another order; rounding to bf16
 
 
 def test_gemm_bf16_weight_gradient_persistent(ctx, tune):
@@ -309,9 +341,8 @@ def test_gemm_bf16_largest_workload_shapes(ctx):
                                         (True, False, (P.EPI_NONE, P.EPI_ACCUM_F32))])
 def test_gemm_bf16_random_shapes(ctx, ta, tb, epis):
     """Seeded random shapes in the library's own choice of kernel and tile: M and N any multiple of 8
-    up to a few tiles (ragged edges in both), K in whole 64-wide tiles (direct-to-LDS kernel, split K
-    where the library picks it) or any multiple of 8 (general kernel); the epilogue drawn from those
-    the layout is used with."""
+    up to a few tiles (ragged edges in both), K in whole 64-wide tiles or any multiple of 8 (a partial
+    last tile), split where the library picks it; the epilogue drawn from those the layout is used with."""
     rng = np.random.default_rng(20240515 + 2 * ta + tb)
     for i in range(14):
         M, N = (int(8 * rng.integers(1, 190)) for _ in range(2))
@@ -327,16 +358,8 @@ def test_gemm_bf16_partial_last_k_tile(ctx, tune, ta, tb, epi, K):
     read from there cannot go unnoticed."""
     M, N = 328, 200
     key = ("k tail", ta, tb, K)
-
-    def view(name, rows, k_fast, scale):
-        m = mat(key + (name,), (rows, K) if k_fast else (K, rows), "bf16", scale)
-        big = torch.full((rows, K + 64) if k_fast else (K + 64, rows), float("nan"), dtype=torch.bfloat16, device="cuda")
-        v = big[:, :K] if k_fast else big[:K]
-        v.copy_(dev(m, "bf16"))
-        return v, (m if k_fast else m.T).astype(np.float64)
-
-    a, A = view("a", M, not ta, 1.0)
-    b, B = view("b", N, tb, 0.05)
+    a, A = _nan_past_k(key + ("a",), M, K, not ta, 1.0)
+    b, B = _nan_past_k(key + ("b",), N, K, tb, 0.05)
     c0 = mat(key + ("c0",), (M, N), "f32")
     accum = epi == P.EPI_ACCUM_F32
     ref = A @ B.T + (c0 if accum else 0.0)
@@ -344,20 +367,81 @@ def test_gemm_bf16_partial_last_k_tile(ctx, tune, ta, tb, epi, K):
         print("k tail", key, switches, flush=True)
         tune(**switches)
         c = dev(c0, "f32" if accum else "bf16")
-        rc = P.lib.pmc_gemm(ctx, P.PMC_BF16, int(ta), int(tb), M, N, K, a.data_ptr(), a.stride(0), b.data_ptr(), b.stride(0),
-                            c.data_ptr(), N, epi, None, None, None)
+        _gemm_views(ctx, ta, tb, M, N, K, a, b, c, epi)
         torch.cuda.synchronize()
         tuned.reset()
-        assert rc == 0
         assert_close(host(c), ref, "bf16", f"{key} {switches}")
+
+
+# sizes of which every layout takes the shape; B adds the 64x128 tile whose waves split K, with odd and even numbers of K tiles
+SMALL_TILES = [(7, 376, 8, 8), (6, 1160, 200, 40), (7, 8, 376, 104), (6, 200, 1160, 104), (5, 1160, 392, 200), (7, 376, 8, 584),
+               (6, 1160, 200, 1000), (5, 1176, 392, 1000), (7, 8, 376, 2040), (5, 1160, 392, 2040), (6, 200, 1168, 2040)]
+
+
+@pytest.mark.parametrize("ta,tb,shape,M,N,K", [(ta, tb, *c) for ta, tb in ((False, False), (False, True), (True, False)) for c in SMALL_TILES] +
+                         [(False, True, 8, 584, 1712, 4496), (False, True, 8, 424, 2336, 4456)])
+def test_gemm_bf16_k_split_tiles_with_a_partial_last_k_tile(ctx, ta, tb, shape, M, N, K):
+    """The tiles whose four waves split a K tile (64x64, 32x64, 32x32, 64x128), in the library's own choice: shorter than
+    one 16-wide step, than one tile, fewer tiles than ring stages, many, on operands with NaN past K; ragged M and N;
+    the same bits from run to run."""
+    epi = P.EPI_ACCUM_F32 if ta else P.EPI_NONE
+    assert U.gemm_plan("bf16", ta, tb, M, N, K, epi, ws_bytes=256 << 20)[0] == U.PLAN_TILE + shape
+    key = ("k-split tile", ta, tb, M, N, K)
+    print(key, flush=True)
+    a, A = _nan_past_k(key + ("a",), M, K, not ta, 1.0)
+    b, B = _nan_past_k(key + ("b",), N, K, tb, 0.05)
+    c0 = mat(key + ("c0",), (M, N), "f32")
+    outs = [dev(c0, "f32" if ta else "bf16") for _ in range(2)]
+    for c in outs:
+        _gemm_views(ctx, ta, tb, M, N, K, a, b, c, epi)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])
+    assert_close(host(outs[0]), A @ B.T + (c0 if ta else 0.0), "f32" if ta else "bf16", str(key))
+
+
+@pytest.mark.parametrize("ta,tb,epi", [(False, False, P.EPI_BIAS_RESID), (False, False, P.EPI_BIAS_GELU_GRAD), (False, True, P.EPI_MUL)])
+@pytest.mark.parametrize("M,N,K", [(72, 200, 104), (264, 520, 1000), (520, 1032, 104)])
+def test_gemm_bf16_epilogue_operands_aligned_to_eight_bytes(ctx, ta, tb, epi, M, N, K):
+    """Bias, residual and second output need 8-byte alignment and a pitch in whole groups of four elements, no more, also
+    on the paths that a partial last K tile takes."""
+    key = ("eight bytes", ta, tb, epi, M, N, K)
+    print(key, flush=True)
+    ldc = N + 4
+
+    def off(m):                                          # rows of pitch N + 4 starting 8 bytes past a 16-byte boundary
+        big = torch.zeros(m.shape[0] * ldc + 8, dtype=torch.bfloat16, device="cuda")
+        v = torch.as_strided(big, m.shape, (ldc, 1), 4)
+        v.copy_(dev(m, "bf16"))
+        assert v.data_ptr() % 16 == 8
+        return v
+
+    a, b = mat(key + ("a",), (M, K), "bf16"), mat(key + ("b",), (N, K) if tb else (K, N), "bf16", 0.05)
+    bias, extra = mat(key + ("bias",), (1, N), "bf16"), mat(key + ("x",), (M, N), "bf16")
+    ref = a.astype(np.float64) @ (b.T if tb else b).astype(np.float64)
+    c = torch.zeros(M, ldc, dtype=torch.bfloat16, device="cuda")
+    bias_d, extra_d = off(bias), off(extra)
+    da, db = dev(a, "bf16"), dev(b, "bf16")
+    rc = P.lib.pmc_gemm(ctx, P.PMC_BF16, int(ta), int(tb), M, N, K, da.data_ptr(), K, db.data_ptr(), db.stride(0), c.data_ptr(), ldc,
+                        epi, bias_d.data_ptr(), extra_d.data_ptr(), extra_d.data_ptr())
+    torch.cuda.synchronize()
+    assert rc == 0
+    if epi == P.EPI_BIAS_RESID:
+        want = ref + bias + extra
+    elif epi == P.EPI_MUL:
+        want = ref * extra
+    else:
+        want = OL.gelu_grad(ref + bias)
+        assert_close(host(extra_d), OL.gelu(ref + bias), "bf16", str(key))
+    assert_close(host(c)[:, :N], want, "bf16", str(key))
+    assert not bool(c[:, N:].any())                      # nothing past the row
 
 
 @pytest.mark.parametrize("ta,tb,epis", [(False, False, (P.EPI_BIAS, P.EPI_BIAS_RESID, P.EPI_BIAS_GELU_GRAD)),
                                         (False, True, (P.EPI_NONE, P.EPI_DGELU, P.EPI_MUL)),
                                         (True, False, (P.EPI_NONE, P.EPI_ACCUM_F32))])
 # M, N, K: one tile, shorter than a 16-wide step, fewer K tiles than ring stages, odd and even numbers of K tiles with a
-# partial last one (32x32, 32x64 and 64x64 tiles whose waves split K); 128x128 tiles with a four-stage ring; K ranges
-# of unequal length (partial sums of 64x64 and 128x128 tiles, the last range ending in a partial K tile)
+# partial last one (32x32, 32x64 and 64x64 tiles whose waves split K); 128x128 tiles with a four-stage ring; long K, cut
+# into ranges or not, with a partial last K tile
 @pytest.mark.parametrize("M,N,K", [(8, 8, 8), (40, 24, 104), (72, 200, 1000), (192, 256, 1088), (264, 520, 584), (488, 840, 840),
                                    (1032, 1000, 392), (1000, 3080, 456), (72, 136, 16392), (264, 1032, 9160)])
 def test_gemm_bf16_library_choice_of_small_tiles(ctx, ta, tb, epis, M, N, K):

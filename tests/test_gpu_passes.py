@@ -8,7 +8,7 @@ import synth
 from oracle import layer as OL
 from oracle import schedule as OS
 from paper_2405_15362_amd import runtime as R
-from gpu_util import assert_close, dev, host, oracle_chunk, rel_l2, tol
+from gpu_util import assert_close, dev, host, oracle_chunk, rel_l2, tol, tuned
 
 pytestmark = pytest.mark.gpu
 
@@ -35,7 +35,7 @@ CASES = {
 }
 
 
-def _run_fbw(cfg, tag, n_mb=1, defer=False):
+def _run_fbw(cfg, tag, n_mb=1, defer=False, before_w=None):
     params = synth.chunk_params(cfg, tag)
     ctx = R.Context(R.cfg_from_synth(cfg), slabs=n_mb)
     ch = ctx.add_chunk(params, cfg.dtype)
@@ -53,6 +53,8 @@ def _run_fbw(cfg, tag, n_mb=1, defer=False):
         for j in range(n_mb):
             P.stage_backward_input(ch.handle, j, dev(dys[j], cfg.dtype), dxs[j])
         assert P.pmc_pool_live_slabs(ctx.ctx) == n_mb
+        if before_w:
+            before_w()
         P.stage_backward_weight(ch.handle, list(range(n_mb)))
     torch.cuda.synchronize()
     assert P.pmc_pool_live_slabs(ctx.ctx) == 0 and P.pmc_pool_peak_slabs(ctx.ctx) == (n_mb if defer else 1)
@@ -140,6 +142,29 @@ def test_queued_w_groups_larger_than_the_maximum():
         for l in range(cfg.layers):
             for k in OL.PARAM_NAMES:
                 assert_close(grads[l][k], total[l][k], cfg.dtype, f"{name} L{l}.{k}")
+
+
+@pytest.mark.parametrize("tokens", [8, 40, 104, 1000])
+def test_queued_w_of_ragged_token_counts_in_every_weight_gradient_kernel(tokens, tune):
+    """Queued microbatches whose token count fills no K tile: a piece boundary inside a K tile (64 or 32 deep) for the
+    tiled, the persistent (from 256 tokens in all; its rotated start) and the two-workgroup kernel and for every forced
+    tile.  The rows after a piece are other tensors of its slab, so a wrong tail would show in the sums, which must
+    agree with the microbatches' own products up to fp32 summation order."""
+    cfg = synth.ChunkCfg(layers=1, hidden=320, heads=5, ffn=584, seq=tokens, dtype="bf16")
+    n_mb = 3
+    params, xs, dys, (_, _, one_by_one) = _run_fbw(cfg, "ragged queue", n_mb, defer=False)
+    total = OL.zero_grads(OL.cast_params(params))
+    for j in range(n_mb):
+        _, _, ln, wg = oracle_chunk(cfg, params, xs[j], dys[j])
+        OL.accumulate(total, ln, wg)
+    for k in OL.PARAM_NAMES:
+        assert_close(one_by_one[0][k], total[0][k], "bf16", f"{tokens} {k}")
+    for switches in [{}] + [{"gemm_wgrad": w} for w in range(3)] + [{"gemm_wgrad": 0, "gemm_tile": t} for t in range(5)]:
+        print("ragged queue", tokens, switches, flush=True)
+        _, _, _, (_, _, queued) = _run_fbw(cfg, "ragged queue", n_mb, defer=True, before_w=lambda: tune(**switches))
+        tuned.reset()
+        for k in OL.PARAM_NAMES:
+            assert rel_l2(queued[0][k], one_by_one[0][k]) <= 1e-5, (tokens, switches, k)
 
 
 def test_pass_order_errors():
