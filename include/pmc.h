@@ -312,7 +312,8 @@ typedef enum pmc_epilogue {
 
 /* C[M,N] = op(A)[M,K] . op(B)[K,N] with the epilogue above.  trans_a = 0: A stored [M,K]
  * (row pitch lda); 1: stored [K,M].  trans_b = 0: B stored [K,N]; 1: stored [N,K].  All device.
- * bf16 mode needs M, N, K multiples of 64 and pitches multiples of 8. */
+ * bf16 mode needs M, N, K multiples of 8, lda and ldb multiples of 8, ldc a multiple of 4, A, B and C
+ * 16-byte aligned, bias, resid and aux 8-byte aligned; fp32 mode takes any sizes, pitches and alignments. */
 int pmc_gemm(pmc_ctx* ctx, int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t M, int32_t N,
              int32_t K, const void* A, int32_t lda, const void* B, int32_t ldb, void* C, int32_t ldc,
              int32_t epilogue, const void* bias, const void* resid, void* aux);

@@ -160,7 +160,7 @@ template <typename T, int DH, bool VEC>
 __global__ __launch_bounds__(kWavesF * 64, 2) void attn_fwd_f32(int block0, int seq, int heads, int dh, int causal, const T* __restrict__ qkv,
                                                              T* __restrict__ o, float* __restrict__ lse) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  extern __shared__ __attribute__((aligned(16))) float fold_f32[];  // [8 waves][16][DH + 4], then [8][16] weights
+  extern __shared__ __attribute__((aligned(16))) float fold_f32[];  // [8 waves][16][DH + 4]
   __shared__ float stat_m[kWavesF][kRows], stat_l[kWavesF][kRows];
   const Place at = place(seq, block0, causal != 0);
   const int h = heads * dh, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, quarter = lane >> 4;

@@ -938,15 +938,17 @@ long tiles_of(int shape, int M, int N) {
 }
 
 // Time of a product in us: fixed + rounds of tiles over the 256 compute units x (per_k for every 1024 of K +
-// per_round).  Fitted to every shape's time at the products of layers of hidden 64 .. 7168 with 16 .. 4096
-// tokens (308 products, kernel durations with operands that rotate through several buffers; the fit is within
-// 6 to 20 % of a time, and the shape it picks is on average 0.5 % slower than the best one).
+// per_round); 1e9 where a layout has no such shape.  Fitted to every shape's time at the products of layers of hidden
+// 64 .. 7168 with 16 .. 4096 tokens (308 products) with operands and C mostly in the memory-side cache; from HBM a time
+// is 1.0 to 1.4 times the fitted one on average, 3 times at most (a 256x256 tile of a short W product, whose C is
+// read and written once per few K tiles).  What the table is for is the order of the shapes, and that holds there too:
+// with operands and C from HBM the shape picked is 1.2 / 0.6 / 2.7 % slower than the best one (F / B / W, 130 products).
 double shape_us(Layout layout, int shape, long tiles, double K) {
   struct T { double fixed, per_k, per_round; };
   static constexpr T kTimes[3][kShapes] = {
       {{0., 19.5, 6.1}, {0., 11.4, 4.9}, {0., 8.1, 4.8}, {2.5, 4.9, 1.1}, {0., 23.1, 8.2}, {2.75, 3.1, 0.93}, {2.5, 2.2, 0.78}, {2.5, 1.8, 0.64}, {1e9, 0., 0.}},
       {{0., 18.3, 4.7}, {0., 10.6, 3.7}, {0., 7.5, 3.7}, {2.5, 5.0, 0.5}, {0., 21.5, 5.9}, {2.2, 2.8, 1.05}, {2.3, 2.0, 0.74}, {2.3, 1.3, 0.68}, {0.3, 4.7, 4.0}},
-      {{0., 21.0, 8.6}, {0., 13.0, 6.6}, {0., 8.3, 5.9}, {0., 8.3, 5.9}, {0., 23.1, 8.2}, {1.8, 2.7, 2.2}, {2.1, 2.3, 1.2}, {2.2, 2.1, 0.96}, {1e9, 0., 0.}}};
+      {{0., 21.0, 8.6}, {0., 13.0, 6.6}, {0., 8.3, 5.9}, {1e9, 0., 0.}, {0., 23.1, 8.2}, {1.8, 2.7, 2.2}, {2.1, 2.3, 1.2}, {2.2, 2.1, 0.96}, {1e9, 0., 0.}}};
   static constexpr T kShallow[3] = {{4.5, 9.4, 0.}, {3.3, 9.2, 0.}, {0., 9.6, 5.3}};  // shape 2, two workgroups per unit
   const T& t = shape == 2 && tiles > 256 ? kShallow[layout] : kTimes[layout][shape];
   return t.fixed + (double)((tiles + 255) / 256) * (t.per_k * K / 1024. + t.per_round);
@@ -957,7 +959,7 @@ int pick_tile(Layout layout, int M, int N, long K, bool wide_ok, double* us = nu
   int best = 0;
   double best_us = 1e300;
   for (int c = 0; c < kShapes; ++c) {
-    if ((c == 3 && layout == kLayoutW) || (c == 4 && !wide_ok)) continue;
+    if (c == 4 && !wide_ok) continue;
     const double t = shape_us(layout, c, tiles_of(c, M, N), (double)K);
     if (t < best_us) {
       best_us = t;

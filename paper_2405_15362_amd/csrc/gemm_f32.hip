@@ -16,8 +16,8 @@
 //    compute units idle and, with element-wise loads, for small products of sizes, pitches or pointers
 //    that are not multiples of four elements.
 //  * gemm_f32_fma_kernel: 64 x 64 tiles of plain FMAs staged element by element through LDS, for the
-//    larger products of such sizes: it reads an operand element once per 64 outputs, the direct kernel
-//    once per 16, one 4-byte load at a time.
+//    larger products of such sizes and of operands of 2 GB and more: it reads an operand element once per
+//    64 outputs, the direct kernel once per 16, one 4-byte load at a time.
 //
 // Measured against a 64 x 64 tile of plain FMAs with scalar loads (before), mean over the products of a
 // pass, F / B / W: hidden 256, 128 tokens 65 / 74 / 23 -> 5.2 / 5.2 / 5.1 us; hidden 1024, 512 tokens

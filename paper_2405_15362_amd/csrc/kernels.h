@@ -40,7 +40,7 @@ struct GemmArgs {
 };
 
 // Weight gradients of several queued microbatches as ONE product: C[M,N] (fp32) += sum_i A_i^T . B_i
-// with A_i stored [K,M] (pitch lda) and B_i stored [K,N] (pitch ldb), bf16.  K a multiple of 64.
+// with A_i stored [K,M] (pitch lda) and B_i stored [K,N] (pitch ldb), bf16.  M, N, K multiples of 8.
 struct GroupedWgradArgs {
   int M = 0, N = 0, K = 0;  // K of ONE piece
   int count = 0;            // 1 .. PMC_MAX_QUEUED_W pieces

@@ -115,6 +115,25 @@ def test_gemm_f32_element_loads(ctx, ta, tb):
 
 @pytest.mark.parametrize("ta", [False, True])
 @pytest.mark.parametrize("tb", [False, True])
+def test_gemm_f32_operand_of_two_gigabytes(ctx, ta, tb):
+    """131072 tokens of hidden 4096: A is exactly 2^31 bytes, past the reach of a 31-bit offset.  Every element against
+    float64."""
+    M, N, K = 131072, 68, 4096
+    assert U.gemm_plan("f32", ta, tb, M, N, K)[0] == U.F32_FMA_ELEMENTS
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    a = torch.randn((K, M) if ta else (M, K), device="cuda", generator=gen)
+    b = torch.randn((N, K) if tb else (K, N), device="cuda", generator=gen)
+    c = torch.empty(M, N, device="cuda")
+    print("fp32 operand of 2^31 bytes", ta, tb, flush=True)
+    P.pmc_gemm(ctx, a, b, c, ta, tb)
+    B = (b.T if tb else b).double().contiguous()
+    for r in range(0, M, 32768):
+        want = (a[:, r:r + 32768].T if ta else a[r:r + 32768]).double().contiguous() @ B
+        assert_close(host(c[r:r + 32768]), want.cpu().numpy(), "f32", f"rows {r}..")
+
+
+@pytest.mark.parametrize("ta", [False, True])
+@pytest.mark.parametrize("tb", [False, True])
 def test_gemm_f32_output_of_2_to_the_31_elements(ctx, ta, tb):
     """More output elements than 2^31 (8.6 GB) of odd sizes: 2^23 and more 16x16 tiles of 512 threads would not fit one
     launch dimension.  Every element against the same three products in float64, a band of rows at a time."""

@@ -247,6 +247,9 @@ def test_fp32_products_of_odd_sizes_pick_the_faster_kernel(ta, tb):
         assert U.gemm_plan("f32", ta, tb, M, N, K)[0] == U.F32_DIRECT_ELEMENTS, (M, N, K)
     for M, N, K in ((1025, 2049, 37), (2049, 3073, 517), (4097, 4099, 4101), (46343, 46351, 3), (131073, 16385, 4097)):
         assert U.gemm_plan("f32", ta, tb, M, N, K)[0] == U.F32_FMA_ELEMENTS, (M, N, K)
+    # a 2 GB operand (131072 tokens of hidden 4096), outside the reach of the tile kernels' loads
+    assert U.gemm_plan("f32", ta, tb, 131072, 16384, 4096)[0] == U.F32_FMA_ELEMENTS
+    assert U.gemm_plan("f32", ta, tb, 131068, 16384, 4096)[0] <= U.F32_TILE64
     for kw in ({"offset": 4}, {"ldc": 4097}):
         assert U.gemm_plan("f32", ta, tb, 4096, 4096, 4096, **kw)[0] == U.F32_FMA_ELEMENTS, kw
         assert U.gemm_plan("f32", ta, tb, 128, 128, 256, **kw)[0] == U.F32_DIRECT_ELEMENTS, kw
