@@ -1056,7 +1056,8 @@ int launch_wgrad_persistent(hipStream_t st, GemmParams p) {
 // take it or none.  What they share is the smaller side, hidden: steps of two layers at 512 / 1000 / 1024 tokens with it
 // everywhere against nowhere, hidden 1024 +5 / +4 / +5 %, 1152 +1 / +3 / +3 %, 1280 0 / +2 / +2 %, 1408 -1 / -1 / -1 %,
 // 1664 -2 / -2 / -2 %, 2560 -2 / -1 / -2 %; a bar on the tile count, which some of the products of hidden 1024 .. 1920
-// passed, cost 1 to 3 %.  gemm_wgrad = 2 forces it.
+// passed, cost 1 to 3 %.  (An FFN narrower than hidden and up to 1280 keeps its two products out beside the others; steps
+// of hidden / FFN 4096 / 1024, 2048 / 1024, 3072 / 1280 are within 0.4 % of the tile-count bar.)  gemm_wgrad = 2 forces it.
 bool use_wgrad_pair(int M, int N, long K) {
   if (const int f = tuning(kTuneGemmWgrad); f >= 0) return f == 2;
   if (tuning(kTuneGemmTile) >= 0) return false;
