@@ -18,7 +18,11 @@
  *  - Pointers named "device" are GPU memory, BORROWED from the caller: the library never allocates
  *    or frees device memory.  Everything else is host memory.
  *  - Work is enqueued on the HIP stream given to pmc_create and is asynchronous unless stated.
- *    One exception inside a call: the bf16 W pass runs every second weight-gradient product and the
+ *    The W pass is one launch (per eight layers) that does every weight-gradient product and bias
+ *    gradient of the call, except in these cases, where its products are launched one by one: at
+ *    2048 tokens and more of a wide bf16 layer; for layers bound to the same gradient memory; while a
+ *    switch forces the kernel of a product; while tracing, whose records are one per operation.
+ *    One by one, the bf16 W pass runs every second product and the
  *    bias-gradient column sums on a second, non-blocking stream of default priority that the
  *    context owns (created at first use).  The pass forks it from the context's stream with an
  *    event when it starts and joins it back before it returns (also when a launch fails), so

@@ -127,6 +127,7 @@ struct pmc_chunk {
   pmc::WorkspaceLayout wsl{};
   std::vector<const void*> params;
   std::vector<float*> grads;
+  bool grads_apart = false;  // no two weight or bias gradients share memory
   bool bound = false;
   std::map<int32_t, pmc::Micro> live;
 };
@@ -404,8 +405,8 @@ int chunk_backward_input(pmc_chunk* ch, int32_t mb, const void* dy, void* dx) {
   return PMC_OK;
 }
 
-// The weight-gradient products of a pass do not depend on each other.  Every second one goes to a
-// second stream (fork and join with events inside the pass): workgroups of two different products
+// The weight-gradient products of a pass do not depend on each other.  Where they do not go out in one launch, every
+// second one goes to a second stream (fork and join with events inside the pass): workgroups of two different products
 // then share the chip, one product's read-modify-write of dW overlaps the other's matrix work, the
 // tail of one fills with the head of the next, and the memory-bound bias-gradient sums run under a
 // product (measured on the W pass: -5 % at hidden 2048 / 1024 tokens, -6 % at 4096 / 2048, -5 % at
@@ -443,6 +444,51 @@ int join_side_streams(pmc_ctx* ctx, int n, int rc) {
   return ok ? (int)PMC_OK : fail(PMC_ERR_HIP, "stage_backward_weight: cannot join a side stream");
 }
 
+k::WgradBatchArgs wgrad_batch_args(const pmc_chunk_cfg& c, char* const* slab, int count) {
+  const int h = c.hidden, f = c.ffn;
+  k::WgradBatchArgs a = {};
+  const int M[4] = {f, h, h, h}, N[4] = {h, f, h, 3 * h};
+  for (int j = 0; j < 4; ++j) {
+    a.M[j] = M[j];
+    a.N[j] = N[j];
+  }
+  a.K = c.seq * c.microbatch;
+  a.pieces = count;
+  for (int i = 0; i < PMC_MAX_QUEUED_W; ++i) a.piece[i] = slab[std::min(i, count - 1)];
+  return a;
+}
+
+// The W pass of one microbatch, or of several queued ones, in one launch per kMaxLayers layers on the context's stream.  False: it is to
+// be done product by product (rc is then untouched); nothing has been launched.
+bool weights_in_one_launch(pmc_chunk* ch, char* const* slab, int count, int* rc) {
+  if (!ch->grads_apart) return false;  // products into one gradient have to follow one another
+  if (ch->ctx->tracing) return false;  // its records are one per product
+  const int L = ch->cfg.layers, per = k::WgradBatchArgs::kMaxLayers;
+  std::vector<std::pair<k::WgradBatchArgs, int>> launches;
+  for (int top = L - 1; top >= 0; top -= per) {
+    k::WgradBatchArgs a = wgrad_batch_args(ch->cfg, slab, count);
+    for (int l = top; l >= 0 && l > top - per; --l) {
+      const LayerOffsets& o = ch->off[l];
+      const size_t off_a[4] = {o.g, o.c, o.o, o.a}, off_b[4] = {l == L - 1 ? ch->off[0].x : ch->off[l + 1].x, o.u, o.xmid, o.qkv};
+      const int weight[4] = {W_2, W_1, W_O, W_QKV}, bias[4] = {B_2, B_1, B_O, B_QKV};
+      k::WgradBatchArgs::Layer& to = a.layer[a.layers++];
+      for (int j = 0; j < 4; ++j) {
+        to.a[j] = off_a[j];
+        to.b[j] = off_b[j];
+        to.c[j] = G(ch, l, weight[j]);
+        to.bias[j] = G(ch, l, bias[j]);
+      }
+    }
+    const int shape = k::wgrad_batch_shape(ch->cfg.dtype, a);
+    if (shape < 0) return false;
+    launches.emplace_back(a, shape);
+  }
+  *rc = PMC_OK;
+  for (auto& l : launches)
+    if (*rc == PMC_OK) *rc = k::wgrad_batch(ch->ctx->stream, ch->cfg.dtype, l.first, l.second);
+  return true;
+}
+
 int chunk_backward_weight_one(pmc_chunk* ch, int32_t mb, bool release) {
   auto it = ch->live.find(mb);
   if (it == ch->live.end() || it->second.state != kBackwardDone)
@@ -453,6 +499,11 @@ int chunk_backward_weight_one(pmc_chunk* ch, int32_t mb, bool release) {
   hipStream_t st = ctx->stream;
   const int T = ch->tokens, h = c.hidden, f = c.ffn, L = c.layers;
   char* s = m.slab;
+  int rc = PMC_OK;
+  if (weights_in_one_launch(ch, &m.slab, 1, &rc)) {
+    PMC_TRY(rc);
+    return release ? chunk_release(ch, mb) : PMC_OK;
+  }
   const int ns = w_pass_streams(ch);
   const bool two = ns > 1;
   if (two) {
@@ -499,7 +550,7 @@ int chunk_backward_weight_one(pmc_chunk* ch, int32_t mb, bool release) {
   };
   // whatever happened in between, the caller's stream waits for the side stream: a failed pass must
   // not leave work on it that still reads the slab or writes the gradients
-  const int rc = products();
+  rc = products();
   PMC_TRY(join_side_streams(ctx, ns - 1, rc));
   if (release) {
     ch->ctx->pool.give(m.slab, m.device, (int64_t)(ch->unit_bytes - ch->stats_bytes));
@@ -518,6 +569,12 @@ int chunk_backward_weight_group(pmc_chunk* ch, const int32_t* mbs, int count) {
   const int T = ch->tokens, h = c.hidden, f = c.ffn, L = c.layers;
   char* slab[PMC_MAX_QUEUED_W];
   for (int i = 0; i < count; ++i) slab[i] = ch->live.find(mbs[i])->second.slab;
+  int rc = PMC_OK;
+  if (weights_in_one_launch(ch, slab, count, &rc)) {
+    PMC_TRY(rc);
+    for (int i = 0; i < count; ++i) PMC_TRY(chunk_release(ch, mbs[i]));
+    return PMC_OK;
+  }
   const int ns = w_pass_streams(ch);  // as in the single-microbatch pass: every second product on a second stream
   if (ns > 1) {
     PMC_TRY(side_streams(ctx, 1));
@@ -561,7 +618,7 @@ int chunk_backward_weight_group(pmc_chunk* ch, const int32_t* mbs, int count) {
     }
     return PMC_OK;
   };
-  const int rc = products();
+  rc = products();
   PMC_TRY(join_side_streams(ctx, ns > 1 ? 1 : 0, rc));
   for (int i = 0; i < count; ++i) {
     auto it = ch->live.find(mbs[i]);
@@ -720,6 +777,25 @@ int pmc_chunk_bind(pmc_chunk* ch, const void* const* params, void* const* grads_
   ch->params.assign(params, params + n);
   ch->grads.resize(n);
   for (size_t i = 0; i < n; ++i) ch->grads[i] = (float*)grads_fp32[i];
+  {
+    const size_t h = ch->cfg.hidden, f = ch->cfg.ffn;
+    std::vector<std::pair<float*, float*>> ranges;
+    for (size_t i = 0; i < n; ++i) {
+      size_t len = 0;  // LayerNorm's gradients are B's
+      switch (i % PMC_PARAMS_PER_LAYER) {
+        case W_QKV: len = 3 * h * h; break;
+        case B_QKV: len = 3 * h; break;
+        case W_O: len = h * h; break;
+        case W_1: case W_2: len = h * f; break;
+        case B_1: len = f; break;
+        case B_O: case B_2: len = h; break;
+      }
+      if (len) ranges.emplace_back(ch->grads[i], ch->grads[i] + len);
+    }
+    std::sort(ranges.begin(), ranges.end());
+    ch->grads_apart = true;
+    for (size_t i = 1; i < ranges.size(); ++i) ch->grads_apart = ch->grads_apart && ranges[i].first >= ranges[i - 1].second;
+  }
   ch->bound = true;
   return PMC_OK;
 }
@@ -823,6 +899,16 @@ int pmc_test_gemm_plan(int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t 
   out[1] = plan.splits;
   out[2] = plan.k_tiles_per_split;
   return PMC_OK;
+}
+
+// For the library's own tests (not in pmc.h): tiles of the one launch that does the W pass of `count` microbatches
+// (-1: the products go out one by one).
+int pmc_test_wgrad_shape(const pmc_chunk_cfg* cfg, int32_t count) {
+  if (check_cfg(cfg) != PMC_OK || count < 1 || count > PMC_MAX_QUEUED_W) return -2;
+  char* none[PMC_MAX_QUEUED_W] = {};
+  k::WgradBatchArgs a = wgrad_batch_args(*cfg, none, count);
+  a.layers = std::min(cfg->layers, (int32_t)k::WgradBatchArgs::kMaxLayers);
+  return k::wgrad_batch_shape(cfg->dtype, a);
 }
 
 // For the library's own tests (not in pmc.h): the part of a pass's workspace that its split products use.

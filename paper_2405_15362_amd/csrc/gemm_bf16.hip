@@ -33,6 +33,7 @@
 
 #include "dev_common.h"
 #include "kernels.h"
+#include "wgrad_batch.h"
 
 namespace pmc {
 namespace k {
@@ -58,6 +59,8 @@ struct GemmParams {
   const bf16_t* Aseg[kMaxSegments];
   const bf16_t* Bseg[kMaxSegments];
   int nseg, seg_k;
+  __device__ __forceinline__ const bf16_t* piece_a(int i) const { return Aseg[i]; }
+  __device__ __forceinline__ const bf16_t* piece_b(int i) const { return Bseg[i]; }
 };
 
 // K tiles of depth BK of the whole (possibly segmented) contraction.
@@ -572,8 +575,8 @@ __device__ __forceinline__ bf16x8 read_frag_swz(const bf16_t* tile, int r0, int 
 // CUT: the last K tile of a contraction-contiguous operand is partial.  (A kernel of its own: the test for
 // that tile in the K loop cost the steps whose K is whole 0.3 to 1 %.)
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64, bool CUT = false,
-          bool KSPLIT = false>
-__device__ __forceinline__ void dma_tile(const GemmParams& p, bf16_t* smem, int tile_m, int tile_n, int kt0, int nk) {
+          bool KSPLIT = false, class Params>
+__device__ __forceinline__ void dma_tile(const Params& p, bf16_t* smem, int tile_m, int tile_n, int kt0, int nk) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int NW = WAVES_M * WAVES_N, WM = KSPLIT ? BM : BM / WAVES_M, WN = KSPLIT ? BN : BN / WAVES_N, TM = WM / 32, TN = WN / 32;
   constexpr int TA = BM * BK, TB = BN * BK, STAGE = TA + TB;
@@ -641,8 +644,8 @@ __device__ __forceinline__ void dma_tile(const GemmParams& p, bf16_t* smem, int 
   if constexpr (SEG) {
     seg = kt0 / seg_tiles;
     local = kt0 - seg * seg_tiles;
-    ra = make_rsrc(p.Aseg[seg], size_a);
-    rb = make_rsrc(p.Bseg[seg], size_b);
+    ra = make_rsrc(p.piece_a(seg), size_a);
+    rb = make_rsrc(p.piece_b(seg), size_b);
   }
   auto request = [&](int t, int stage) {
     const int kt = SEG ? local : tile_k(t);
@@ -658,8 +661,8 @@ __device__ __forceinline__ void dma_tile(const GemmParams& p, bf16_t* smem, int 
       if (++local == seg_tiles) {
         local = 0;
         ++seg;
-        ra = make_rsrc(p.Aseg[seg], size_a);
-        rb = make_rsrc(p.Bseg[seg], size_b);
+        ra = make_rsrc(p.piece_a(seg), size_a);
+        rb = make_rsrc(p.piece_b(seg), size_b);
       }
     }
   };
@@ -783,6 +786,42 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_wgrad_pair_kernel(GemmParams
   int tile_m, tile_n;
   tile_of_block(p, tile_m, tile_n);
   dma_tile<256, 128, 2, 2, false, false, 3, PMC_EPI_ACCUM_F32, SEG, 32>(p, smem, tile_m, tile_n, 0, k_tiles<SEG, 32>(p));
+#endif
+}
+
+// One product of a W pass in one launch: what dma_tile and the epilogue read, with the operands taken from the slabs.
+struct BatchProduct : GemmParams {
+  const WgradBatchParams* q;
+  size_t off_a, off_b;
+  __device__ __forceinline__ const bf16_t* piece_a(int i) const { return reinterpret_cast<const bf16_t*>(q->w.piece[i] + off_a); }
+  __device__ __forceinline__ const bf16_t* piece_b(int i) const { return reinterpret_cast<const bf16_t*>(q->w.piece[i] + off_b); }
+};
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTAGE, int BK, bool KSPLIT, int WAVES_PER_SIMD>
+__global__ __launch_bounds__(WAVES_M * WAVES_N * 64, WAVES_PER_SIMD) void gemm_bf16_wgrad_batch_kernel(WgradBatchParams q) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+  if ((int)blockIdx.x < q.sum_blocks) {
+    batch_column_sums<bf16_t, WAVES_M * WAVES_N * 64>(q, blockIdx.x, reinterpret_cast<float*>(smem));
+    return;
+  }
+  const BatchTile t = batch_tile(q, (int)blockIdx.x - q.sum_blocks);
+  const WgradBatchArgs::Layer& l = q.w.layer[t.layer];
+  BatchProduct p;
+  p.q = &q;
+  p.off_a = l.a[t.product];
+  p.off_b = l.b[t.product];
+  p.C = l.c[t.product];
+  p.A = p.B = nullptr;
+  p.bias = p.resid = nullptr;
+  p.aux = nullptr;
+  p.M = p.lda = q.w.M[t.product];
+  p.N = p.ldb = p.ldc = q.w.N[t.product];
+  p.nseg = q.w.pieces;
+  p.seg_k = q.w.K;
+  p.K = q.w.K;
+  dma_tile<BM, BN, WAVES_M, WAVES_N, false, false, NSTAGE, PMC_EPI_ACCUM_F32, true, BK, false, KSPLIT>(p, smem, t.tile_m, t.tile_n, 0,
+                                                                                                  k_tiles<true, BK>(p));
 #endif
 }
 
@@ -1286,6 +1325,66 @@ int gemm_bf16_grouped_wgrad(hipStream_t st, const GroupedWgradArgs& a) {
   if (kernel == kPlanPair) return launch_wgrad_pair<true>(st, p);
   if (kernel == kPlanPersistent) return launch_wgrad_persistent<true>(st, p);
   return launch_dma_tile<false, false, PMC_EPI_ACCUM_F32, true>(st, p, kernel - kPlanTile);
+}
+
+namespace {
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTAGE, int BK, bool KSPLIT, int WPS>
+int launch_wgrad_batch(hipStream_t st, WgradBatchParams& p) {
+  constexpr size_t lds = (size_t)NSTAGE * (BM + BN) * BK * sizeof(bf16_t);
+  auto kern = gemm_bf16_wgrad_batch_kernel<BM, BN, WAVES_M, WAVES_N, NSTAGE, BK, KSPLIT, WPS>;
+  static std::atomic<bool> configured{false};
+  if (int rc = reserve_lds(kern, lds, configured, "gemm_bf16")) return rc;
+  wgrad_batch_layout(p, BM, BN, WAVES_M * WAVES_N * 64);
+  kern<<<dim3(p.sum_blocks + p.first_tile[4] * p.w.layers), dim3(WAVES_M * WAVES_N * 64), lds, st>>>(p);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(PMC_ERR_HIP, "gemm_bf16 weight-gradient launch failed: %s", hipGetErrorString(e));
+  return PMC_OK;
+}
+}  // namespace
+
+// Tiles of the one launch; picked by fitted times (see batch_us in wgrad_batch.h) of 2061 W passes, hidden 64 .. 7168, 16 .. 8192
+// tokens, 1 .. 4 layers, FFN 1 .. 4.5 x hidden: the shape picked is 1.7 % slower than the best one on average (1.29 times at
+// worst), and 2.7 times as fast as the products launched one by one on two streams (geometric mean over the 2061).  Some of them, us one by
+// one / in one launch: 2 layers of hidden 256, 192 tokens 52 / 9; 2 of 1024, 4096 tokens 320 / 214; 2 of 2048, 1024 tokens
+// 312 / 283; 2 of 4096, 1024 tokens 1140 / 1015.
+//   0: 256x256, four 32-deep stages   1: 256x128, two workgroups per compute unit   2: 128x128, likewise
+//   3: 64x128   4: 64x64   5: 32x32 whose waves split K (few outputs over many tokens)
+enum BatchShape { kBatch256, kBatchPair, kBatch128, kBatch64x128, kBatch64, kBatch32, kBatchShapes };
+
+// The shape, or -1 where the products go out one by one: at 2048 tokens and more with twelve and more rounds of 256x256 tiles
+// over the compute units in each layer the products fill the chip by themselves, and the persistent kernel beside a
+// second stream is as fast or faster (3072 .. 9408 tiles per layer, 2048 .. 8192 tokens: one launch 0.99 of it, 0.97 .. 1.02).
+int gemm_bf16_wgrad_batch_shape(const WgradBatchArgs& a) {
+  constexpr int kBm[kBatchShapes] = {256, 256, 128, 64, 64, 32}, kBn[kBatchShapes] = {256, 128, 128, 128, 64, 32};
+  static constexpr BatchTime kTimes[kBatchShapes] = {
+      {11.06, 0.86, 8.73, 26.8, 13.6, 0., 1},  {6.78, 1.87, 6.93, 11.4, 9.66, 3.07, 2}, {6.48, 1.41, 4.35, 5.60, 5.97, 1.18, 2},
+      {4.52, 2.57, 3.42, 2.40, 3.47, 2.20, 3}, {4.51, 2.71, 2.70, 1.15, 1.19, 1.82, 4}, {5.33, 1.57, 1.75, 0.65, 0.74, 1.01, 2}};
+  const double K = (double)a.K * a.pieces;
+  if (K >= 2048 && batch_tiles(a, 256, 256) >= 12 * 256) return -1;
+  int best = -1;
+  double best_us = 1e300;
+  for (int s = 0; s < kBatchShapes; ++s) {
+    const double us = batch_us(kTimes[s], (double)batch_tiles(a, kBm[s], kBn[s]) * a.layers, K);
+    if (us < best_us) {
+      best_us = us;
+      best = s;
+    }
+  }
+  return best;
+}
+
+int gemm_bf16_wgrad_batch(hipStream_t st, const WgradBatchArgs& a, int shape) {
+  WgradBatchParams p;
+  p.w = a;
+  switch (shape) {
+    case kBatch256: return launch_wgrad_batch<256, 256, 2, 4, 4, 32, false, 1>(st, p);
+    case kBatchPair: return launch_wgrad_batch<256, 128, 2, 2, 3, 32, false, 2>(st, p);
+    case kBatch128: return launch_wgrad_batch<128, 128, 2, 2, 4, 32, false, 2>(st, p);
+    case kBatch64x128: return launch_wgrad_batch<64, 128, 2, 2, 4, 32, false, 3>(st, p);
+    case kBatch64: return launch_wgrad_batch<64, 64, 2, 2, 4, 32, false, 3>(st, p);
+    case kBatch32: return launch_wgrad_batch<32, 32, 2, 2, 8, 64, true, 1>(st, p);
+  }
+  return fail(PMC_ERR_INVALID, "gemm_bf16: no weight-gradient tiles %d", shape);
 }
 
 size_t gemm_scratch_bytes(GemmArgs a) {

@@ -52,6 +52,35 @@ struct GroupedWgradArgs {
 };
 int gemm_bf16_grouped_wgrad(hipStream_t stream, const GroupedWgradArgs& a);
 
+// The W pass of one microbatch (fp32, bf16) or of several queued ones (bf16) as ONE launch: for every layer the four
+// products C_j[M_j,N_j] (fp32) += sum over the pieces of A_j^T . B_j and the four bias gradients bias_j[n] += column sums
+// of B_j.  Every operand of piece i lies at piece[i] + its offset, A_j stored [K,M_j] and B_j stored [K,N_j] without
+// padding, C_j without padding.
+struct WgradBatchArgs {
+  static constexpr int kMaxLayers = 8;
+  struct Layer {
+    size_t a[4], b[4];  // byte offsets
+    float* c[4];
+    float* bias[4];
+  };
+  Layer layer[kMaxLayers];
+  const char* piece[PMC_MAX_QUEUED_W];
+  int M[4], N[4];
+  int K = 0, layers = 0, pieces = 0;
+};
+// Kernel argument of the batch: the products of a layer are cut into tiles numbered one product after the other (first_tile),
+// layer after layer; the first sum_blocks workgroups (64 columns of a bias gradient to 256 threads, first_sum per layer) do the column sums.
+struct WgradBatchParams {
+  WgradBatchArgs w;
+  int tiles_n[4], first_tile[5], first_sum[5];
+  int group_m, sum_blocks;
+};
+void wgrad_batch_layout(WgradBatchParams& p, int bm, int bn, int threads);
+int wgrad_batch_shape(int dtype, const WgradBatchArgs& a);  // -1: not in one launch
+int wgrad_batch(hipStream_t stream, int dtype, const WgradBatchArgs& a, int shape);
+int gemm_bf16_wgrad_batch_shape(const WgradBatchArgs& a);
+int gemm_bf16_wgrad_batch(hipStream_t stream, const WgradBatchArgs& a, int shape);
+
 // Scratch for the plan that this product gets where there is room for any (0: it is not split).
 size_t gemm_scratch_bytes(GemmArgs a);
 

@@ -7,6 +7,7 @@
 
 #include "dev_common.h"
 #include "kernels.h"
+#include "wgrad_batch.h"
 
 namespace pmc {
 namespace k {
@@ -265,52 +266,14 @@ __global__ __launch_bounds__(kSumWaves * 64) void sum_partials_kernel(LnPartialJ
 }
 
 // Column sums of up to four matrices with the same row count in one launch: out_j[c] += sum over
-// rows of a_j[row][c].  A workgroup owns 64 columns of one matrix; its 256 threads form 256/LPR
-// row slots of LPR lanes (16 bytes of a row each), slot s adds rows s, s + slots, ... in that
-// order (sixteen loads in flight), and 64 threads then add the slots in slot order: the result
-// depends on the shapes alone.
+// rows of a_j[row][c].  A workgroup owns 64 columns of one matrix.
 template <typename T>
 __global__ __launch_bounds__(256) void colsum_kernel(int rows, ColumnSumJobs jobs) {
-  constexpr int V = Vec<T>::N, LPR = 64 / V, SLOTS = 256 / LPR, UNROLL = 16;
-  __shared__ float red[SLOTS][64 + 1];
+  __shared__ float red[256 / (64 / Vec<T>::N) * 65];
   int j = 0;
   while (j + 1 < jobs.count && (int)blockIdx.x >= jobs.first_block[j + 1]) ++j;
-  const T* a = static_cast<const T*>(jobs.a[j]);
-  const int n = jobs.n[j], lda = jobs.lda[j];
-  const int slot = threadIdx.x / LPR, sub = (threadIdx.x % LPR) * V;
-  const int col = ((int)blockIdx.x - jobs.first_block[j]) * 64 + sub;
-  float acc[V];
-#pragma unroll
-  for (int i = 0; i < V; ++i) acc[i] = 0.f;
-  if (col < n) {
-    const T* p = a + col;
-    int r = slot;
-    for (; r + (UNROLL - 1) * SLOTS < rows; r += UNROLL * SLOTS) {
-      float v[UNROLL][V];
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) Vec<T>::load(p + (size_t)(r + u * SLOTS) * lda, v[u]);
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u)
-#pragma unroll
-        for (int i = 0; i < V; ++i) acc[i] += v[u][i];
-    }
-    for (; r < rows; r += SLOTS) {
-      float v[V];
-      Vec<T>::load(p + (size_t)r * lda, v);
-#pragma unroll
-      for (int i = 0; i < V; ++i) acc[i] += v[i];
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < V; ++i) red[slot][sub + i] = acc[i];
-  __syncthreads();
-  const int c = ((int)blockIdx.x - jobs.first_block[j]) * 64 + threadIdx.x;
-  if (threadIdx.x < 64 && c < n) {
-    float total = 0.f;
-#pragma unroll
-    for (int sl = 0; sl < SLOTS; ++sl) total += red[sl][threadIdx.x];
-    jobs.out[j][c] += total;
-  }
+  column_sum_block<T>([&](int) { return static_cast<const T*>(jobs.a[j]); }, 1, rows, jobs.n[j], jobs.lda[j],
+                           ((int)blockIdx.x - jobs.first_block[j]) * 64, jobs.out[j], red, threadIdx.x);
 }
 
 template <typename T>
@@ -510,6 +473,23 @@ int column_sums(hipStream_t st, int dtype, int rows, ColumnSumJobs jobs) {
   else colsum_kernel<bf16_t><<<dim3(blocks), dim3(256), 0, st>>>(rows, jobs);
   PMC_LAUNCH_CHECK("column_sum");
   return PMC_OK;
+}
+
+// Tiles of bm x bn and the column-sum workgroups of a W pass in one launch.
+void wgrad_batch_layout(WgradBatchParams& p, int bm, int bn, int threads) {
+  const int sum_cols = 64 * (threads / 256);
+  int tiles = 0, sums = 0;
+  for (int j = 0; j < 4; ++j) {
+    p.first_tile[j] = tiles;
+    p.first_sum[j] = sums;
+    p.tiles_n[j] = (p.w.N[j] + bn - 1) / bn;
+    tiles += p.tiles_n[j] * ((p.w.M[j] + bm - 1) / bm);
+    sums += (p.w.N[j] + sum_cols - 1) / sum_cols;
+  }
+  p.first_tile[4] = tiles;
+  p.first_sum[4] = sums;
+  p.sum_blocks = (sums * p.w.layers + 7) & ~7;  // whole rounds over the 8 XCDs, so that a tile's XCD is its id modulo 8
+  p.group_m = bm >= 256 ? 4 : 8;
 }
 
 int column_sum(hipStream_t st, int dtype, int rows, int n, const void* a, int lda, float* out) {

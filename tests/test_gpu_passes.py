@@ -8,6 +8,7 @@ import synth
 from oracle import layer as OL
 from oracle import schedule as OS
 from paper_2405_15362_amd import runtime as R
+import gpu_util as U
 from gpu_util import assert_close, dev, host, oracle_chunk, rel_l2, tol, tuned
 
 pytestmark = pytest.mark.gpu
@@ -464,3 +465,70 @@ def test_replay_config5_full_size():
     assert worst["vhalf"] * 4 == worst["1f1b"] * 3 and worst["vmin"] * 2 == worst["1f1b"]
     assert worst["1f1bv"] == -(-(4 * d + 2) // 3) * m                     # ceil((4d + 2) / 3) units: 6 of 8 at d = 4
     ctx.close()
+
+
+W_NAMES = [k for k in R.PARAM_NAMES if not k.startswith("ln")]  # what W adds into
+
+
+def _w_pass(cfg, pieces, same_gradients=False):
+    """F and B of `pieces` microbatches, then one W call into gradients that start at 0.25; every gradient."""
+    params = synth.chunk_params(cfg, "one_launch")
+    ctx = R.Context(R.cfg_from_synth(cfg), slabs=pieces)
+    ch = ctx.add_chunk(params, cfg.dtype)
+    for g in ch.grads:
+        for t in g.values():
+            t.fill_(0.25)
+    if same_gradients:
+        flat = [ch.grads[0 if k in W_NAMES else l][k] for l in range(cfg.layers) for k in R.PARAM_NAMES]
+        P.pmc_chunk_bind(ch.handle, [p[k] for p in ch.params for k in R.PARAM_NAMES], flat)
+    keep = []
+    for j in range(pieces):
+        x, dy = dev(synth.chunk_input(cfg, "one_launch", j), cfg.dtype), dev(synth.upstream_grad(cfg, "one_launch", j), cfg.dtype)
+        y, dx = torch.empty_like(x), torch.empty_like(x)
+        P.stage_forward(ch.handle, j, x, y)
+        P.stage_backward_input(ch.handle, j, dy, dx)
+        keep += [x, dy, y, dx]
+    P.stage_backward_weight(ch.handle, list(range(pieces)))
+    torch.cuda.synchronize()
+    got = [{k: host(v) for k, v in g.items()} for g in ch.grads]
+    ctx.close()
+    return got
+
+
+ONE_LAUNCH = [  # dtype, layers, hidden, heads, ffn, seq, microbatch, queued, tiles: partial tiles in both directions, K tails
+    ("bf16", 2, 72, 3, 136, 8, 1, 1, U.WGRAD_64), ("bf16", 1, 192, 3, 328, 104, 1, 3, U.WGRAD_64),
+    ("bf16", 3, 64, 2, 120, 1032, 1, 1, U.WGRAD_32), ("bf16", 1, 72, 3, 264, 520, 1, 4, U.WGRAD_32),
+    ("bf16", 9, 128, 1, 264, 40, 1, 1, U.WGRAD_64),
+    ("bf16", 4, 520, 5, 2056, 1000, 2, 1, U.WGRAD_64X128), ("bf16", 4, 520, 5, 2056, 680, 1, 3, U.WGRAD_64X128),
+    ("bf16", 4, 520, 5, 1992, 400, 1, 1, U.WGRAD_128), ("bf16", 4, 520, 5, 1992, 200, 1, 2, U.WGRAD_128),
+    ("bf16", 2, 1032, 12, 4104, 1000, 1, 1, U.WGRAD_PAIR), ("bf16", 2, 1032, 12, 4104, 360, 1, 3, U.WGRAD_PAIR),
+    ("bf16", 1, 1000, 10, 4008, 8200, 1, 1, U.WGRAD_256), ("bf16", 1, 1000, 10, 4008, 1368, 1, 6, U.WGRAD_256),
+    ("f32", 2, 68, 1, 132, 12, 1, 1, U.WGRAD_F32_32), ("f32", 3, 300, 5, 1204, 100, 2, 2, U.WGRAD_F32_64),
+    ("f32", 9, 132, 3, 260, 44, 1, 1, U.WGRAD_F32_32), ("f32", 1, 36, 1, 100, 1036, 1, 1, U.WGRAD_F32_32_KSPLIT),
+]
+
+
+@pytest.mark.parametrize("case", ONE_LAUNCH, ids=lambda c: "-".join(map(str, c)))
+def test_w_pass_in_one_launch_against_products_one_by_one(case):
+    """Both add the same exact products in fp32; only the order of at most T * queued summands differs.  Two orders
+    differ by at most 2 T eps times the sum of magnitudes, and by sqrt(T) eps or so in norm: 1e-5 covers T = 8200."""
+    dtype, layers, h, heads, f, seq, mb, queued, shape = case
+    cfg = synth.ChunkCfg(layers=layers, hidden=h, heads=heads, ffn=f, seq=seq, microbatch=mb, dtype=dtype)
+    assert U.wgrad_shape(cfg, queued if dtype == "bf16" else 1) == shape
+    got = _w_pass(cfg, queued)
+    with tuned(w_streams=1):
+        assert U.wgrad_shape(cfg, 1) == -1
+        want = _w_pass(cfg, queued)
+    for l in range(layers):
+        for k in R.PARAM_NAMES:
+            assert np.isfinite(got[l][k]).all() and rel_l2(got[l][k], want[l][k]) <= 1e-5, (l, k)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_w_pass_of_layers_that_share_gradients(dtype):
+    """Layers bound to the same weight and bias gradients add up in them, as one product after the other does."""
+    cfg = synth.ChunkCfg(layers=3, hidden=64, heads=2, ffn=136, seq=40, dtype=dtype)
+    apart, shared = _w_pass(cfg, 1), _w_pass(cfg, 1, same_gradients=True)
+    for k in W_NAMES:
+        want = sum(g[k].astype(np.float64) - 0.25 for g in apart) + 0.25
+        assert rel_l2(shared[0][k], want) <= 1e-5, k
