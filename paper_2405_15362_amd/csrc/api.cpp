@@ -9,7 +9,7 @@
 // B overwrites what only it needs with what W needs, one for one:
 //     U <- dU (GeLU' epilogue, in place),  XMID <- dX_mid,  QKV <- dQKV,
 //     X[l+1] <- dX of layer l+1 (= dX_out of layer l),  X[0] <- dY of the chunk,
-// so the slab never grows.  Tensors that exist only inside B (dC, dO, dA, the dQ staging buffer,
+// so the slab never grows.  Tensors that exist only inside B (dC, dO, dA, what attention's backward keeps of q|k|v,
 // partial sums) live in the workspace.
 #include <algorithm>
 #include <cstdlib>
@@ -112,7 +112,7 @@ struct LayerOffsets {  // byte offsets inside the slab
 };
 
 struct WorkspaceLayout {
-  size_t t_h, attn, partial, partial_stride, gemm, gemm_bytes, total;
+  size_t t_h, attn, kept, partial, partial_stride, gemm, gemm_bytes, total;
 };
 
 }  // namespace pmc
@@ -120,7 +120,7 @@ struct WorkspaceLayout {
 struct pmc_chunk {
   pmc_ctx* ctx = nullptr;
   pmc_chunk_cfg cfg{};
-  int tokens = 0, head_dim = 0;
+  int tokens = 0, head_dim = 0, kept_columns = 0;
   size_t esz = 0;
   size_t unit_bytes = 0, stats_bytes = 0;
   std::vector<pmc::LayerOffsets> off;
@@ -181,6 +181,8 @@ WorkspaceLayout workspace_of(const pmc_chunk_cfg& c) {
   at += align256((size_t)t * c.hidden * e);
   w.attn = at;
   at += k::attention_backward_scratch_bytes(c.dtype, c.microbatch, c.seq, c.heads, c.hidden / c.heads);
+  w.kept = at;
+  at += align256((size_t)t * k::attention_backward_kept_columns(c.dtype, c.microbatch, c.seq, c.heads, c.hidden / c.heads) * e);
   w.partial = at;
   // one region per LayerNorm of the backward pass (their reductions are run together at its end)
   const size_t pf = k::layernorm_backward_scratch_floats(t, c.hidden);
@@ -360,20 +362,25 @@ int chunk_backward_input(pmc_chunk* ch, int32_t mb, const void* dy, void* dx) {
   char* s = m.slab;
   char* ws = ch->ctx->ws;
   void* t_h = ws + ch->wsl.t_h;
-  void* attn_ws = ws + ch->wsl.attn;
+  // q|k|v for an attention backward of one launch, which cannot write over what it reads; LN2's backward copies them on its way
+  k::RowCopy keep;
+  keep.cols = keep.ld_dst = ch->kept_columns;
+  keep.ld_src = 3 * h;
+  keep.dst = ws + ch->wsl.kept;
   // LayerNorm gain/bias gradients: each call leaves its partial sums in a region of its own and
   // one launch adds them all up (when the regions run out, and at the end of the pass)
   k::LnPartialJobs ln_jobs;
   auto next_partial = [&]() { return (float*)(ws + ch->wsl.partial + (size_t)ln_jobs.count * ch->wsl.partial_stride); };
-  auto flush_ln = [&](bool force) {
+  auto flush_ln = [&](bool force, k::RowCopy copy = {}) {
     if (ln_jobs.count == 0 || (!force && ln_jobs.count < k::LnPartialJobs::kMax)) return (int)PMC_OK;
-    const int rc = traced(ch->ctx, PMC_OP_LN_BWD, PMC_B, ln_jobs.count, 2 * h, 0, 1, [&] { return k::layernorm_backward_reduce(st, h, ln_jobs); });
+    const int rc = traced(ch->ctx, PMC_OP_LN_BWD, PMC_B, ln_jobs.count, 2 * h, 0, 1, [&] { return k::layernorm_backward_reduce(st, h, ln_jobs, c.dtype, T, copy); });
     ln_jobs.count = 0;
     return rc;
   };
   for (int l = L - 1; l >= 0; --l) {
     const LayerOffsets& o = ch->off[l];
     const void* dyl = l == L - 1 ? dy : (const void*)(s + ch->off[l + 1].x);
+    keep.src = s + o.qkv;
     // dU = (dY . W2^T) * gelu'(U), written over the gelu'(U) that F left
     PMC_TRY(t_gemm(ch->ctx, PMC_B, gemm_args(ch, false, true, T, f, h, dyl, h, P(ch, l, W_2), h, s + o.u, f, PMC_EPI_MUL, nullptr,
                                   nullptr, s + o.u), ch->wsl));
@@ -381,13 +388,13 @@ int chunk_backward_input(pmc_chunk* ch, int32_t mb, const void* dy, void* dx) {
     PMC_TRY(t_gemm(ch->ctx, PMC_B, gemm_args(ch, false, true, T, h, f, s + o.u, f, P(ch, l, W_1), f, t_h, h, PMC_EPI_NONE), ch->wsl));
     // dX_mid = dY + LN2 input-gradient(dC), written over X_mid; LN2 gain/bias gradients
     PMC_TRY(traced(ch->ctx, PMC_OP_LN_BWD, PMC_B, T, h, 0, 0, [&] { return k::layernorm_backward(st, c.dtype, T, h, t_h, s + o.xmid, P(ch, l, LN2_G), (const float*)(s + o.mean2),
-                                  (const float*)(s + o.rstd2), dyl, s + o.xmid, G(ch, l, LN2_G), G(ch, l, LN2_B), next_partial(), &ln_jobs); }));
+                                  (const float*)(s + o.rstd2), dyl, s + o.xmid, G(ch, l, LN2_G), G(ch, l, LN2_B), next_partial(), &ln_jobs, keep); }));
     PMC_TRY(flush_ln(false));
     // dO = dX_mid . Wo^T
     PMC_TRY(t_gemm(ch->ctx, PMC_B, gemm_args(ch, false, true, T, h, h, s + o.xmid, h, P(ch, l, W_O), h, t_h, h, PMC_EPI_NONE), ch->wsl));
     // dQKV, written over QKV
-    PMC_TRY(traced(ch->ctx, PMC_OP_ATTN_BWD, PMC_B, T, c.heads, ch->head_dim, 0, [&] { return k::attention_backward(st, c.dtype, c.microbatch, c.seq, c.heads, ch->head_dim, c.causal, s + o.qkv, s + o.o,
-                                  (const float*)(s + o.lse), t_h, s + o.qkv, attn_ws); }));
+    PMC_TRY(traced(ch->ctx, PMC_OP_ATTN_BWD, PMC_B, T, c.heads, ch->head_dim, 0, [&] { return k::attention_backward(st, c.dtype, c.microbatch, c.seq, c.heads, ch->head_dim, c.causal,
+                                  keep.cols ? keep.dst : s + o.qkv, s + o.o, (const float*)(s + o.lse), t_h, s + o.qkv, ws + ch->wsl.attn); }));
     // dA = dQKV . Wqkv^T
     PMC_TRY(t_gemm(ch->ctx, PMC_B, gemm_args(ch, false, true, T, h, 3 * h, s + o.qkv, 3 * h, P(ch, l, W_QKV), 3 * h, t_h, h,
                                   PMC_EPI_NONE), ch->wsl));
@@ -395,11 +402,14 @@ int chunk_backward_input(pmc_chunk* ch, int32_t mb, const void* dy, void* dx) {
     void* out = l == 0 ? dx : (void*)(s + o.x);
     PMC_TRY(traced(ch->ctx, PMC_OP_LN_BWD, PMC_B, T, h, 0, 0, [&] { return k::layernorm_backward(st, c.dtype, T, h, t_h, s + o.x, P(ch, l, LN1_G), (const float*)(s + o.mean1),
                                   (const float*)(s + o.rstd1), s + o.xmid, out, G(ch, l, LN1_G), G(ch, l, LN1_B), next_partial(), &ln_jobs); }));
-    PMC_TRY(flush_ln(false));
+    if (l > 0) PMC_TRY(flush_ln(false));
   }
-  PMC_TRY(flush_ln(true));
   // keep the chunk's dY for W of the top layer in the slot of the (now dead) chunk input
-  PMC_TRY(traced(ch->ctx, PMC_OP_COPY, PMC_B, T, h, 0, 0, [&] { return k::copy_rows(st, c.dtype, T, h, dy, h, s + ch->off[0].x, h); }));
+  k::RowCopy keep_dy;
+  keep_dy.src = dy;
+  keep_dy.dst = s + ch->off[0].x;
+  keep_dy.ld_src = keep_dy.ld_dst = keep_dy.cols = h;
+  PMC_TRY(flush_ln(true, keep_dy));
   m.state = kBackwardDone;
   ch->ctx->pool.shrink(m.device, (int64_t)ch->stats_bytes);
   return PMC_OK;
@@ -727,6 +737,7 @@ int pmc_chunk_create(pmc_ctx* ctx, const pmc_chunk_cfg* cfg, pmc_chunk** out) {
   ch->unit_bytes = unit_bytes_of(*cfg);
   ch->stats_bytes = stats_bytes_of(*cfg);
   ch->wsl = workspace_of(*cfg);
+  ch->kept_columns = k::attention_backward_kept_columns(cfg->dtype, cfg->microbatch, cfg->seq, cfg->heads, ch->head_dim);
   const size_t th = (size_t)ch->tokens * cfg->hidden * ch->esz, tf = (size_t)ch->tokens * cfg->ffn * ch->esz;
   const size_t per_layer = 8 * th + 2 * tf;
   const size_t st_layer = (size_t)(4 + cfg->heads) * ch->tokens * 4;

@@ -151,8 +151,8 @@ __device__ __forceinline__ float quarters_sum(float v) {
 struct Place {
   int row0, head, b;
 };
-__device__ __forceinline__ Place place(int seq, int block0, bool late_first) {
-  const int blocks = (seq + kRows - 1) / kRows, block = block0 + (int)blockIdx.z;
+__device__ __forceinline__ Place place(int seq, int block, bool late_first) {
+  const int blocks = (seq + kRows - 1) / kRows;
   return {(late_first ? blocks - 1 - block : block) * kRows, (int)blockIdx.x, (int)blockIdx.y};
 }
 
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kWavesF * 64, 2) void attn_fwd_f32(int block0, int 
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(16))) float fold_f32[];  // [8 waves][16][DH + 4]
   __shared__ float stat_m[kWavesF][kRows], stat_l[kWavesF][kRows];
-  const Place at = place(seq, block0, causal != 0);
+  const Place at = place(seq, block0 + (int)blockIdx.z, causal != 0);
   const int h = heads * dh, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, quarter = lane >> 4;
   const size_t pitch = (size_t)3 * h;
   const T* base = qkv + (size_t)at.b * seq * pitch + (size_t)at.head * dh;
@@ -233,16 +233,12 @@ __global__ __launch_bounds__(kWavesF * 64, 2) void attn_fwd_f32(int block0, int 
 #endif
 }
 
-// dq[i] = sigma * sum_j dS[i][j] k[j],  dS = P * (dP - delta),  P = exp(S - lse),  dP = dO . V^T; also
-// emits delta = rowsum(dO * O).
+// dq[i] = sigma * sum_j dS[i][j] k[j],  dS = P * (dP - delta),  P = exp(S - lse),  dP = dO . V^T, for 16 queries; also
+// emits delta = rowsum(dO * O) unless it is NULL.
 template <typename T, int DH, bool VEC>
-__global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dq_f32(int block0, int seq, int heads, int dh, int causal, const T* __restrict__ qkv,
-                                                                const T* __restrict__ o, const float* __restrict__ lse,
-                                                                const T* __restrict__ d_o, T* __restrict__ dq,
-                                                                float* __restrict__ delta) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  extern __shared__ __attribute__((aligned(16))) float fold_f32[];
-  const Place at = place(seq, block0, causal != 0);
+__device__ __forceinline__ void dq_block_f32(float* fold_f32, const Place at, int seq, int heads, int dh, int causal, const T* __restrict__ qkv,
+                                             const T* __restrict__ o, const float* __restrict__ lse, const T* __restrict__ d_o, T* __restrict__ dq,
+                                             size_t ld_dq, float* __restrict__ delta) {
   const int h = heads * dh, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, quarter = lane >> 4;
   const size_t pitch = (size_t)3 * h, own = (size_t)at.b * seq * h + (size_t)at.head * dh;
   const T* base = qkv + (size_t)at.b * seq * pitch + (size_t)at.head * dh;
@@ -262,7 +258,7 @@ __global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dq_f32(int block0, i
       for (int e = 0; e < 4; ++e) dl = fmaf(df[c][e], of[c][e], dl);
   }
   dl = quarters_sum(dl);
-  if (wave == 0 && quarter == 0 && qi < seq) delta[stat] = dl;
+  if (delta && wave == 0 && quarter == 0 && qi < seq) delta[stat] = dl;
   const float my_lse = lse[stat];
 #pragma unroll
   for (int b = 0; b < DH / 64; ++b)
@@ -287,26 +283,24 @@ __global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dq_f32(int block0, i
   __syncthreads();
   for (int i = threadIdx.x; i < kRows * (DH / 4); i += kWavesF * 64) {
     const int row = i / (DH / 4), col = 4 * (i % (DH / 4));
-    if (at.row0 + row < seq) store4<T, VEC>(dq + own + (size_t)(at.row0 + row) * h, col, dh, fold<DH>(fold_f32, row, col) * sigma);
+    if (at.row0 + row < seq)
+      store4<T, VEC>(dq + ((size_t)at.b * seq + at.row0 + row) * ld_dq + (size_t)at.head * dh, col, dh, fold<DH>(fold_f32, row, col) * sigma);
   }
-#endif
 }
 
-// For 16 keys: dv[j] = sum_i P[i][j] dO[i],  dk[j] = sigma * sum_i dS[i][j] q[i]; written over v[j] and
-// k[j] inside the packed buffer (a key block is read only by the workgroup that owns it, before its fold).
-template <typename T, int DH, bool VEC>
-__global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dkv_f32(int block0, int seq, int heads, int dh, int causal, const T* qkv,
-                                                                 const float* __restrict__ lse, const float* __restrict__ delta,
-                                                                 const T* __restrict__ d_o, T* dqkv) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  extern __shared__ __attribute__((aligned(16))) float fold_f32[];
-  const Place at = place(seq, block0, false);
+// For 16 keys: dv[j] = sum_i P[i][j] dO[i],  dk[j] = sigma * sum_i dS[i][j] q[i].  dqkv may be qkv itself (a key block is read only by
+// the workgroup that owns it, before its fold).  DELTA: delta is formed
+// here from dO and O (o), otherwise read from `delta`.
+template <typename T, int DH, bool VEC, bool DELTA>
+__device__ __forceinline__ void dkv_block_f32(float* fold_f32, const Place at, int seq, int heads, int dh, int causal, const T* qkv,
+                                              const T* __restrict__ o, const float* __restrict__ lse,
+                                              const float* __restrict__ delta, const T* __restrict__ d_o, T* dqkv) {
   const int h = heads * dh, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, quarter = lane >> 4;
   const size_t pitch = (size_t)3 * h;
   const T* base = qkv + (size_t)at.b * seq * pitch + (size_t)at.head * dh;
   const T* dob = d_o + (size_t)at.b * seq * h + (size_t)at.head * dh;
   const float* lse_b = lse + ((size_t)at.b * heads + at.head) * seq;
-  const float* delta_b = delta + ((size_t)at.b * heads + at.head) * seq;
+  const float* delta_b = DELTA ? nullptr : delta + ((size_t)at.b * heads + at.head) * seq;
   const int kj = at.row0 + (lane & 15);
   const float sigma = 1.0f / sqrtf((float)dh);
   f32x4 kf[DH / 16], vf[DH / 16], acck[DH / 64][4], accv[DH / 64][4];
@@ -322,12 +316,22 @@ __global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dkv_f32(int block0, 
       f32x4 qf[DH / 16], df[DH / 16];
       load_rows<T, DH, VEC>(qf, base, pitch, q0, seq - 1, dh, lane);
       load_rows<T, DH, VEC>(df, dob, (size_t)h, q0, seq - 1, dh, lane);
+      float dl = 0.f;  // of query q0 + lane % 16
+      if constexpr (DELTA) {
+        f32x4 of[DH / 16];
+        load_rows<T, DH, VEC>(of, o + (dob - d_o), (size_t)h, q0, seq - 1, dh, lane);
+#pragma unroll
+        for (int c = 0; c < DH / 16; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dl = fmaf(df[c][e], of[c][e], dl);
+        dl = quarters_sum(dl);
+      }
       const f32x4 s = dot_rows(qf, kf), dp = dot_rows(df, vf);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int qi = q0 + 4 * quarter + r, qc = min(qi, seq - 1);
         p[r] = (qi < seq && (!causal || kj <= qi)) ? expf(s[r] * sigma - lse_b[qc]) : 0.f;
-        ds[r] = p[r] * (dp[r] - delta_b[qc]);
+        ds[r] = p[r] * (dp[r] - (DELTA ? __shfl(dl, 4 * quarter + r, 64) : delta_b[qc]));
       }
     }
     f32x4 qc[4][DH / 64], dc[4][DH / 64];
@@ -348,6 +352,45 @@ __global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dkv_f32(int block0, 
                        fold<DH>(fold_f32, row, col) * (which ? sigma : 1.0f));
     }
   }
+}
+
+template <typename T, int DH, bool VEC>
+__global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dq_f32(int block0, int seq, int heads, int dh, int causal, const T* __restrict__ qkv,
+                                                                const T* __restrict__ o, const float* __restrict__ lse,
+                                                                const T* __restrict__ d_o, T* __restrict__ dq, size_t ld_dq,
+                                                                float* __restrict__ delta) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(16))) float fold_f32[];
+  dq_block_f32<T, DH, VEC>(fold_f32, place(seq, block0 + (int)blockIdx.z, causal != 0), seq, heads, dh, causal, qkv, o, lse, d_o, dq, ld_dq,
+                           delta);
+#endif
+}
+
+template <typename T, int DH, bool VEC>
+__global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_dkv_f32(int block0, int seq, int heads, int dh, int causal, const T* qkv,
+                                                                 const float* __restrict__ lse,
+                                                                 const float* __restrict__ delta, const T* __restrict__ d_o, T* dqkv) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(16))) float fold_f32[];
+  dkv_block_f32<T, DH, VEC, false>(fold_f32, place(seq, block0 + (int)blockIdx.z, false), seq, heads, dh, causal, qkv, nullptr, lse,
+                                   delta, d_o, dqkv);
+#endif
+}
+
+// Both halves in one launch: a workgroup is a block of 16 queries (odd blocks) or of 16 keys, dealt out alternately with the
+// longest of each first.  Nothing passes between them, and qkv must not be dqkv: every query block reads all keys.
+template <typename T, int DH, bool VEC>
+__global__ __launch_bounds__(kWavesF * 64, 2) void attn_bwd_f32(int block0, int seq, int heads, int dh, int causal, const T* __restrict__ qkv,
+                                                             const T* __restrict__ o, const float* __restrict__ lse,
+                                                             const T* __restrict__ d_o, T* __restrict__ dqkv) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(16))) float fold_f32[];
+  const int block = block0 + (int)blockIdx.z;
+  const size_t pitch = (size_t)3 * heads * dh;
+  if (block & 1)
+    dq_block_f32<T, DH, VEC>(fold_f32, place(seq, block >> 1, causal != 0), seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, pitch, nullptr);
+  else
+    dkv_block_f32<T, DH, VEC, true>(fold_f32, place(seq, block >> 1, false), seq, heads, dh, causal, qkv, o, lse, nullptr, d_o, dqkv);
 #endif
 }
 
@@ -361,11 +404,12 @@ int check(const char* what, int batch, int seq, int heads, int dh) {
 // Calls launch(first row block, grid) for the row blocks of every (head, sequence) pair, in as many launches as the
 // grid's third dimension needs.  (One dimension for all three holds fewer than 2^32 threads, 2^23 of these workgroups;
 // a launch past that is not refused but leaves workgroups out.)
+// halves = 2: query and key blocks are both counted.
 template <typename Launch>
-int for_row_blocks(const char* what, int batch, int seq, int heads, Launch launch) {
-  const int blocks = (int)(((int64_t)seq + kRows - 1) / kRows);
-  for (int b0 = 0; b0 < blocks; b0 += kMaxGrid) {
-    launch(b0, dim3(heads, batch, blocks - b0 < kMaxGrid ? blocks - b0 : kMaxGrid));
+int for_row_blocks(const char* what, int batch, int seq, int heads, int halves, Launch launch) {
+  const int64_t blocks = ((int64_t)seq + kRows - 1) / kRows * halves;
+  for (int64_t b0 = 0; b0 < blocks; b0 += kMaxGrid) {
+    launch((int)b0, dim3(heads, batch, (unsigned)(blocks - b0 < kMaxGrid ? blocks - b0 : kMaxGrid)));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(PMC_ERR_HIP, "%s launch failed: %s", what, hipGetErrorString(e));
   }
@@ -388,25 +432,34 @@ template <typename T, int DH, bool VEC>
 int fwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, void* o, float* lse) {
   static std::atomic<bool> done{false};
   if (int rc = reserve_lds(attn_fwd_f32<T, DH, VEC>, fold_bytes<DH>(), done, "attention_forward")) return rc;
-  return for_row_blocks("attention_forward", batch, seq, heads, [&](int block0, dim3 grid) {
+  return for_row_blocks("attention_forward", batch, seq, heads, 1, [&](int block0, dim3 grid) {
     attn_fwd_f32<T, DH, VEC><<<grid, dim3(kWavesF * 64), fold_bytes<DH>(), st>>>(block0, seq, heads, dh, causal, (const T*)qkv, (T*)o, lse);
   });
 }
 
+// dq (pitch ld_dq): a buffer of its own if dqkv is qkv, otherwise dqkv.
 template <typename T, int DH, bool VEC>
 int bwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, const void* o, const float* lse,
-               const void* d_o, void* dqkv, void* dq_stage, float* delta) {
-  static std::atomic<bool> done_dq{false}, done_dkv{false};
-  if (int rc = reserve_lds(attn_bwd_dq_f32<T, DH, VEC>, fold_bytes<DH>(), done_dq, "attention_backward")) return rc;
-  if (int rc = reserve_lds(attn_bwd_dkv_f32<T, DH, VEC>, fold_bytes<DH>(), done_dkv, "attention_backward")) return rc;
-  int rc = for_row_blocks("attention_backward", batch, seq, heads, [&](int block0, dim3 grid) {
-    attn_bwd_dq_f32<T, DH, VEC><<<grid, dim3(kWavesF * 64), fold_bytes<DH>(), st>>>(block0, seq, heads, dh, causal, (const T*)qkv,
-                                                                                     (const T*)o, lse, (const T*)d_o, (T*)dq_stage, delta);
+               const void* d_o, void* dqkv, void* dq, int ld_dq, float* delta) {
+  static std::atomic<bool> done_dq{false}, done_dkv{false}, done_both{false};
+  constexpr size_t lds = fold_bytes<DH>();
+  if (dq == dqkv && attention_merged_f32(batch, seq, heads)) {
+    if (int rc = reserve_lds(attn_bwd_f32<T, DH, VEC>, lds, done_both, "attention_backward")) return rc;
+    return for_row_blocks("attention_backward", batch, seq, heads, 2, [&](int block0, dim3 grid) {
+      attn_bwd_f32<T, DH, VEC><<<grid, dim3(kWavesF * 64), lds, st>>>(block0, seq, heads, dh, causal, (const T*)qkv, (const T*)o, lse,
+                                                                       (const T*)d_o, (T*)dqkv);
+    });
+  }
+  if (int rc = reserve_lds(attn_bwd_dq_f32<T, DH, VEC>, lds, done_dq, "attention_backward")) return rc;
+  if (int rc = reserve_lds(attn_bwd_dkv_f32<T, DH, VEC>, lds, done_dkv, "attention_backward")) return rc;
+  int rc = for_row_blocks("attention_backward", batch, seq, heads, 1, [&](int block0, dim3 grid) {
+    attn_bwd_dq_f32<T, DH, VEC><<<grid, dim3(kWavesF * 64), lds, st>>>(block0, seq, heads, dh, causal, (const T*)qkv, (const T*)o, lse,
+                                                                        (const T*)d_o, (T*)dq, (size_t)ld_dq, delta);
   });
   if (rc) return rc;
-  return for_row_blocks("attention_backward", batch, seq, heads, [&](int block0, dim3 grid) {
-    attn_bwd_dkv_f32<T, DH, VEC><<<grid, dim3(kWavesF * 64), fold_bytes<DH>(), st>>>(block0, seq, heads, dh, causal, (const T*)qkv, lse,
-                                                                                      delta, (const T*)d_o, (T*)dqkv);
+  return for_row_blocks("attention_backward", batch, seq, heads, 1, [&](int block0, dim3 grid) {
+    attn_bwd_dkv_f32<T, DH, VEC><<<grid, dim3(kWavesF * 64), lds, st>>>(block0, seq, heads, dh, causal, (const T*)qkv, lse, delta,
+                                                                         (const T*)d_o, (T*)dqkv);
   });
 }
 
@@ -422,13 +475,13 @@ int fwd_t(hipStream_t st, int batch, int seq, int heads, int dh, int causal, con
 
 template <typename T>
 int bwd_t(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, const void* o, const float* lse,
-          const void* d_o, void* dqkv, void* dq_stage, float* delta) {
-  const bool vec = four_columns_aligned<T>(dh, qkv, o, d_o) && four_columns_aligned<T>(dh, dqkv, dq_stage, dq_stage);
+          const void* d_o, void* dqkv, void* dq, int ld_dq, float* delta) {
+  const bool vec = four_columns_aligned<T>(dh, qkv, o, d_o) && four_columns_aligned<T>(dh, dqkv, dq, dq);
   if (dh <= 64)
-    return vec ? bwd_launch<T, 64, true>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta)
-               : bwd_launch<T, 64, false>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta);
-  return vec ? bwd_launch<T, 128, true>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta)
-             : bwd_launch<T, 128, false>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta);
+    return vec ? bwd_launch<T, 64, true>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta)
+               : bwd_launch<T, 64, false>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
+  return vec ? bwd_launch<T, 128, true>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta)
+             : bwd_launch<T, 128, false>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
 }
 
 }  // namespace
@@ -440,12 +493,12 @@ int attention_forward_f32(hipStream_t st, int dtype, int batch, int seq, int hea
   return fwd_t<bf16_t>(st, batch, seq, heads, dh, causal, qkv, o, lse);
 }
 
-// dq_stage: [batch*seq, h] storage type; delta: fp32 [batch, heads, seq].
-int attention_backward_f32(hipStream_t st, int dtype, int batch, int seq, int heads, int dh, int causal, const void* qkv,
-                           const void* o, const float* lse, const void* d_o, void* dqkv, void* dq_stage, float* delta) {
+// dq: see bwd_launch.  delta: fp32 [batch, heads, seq].
+int attention_backward_f32(hipStream_t st, int dtype, int batch, int seq, int heads, int dh, int causal, const void* qkv, const void* o,
+                           const float* lse, const void* d_o, void* dqkv, void* dq, int ld_dq, float* delta) {
   if (int rc = check("attention_backward", batch, seq, heads, dh)) return rc;
-  if (dtype == PMC_F32) return bwd_t<float>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta);
-  return bwd_t<bf16_t>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta);
+  if (dtype == PMC_F32) return bwd_t<float>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
+  return bwd_t<bf16_t>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
 }
 
 }  // namespace k

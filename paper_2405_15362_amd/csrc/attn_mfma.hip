@@ -10,13 +10,12 @@
 // O^T = V^T . P^T.  V^T is never formed in memory: the V tile stays [key][dh] in LDS and is read
 // with the transposing LDS load.  Saves O and the log-sum-exp.
 //
-// Backward is two kernels, each output element having one writer and a fixed summation order
-// (results are reproducible run to run):
+// Backward is two halves, one kernel each or both in one launch, each output element having one writer and a fixed
+// summation order (results are reproducible run to run):
 //   dQ   per query block, streaming K/V blocks: recomputes P from the saved log-sum-exp,
 //        dS = P * (dO.V^T - delta), dQ^T += K^T . dS^T; also emits delta = rowsum(dO * O).
-//   dKdV per key block, streaming Q/dO blocks: dV^T += dO^T . P, dK^T += Q^T . dS, written
-//        in place over K and V (a key block is read only by the workgroup that owns it).
-// The launch shapes are chosen by the number of (128-row block, head) pairs: few pairs get small
+//   dKdV per key block, streaming Q/dO blocks: dV^T += dO^T . P, dK^T += Q^T . dS.
+// The launch shapes are chosen by the number of (row block, head) pairs: few pairs get small
 // row blocks and more waves per block so that all compute units have work.
 #include <cstdlib>
 
@@ -346,30 +345,26 @@ __global__ __launch_bounds__(QW * KW * 64, QW * KW == 4 ? 2 : 1) void attn_fwd_m
   }
 }
 
-// Backward, dQ.  Same wave grid as the forward kernel: wave (qg, kg) owns 32 queries and the 32 NKT
+// Backward, dQ of one block of queries.  Same wave grid as the forward kernel: wave (qg, kg) owns 32 queries and the 32 NKT
 // keys starting at 32 NKT kg of every streamed block; 32-key tiles are taken one at a time
 // (S and dP, then dS, then dQ^T += K^T dS^T) to keep the register footprint at two waves per SIMD.
-// The KW partial dQ of a query group are added in key-group order through LDS at the end.
+// The KW partial dQ of a query group are added in key-group order through LDS at the end.  delta may be NULL.
 template <int DH, int QW, int KW, int NKT, bool PAD>
-__global__ __launch_bounds__(QW * KW * 64, QW * KW == 4 ? 2 : 1) void attn_bwd_dq_mfma(
-    int seq, int heads, int dh, int causal, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
-    const float* __restrict__ lse, const bf16_t* __restrict__ d_o, bf16_t* __restrict__ dq, float* __restrict__ delta,
-    float scale, float scale_log2) {
+__device__ __forceinline__ void dq_block(bf16_t* smem, int head_batch, int block, int seq, int heads, int dh, int causal,
+                                         const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const float* __restrict__ lse,
+                                         const bf16_t* __restrict__ d_o, bf16_t* __restrict__ dq, int ld_dq, float* __restrict__ delta, float scale, float scale_log2) {
   constexpr int NT = QW * KW * 64, BQW = 32 * QW, WK = 32 * NKT, BSW = WK * KW;
   constexpr int KT = BSW * DH, VT = BSW * DH;
-  extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hl = lane >> 5;
   const int qg = wave % QW, kg = wave / QW;
-  // grid = (heads * batch, query blocks); under a causal mask late query blocks see the most keys,
-  // so they are dealt out first and the short ones fill the tail
-  const int h = heads * dh, head = blockIdx.x % heads, b = blockIdx.x / heads;
-  const int q0 = (causal ? (int)(gridDim.y - 1 - blockIdx.y) : (int)blockIdx.y) * BQW, qw0 = q0 + 32 * qg, qrow = qw0 + (lane & 31);
+  const int h = heads * dh, head = head_batch % heads, b = head_batch / heads;
+  const int q0 = block * BQW, qw0 = q0 + 32 * qg, qrow = qw0 + (lane & 31);
   const int qclamp = min(qrow, seq - 1);
   const size_t ld = (size_t)3 * h;
   const bf16_t* base = qkv + (size_t)b * seq * ld + (size_t)head * dh;
 
   bf16x8 qf[DH / 16], dof[DH / 16];
-  float dl = 0.f;
+  float dl4[4] = {0.f, 0.f, 0.f, 0.f};
   {
     const bf16_t* qp = base + (size_t)qclamp * ld;
     const size_t orow = ((size_t)b * seq + qclamp) * h + (size_t)head * dh;
@@ -380,12 +375,14 @@ __global__ __launch_bounds__(QW * KW * 64, QW * KW == 4 ? 2 : 1) void attn_bwd_d
       dof[ks] = load_frag(d_o + orow, 16 * ks + 8 * hl, cols);
       const bf16x8 of = load_frag(o + orow, 16 * ks + 8 * hl, cols);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) dl += (float)dof[ks][e] * (float)of[e];
+      for (int e = 0; e < 8; ++e) dl4[ks & 3] = __builtin_fmaf((float)dof[ks][e], (float)of[e], dl4[ks & 3]);
     }
   }
+  // in the order of the key blocks' own delta, eight lanes to a query: both forms of the backward pass give the same bits
+  float dl = (dl4[0] + dl4[2]) + (dl4[1] + dl4[3]);
   dl += __shfl_xor(dl, 32, 64);
   const size_t stat = ((size_t)b * heads + head) * seq + qclamp;
-  if (kg == 0 && hl == 0 && qrow < seq) delta[stat] = dl;
+  if (delta && kg == 0 && hl == 0 && qrow < seq) delta[stat] = dl;
   const float lse2 = lse[stat] * kLog2e;
   f32x16 acc[DH / 32];
 #pragma unroll
@@ -470,11 +467,54 @@ __global__ __launch_bounds__(QW * KW * 64, QW * KW == 4 ? 2 : 1) void attn_bwd_d
     }
   }
   if (qrow < seq) {
-    bf16_t* row = dq + ((size_t)b * seq + qrow) * h + (size_t)head * dh;
+    bf16_t* row = dq + ((size_t)b * seq + qrow) * ld_dq + (size_t)head * dh;
 #pragma unroll
     for (int dt = 0; dt < DH / 32; ++dt) store_tile_t(row + 32 * dt, acc[dt], scale, lane, PAD ? dh - 32 * dt : 32);
   }
 }
+
+template <int DH, int QW, int KW, int NKT, bool PAD>
+__global__ __launch_bounds__(QW * KW * 64, QW * KW == 4 ? 2 : 1) void attn_bwd_dq_mfma(
+    int seq, int heads, int dh, int causal, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const float* __restrict__ lse,
+    const bf16_t* __restrict__ d_o, bf16_t* __restrict__ dq, int ld_dq, float* __restrict__ delta, float scale, float scale_log2) {
+  extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+  // grid = (heads * batch, query blocks); under a causal mask late query blocks see the most keys,
+  // so they are dealt out first and the short ones fill the tail
+  const int block = causal ? (int)(gridDim.y - 1 - blockIdx.y) : (int)blockIdx.y;
+  dq_block<DH, QW, KW, NKT, PAD>(smem, blockIdx.x, block, seq, heads, dh, causal, qkv, o, lse, d_o, dq, ld_dq, delta, scale, scale_log2);
+}
+
+// delta = rowsum(dO * O) of a block of BSQ queries by NT = 8 BSQ threads, eight to a query: rows requested with load(), sums left
+// in LDS by put().
+template <int DH, int BSQ, int NT, bool PAD>
+struct OwnDelta {
+  static_assert(NT == 0 || NT == 8 * BSQ, "eight threads to a query");
+  u32x4 rd[DH / 64], ro[DH / 64];
+  __device__ __forceinline__ void load(const bf16_t* dob, const bf16_t* d_o, const bf16_t* o, int q0, int seq, int h, int dh, int tid) {
+    const size_t row = (size_t)(dob - d_o) + (size_t)min(q0 + (tid >> 3), seq - 1) * h;
+#pragma unroll
+    for (int v = 0; v < DH / 64; ++v) {
+      const int col = 8 * ((tid & 7) + 8 * v);
+      const u32x4 z = {0u, 0u, 0u, 0u};
+      const bool in = !PAD || col < dh;
+      rd[v] = in ? *reinterpret_cast<const u32x4*>(d_o + row + col) : z;
+      ro[v] = in ? *reinterpret_cast<const u32x4*>(o + row + col) : z;
+    }
+  }
+  __device__ __forceinline__ void put(float* to, int tid) const {
+    float d = 0.f;
+#pragma unroll
+    for (int v = 0; v < DH / 64; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        d = __builtin_fmaf(bf16lo_to_f32(rd[v][e]), bf16lo_to_f32(ro[v][e]), d);
+        d = __builtin_fmaf(bf16hi_to_f32(rd[v][e]), bf16hi_to_f32(ro[v][e]), d);
+      }
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) d += __shfl_xor(d, off, 64);
+    if ((tid & 7) == 0) to[tid >> 3] = d;
+  }
+};
 
 // Backward, dK and dV.  A workgroup owns 32 KG keys of one head and streams blocks of 32 QG queries
 // (Q and dO tiles plus their log-sum-exp and delta).  Each (key group, query group) pair is served
@@ -483,22 +523,37 @@ __global__ __launch_bounds__(QW * KW * 64, QW * KW == 4 ? 2 : 1) void attn_bwd_d
 //   role 1 keeps V:  dP = dO V^T,  dS = P (dP - delta),     dK^T += Q^T dS.
 // Both roles run the same two matrix products per tile (one against Q, one against dO); only the
 // elementwise step between them differs.  The QG partial sums of a key group are added in
-// query-group order through LDS at the end and written in place over K and V (a key block is read
-// only by its own workgroup).
-template <int DH, int KG, int QG, bool PAD>
+// query-group order through LDS at the end.  dqkv may be qkv itself: a key block is read only by the workgroup that owns it.
+//
+// KW > 0: both halves of the backward pass in one launch, for shapes that leave compute units idle: a workgroup is either a block
+// of queries (odd blockIdx.y, a wave grid of KG x KW) or one of keys, dealt out alternately with the longest of each first, so one kind
+// fills what the other leaves.  Nothing passes between them: delta = rowsum(dO * O) is formed here too, eight threads to a
+// query, from rows of dO and O requested a block ahead.  qkv must not be dqkv then: every query block reads all keys.
+// bf16, causal, two launches / one: 2 heads of 128, 192 tokens 24 / 12 us; 16 heads of 128, 1024 tokens 50 / 44 us.
+template <int DH, int KG, int QG, bool PAD, int KW>
 __global__ __launch_bounds__(KG * QG * 128, KG * QG == 2 ? 3 : 1) void attn_bwd_dkv_mfma(
-    int seq, int heads, int dh, int causal, const bf16_t* qkv, const float* __restrict__ lse, const float* __restrict__ delta,
-    const bf16_t* __restrict__ d_o, bf16_t* dqkv, float scale, float scale_log2) {
+    int seq, int heads, int dh, int causal, const bf16_t* qkv, const bf16_t* __restrict__ o, const float* __restrict__ lse,
+    const float* __restrict__ delta, const bf16_t* __restrict__ d_o, bf16_t* dqkv, float scale, float scale_log2) {
+  constexpr bool DELTA = KW > 0;
   constexpr int NP = KG * QG, NT = NP * 128, BK = 32 * KG, BSQ = 32 * QG;
   constexpr int QT = BSQ * DH;
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];  // [2][Q tile | dO tile], stats, P exchange
+  if constexpr (KW > 0) {
+    static_assert(KG * KW * 64 == NT, "one block size for both halves");
+    if (blockIdx.y & 1) {
+      const int block = causal ? (int)((gridDim.y - 1 - blockIdx.y) >> 1) : (int)(blockIdx.y >> 1);
+      dq_block<DH, KG, KW, 1, PAD>(smem, blockIdx.x, block, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, 3 * heads * dh, nullptr, scale,
+                                   scale_log2);
+      return;
+    }
+  }
   float* stats = reinterpret_cast<float*>(smem + 4 * QT);       // [2][lse2[BSQ] | delta[BSQ]]
   float* xch = stats + 4 * BSQ;                                  // [NP][16 registers][64 lanes]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hl = lane >> 5;
   const int role = wave / NP, pair = wave % NP, kg = pair % KG, qg = pair / KG;
   // grid = (heads * batch, key blocks): early key blocks see the most queries and go first
   const int h = heads * dh, head = blockIdx.x % heads, b = blockIdx.x / heads;
-  const int k0 = blockIdx.y * BK, kw0 = k0 + 32 * kg, krow = kw0 + (lane & 31);
+  const int k0 = (KW > 0 ? blockIdx.y >> 1 : blockIdx.y) * BK, kw0 = k0 + 32 * kg, krow = kw0 + (lane & 31);
   const size_t ld = (size_t)3 * h;
   const bf16_t* base = qkv + (size_t)b * seq * ld + (size_t)head * dh;
   const bf16_t* dob = d_o + (size_t)b * seq * h + (size_t)head * dh;
@@ -525,13 +580,16 @@ __global__ __launch_bounds__(KG * QG * 128, KG * QG == 2 ? 3 : 1) void attn_bwd_
   auto load_stats = [&](int q0) {
     if (tid < 2 * BSQ) {
       const int qi = q0 + (tid % BSQ);
-      st_reg = qi < seq ? (tid < BSQ ? lse_b[qi] * kLog2e : delta_b[qi]) : 0.f;
+      st_reg = qi < seq ? (tid < BSQ ? lse_b[qi] * kLog2e : DELTA ? 0.f : delta_b[qi]) : 0.f;
     }
   };
+  OwnDelta<DH, BSQ, DELTA ? NT : 0, PAD> own;
   dma.template issue<PAD>(rq, smem, ldb, qstart, seq - 1, wave);
   dma.template issue<PAD>(rdo, smem + QT, hb, qstart, seq - 1, wave);
   load_stats(qstart);
-  if (tid < 2 * BSQ) stats[tid] = st_reg;
+  if constexpr (DELTA) own.load(dob, d_o, o, qstart, seq, h, dh, tid);
+  if (tid < (DELTA ? 1 : 2) * BSQ) stats[tid] = st_reg;
+  if constexpr (DELTA) own.put(stats + BSQ, tid);
   __builtin_amdgcn_s_waitcnt(kWaitAllLoads);
   __syncthreads();
   float* my_xch = xch + pair * (16 * 64) + lane;
@@ -548,6 +606,7 @@ __global__ __launch_bounds__(KG * QG * 128, KG * QG == 2 ? 3 : 1) void attn_bwd_
       dma.template issue<PAD>(rq, nxt, ldb, qstart + (blk + 1) * BSQ, seq - 1, wave);
       dma.template issue<PAD>(rdo, nxt + QT, hb, qstart + (blk + 1) * BSQ, seq - 1, wave);
       load_stats(qstart + (blk + 1) * BSQ);
+      if constexpr (DELTA) own.load(dob, d_o, o, qstart + (blk + 1) * BSQ, seq, h, dh, tid);
     }
     const bool active = q0 < seq && (!causal || q0 + 31 >= kw0);  // the same for both waves of a pair
     f32x16 t;
@@ -594,7 +653,10 @@ __global__ __launch_bounds__(KG * QG * 128, KG * QG == 2 ? 3 : 1) void attn_bwd_
                                                             acc[dt], 0, 0, 0);
       }
     }
-    if (blk + 1 < nblk && tid < 2 * BSQ) stats[((blk + 1) & 1) * 2 * BSQ + tid] = st_reg;
+    if (blk + 1 < nblk && tid < (DELTA ? 1 : 2) * BSQ) stats[((blk + 1) & 1) * 2 * BSQ + tid] = st_reg;
+    if constexpr (DELTA) {
+      if (blk + 1 < nblk) own.put(stats + ((blk + 1) & 1) * 2 * BSQ + BSQ, tid);
+    }
     __builtin_amdgcn_s_waitcnt(kWaitAllLoads);
     __syncthreads();  // next tiles staged; the exchange slots may be rewritten
   }
@@ -642,39 +704,68 @@ int fwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal
   return PMC_OK;
 }
 
-// Few (128-query block, head) pairs: 64-query workgroups whose 8 waves split 128-key blocks four
-// ways, so that every compute unit gets work; otherwise 128-query workgroups of 4 waves, each
-// taking whole 64-key blocks, two workgroups to a compute unit.
+// Family 0: 64-row workgroups whose 8 waves split 128 rows of the other side four ways, so that few heads or tokens still
+// occupy the compute units and the chain of one workgroup is short; one workgroup fills a unit.  Family 1: 128-query
+// workgroups (64-key ones in the dK/dV kernel) of 4 waves, each taking whole 64-row blocks, two or three to a unit.
+// Family 0 as long as its workgroups fit the 256 units at once; under a causal mask, where their lengths differ and the short ones fill
+// up, also beyond, up to 512 (128-row block, head) pairs, for sequences long enough that the chain counts.  A sequence of one 64-row
+// block has nothing to split.  us of family 0 / 1, heads of 128, forward and backward, w = 64-row workgroups: causal 16 heads x
+// 1000 (w 256) 18 / 26 and 50 / 87; 32 x 768 (w 384) 21 / 22 and 58 / 73; 128 x 256 (w 512) 18 / 12 and 52 / 42; 64 x 512 (w 512) 21 / 17 and
+// 60 / 58; 16 x 64 8.4 / 5.9 forward; not causal 32 x 768 28 / 21 and 84 / 75, 32 x 1000 35 / 28 and 115 / 117.
 // The attn_shape tuning switch (0|1|2) forces a family of launch shapes (tests and tuning).
-int shape_family(int batch, int seq, int heads) {
+int shape_family(bool backward, int batch, int seq, int heads, int dh, int causal) {
   if (const int f = tuning(kTuneAttnShape); f >= 0) return f;
-  return (long)((seq + 127) / 128) * heads * batch < 512 ? 0 : 1;
+  if (!backward && seq <= 64) return 1;
+  const int64_t pairs = (int64_t)heads * batch;
+  if ((seq + 63) / 64 * pairs <= 256) return 0;
+  if ((seq + 127) / 128 * pairs >= 512 || !(causal || backward)) return 1;
+  return (int64_t)seq * 64 >= (int64_t)(causal ? 384 : 768) * dh ? 0 : 1;
 }
 
 template <int DH, bool PAD>
 int fwd_t(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, void* o, float* lse) {
-  if (shape_family(batch, seq, heads) == 0) return fwd_launch<DH, 2, 4, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
+  if (shape_family(false, batch, seq, heads, dh, causal) == 0) return fwd_launch<DH, 2, 4, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
   return fwd_launch<DH, 4, 1, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
 }
 
+template <int DH, int QW, int KW, int NKT>
+constexpr size_t lds_dq() { return 2 * sizeof(bf16_t) * 32 * NKT * KW * 2 * DH; }
+template <int DH, int KG, int QG>
+constexpr size_t lds_dkv() {
+  constexpr size_t tiles = 4 * sizeof(bf16_t) * 32 * QG * DH + (4 * 32 * QG + (size_t)KG * QG * 16 * 64) * sizeof(float);
+  constexpr size_t merge = QG > 1 ? (size_t)2 * KG * (DH / 2) * 64 * sizeof(float) : 0;
+  return tiles > merge ? tiles : merge;
+}
+
 template <int DH, int QW, int KW, int NKT, int KG, int QG, bool PAD>
-int bwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, const void* o,
-               const float* lse, const void* d_o, void* dqkv, void* dq_stage, float* delta) {
-  constexpr size_t lds_dq = 2 * sizeof(bf16_t) * 32 * NKT * KW * 2 * DH;
-  constexpr size_t tiles_dkv =
-      4 * sizeof(bf16_t) * 32 * QG * DH + (4 * 32 * QG + (size_t)KG * QG * 16 * 64) * sizeof(float);
-  constexpr size_t merge_dkv = QG > 1 ? (size_t)2 * KG * (DH / 2) * 64 * sizeof(float) : 0;
-  constexpr size_t lds_dkv = tiles_dkv > merge_dkv ? tiles_dkv : merge_dkv;
-  static_assert(lds_dq <= 160 * 1024 && lds_dkv <= 160 * 1024, "tiles exceed the LDS of a compute unit");
+int bwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, const void* o, const float* lse,
+               const void* d_o, void* dqkv, void* dq, int ld_dq, float* delta) {
+  constexpr size_t dq_bytes = lds_dq<DH, QW, KW, NKT>(), dkv_bytes = lds_dkv<DH, KG, QG>();
+  static_assert(dq_bytes <= 160 * 1024 && dkv_bytes <= 160 * 1024, "tiles exceed the LDS of a compute unit");
   static std::atomic<bool> done_dq{false}, done_dkv{false};
-  if (int rc = reserve_lds(attn_bwd_dq_mfma<DH, QW, KW, NKT, PAD>, lds_dq, done_dq, "attention_backward")) return rc;
-  if (int rc = reserve_lds(attn_bwd_dkv_mfma<DH, KG, QG, PAD>, lds_dkv, done_dkv, "attention_backward")) return rc;
+  if (int rc = reserve_lds(attn_bwd_dq_mfma<DH, QW, KW, NKT, PAD>, dq_bytes, done_dq, "attention_backward")) return rc;
+  if (int rc = reserve_lds(attn_bwd_dkv_mfma<DH, KG, QG, PAD, 0>, dkv_bytes, done_dkv, "attention_backward")) return rc;
   const float scale = 1.0f / sqrtf((float)dh), scale_log2 = kLog2e * scale;
-  attn_bwd_dq_mfma<DH, QW, KW, NKT, PAD><<<dim3(heads * batch, (seq + 32 * QW - 1) / (32 * QW)), dim3(QW * KW * 64), lds_dq, st>>>(
-      seq, heads, dh, causal, (const bf16_t*)qkv, (const bf16_t*)o, lse, (const bf16_t*)d_o, (bf16_t*)dq_stage, delta, scale,
-      scale_log2);
-  attn_bwd_dkv_mfma<DH, KG, QG, PAD><<<dim3(heads * batch, (seq + 32 * KG - 1) / (32 * KG)), dim3(KG * QG * 128), lds_dkv, st>>>(
-      seq, heads, dh, causal, (const bf16_t*)qkv, lse, delta, (const bf16_t*)d_o, (bf16_t*)dqkv, scale, scale_log2);
+  attn_bwd_dq_mfma<DH, QW, KW, NKT, PAD><<<dim3(heads * batch, (seq + 32 * QW - 1) / (32 * QW)), dim3(QW * KW * 64), dq_bytes, st>>>(
+      seq, heads, dh, causal, (const bf16_t*)qkv, (const bf16_t*)o, lse, (const bf16_t*)d_o, (bf16_t*)dq, ld_dq, delta, scale, scale_log2);
+  attn_bwd_dkv_mfma<DH, KG, QG, PAD, 0><<<dim3(heads * batch, (seq + 32 * KG - 1) / (32 * KG)), dim3(KG * QG * 128), dkv_bytes, st>>>(
+      seq, heads, dh, causal, (const bf16_t*)qkv, nullptr, lse, delta, (const bf16_t*)d_o, (bf16_t*)dqkv, scale, scale_log2);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(PMC_ERR_HIP, "attention_backward launch failed: %s", hipGetErrorString(e));
+  return PMC_OK;
+}
+
+template <int DH, int QW, int KW, int NKT, int KG, int QG, bool PAD>
+int bwd_merged_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, const void* o, const float* lse,
+                      const void* d_o, void* dqkv) {
+  constexpr size_t lds = lds_dq<DH, QW, KW, NKT>() > lds_dkv<DH, KG, QG>() ? lds_dq<DH, QW, KW, NKT>() : lds_dkv<DH, KG, QG>();
+  static std::atomic<bool> done{false};
+  static_assert(QW == KG && NKT == 1, "one row block for both halves");
+  auto kern = attn_bwd_dkv_mfma<DH, KG, QG, PAD, KW>;
+  if (int rc = reserve_lds(kern, lds, done, "attention_backward")) return rc;
+  const float scale = 1.0f / sqrtf((float)dh);
+  kern<<<dim3(heads * batch, 2 * ((seq + 32 * QW - 1) / (32 * QW))), dim3(QW * KW * 64), lds, st>>>(
+      seq, heads, dh, causal, (const bf16_t*)qkv, (const bf16_t*)o, lse, nullptr, (const bf16_t*)d_o, (bf16_t*)dqkv, scale, kLog2e * scale);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(PMC_ERR_HIP, "attention_backward launch failed: %s", hipGetErrorString(e));
   return PMC_OK;
@@ -682,13 +773,15 @@ int bwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal
 
 template <int DH, bool PAD>
 int bwd_t(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, const void* o, const float* lse,
-          const void* d_o, void* dqkv, void* dq_stage, float* delta) {
-  const int fam = shape_family(batch, seq, heads);
+          const void* d_o, void* dqkv, void* dq, int ld_dq, float* delta) {
+  const int fam = shape_family(true, batch, seq, heads, dh, causal);
+  if (fam == 0 && dq == dqkv && attention_merged(batch, seq, heads))
+    return bwd_merged_launch<DH, 2, 4, 1, 2, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv);
   if (fam == 0)
-    return bwd_launch<DH, 2, 4, 1, 2, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta);
+    return bwd_launch<DH, 2, 4, 1, 2, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
   if (fam == 2)
-    return bwd_launch<DH, 4, 1, 2, 4, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta);
-  return bwd_launch<DH, 4, 1, 2, 2, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta);
+    return bwd_launch<DH, 4, 1, 2, 4, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
+  return bwd_launch<DH, 4, 1, 2, 2, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
 }
 
 int check(const char* what, int batch, int seq, int heads, int dh, const void* qkv) {
@@ -717,16 +810,17 @@ int attention_forward_mfma(hipStream_t st, int batch, int seq, int heads, int dh
   return fwd_t<128, true>(st, batch, seq, heads, dh, causal, qkv, o, lse);
 }
 
-int attention_backward_mfma(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv,
-                            const void* o, const float* lse, const void* d_o, void* dqkv, void* dq_stage, float* delta) {
+// dq (pitch ld_dq): a buffer of its own if dqkv is qkv, otherwise dqkv.
+int attention_backward_mfma(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, const void* o,
+                            const float* lse, const void* d_o, void* dqkv, void* dq, int ld_dq, float* delta) {
   if (int rc = check("attention_backward", batch, seq, heads, dh, qkv)) return rc;
   if ((reinterpret_cast<uintptr_t>(o) | reinterpret_cast<uintptr_t>(d_o) | reinterpret_cast<uintptr_t>(dqkv) |
-       reinterpret_cast<uintptr_t>(dq_stage)) & 15)
+       reinterpret_cast<uintptr_t>(dq)) & 15)
     return fail(PMC_ERR_INVALID, "attention_backward: tensors must be 16-byte aligned");
-  if (dh == 64) return bwd_t<64, false>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta);
-  if (dh == 128) return bwd_t<128, false>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta);
-  if (dh < 64) return bwd_t<64, true>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta);
-  return bwd_t<128, true>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq_stage, delta);
+  if (dh == 64) return bwd_t<64, false>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
+  if (dh == 128) return bwd_t<128, false>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
+  if (dh < 64) return bwd_t<64, true>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
+  return bwd_t<128, true>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
 }
 
 }  // namespace k

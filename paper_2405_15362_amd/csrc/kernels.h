@@ -114,10 +114,18 @@ struct LnPartialJobs {
   int count = 0;
 };
 size_t layernorm_backward_scratch_floats(int rows, int h);
+// Rows that a launch copies beside its own work, whose tensors must not overlap them: dst[row][0..cols) = src[row][0..cols), columns
+// and pitches in whole 16-byte chunks.
+struct RowCopy {
+  const void* src = nullptr;
+  int ld_src = 0;
+  void* dst = nullptr;
+  int ld_dst = 0, cols = 0;
+};
 int layernorm_backward(hipStream_t stream, int dtype, int rows, int h, const void* dy, const void* x,
                        const void* gain, const float* mean, const float* rstd, const void* resid, void* dx,
-                       float* dgain, float* dbias, float* partial, LnPartialJobs* defer = nullptr);
-int layernorm_backward_reduce(hipStream_t stream, int h, const LnPartialJobs& jobs);
+                       float* dgain, float* dbias, float* partial, LnPartialJobs* defer = nullptr, RowCopy copy = {});
+int layernorm_backward_reduce(hipStream_t stream, int h, const LnPartialJobs& jobs, int dtype = PMC_F32, int rows = 0, RowCopy copy = {});
 // As layernorm_backward with the partial sums in a device array built into the library (no workspace,
 // no allocation); PMC_ERR_NOMEM when layernorm_backward_scratch_floats(rows, h) floats do not fit in
 // layernorm_backward_static_scratch_bytes().
@@ -133,6 +141,11 @@ size_t attention_backward_scratch_bytes(int dtype, int batch, int seq, int heads
 int attention_backward(hipStream_t stream, int dtype, int batch, int seq, int heads, int head_dim, int causal,
                        const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv,
                        void* scratch);
+// Columns of qkv (3 heads head_dim or 0) that a caller who wants dqkv in qkv's place is better off copying elsewhere first, to call
+// attention_backward from the copy: with qkv and dqkv apart few blocks run as one launch.
+int attention_backward_kept_columns(int dtype, int batch, int seq, int heads, int head_dim);
+bool attention_merged(int batch, int seq, int heads);
+bool attention_merged_f32(int batch, int seq, int heads);
 
 // out[c] += sum over rows of a[row][c] (fp32 out), for up to four matrices of `rows` rows in one
 // launch; first_block is filled in by column_sums.

@@ -95,6 +95,27 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(int rows, int h, const T* _
   }
 }
 
+// Workgroup `block` of `blocks` copies its share of the rows.  It rides along in a launch that is there anyway: a kernel of its own
+// took 2 to 5 us at up to 1024 tokens, nearly all of it launch and ramp.
+template <typename T, int NT>
+__device__ __forceinline__ void copy_rows_part(const RowCopy& copy, int rows, int block, int blocks) {
+  constexpr int V = Vec<T>::N;
+  const int chunks = copy.cols / V, across = min(chunks, NT), down = NT / across, r0 = threadIdx.x / across, c0 = threadIdx.x % across;
+  if (r0 >= down) return;
+  for (int r = block * down + r0; r < rows; r += blocks * down)
+    for (int c = c0; c < chunks; c += across)
+      Vec<T>::store_raw(static_cast<T*>(copy.dst) + (size_t)r * copy.ld_dst + V * c,
+                        Vec<T>::load_raw(static_cast<const T*>(copy.src) + (size_t)r * copy.ld_src + V * c));
+}
+template <typename T>
+int copy_blocks(const RowCopy& copy, int rows, int threads) {
+  if (!copy.cols) return 0;
+  const int down = std::max(1, threads / (copy.cols / Vec<T>::N));
+  return std::min((rows + down - 1) / down, 1024);
+}
+// (larger copies are faster by themselves: they would wait for the workgroups that they share the launch with)
+bool rides_along(const RowCopy& copy, int rows, int elem) { return copy.cols && (size_t)rows * copy.cols * elem <= 8u << 20; }
+
 // dx = resid + rstd * (g - mean(g) - xhat * mean(g * xhat)),  g = dy * gain,  xhat = (x - mean) * rstd.
 // A workgroup is 8 waves; WR of them share a row (wave w takes the column slice w % WR, NC chunks
 // of 64 lanes x V elements), so a lane holds at most 3*V elements per tensor and 8/WR rows are in
@@ -106,7 +127,11 @@ template <typename T, int NC, int WR>
 __global__ __launch_bounds__(kBwdWaves * 64) void ln_bwd_kernel(int rows, int h, const T* __restrict__ dy,
                                                       const T* x, const T* __restrict__ gain,
                                                       const float* __restrict__ mean, const float* __restrict__ rstd,
-                                                      const T* resid, T* dx, float* __restrict__ partial) {
+                                                      const T* resid, T* dx, float* __restrict__ partial, int blocks, RowCopy copy) {
+  if ((int)blockIdx.x >= blocks) {
+    copy_rows_part<T, kBwdWaves * 64>(copy, rows, blockIdx.x - blocks, gridDim.x - blocks);
+    return;
+  }
   constexpr int V = Vec<T>::N;
   constexpr int RG = kBwdWaves / WR;  // rows in flight
   constexpr int COPIES = ln_bwd_copies(WR);
@@ -124,7 +149,7 @@ __global__ __launch_bounds__(kBwdWaves * 64) void ln_bwd_kernel(int rows, int h,
     if (col < h) Vec<T>::load(gain + col, gn[c]);
   }
   int it = 0;
-  for (int base = blockIdx.x * RG; base < rows; base += gridDim.x * RG, ++it) {
+  for (int base = blockIdx.x * RG; base < rows; base += blocks * RG, ++it) {
     const int row = base + rg;
     const bool live = row < rows;
     float xh[NC][V], g[NC][V], r[NC][V];
@@ -227,20 +252,27 @@ __global__ __launch_bounds__(kBwdWaves * 64) void ln_bwd_kernel(int rows, int h,
   }
 }
 
-// For every job j (blockIdx.y): out_a[i] += sum_p partial_j[p*stride + i] (i < split),
+// For every job j: out_a[i] += sum_p partial_j[p*stride + i] (i < split),
 // out_b[i - split] += ... (i >= split).  A block handles 64 columns; its sixteen waves each sum a
 // contiguous sixteenth of the parts (loads are independent, so many are in flight), and these sums
 // are added in ascending order: the summation order is fixed by (parts) alone.  The chain of loads of one wave is
 // the whole time: with four waves four jobs
 // of 512 parts of 2048 columns took 15.1 us, now 8.2; 128 parts of 4096 columns 10.5, now 7.1.
 constexpr int kSumWaves = 16;
-__global__ __launch_bounds__(kSumWaves * 64) void sum_partials_kernel(LnPartialJobs jobs, int width, int split, size_t stride) {
+__global__ __launch_bounds__(kSumWaves * 64) void sum_partials_kernel(LnPartialJobs jobs, int width, int split, size_t stride, int copy_rows, bool copy_f32, RowCopy copy) {
+  const int sum_blocks = (width + 63) / 64;
+  if ((int)blockIdx.x >= sum_blocks * jobs.count) {
+    const int block = blockIdx.x - sum_blocks * jobs.count, blocks = gridDim.x - sum_blocks * jobs.count;
+    if (copy_f32) copy_rows_part<float, kSumWaves * 64>(copy, copy_rows, block, blocks);
+    else copy_rows_part<bf16_t, kSumWaves * 64>(copy, copy_rows, block, blocks);
+    return;
+  }
   __shared__ float share[kSumWaves][64];
-  const int job = blockIdx.y;
+  const int job = blockIdx.x / sum_blocks;
   const float* __restrict__ partial = jobs.partial[job];
   const int parts = jobs.parts[job];
   const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int i = blockIdx.x * 64 + lane;
+  const int i = ((int)blockIdx.x - job * sum_blocks) * 64 + lane;
   const int per = (parts + kSumWaves - 1) / kSumWaves, p0 = g * per, p1 = min(parts, p0 + per);
   float acc = 0.f;
   if (i < width) {
@@ -346,10 +378,10 @@ int ln_fwd_t(hipStream_t st, int rows, int h, const void* x, const void* gain, c
 template <typename T>
 int ln_bwd_t(hipStream_t st, int rows, int h, const void* dy, const void* x, const void* gain, const float* mean,
              const float* rstd, const void* resid, void* dx, float* dgain, float* dbias, float* partial,
-             LnPartialJobs* defer) {
+             LnPartialJobs* defer, const RowCopy& copy) {
   const LnBwdShape sh = ln_bwd_shape(h, Vec<T>::N);
   if (!sh.nc) return fail(PMC_ERR_INVALID, "LayerNorm width %d too large", h);
-  const int blocks = ln_bwd_blocks(rows, kBwdWaves / sh.wr);
+  const int blocks = ln_bwd_blocks(rows, kBwdWaves / sh.wr), copying = copy_blocks<T>(copy, rows, kBwdWaves * 64);
   const size_t lds = ((size_t)ln_bwd_copies(sh.wr) * 2 * sh.wr * sh.nc * Vec<T>::N * 64 + 4 * kBwdWaves) * sizeof(float);
 #define LN_BWD_CASE(NC, WR)                                                                                  \
   case NC * 16 + WR:                                                                                         \
@@ -357,8 +389,8 @@ int ln_bwd_t(hipStream_t st, int rows, int h, const void* dy, const void* x, con
         hipFuncSetAttribute(reinterpret_cast<const void*>(ln_bwd_kernel<T, NC, WR>),                         \
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)             \
       return fail(PMC_ERR_HIP, "layernorm_backward: cannot reserve %zu bytes of LDS", lds);                  \
-    ln_bwd_kernel<T, NC, WR><<<dim3(blocks), dim3(kBwdWaves * 64), lds, st>>>(                               \
-        rows, h, (const T*)dy, (const T*)x, (const T*)gain, mean, rstd, (const T*)resid, (T*)dx, partial);   \
+    ln_bwd_kernel<T, NC, WR><<<dim3(blocks + copying), dim3(kBwdWaves * 64), lds, st>>>(                               \
+        rows, h, (const T*)dy, (const T*)x, (const T*)gain, mean, rstd, (const T*)resid, (T*)dx, partial, blocks, copy); \
     break;
   switch (sh.nc * 16 + sh.wr) {
     LN_BWD_CASE(1, 1) LN_BWD_CASE(2, 1) LN_BWD_CASE(3, 1) LN_BWD_CASE(2, 2) LN_BWD_CASE(3, 2) LN_BWD_CASE(2, 4)
@@ -399,16 +431,32 @@ size_t layernorm_backward_scratch_floats(int rows, int h) {
   return (size_t)ln_bwd_blocks(rows, 1) * 2 * h;
 }
 
-int layernorm_backward_reduce(hipStream_t st, int h, const LnPartialJobs& jobs) {
+int check_copy(int dtype, const RowCopy& copy) {
+  const int vec = dtype == PMC_F32 ? 4 : 8;
+  if (copy.cols && (copy.cols < 0 || !copy.src || !copy.dst || !aligned16(copy.src) || !aligned16(copy.dst) || copy.cols % vec || copy.ld_src % vec ||
+                    copy.ld_dst % vec || copy.ld_src < copy.cols || copy.ld_dst < copy.cols))
+    return fail(PMC_ERR_INVALID, "rows to copy: %d columns, pitches %d and %d, must be multiples of %d and 16-byte aligned", copy.cols, copy.ld_src,
+                copy.ld_dst, vec);
+  return PMC_OK;
+}
+
+int layernorm_backward_reduce(hipStream_t st, int h, const LnPartialJobs& jobs, int dtype, int rows, RowCopy copy) {
   if (jobs.count < 1 || jobs.count > LnPartialJobs::kMax) return fail(PMC_ERR_INVALID, "layernorm_backward_reduce: %d jobs", jobs.count);
-  sum_partials_kernel<<<dim3((2 * h + 63) / 64, jobs.count), dim3(kSumWaves * 64), 0, st>>>(jobs, 2 * h, h, (size_t)2 * h);
+  const bool f32 = dtype == PMC_F32;
+  if (copy.cols && !rides_along(copy, rows, f32 ? 4 : 2)) {
+    if (int rc = copy_rows(st, dtype, rows, copy.cols, copy.src, copy.ld_src, copy.dst, copy.ld_dst)) return rc;
+    copy.cols = 0;
+  }
+  if (int rc = check_copy(dtype, copy)) return rc;
+  const int copying = f32 ? copy_blocks<float>(copy, rows, kSumWaves * 64) : copy_blocks<bf16_t>(copy, rows, kSumWaves * 64);
+  sum_partials_kernel<<<dim3((2 * h + 63) / 64 * jobs.count + copying), dim3(kSumWaves * 64), 0, st>>>(jobs, 2 * h, h, (size_t)2 * h, rows, f32, copy);
   PMC_LAUNCH_CHECK("layernorm_backward reduce");
   return PMC_OK;
 }
 
 int layernorm_backward(hipStream_t st, int dtype, int rows, int h, const void* dy, const void* x, const void* gain,
                        const float* mean, const float* rstd, const void* resid, void* dx, float* dgain, float* dbias,
-                       float* partial, LnPartialJobs* defer) {
+                       float* partial, LnPartialJobs* defer, RowCopy copy) {
   if (rows <= 0 || h <= 0) return fail(PMC_ERR_INVALID, "layernorm_backward: rows=%d h=%d", rows, h);
   const int vec = dtype == PMC_F32 ? 4 : 8;
   if (h % vec) return fail(PMC_ERR_INVALID, "layernorm_backward: h=%d must be a multiple of %d", h, vec);
@@ -416,8 +464,13 @@ int layernorm_backward(hipStream_t st, int dtype, int rows, int h, const void* d
     return fail(PMC_ERR_INVALID, "layernorm_backward: NULL pointer");
   if (!aligned16(dy) || !aligned16(x) || !aligned16(gain) || !aligned16(dx) || (resid && !aligned16(resid)))
     return fail(PMC_ERR_INVALID, "layernorm_backward: pointers must be 16-byte aligned");
-  if (dtype == PMC_F32) return ln_bwd_t<float>(st, rows, h, dy, x, gain, mean, rstd, resid, dx, dgain, dbias, partial, defer);
-  if (dtype == PMC_BF16) return ln_bwd_t<bf16_t>(st, rows, h, dy, x, gain, mean, rstd, resid, dx, dgain, dbias, partial, defer);
+  if (copy.cols && !rides_along(copy, rows, dtype == PMC_F32 ? 4 : 2)) {
+    if (int rc = copy_rows(st, dtype, rows, copy.cols, copy.src, copy.ld_src, copy.dst, copy.ld_dst)) return rc;
+    copy.cols = 0;
+  }
+  if (int rc = check_copy(dtype, copy)) return rc;
+  if (dtype == PMC_F32) return ln_bwd_t<float>(st, rows, h, dy, x, gain, mean, rstd, resid, dx, dgain, dbias, partial, defer, copy);
+  if (dtype == PMC_BF16) return ln_bwd_t<bf16_t>(st, rows, h, dy, x, gain, mean, rstd, resid, dx, dgain, dbias, partial, defer, copy);
   return fail(PMC_ERR_INVALID, "layernorm_backward: bad dtype %d", dtype);
 }
 

@@ -542,6 +542,38 @@ def test_layernorm_forward_backward(ctx, dtype, rows, h):
     assert_close(host(dbias) + 0.5, db_ref, "f32", "dbias")
 
 
+# (batch, seq, heads, head size, one launch): one row, a row past a block, the last size of one launch and the first of two
+MERGED = [("bf16", 1, 8, 1, 64, True), ("bf16", 1, 65, 2, 128, True), ("bf16", 2, 520, 14, 40, True), ("bf16", 1, 1024, 16, 64, True),
+          ("bf16", 1, 1032, 16, 64, False), ("bf16", 3, 96, 8, 112, True), ("f32", 1, 4, 1, 64, True), ("f32", 1, 256, 16, 20, True),
+          ("f32", 1, 260, 16, 20, False), ("bf16", 1, 264, 8, 20, True), ("f32", 2, 68, 3, 128, True)]
+
+
+@pytest.mark.parametrize("case", MERGED, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("causal", [True, False])
+def test_attention_backward_in_one_launch(ctx, case, causal):
+    """Apart from qkv, where few blocks run as one launch, against the oracle, and bit for bit what the two launches in place give."""
+    dtype, batch, seq, heads, dh, one = case
+    h = heads * dh
+    row = 64 if dtype == "bf16" and dh % 8 == 0 else 16
+    assert one == (-(-seq // row) * heads * batch <= 256)
+    print("one-launch attention case", case, causal, flush=True)
+    qkv = mat(("merged", case, causal, "qkv"), (batch * seq, 3 * h), dtype)
+    d_o = mat(("merged", case, causal, "do"), (batch * seq, h), dtype)
+    q64 = qkv.astype(np.float64)
+    o_ref, probs, _ = OL.attention(q64, heads, causal, batch)
+    want = OL.attention_input_grad(d_o.astype(np.float64), q64, probs, heads, batch)
+    qd, dod = dev(qkv, dtype), dev(d_o, dtype)
+    o, lse = dev(np.zeros((batch * seq, h)), dtype), torch.zeros(batch * heads * seq, device="cuda")
+    P.pmc_attention_forward(ctx, qd, o, lse, batch, seq, heads, dh, causal)
+    apart, inplace = torch.full_like(qd, float("nan")), qd.clone()
+    P.pmc_attention_backward(ctx, qd, o, lse, dod, apart, batch, seq, heads, dh, causal)
+    P.pmc_attention_backward(ctx, inplace, o, lse, dod, inplace, batch, seq, heads, dh, causal)
+    torch.cuda.synchronize()
+    assert_close(host(o), o_ref, dtype, "o")
+    assert_close(host(apart), want, dtype, "dqkv", scale=np.sqrt(np.mean(want ** 2)))
+    assert torch.equal(apart, inplace)
+
+
 @pytest.mark.parametrize("dtype,dh", [("f32", 4), ("f32", 16), ("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128),
                                       ("bf16", 8), ("bf16", 40), ("bf16", 96), ("bf16", 112)])
 @pytest.mark.parametrize("causal", [True, False])
