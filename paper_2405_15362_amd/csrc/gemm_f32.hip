@@ -8,8 +8,7 @@
 //  * gemm_f32_tile_kernel: operand tiles go straight from global memory into an LDS ring
 //    (buffer_load ... lds), waves are a WAVES_M x WAVES_N grid times WK groups that share K (each
 //    group has its own ring and takes every WK-th 32-deep tile; the partial sums are added in group
-//    order through LDS).  WK > 1 puts four waves on a compute unit that owns only a 32 x 64 or
-//    32 x 32 output tile.
+//    order through LDS).  WK > 1 puts eight waves on an output tile too small for as many.
 //  * gemm_f32_direct_kernel: a 16 x 16 output tile per workgroup, K dealt over its eight waves in
 //    16-deep groups, operands loaded in the fragment layout without LDS (one memory latency per few
 //    groups, no barrier before the final fold).  For products whose 32 x 32 tiles would leave most
@@ -444,33 +443,55 @@ int launch_fma_f32(hipStream_t st, const F32Params& p) {
   return PMC_OK;
 }
 
-// Kernel and output tile of a product: 128 x 128, 64 x 64, 32 x 64 and 32 x 32 tiles staged in LDS, 16 x 16
+// Kernel and output tile of a product: 128 x 128, 64 x 128, 64 x 64, 32 x 64 and 32 x 32 tiles staged in LDS, 16 x 16
 // ones in the direct kernel with 16-byte loads, and, with element-wise loads, 16 x 16 ones in the direct
 // kernel or 64 x 64 ones in the FMA kernel.
-enum F32Shape { kTile128, kTile64, kTile32x64, kTile32, kDirect, kDirectElements, kFmaElements };
+enum F32Shape { kTile128, kTile64, kTile32x64, kTile32, kDirect, kDirectElements, kFmaElements, kTile64x128, kTile32Four };
 
-// With 16-byte loads: the tile whose rounds over the 256 compute units take least.  A round costs
-// kPerK us per 1024 of K plus kFixed us (ring fill, fold, epilogue), both measured over M = 40 .. 16384,
-// N = 96 .. 16384, K = 40 .. 16384; at few tiles the small shapes win although they read more (for
-// 128 x 256 x 1024: 71 / 22.7 / 14.0 / 9.1 / 5.9 us), at many the 64 x 64 and 128 x 128 ones
-// (768 x 5120 x 1280: 98 / 96 / 124 / 147 / 232 us).  The gemm_tile switch forces one (tests).
-F32Shape pick_tile_f32(int M, int N, int K) {
-  constexpr int kBm[5] = {128, 64, 32, 32, 16}, kBn[5] = {128, 64, 64, 32, 16};
-  constexpr double kPerK[5] = {68.0, 20.5, 13.0, 8.8, 3.25}, kFixed[5] = {2.6, 0.3, 0.9, 1.2, 0.4};
-  int best = 0;
+// With 16-byte loads: the tile with the least fitted time, us = fixed + n (tile_k k + tile) + ceil(n / per_cu) (group_k k + group)
+// + ceil(n) (round_k k + round) at n tiles per compute unit, per_cu of them side by side, and k = K / 1024.  Fitted to
+// 2323 products of more than 12 us (operands of 200 MB in turn) and 4697 smaller ones (in a graph, so that the host does
+// not count), M = 16 .. 6144, N = 64 .. 5120, K = 64 .. 5120: the tile picked is 0.5 % slower than the best one on average, 1.18
+// times at worst.  All but the 32 x 32 tile of four waves have two waves to a SIMD or more, eight waves to a workgroup, with K
+// in two groups where the tile is too small for eight: with four waves to a unit nothing covered the reads from LDS.  The
+// larger products run in 0.89 and the smaller in 0.95 of the time that the same tiles with four waves take; four waves / eight:
+// 512 x 1024 x 4096 (F, 32 x 64) 49.2 / 45.3 us, 768 x 5120 x 1280 (F, 64 x 64 / 64 x 128) 97 / 88, 512 x 3072 x 1024 (F) 45 / 38,
+// 128 x 128 tiles of 512 x 4096 x 1024 79.7 / 74.5; what few tiles gain by sixteen rows and no LDS: 128 x 256 x 1024 5.8 us
+// against 9.2 in 32 x 32 tiles.  64 x 128 tiles are measured up to four rounds of 128 x 128 ones, which read less, and not taken beyond.
+// The gemm_tile switch forces one of the first five (tests).
+F32Shape pick_tile_f32(bool tb, int M, int N, int K) {
+  struct T {
+    F32Shape shape;
+    int bm, bn, per_cu;
+    double fixed[2], tile_k[2], tile[2], group_k[2], group[2], round_k[2], round[2];  // B stored [K,N] / [N,K]
+  };
+  static constexpr T kTimes[7] = {
+      {kTile128, 128, 128, 1, {2.91, 2.48}, {0.851, 0.}, {5.08, 3.95}, {0., 0.}, {4.21, 0.}, {65.6, 61.9}, {0., 2.45}},
+      {kTile64x128, 64, 128, 2, {3.96, 3.31}, {1.09, 0.427}, {2.23, 2.01}, {5.4, 4.67}, {0., 0.}, {28.4, 29.2}, {0.833, 0.744}},
+      {kTile64, 64, 64, 2, {3.03, 2.65}, {0.165, 0.197}, {1.62, 1.58}, {4.07, 3.15}, {0., 0.}, {15.5, 15.3}, {0.294, 0.159}},
+      {kTile32x64, 32, 64, 2, {2.64, 2.57}, {0., 0.0612}, {1.06, 0.991}, {2.17, 2.07}, {0.486, 0.0135}, {8.2, 8.33}, {0.249, 0.364}},
+      {kTile32, 32, 32, 4, {2.2, 2.33}, {0., 0.0676}, {0.718, 0.68}, {1.54, 1.44}, {0.319, 0.}, {4.72, 4.55}, {0.394, 0.35}},
+      {kTile32Four, 32, 32, 5, {2.47, 2.24}, {0.189, 0.176}, {0.545, 0.53}, {3.27, 2.7}, {0., 0.}, {4.55, 4.5}, {0., 0.}},
+      {kDirect, 16, 16, 4, {2.54, 2.21}, {0., 0.0346}, {0.373, 0.247}, {0.713, 0.508}, {0., 0.}, {2.5, 2.91}, {0.234, 0.}}};
+  auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  F32Shape best = kTile128;
   double best_us = 1e300;
-  for (int c = 0; c < 5; ++c) {
-    const long tiles = (long)((M + kBm[c] - 1) / kBm[c]) * ((N + kBn[c] - 1) / kBn[c]);
-    const double us = (double)((tiles + 255) / 256) * (kPerK[c] * K / 1024.0 + kFixed[c]);
+  for (const T& t : kTimes) {
+    if (t.shape == kTile64x128 && tiles(128, 128) >= 4 * 256) continue;
+    const long count = tiles(t.bm, t.bn), rounds = (count + 255) / 256, groups = (count + 256L * t.per_cu - 1) / (256L * t.per_cu);
+    const double k = K / 1024.0, n = (double)count / 256.0;
+    double us = t.fixed[tb] + n * (t.tile_k[tb] * k + t.tile[tb]) + (double)groups * (t.group_k[tb] * k + t.group[tb]) +
+                (double)rounds * (t.round_k[tb] * k + t.round[tb]);
+    if (t.shape == kDirect) us *= 0.88;  // what it gains inside a pass: 128 x 1024 x 256 (F) 4.8 us in a graph and 5.3 in a step, 32 x 32 tiles 4.75 and 5.9
     if (us < best_us) {
       best_us = us;
-      best = c;
+      best = t.shape;
     }
   }
-  if (const int f = tuning(kTuneGemmTile); f >= 0) best = f;
+  if (const int f = tuning(kTuneGemmTile); f >= 0) best = (F32Shape)f;
   // one dimension of a launch holds fewer than 2^32 threads, 512 to a 16 x 16 tile
-  if (best == kDirect && (long)((M + 15) / 16) * ((N + 15) / 16) >= 1L << 23) best = kTile64;
-  return (F32Shape)best;
+  if (best == kDirect && tiles(16, 16) >= 1L << 23) best = kTile64;
+  return best;
 }
 
 // With element-wise loads: the kernel with the smaller fitted time in us, u = 16 x 16 tiles per compute unit.
@@ -494,16 +515,18 @@ F32Shape shape_of(const GemmArgs& a) {
   const size_t a_bytes = (size_t)(a.trans_a ? a.K : a.M) * a.lda * 4, b_bytes = (size_t)(a.trans_b ? a.N : a.K) * a.ldb * 4;
   const bool vec = a.M % 4 == 0 && a.N % 4 == 0 && a.K % 4 == 0 && a.lda % 4 == 0 && a.ldb % 4 == 0 && a.ldc % 4 == 0 && al(a.A) &&
                    al(a.B) && al(a.C) && al(a.bias) && al(a.resid) && al(a.aux) && a_bytes < 0x7fffffffull && b_bytes < 0x7fffffffull;
-  return vec ? pick_tile_f32(a.M, a.N, a.K) : pick_elements_f32(a.trans_a, a.trans_b, a.M, a.N, a.K);
+  return vec ? pick_tile_f32(a.trans_b, a.M, a.N, a.K) : pick_elements_f32(a.trans_a, a.trans_b, a.M, a.N, a.K);
 }
 
 template <bool TA, bool TB>
 int launch_f32(hipStream_t st, const F32Params& p, F32Shape shape) {
   switch (shape) {
-    case kTile128: return launch_tile_f32<128, 128, 2, 2, 1, 4, TA, TB>(st, p);
-    case kTile64: return launch_tile_f32<64, 64, 2, 2, 1, 4, TA, TB>(st, p);
-    case kTile32x64: return launch_tile_f32<32, 64, 1, 2, 2, 4, TA, TB>(st, p);
-    case kTile32: return launch_tile_f32<32, 32, 1, 1, 4, 4, TA, TB>(st, p);
+    case kTile128: return launch_tile_f32<128, 128, 4, 2, 1, 3, TA, TB>(st, p);
+    case kTile64x128: return launch_tile_f32<64, 128, 2, 4, 1, 3, TA, TB>(st, p);
+    case kTile64: return launch_tile_f32<64, 64, 4, 2, 1, 4, TA, TB>(st, p);
+    case kTile32x64: return launch_tile_f32<32, 64, 2, 2, 2, 3, TA, TB>(st, p);
+    case kTile32: return launch_tile_f32<32, 32, 2, 2, 2, 4, TA, TB>(st, p);
+    case kTile32Four: return launch_tile_f32<32, 32, 2, 2, 1, 4, TA, TB>(st, p);
     case kDirect: return launch_direct_f32<TA, TB>(st, p, true);
     case kDirectElements: return launch_direct_f32<TA, TB>(st, p, false);
     case kFmaElements: return launch_fma_f32<TA, TB>(st, p);

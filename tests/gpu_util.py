@@ -113,6 +113,7 @@ def oracle_chunk(cfg, params, x, dy):
 # what the library would launch for a product (host arithmetic, no GPU needed)
 PLAN_TILE, PLAN_PERSISTENT, PLAN_PAIR, PLAN_GENERAL, PLAN_SPLIT = 0, 20, 21, 22, 30   # PLAN_TILE / PLAN_SPLIT + tile shape
 F32_TILE128, F32_TILE64, F32_TILE32X64, F32_TILE32, F32_DIRECT, F32_DIRECT_ELEMENTS, F32_FMA_ELEMENTS = range(100, 107)
+F32_TILE64X128, F32_TILE32_FOUR = 107, 108
 
 
 def gemm_plan(dtype, ta, tb, M, N, K, epi=0, lda=None, ldb=None, ldc=None, offset=0, ws_bytes=0):

@@ -99,6 +99,23 @@ def test_gemm_f32_tile_shapes(ctx, tune, tile):
                     _gemm_case(ctx, "f32", ta, tb, M, N, K, epi)
 
 
+@pytest.mark.parametrize("M,N,K,shape", [(3084, 1036, 68, U.F32_TILE64X128), (1540, 2044, 100, U.F32_TILE64X128), (516, 1036, 516, U.F32_TILE32_FOUR),
+                                         (2060, 520, 40, U.F32_TILE32_FOUR), (1028, 1036, 12, U.F32_TILE32_FOUR)])
+def test_gemm_f32_tiles_that_no_switch_forces(ctx, M, N, K, shape):
+    for ta, tb in ((False, False), (False, True), (True, False)):
+        assert U.gemm_plan("f32", ta, tb, M, N, K)[0] == shape, (ta, tb)
+        _gemm_case(ctx, "f32", ta, tb, M, N, K, P.EPI_ACCUM_F32 if ta else P.EPI_BIAS_GELU_GRAD)
+
+
+@pytest.mark.parametrize("tb,epis", [(False, (P.EPI_BIAS_RESID, P.EPI_BIAS_GELU_GRAD)), (True, (P.EPI_NONE, P.EPI_MUL))])
+def test_gemm_bf16_128_tiles_in_two_k_groups(ctx, tune, tb, epis):
+    """128x128 tiles of at most one round: K of less than one group's half tile, of half a tile, of whole ones, ragged."""
+    tune(gemm_tile=2)
+    for K in (8, 32, 40, 64, 72, 128, 200, 328):
+        for epi in epis:
+            _gemm_case(ctx, "bf16", False, tb, 136, 264, K, epi)
+
+
 @pytest.mark.parametrize("ta", [False, True])
 @pytest.mark.parametrize("tb", [False, True])
 def test_gemm_f32_element_loads(ctx, ta, tb):
