@@ -572,17 +572,27 @@ __device__ __forceinline__ bf16x8 read_frag_swz(const bf16_t* tile, int r0, int 
 // is read once; the four partial tiles are added at the end.  Kernel times, 128x128 / 64x128 tiles (before)
 // against these: 192 x 256 x 1024 (F) 13.7 / 8.3 -> 5.7 us, 496 x 832 x 3328 (F) 39 / 18.6 -> 10.3,
 // 1024 x 1024 x 4096 (W) 46.7 -> 17.1, 256 x 256 x 2048 (W) 25.6 -> 7.0.
+// KG = 2: two groups of waves cover the output tile, each with one half of every K tile, and add their sums at the end.  For a
+// workgroup that is alone on its compute unit with a wave to a SIMD: nothing covers that wave's reads from LDS and its waits, while
+// more waves on smaller pieces of the tile would read more from LDS.  128x128 tiles, 4 waves / 8 in two groups, operands in the
+// memory-side cache and from HBM: 2000 x 1600 x 6400 (F) 58.2 / 49.9 and 59.5 / 54.6 us, 2000 x 1600 x 1600 (F) 19.5 / 17.2 and 20.7 /
+// 19.6, 4096 x 1024 x 4096 (F) 42.0 / 38.1 and 44.2 / 42.4, (B) 40.0 / 36.5 and 42.3 / 41.9, 4096 x 1024 x 1024 (B) 13.1 / 12.6 and 15.7 /
+// 16.1.  Not for weight gradients (2048 x 2048 x 1024 from HBM 19.1 / 20.4) and not for 256x128 tiles, whose eight waves are two to
+// a SIMD already (1024 x 8192 x 2048 36.9 / 37.6).
 // CUT: the last K tile of a contraction-contiguous operand is partial.  (A kernel of its own: the test for
 // that tile in the K loop cost the steps whose K is whole 0.3 to 1 %.)
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64, bool CUT = false,
-          bool KSPLIT = false, class Params>
+          bool KSPLIT = false, int KG = 1, class Params>
 __device__ __forceinline__ void dma_tile(const Params& p, bf16_t* smem, int tile_m, int tile_n, int kt0, int nk) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  constexpr int NW = WAVES_M * WAVES_N, WM = KSPLIT ? BM : BM / WAVES_M, WN = KSPLIT ? BN : BN / WAVES_N, TM = WM / 32, TN = WN / 32;
+  constexpr int NWG = WAVES_M * WAVES_N, NW = NWG * KG, WM = KSPLIT ? BM : BM / WAVES_M, WN = KSPLIT ? BN : BN / WAVES_N, TM = WM / 32, TN = WN / 32;
   constexpr int TA = BM * BK, TB = BN * BK, STAGE = TA + TB;
   static_assert(!KSPLIT || BK == 16 * NW, "K split over the waves: one 16-wide step of a K tile each");
+  static_assert(KG == 1 || (KG == 2 && BK == 64 && !KSPLIT && TM % 2 == 0), "K groups");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = KSPLIT ? 0 : (wave / WAVES_N) * WM, wn0 = KSPLIT ? 0 : (wave % WAVES_N) * WN;
+  const int wg = wave % NWG, kg = KG > 1 ? wave / NWG : 0;
+  const int wm0 = KSPLIT ? 0 : (wg / WAVES_N) * WM, wn0 = KSPLIT ? 0 : (wg % WAVES_N) * WN;
+  const int ks0 = KSPLIT ? 16 * wave : (BK / KG) * kg;  // first contraction index of this wave in a K tile
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
   // Raw buffer descriptor: base, no stride, size.  A [k][rows] operand's size ends with its last k-row,
@@ -671,9 +681,9 @@ __device__ __forceinline__ void dma_tile(const Params& p, bf16_t* smem, int tile
   __builtin_amdgcn_s_waitcnt(WAIT_TILE);
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < TM; ++i) fa[0][i] = read_frag_swz<BM, A_KMAJ>(smem, wm0 + 32 * i, KSPLIT ? 16 * wave : 0, lane);
+  for (int i = 0; i < TM; ++i) fa[0][i] = read_frag_swz<BM, A_KMAJ>(smem, wm0 + 32 * i, ks0, lane);
 #pragma unroll
-  for (int j = 0; j < TN; ++j) fb[0][j] = read_frag_swz<BN, B_KMAJ>(smem + TA, wn0 + 32 * j, KSPLIT ? 16 * wave : 0, lane);
+  for (int j = 0; j < TN; ++j) fb[0][j] = read_frag_swz<BN, B_KMAJ>(smem + TA, wn0 + 32 * j, ks0, lane);
   int cur = 0;
   if constexpr (KSPLIT) {
     auto k_tile = [&](int c, int kt) {
@@ -699,8 +709,8 @@ __device__ __forceinline__ void dma_tile(const Params& p, bf16_t* smem, int tile
     const int nxt = cur + 1 == NSTAGE ? 0 : cur + 1;
     const int fill = cur == 0 ? NSTAGE - 1 : cur - 1;  // all its readers passed the last barrier
     request(kt + NSTAGE - 1, fill);
-    step(0, cur_a, cur_b, 16);
-    if constexpr (BK == 64) {
+    step(0, cur_a, cur_b, ks0 + 16);
+    if constexpr (BK / KG == 64) {
       step(1, cur_a, cur_b, 32);
       step(0, cur_a, cur_b, 48);
     }
@@ -708,7 +718,7 @@ __device__ __forceinline__ void dma_tile(const Params& p, bf16_t* smem, int tile
     // kt is in registers, so after this barrier its stage may be refilled.
     __builtin_amdgcn_s_waitcnt(WAIT_TILE);
     __syncthreads();
-    step(1, smem + nxt * STAGE, smem + nxt * STAGE + TA, 0);  // after the last tile: a clamped tile, unused
+    step(1, smem + nxt * STAGE, smem + nxt * STAGE + TA, ks0);  // after the last tile: a clamped tile, unused
     cur = nxt;
   }
   // vmcnt(0): drain the clamped tail loads; after the barrier no wave reads or fills a stage any
@@ -718,20 +728,46 @@ __device__ __forceinline__ void dma_tile(const Params& p, bf16_t* smem, int tile
   constexpr int JN = TN == 5 ? 4 : TN;  // widest column group of the staged epilogue
   static_assert(NW * 32 * (32 * JN + 4) * 4 <= NSTAGE * STAGE * 2, "epilogue slabs must fit in the stage ring");
   float* slab = reinterpret_cast<float*>(smem) + wave * (32 * (32 * JN + 4));
+  if constexpr (KG == 2) {
+    // The two waves of a tile exchange halves of their sums: group g finishes the rows 32 (TM / 2) g on.  What a wave
+    // receives lies where its own slab will be.
+    constexpr int H = TM / 2;
+    static_assert(H * TN * 1024 <= 32 * (32 * JN + 4) || H == 1, "the sums of half a tile must fit in a slab");
+    float* to = reinterpret_cast<float*>(smem) + ((1 - kg) * NWG + wg) * (32 * (32 * JN + 4)) + lane;
+    f32x16 half[H][TN];
+#pragma unroll
+    for (int i = 0; i < H; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const f32x16 give = kg ? acc[i][j] : acc[H + i][j];
+        half[i][j] = kg ? acc[H + i][j] : acc[i][j];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) to[((i * TN + j) * 16 + r) * 64] = give[r];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < H; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) half[i][j][r] += slab[((i * TN + j) * 16 + r) * 64 + lane];
+    epilogue_staged<H, TN, EPI, 0, JN>(p, half, slab, m0 + wm0 + 32 * H * kg, n0 + wn0, lane);
+    return;
+  }
   epilogue_staged<TM, TN, EPI, 0, JN>(p, acc, slab, m0 + wm0, n0 + wn0, lane);
   if constexpr (TN == 5) epilogue_staged<TM, TN, EPI, 4, 1>(p, acc, slab, m0 + wm0, n0 + wn0, lane);
 #endif
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64,
-          bool CUT = false, bool KSPLIT = false>
-__global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void gemm_bf16_dma_kernel(GemmParams p) {
+          bool CUT = false, bool KSPLIT = false, int KG = 1>
+__global__ __launch_bounds__(WAVES_M * WAVES_N * KG * 64) void gemm_bf16_dma_kernel(GemmParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   int tile_m, tile_n;
   tile_of_block(p, tile_m, tile_n);
   const int per = p.k_tiles_per_split * (64 / BK), kt0 = (int)blockIdx.y * per;
-  dma_tile<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT, KSPLIT>(p, smem, tile_m, tile_n, kt0,
+  dma_tile<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT, KSPLIT, KG>(p, smem, tile_m, tile_n, kt0,
                                                                                    min(per, k_tiles<SEG, BK>(p) - kt0));
 #endif
 }
@@ -931,14 +967,14 @@ int launch_tile(hipStream_t st, const GemmParams& p, int epi) {
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64,
-          bool CUT = false, bool KSPLIT = false>
+          bool CUT = false, bool KSPLIT = false, int KG = 1>
 int launch_dma(hipStream_t st, GemmParams p) {
   if constexpr ((A_KMAJ || B_KMAJ) && !CUT)
-    if (p.K & 63) return launch_dma<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, true, KSPLIT>(st, p);
-  constexpr int NT = WAVES_M * WAVES_N * 64;
+    if (p.K & 63) return launch_dma<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, true, KSPLIT, KG>(st, p);
+  constexpr int NT = WAVES_M * WAVES_N * KG * 64;
   constexpr size_t lds = (size_t)NSTAGE * (BM + BN) * BK * sizeof(bf16_t);
   static_assert(lds <= 160 * 1024, "stages do not fit the 160 KB LDS");
-  auto kern = gemm_bf16_dma_kernel<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT, KSPLIT>;
+  auto kern = gemm_bf16_dma_kernel<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT, KSPLIT, KG>;
   static std::atomic<bool> configured{false};  // per instantiation
   if (int rc = reserve_lds(kern, lds, configured, "gemm_bf16")) return rc;
   p.tiles_m = (p.M + BM - 1) / BM;
@@ -961,7 +997,8 @@ constexpr Layout layout_of(bool a_kmaj, bool b_kmaj) { return !a_kmaj ? kLayoutW
 //   0: 256x256, 8 waves, 2 stages    1: 256x128, 8 waves, 3 stages
 //   2: 128x128, 4 waves: 4 stages as long as a compute unit gets one tile at most, otherwise 2 stages, so that
 //      two workgroups fit a unit.  With one workgroup per unit nothing else covers the latency of a tile's
-//      loads: 4096 x 1024 x 4096, F / B / W layout, 2 stages 52.1 / 47.2 / 52.8 us, 4 stages 39.8 / 36.4 / 43.0
+//      loads: 4096 x 1024 x 4096, F / B / W layout, 2 stages 52.1 / 47.2 / 52.8 us, 4 stages 39.8 / 36.4 / 43.0.  In the F and
+//      B layouts such a workgroup has eight waves in two groups that share the K of every tile (see dma_tile)
 //   3: 64x128, 4 waves, 3 stages (skinny outputs; only where A is contraction-contiguous)
 //   4: 256x320, 8 waves, 2 stages (not with the fp32 read-modify-write epilogue: registers)
 //   5: 64x64, 5 stages   6: 32x64, 6 stages   7: 32x32, 8 stages; 4 waves that split K (see dma_tile)
@@ -1036,7 +1073,7 @@ int launch_dma_tile(hipStream_t st, const GemmParams& p, int shape) {
       else break;
     default: break;
   }
-  if (tiles_of(2, p.M, p.N) <= 256) return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 4, EPI, SEG>(st, p);
+  if (tiles_of(2, p.M, p.N) <= 256) return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 4, EPI, SEG, 64, false, false, A_KMAJ ? 2 : 1>(st, p);
   return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 2, EPI, SEG>(st, p);
 }
 
