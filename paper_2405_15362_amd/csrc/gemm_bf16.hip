@@ -51,7 +51,7 @@ struct GemmParams {
   int M, N, K, lda, ldb, ldc;
   int tiles_m, tiles_n;
   int group_m;            // height, in tiles, of the column groups the tiles are walked in (see tile_of_pid)
-  int splits, k_tiles_per_split;  // fast path: 64-wide K tiles each blockIdx.y handles (all of K when not split)
+  int splits, k_tiles_per_split;  // fast path: 64-wide K tiles of each range (all of K when not split)
   // Segmented contraction (weight gradients of several queued microbatches in one product): the K
   // axis is the concatenation of nseg pieces of seg_k rows each (every piece fills whole K tiles of its
   // own, the last one with zeros), piece i living at (Aseg[i], Bseg[i]) with the pitches lda, ldb.
@@ -69,7 +69,7 @@ __host__ __device__ inline int k_tiles(const GemmParams& p) {
   return SEG ? p.nseg * ((p.seg_k + BK - 1) / BK) : (p.K + BK - 1) / BK;
 }
 
-constexpr int kEpiPartial = 100;  // fast path, split K: store the fp32 partial product of split blockIdx.y
+constexpr int kEpiPartial = 100;  // fast path, split K: store an fp32 partial product
 
 constexpr int kPadK = 8;    // K-major tile: row pitch BK + 8 elements (144 B for BK = 64)
 constexpr int kPadMN = 32;  // MN-major tile: row pitch ROWS + 32 elements (pitch = 64 mod 256 bytes)
@@ -154,7 +154,7 @@ template <int EPI>
 __device__ __forceinline__ void store_quad(const GemmParams& p, float (&v)[4], int m, int n) {
   const size_t idx = (size_t)m * p.ldc + n;
   if (EPI == kEpiPartial) {
-    float* c = reinterpret_cast<float*>(p.C) + (size_t)blockIdx.y * p.M * p.N + (size_t)m * p.N + n;
+    float* c = reinterpret_cast<float*>(p.C) + (size_t)m * p.N + n;
     f32x4 out = {v[0], v[1], v[2], v[3]};
     *reinterpret_cast<f32x4*>(c) = out;
     return;
@@ -272,7 +272,7 @@ __device__ __forceinline__ void store_oct(const GemmParams& p, float (&v)[8], in
   const size_t idx = (size_t)m * p.ldc + n;
   if (EPI == kEpiPartial || EPI == PMC_EPI_ACCUM_F32) {
     float* c = EPI == kEpiPartial
-                   ? reinterpret_cast<float*>(p.C) + (size_t)blockIdx.y * p.M * p.N + (size_t)m * p.N + n
+                   ? reinterpret_cast<float*>(p.C) + (size_t)m * p.N + n
                    : reinterpret_cast<float*>(p.C) + idx;
     f32x4 lo = {v[0], v[1], v[2], v[3]}, hi = {v[4], v[5], v[6], v[7]};
     if (EPI == PMC_EPI_ACCUM_F32) {
@@ -447,10 +447,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmParams p, const 
 // panels (group_m BM rows of A, 32/group_m BN rows of B per K step) are what that XCD's L2 has to
 // fetch.  Measured on whole steps: 4 for the 256-row tiles (+1 % at hidden 4096 over 8, nothing at
 // 5120), 8 for the smaller ones (4 costs the 64 x 128 products 2 %).  The gemm_group tuning switch forces a height.
-__device__ __forceinline__ void tile_of_pid(const GemmParams& p, int pid, int& tile_m, int& tile_n) {
-  const int ntiles = p.tiles_m * p.tiles_n;
-  const int xcd = pid & 7, local = pid >> 3, lo = ntiles >> 3, rem = ntiles & 7;
-  pid = xcd * lo + (xcd < rem ? xcd : rem) + local;
+__device__ __forceinline__ void walk_tiles(const GemmParams& p, int pid, int& tile_m, int& tile_n) {
   const int GROUP = p.group_m;
   const int per_group = GROUP * p.tiles_n;
   const int group = pid / per_group;
@@ -458,6 +455,28 @@ __device__ __forceinline__ void tile_of_pid(const GemmParams& p, int pid, int& t
   const int group_m = min(p.tiles_m - first_m, GROUP);
   tile_m = first_m + (pid % per_group) % group_m;
   tile_n = (pid % per_group) / group_m;
+}
+__device__ __forceinline__ void tile_of_pid(const GemmParams& p, int pid, int& tile_m, int& tile_n) {
+  const int ntiles = p.tiles_m * p.tiles_n;
+  const int xcd = pid & 7, local = pid >> 3, lo = ntiles >> 3, rem = ntiles & 7;
+  walk_tiles(p, xcd * lo + (xcd < rem ? xcd : rem) + local, tile_m, tile_n);
+}
+// Partial product: workgroup -> (range of K, tile).  2, 4 or 8 ranges go to XCDs of their own, 4, 2 or 1 to a range, each a
+// contiguous run of tiles: an XCD then fetches a share of K only, over a block of tiles that much larger, and an operand crosses the
+// fabric 2 to 4 times less often (1024 x 2048 x 8192 in 4 ranges of 128x128 tiles: 67 MB instead of 168).  The grid is
+// 8 x tiles per XCD; false: nothing to do.  Other counts (7 ranges of a K that is not divisible) deal the ranges out one after the other.
+__host__ __device__ inline int tiles_per_xcd(int tiles, int splits) { return (tiles * splits + 7) / 8; }
+__device__ __forceinline__ bool split_of_block(const GemmParams& p, int& split, int& tile) {
+  const int ntiles = p.tiles_m * p.tiles_n, id = blockIdx.x;
+  if (8 % p.splits == 0) {
+    const int xcd = id & 7, local = id >> 3, per = tiles_per_xcd(ntiles, p.splits);
+    split = xcd % p.splits;
+    tile = (xcd / p.splits) * per + local;
+    return tile < ntiles && local < per;
+  }
+  split = id / ntiles;
+  tile = id - split * ntiles;
+  return split < p.splits;
 }
 __device__ __forceinline__ void tile_of_block(const GemmParams& p, int& tile_m, int& tile_n) {
   tile_of_pid(p, blockIdx.x, tile_m, tile_n);
@@ -765,10 +784,19 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KG * 64) void gemm_bf16_dma_ker
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   int tile_m, tile_n;
-  tile_of_block(p, tile_m, tile_n);
-  const int per = p.k_tiles_per_split * (64 / BK), kt0 = (int)blockIdx.y * per;
-  dma_tile<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT, KSPLIT, KG>(p, smem, tile_m, tile_n, kt0,
-                                                                                   min(per, k_tiles<SEG, BK>(p) - kt0));
+  const int per = p.k_tiles_per_split * (64 / BK);
+  if constexpr (EPI == kEpiPartial) {
+    int split, tile;
+    if (!split_of_block(p, split, tile)) return;
+    walk_tiles(p, tile, tile_m, tile_n);
+    GemmParams part = p;
+    part.C = reinterpret_cast<float*>(p.C) + (size_t)split * p.M * p.N;
+    dma_tile<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT, KSPLIT, KG>(part, smem, tile_m, tile_n, split * per,
+                                                                                         min(per, k_tiles<SEG, BK>(p) - split * per));
+  } else {
+    tile_of_block(p, tile_m, tile_n);
+    dma_tile<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT, KSPLIT, KG>(p, smem, tile_m, tile_n, 0, k_tiles<SEG, BK>(p));
+  }
 #endif
 }
 
@@ -983,7 +1011,8 @@ int launch_dma(hipStream_t st, GemmParams p) {
     const int forced = tuning(kTuneGemmGroup);
     p.group_m = forced > 0 ? forced : (BM >= 256 ? 4 : 8);
   }
-  kern<<<dim3(p.tiles_m * p.tiles_n, p.splits), dim3(NT), lds, st>>>(p);
+  const int tiles = p.tiles_m * p.tiles_n;
+  kern<<<dim3(EPI == kEpiPartial ? 8 * tiles_per_xcd(tiles, p.splits) : tiles), dim3(NT), lds, st>>>(p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(PMC_ERR_HIP, "gemm_bf16 launch failed: %s", hipGetErrorString(e));
   return PMC_OK;
@@ -1160,7 +1189,10 @@ int launch_wgrad_pair(hipStream_t st, GemmParams p) {
 
 // Split K: when the output has too few tiles for the compute units and K is long, K is cut into ranges, each
 // range writes an fp32 partial product to the workspace and a second kernel adds them and applies the epilogue.
-// The partial products run in 128x128 tiles (2 stages, two workgroups per unit) or 64x64 ones.
+// The partial products run in 64x64 tiles or in large ones: 128x128 (2 stages, two workgroups per unit) or, in the F and B layouts,
+// 256x128, whichever split_us says is faster.  From HBM, 128x128 as they were before a range had XCDs of its own / since / 256x128:
+// 1024 x 2048 x 8192 (F) in 4 ranges 62 / 53 / 48 us, 512 x 4096 x 16384 (F) 94 / 92 / 78; 200 x 5120 x 20480 (F) in 8 ranges
+// 104 / 102 / 95, in 4 of 256x128 tiles 81.
 struct SplitPlan {
   int splits, tiles_per_split, shape;  // splits = 1: no split
 };
@@ -1179,9 +1211,20 @@ struct SplitPlan {
 //    32 MB and more, from HBM: F 0.90, B 0.93, W 0.59, worst 1.10 (40 x 16680 x 5560: 54 -> 60 us); smaller ones,
 //    cached: 0.98, 1.00, 0.90, worst 1.07.  From HBM, one piece / split: F 56 x 4000 x 16000 49.1 / 31.6 us,
 //    W 96 x 288 x 12376 50.3 / 16.9; inside a step F 1024 x 2048 x 8192 69 / 64, F 512 x 4096 x 16384 121 / 94.
+double split_us(int shape, int M, int N, int ranges, int k_tiles) {
+  const long tiles = tiles_of(shape, M, N) * ranges;
+  const double sums = 1.6e-6 * (double)M * N * ranges, rounds = (double)((tiles + 255) / 256);
+  if (shape == 1) return 9.1 + rounds * (15. * k_tiles / 16. - 4.5) + sums;
+  return 9.1 + (tiles <= 256 ? 14. : 7.6 * rounds) * k_tiles / 16. + sums;
+}
 SplitPlan pick_splits(Layout layout, int M, int N, int K, int epi, size_t ws_bytes) {
   SplitPlan best = {1, 0, 0};
   if (tuning(kTuneGemmTile) >= 0 || K < 2048) return best;
+  if (ws_bytes != (size_t)-1) {  // the plan of unlimited scratch, if it fits
+    best = pick_splits(layout, M, N, K, epi, (size_t)-1);
+    if (best.splits == 1 || (size_t)best.splits * M * N * sizeof(float) <= ws_bytes) return best;
+    best = {1, 0, 0};
+  }
   double limit;
   const int whole = pick_tile(layout, M, N, K, wide_ok(epi), &limit);
   const bool small = whole == 3 || whole >= 5;
@@ -1192,13 +1235,21 @@ SplitPlan pick_splits(Layout layout, int M, int N, int K, int epi, size_t ws_byt
     for (int s : {2, 4, 8}) {
       const int per = (nkt + s - 1) / s, n = (nkt + per - 1) / per;
       if (per < 4 || (size_t)n * M * N * sizeof(float) > ws_bytes) continue;
-      const long tiles = tiles_of(shape, M, N) * n;
-      const double sums = 1.6e-6 * (double)M * N * n;
-      const double us = shape == 2 ? 9.1 + (tiles <= 256 ? 14. : 7.6 * (double)((tiles + 255) / 256)) * per / 16. + sums
-                                   : 4.5 + shape_us(layout, 5, tiles, per * 64.) + sums;
+      const double us = shape == 2 ? split_us(2, M, N, n, per)
+                                   : 4.5 + shape_us(layout, 5, tiles_of(5, M, N) * n, per * 64.) + 1.6e-6 * (double)M * N * n;
       if (us < limit) {
         limit = us;
         best = {n, per, shape};
+      }
+    }
+  // the number of ranges that suits 256x128 tiles
+  if (best.splits > 1 && best.shape == 2 && layout != kLayoutW)
+    for (int s : {2, 4, 8}) {
+      const int per = (nkt + s - 1) / s, n = (nkt + per - 1) / per;
+      if (per < 4 || (size_t)n * M * N * sizeof(float) > ws_bytes) continue;
+      if (const double us = split_us(1, M, N, n, per); us < limit) {
+        limit = us;
+        best = {n, per, 2};
       }
     }
   return best;
@@ -1210,6 +1261,9 @@ int launch_partial(hipStream_t st, GemmParams p, void* ws, const GemmPlan& plan)
   p.splits = plan.splits;
   p.k_tiles_per_split = plan.k_tiles_per_split;
   if (plan.kernel == kPlanSplit + 5) return launch_dma<64, 64, 2, 2, A_KMAJ, B_KMAJ, 5, kEpiPartial, false, 64, false, true>(st, p);
+  if constexpr (A_KMAJ)
+    if (split_us(1, p.M, p.N, plan.splits, plan.k_tiles_per_split) < split_us(2, p.M, p.N, plan.splits, plan.k_tiles_per_split))
+      return launch_dma<256, 128, 4, 2, A_KMAJ, B_KMAJ, 3, kEpiPartial>(st, p);
   return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 2, kEpiPartial>(st, p);
 }
 

@@ -236,6 +236,15 @@ def test_gemm_bf16_split_k(ctx, ta, tb, epis):
         assert rel_l2(host(outs[0]), host(outs[2])) <= (1e-6 if accum else 3e-3), key   # fp32 sums in another order; rounding to bf16
 
 
+@pytest.mark.parametrize("ta,tb,M,N,K,ranges", [(False, False, 536, 2096, 7680, 4), (False, True, 536, 2096, 7680, 4),
+                                                (False, False, 208, 3080, 9088, 8), (True, False, 72, 8440, 3104, 7)])
+def test_gemm_bf16_split_k_ranges_on_xcds_of_their_own(ctx, ta, tb, M, N, K, ranges):
+    """Large tiles whose number does not divide over the XCDs of a range, and a number of ranges that does not divide the XCDs."""
+    epi = P.EPI_ACCUM_F32 if ta else P.EPI_NONE if tb else P.EPI_BIAS_RESID
+    assert U.gemm_plan("bf16", ta, tb, M, N, K, epi, ws_bytes=256 << 20)[:2] == (U.PLAN_SPLIT + 2, ranges)
+    _gemm_case(ctx, "bf16", ta, tb, M, N, K, epi)
+
+
 def test_gemm_bf16_weight_gradient_persistent(ctx, tune):
     """The persistent W-pass kernel (fp32 C += A^T B; one workgroup per compute unit walks its
     256x256 tiles, its first tile cut in two along K to put the workgroups out of phase): fewer tiles
