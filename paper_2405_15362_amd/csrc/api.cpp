@@ -182,7 +182,7 @@ WorkspaceLayout workspace_of(const pmc_chunk_cfg& c) {
   w.attn = at;
   at += k::attention_backward_scratch_bytes(c.dtype, c.microbatch, c.seq, c.heads, c.hidden / c.heads);
   w.kept = at;
-  at += align256((size_t)t * k::attention_backward_kept_columns(c.dtype, c.microbatch, c.seq, c.heads, c.hidden / c.heads) * e);
+  at += align256((size_t)t * k::attention_backward_kept_columns(c.dtype, c.microbatch, c.seq, c.heads, c.hidden / c.heads, c.causal) * e);
   w.partial = at;
   // one region per LayerNorm of the backward pass (their reductions are run together at its end)
   const size_t pf = k::layernorm_backward_scratch_floats(t, c.hidden);
@@ -737,7 +737,7 @@ int pmc_chunk_create(pmc_ctx* ctx, const pmc_chunk_cfg* cfg, pmc_chunk** out) {
   ch->unit_bytes = unit_bytes_of(*cfg);
   ch->stats_bytes = stats_bytes_of(*cfg);
   ch->wsl = workspace_of(*cfg);
-  ch->kept_columns = k::attention_backward_kept_columns(cfg->dtype, cfg->microbatch, cfg->seq, cfg->heads, ch->head_dim);
+  ch->kept_columns = k::attention_backward_kept_columns(cfg->dtype, cfg->microbatch, cfg->seq, cfg->heads, ch->head_dim, cfg->causal);
   const size_t th = (size_t)ch->tokens * cfg->hidden * ch->esz, tf = (size_t)ch->tokens * cfg->ffn * ch->esz;
   const size_t per_layer = 8 * th + 2 * tf;
   const size_t st_layer = (size_t)(4 + cfg->heads) * ch->tokens * 4;

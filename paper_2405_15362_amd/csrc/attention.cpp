@@ -35,16 +35,26 @@ size_t attention_backward_scratch_bytes(int dtype, int batch, int seq, int heads
   return align256(tokens * heads * head_dim * elem(dtype)) + align256(tokens * heads * sizeof(float));
 }
 
-// Where both halves of the backward pass go out as one launch: as long as each half has at most one workgroup per compute unit.
-// Beyond, two launches are faster, whose workgroups need less LDS and fewer registers each.  us of the one launch / of two, without
-// the copy that in-place results need (bf16, causal): 16 heads of 64, 512 tokens 15.6 / 22; 16 of 128, 1024 tokens 44 / 50;
-// 32 of 128, 4 x 256 tokens 49 / 48; 16 of 64, 2048 tokens 95 / 65; 8 of 128, 4096 tokens 242 / 165.  fp32 (16-row blocks): 8 heads of
-// 64, 512 tokens 31 / 36; 16 heads 57 / 50.
-bool attention_merged(int batch, int seq, int heads) { return (int64_t)((seq + 63) / 64) * heads * batch <= 256; }
+// Where both halves of the backward pass go out as one launch, by w = 64-row workgroups of one half.
+//   1: 8 waves to a workgroup, one workgroup to a compute unit; as long as each half has at most one per unit (w <= 256).
+//   2: 4 waves, two to a unit; for one block of rows, where there is nothing to split over more waves, and for short sequences
+//      beyond w = 128, where two rounds of the larger ones meet.
+// Otherwise two launches are faster, whose workgroups need less LDS and fewer registers each.  us of 1 / 2 / two launches, without
+// the copy that in-place results need, heads of 128, causal unless said: 16 heads x 512 tokens 21.8 / 29.1 / 30; 16 x 1000 (w 256) 45 / 53 / 50;
+// 16 x 64 11.4 / 9.6 / 16; 128 x 128 (w 256) 22.9 / 15.8 / 25; 64 x 192 (w 192) 22.7 / 18.2; 128 x 192 (w 384) - / 25.9 / 29.5, not causal
+// 30.2 / 30.5; 64 x 512 (w 512) - / 43 / 51, not causal 65 / 54; 16 x 2048 (w 512) - / 122 / 106.  fp32 (16-row blocks): 8 heads of 64, 512
+// tokens 31 in one, 36 in two; 16 heads 57 and 50.
+int attention_merged(int batch, int seq, int heads, int head_dim, int causal) {
+  const int64_t w = (int64_t)((seq + 63) / 64) * heads * batch;
+  if (seq <= 64) return w <= 512 ? 2 : 0;
+  if (w > 128 && w <= (causal ? 512 : 384) && seq <= (causal && w > 256 ? 512 : 256)) return 2;
+  return w <= 256 ? 1 : 0;
+}
 bool attention_merged_f32(int batch, int seq, int heads) { return (int64_t)((seq + 15) / 16) * heads * batch <= 256; }
 
-int attention_backward_kept_columns(int dtype, int batch, int seq, int heads, int head_dim) {
-  const bool merged = use_mfma(dtype, head_dim) ? attention_merged(batch, seq, heads) : attention_merged_f32(batch, seq, heads);
+int attention_backward_kept_columns(int dtype, int batch, int seq, int heads, int head_dim, int causal) {
+  const bool merged =
+      use_mfma(dtype, head_dim) ? attention_merged(batch, seq, heads, head_dim, causal) > 0 : attention_merged_f32(batch, seq, heads);
   return merged ? 3 * heads * head_dim : 0;
 }
 

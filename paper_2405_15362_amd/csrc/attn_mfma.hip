@@ -531,7 +531,7 @@ struct OwnDelta {
 // query, from rows of dO and O requested a block ahead.  qkv must not be dqkv then: every query block reads all keys.
 // bf16, causal, two launches / one: 2 heads of 128, 192 tokens 24 / 12 us; 16 heads of 128, 1024 tokens 50 / 44 us.
 template <int DH, int KG, int QG, bool PAD, int KW>
-__global__ __launch_bounds__(KG * QG * 128, KG * QG == 2 ? 3 : 1) void attn_bwd_dkv_mfma(
+__global__ __launch_bounds__(KG * QG * 128, KG * QG == 2 ? (KW > 0 ? 2 : 3) : 1) void attn_bwd_dkv_mfma(
     int seq, int heads, int dh, int causal, const bf16_t* qkv, const bf16_t* __restrict__ o, const float* __restrict__ lse,
     const float* __restrict__ delta, const bf16_t* __restrict__ d_o, bf16_t* dqkv, float scale, float scale_log2) {
   constexpr bool DELTA = KW > 0;
@@ -704,28 +704,60 @@ int fwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal
   return PMC_OK;
 }
 
-// Family 0: 64-row workgroups whose 8 waves split 128 rows of the other side four ways, so that few heads or tokens still
-// occupy the compute units and the chain of one workgroup is short; one workgroup fills a unit.  Family 1: 128-query
-// workgroups (64-key ones in the dK/dV kernel) of 4 waves, each taking whole 64-row blocks, two or three to a unit.
-// Family 0 as long as its workgroups fit the 256 units at once; under a causal mask, where their lengths differ and the short ones fill
-// up, also beyond, up to 512 (128-row block, head) pairs, for sequences long enough that the chain counts.  A sequence of one 64-row
-// block has nothing to split.  us of family 0 / 1, heads of 128, forward and backward, w = 64-row workgroups: causal 16 heads x
-// 1000 (w 256) 18 / 26 and 50 / 87; 32 x 768 (w 384) 21 / 22 and 58 / 73; 128 x 256 (w 512) 18 / 12 and 52 / 42; 64 x 512 (w 512) 21 / 17 and
-// 60 / 58; 16 x 64 8.4 / 5.9 forward; not causal 32 x 768 28 / 21 and 84 / 75, 32 x 1000 35 / 28 and 115 / 117.
-// The attn_shape tuning switch (0|1|2) forces a family of launch shapes (tests and tuning).
-int shape_family(bool backward, int batch, int seq, int heads, int dh, int causal) {
+// Forward, by w = 64-row workgroups of the whole call.  Few tokens and heads leave the chain of one workgroup as the time, so rows
+// get small workgroups whose waves split the other side, as long as all of them run at once:
+//   32 queries, four waves that take every fourth 32-key tile: from 256 tokens a sequence on, up to 256 of these workgroups
+//   64 queries, two key groups, 32 keys at a time: up to 192 tokens, and heads of more than 64 under a causal mask up to w = 512 (two
+//       workgroups to a compute unit)
+//   64 queries, two key groups, 64 keys at a time: up to w = 256, heads of up to 64 w = 512
+//   64 queries, four key groups of two waves each: the longest sequences of few heads of more than 64, causal
+//   128 queries, every wave all keys, two workgroups to a unit: everything else, and one block of up to 64 tokens
+// us of these five in turn, heads of 128, causal: 16 x 256 tokens (w 64) 7.8 / 8.4 / 8.5 / 9.9 / 11.1, 16 x 1000 (w 256) 20.5 / 18.9 / 18.0 /
+// 18.1 / 26.6, 64 x 192 (w 192) 12.4 / 7.9 / 8.7 / 9.9 / 9.0, 64 x 512 (w 512) 30 / 14.9 / 18.6 / 21 / 17.5, 16 x 2048 (w 512) 56 / 39.5 /
+// 36.7 / 38.7 / 48.6, 8 x 4096 (w 512) - / 77 / 68 / 62 / 88, 16 x 64 6.8 / 5.9 / 6.9 / 8.3 / 5.7; not causal 64 x 512 34 / 18.4 / 21.5 / 24 / 17.3;
+// heads of 64, causal 16 x 2048 (w 512) 28 / 26.5 / 22.9 / 24.2 / 34, 12 x 4096 (w 768) - / - / 46.8 / 50.5 / 63.4, 48 x 768 (w 576) - / - /
+// 13.8 / 16.9 / 17.0, 4 x 24 x 512 (w 768) - / - / 14.5 / 16.6 / 13.4; not causal 16 x 2048 42 / 33 / 29 / 32 / 35, 24 x 2048 (w 768) - / - / 43.2 / 44.4 / 45.7.
+// The attn_shape tuning switch (0|1|2) forces the third (0) or the last (1, 2), and a family of launch shapes of the backward
+// pass (tests and tuning).
+enum FwdShape { kFwd32, kFwd64, kFwd64Wide, kFwd64Eight, kFwd128 };
+FwdShape fwd_shape(int batch, int seq, int heads, int dh, int causal) {
+  if (const int f = tuning(kTuneAttnShape); f >= 0) return f == 0 ? kFwd64Wide : kFwd128;
+  const int64_t pairs = (int64_t)heads * batch, w = (seq + 63) / 64 * pairs;
+  if (seq <= 64) return kFwd128;
+  if (w > 512) return dh <= 64 && w < 1024 && seq >= (causal ? 704 : 2048) ? kFwd64Wide : kFwd128;
+  if (seq <= 192) return kFwd64;
+  if ((seq + 31) / 32 * pairs <= 256) return kFwd32;
+  if (w <= 256 || dh <= 64) return kFwd64Wide;
+  if (!causal) return kFwd128;
+  return seq < 1536 ? kFwd64 : seq < 3072 ? kFwd64Wide : kFwd64Eight;
+}
+
+// Backward, family 0: 64-row workgroups of 8 waves, the dQ ones with four key groups; one workgroup fills a unit.  Family 1: 128-query
+// workgroups (64-key ones in the dK/dV kernel) of 4 waves, two or three to a unit.  Family 0 as long as its workgroups fit the 256 units at
+// once; under a causal mask, where their lengths differ and the short ones fill up, also beyond, up to 512 (128-row block, head) pairs, for
+// sequences long enough that the chain counts: longer the more workgroups there are.  us of family 0 / 1, heads of 128, w = 64-row
+// workgroups: causal 60 heads x 1000 (w 960) 146 / 107, 20 x 2048 (w 640) 148 / 163, 12 x 4096 (w 768) 266 / 302; 16 x
+// 1000 (w 256) 50 / 87; 32 x 768 (w 384) 58 / 73; 128 x 256 (w 512) 52 / 42; 64 x 512 (w 512) 60 / 58; not causal 32 x 768 84 / 75,
+// 32 x 1000 115 / 117.  Where attention_merged says 2, the shapes of that one launch also do the two launches in place, so that both
+// give the same bits.
+int bwd_family(int batch, int seq, int heads, int dh, int causal) {
   if (const int f = tuning(kTuneAttnShape); f >= 0) return f;
-  if (!backward && seq <= 64) return 1;
-  const int64_t pairs = (int64_t)heads * batch;
-  if ((seq + 63) / 64 * pairs <= 256) return 0;
-  if ((seq + 127) / 128 * pairs >= 512 || !(causal || backward)) return 1;
+  if (attention_merged(batch, seq, heads, dh, causal) == 2) return 3;
+  const int64_t pairs = (int64_t)heads * batch, w = (seq + 63) / 64 * pairs;
+  if (w <= 256) return 0;
+  if ((seq + 127) / 128 * pairs >= 512 || (w > 512 && (int64_t)seq * 10 < w * 13)) return 1;
   return (int64_t)seq * 64 >= (int64_t)(causal ? 384 : 768) * dh ? 0 : 1;
 }
 
 template <int DH, bool PAD>
 int fwd_t(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, void* o, float* lse) {
-  if (shape_family(false, batch, seq, heads, dh, causal) == 0) return fwd_launch<DH, 2, 4, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
-  return fwd_launch<DH, 4, 1, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
+  switch (fwd_shape(batch, seq, heads, dh, causal)) {
+    case kFwd32: return fwd_launch<DH, 1, 4, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
+    case kFwd64: return fwd_launch<DH, 2, 2, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
+    case kFwd64Eight: return fwd_launch<DH, 2, 4, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
+    case kFwd64Wide: return fwd_launch<DH, 2, 2, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
+    default: return fwd_launch<DH, 4, 1, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
+  }
 }
 
 template <int DH, int QW, int KW, int NKT>
@@ -774,9 +806,13 @@ int bwd_merged_launch(hipStream_t st, int batch, int seq, int heads, int dh, int
 template <int DH, bool PAD>
 int bwd_t(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, const void* o, const float* lse,
           const void* d_o, void* dqkv, void* dq, int ld_dq, float* delta) {
-  const int fam = shape_family(true, batch, seq, heads, dh, causal);
-  if (fam == 0 && dq == dqkv && attention_merged(batch, seq, heads))
+  const int fam = bwd_family(batch, seq, heads, dh, causal), merged = fam == 1 || fam == 2 ? 0 : attention_merged(batch, seq, heads, dh, causal);
+  if (dq == dqkv && merged == 1)
     return bwd_merged_launch<DH, 2, 4, 1, 2, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv);
+  if (dq == dqkv && merged == 2)
+    return bwd_merged_launch<DH, 2, 2, 1, 2, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv);
+  if (fam == 3)
+    return bwd_launch<DH, 2, 2, 1, 2, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
   if (fam == 0)
     return bwd_launch<DH, 2, 4, 1, 2, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv, dq, ld_dq, delta);
   if (fam == 2)

@@ -143,8 +143,8 @@ int attention_backward(hipStream_t stream, int dtype, int batch, int seq, int he
                        void* scratch);
 // Columns of qkv (3 heads head_dim or 0) that a caller who wants dqkv in qkv's place is better off copying elsewhere first, to call
 // attention_backward from the copy: with qkv and dqkv apart few blocks run as one launch.
-int attention_backward_kept_columns(int dtype, int batch, int seq, int heads, int head_dim);
-bool attention_merged(int batch, int seq, int heads);
+int attention_backward_kept_columns(int dtype, int batch, int seq, int heads, int head_dim, int causal);
+int attention_merged(int batch, int seq, int heads, int head_dim, int causal);  // 0: two launches
 bool attention_merged_f32(int batch, int seq, int heads);
 
 // out[c] += sum over rows of a[row][c] (fp32 out), for up to four matrices of `rows` rows in one

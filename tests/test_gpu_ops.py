@@ -568,20 +568,22 @@ def test_layernorm_forward_backward(ctx, dtype, rows, h):
     assert_close(host(dbias) + 0.5, db_ref, "f32", "dbias")
 
 
-# (batch, seq, heads, head size, one launch): one row, a row past a block, the last size of one launch and the first of two
-MERGED = [("bf16", 1, 8, 1, 64, True), ("bf16", 1, 65, 2, 128, True), ("bf16", 2, 520, 14, 40, True), ("bf16", 1, 1024, 16, 64, True),
-          ("bf16", 1, 1032, 16, 64, False), ("bf16", 3, 96, 8, 112, True), ("f32", 1, 4, 1, 64, True), ("f32", 1, 256, 16, 20, True),
-          ("f32", 1, 260, 16, 20, False), ("bf16", 1, 264, 8, 20, True), ("f32", 2, 68, 3, 128, True)]
+# dtype, batch, seq, heads, head size: one row, one row past a block, sizes on both sides of every rule of the launch shapes (forward:
+# up to 64 tokens, up to 192, 32-row workgroups, 64-row ones, 128-row ones; backward: one launch of either kind, two launches)
+ATTN_SHAPES = [("bf16", 1, 8, 1, 64), ("bf16", 1, 64, 3, 128), ("bf16", 1, 65, 2, 128), ("bf16", 2, 192, 3, 64), ("bf16", 3, 200, 5, 112),
+               ("bf16", 1, 264, 8, 128), ("bf16", 2, 520, 14, 40), ("bf16", 1, 1024, 16, 64), ("bf16", 1, 1032, 16, 64), ("bf16", 8, 72, 24, 64),
+               ("bf16", 9, 136, 16, 128), ("bf16", 4, 328, 15, 128), ("bf16", 4, 328, 16, 72), ("bf16", 8, 64, 64, 32), ("bf16", 9, 64, 57, 16),
+               ("bf16", 1, 704, 50, 16), ("bf16", 1, 1544, 16, 72), ("bf16", 1, 3080, 8, 72),
+               ("f32", 1, 4, 1, 64), ("f32", 1, 256, 16, 20), ("f32", 1, 260, 16, 20), ("bf16", 1, 264, 8, 20), ("f32", 2, 68, 3, 128)]
 
 
-@pytest.mark.parametrize("case", MERGED, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("case", ATTN_SHAPES, ids=lambda c: "-".join(map(str, c)))
 @pytest.mark.parametrize("causal", [True, False])
-def test_attention_backward_in_one_launch(ctx, case, causal):
-    """Apart from qkv, where few blocks run as one launch, against the oracle, and bit for bit what the two launches in place give."""
-    dtype, batch, seq, heads, dh, one = case
+def test_attention_launch_shapes(ctx, case, causal):
+    """Forward; backward apart from qkv, where few blocks run as one launch; both against the oracle, and bit for bit what the two
+    launches in place give."""
+    dtype, batch, seq, heads, dh = case
     h = heads * dh
-    row = 64 if dtype == "bf16" and dh % 8 == 0 else 16
-    assert one == (-(-seq // row) * heads * batch <= 256)
     print("one-launch attention case", case, causal, flush=True)
     qkv = mat(("merged", case, causal, "qkv"), (batch * seq, 3 * h), dtype)
     d_o = mat(("merged", case, causal, "do"), (batch * seq, h), dtype)
