@@ -113,8 +113,9 @@ int copy_blocks(const RowCopy& copy, int rows, int threads) {
   const int down = std::max(1, threads / (copy.cols / Vec<T>::N));
   return std::min((rows + down - 1) / down, 1024);
 }
-// (larger copies are faster by themselves: they would wait for the workgroups that they share the launch with)
-bool rides_along(const RowCopy& copy, int rows, int elem) { return copy.cols && (size_t)rows * copy.cols * elem <= 8u << 20; }
+// Larger copies stay launches of their own: their workgroups would wait for those that they share the launch with, and move their
+// bytes no faster.  12.6 MB (q|k|v of 1024 tokens of hidden 2048) by themselves 6.1 us, riding along 1.8 (a step of two layers 1140 -> 1132).
+bool rides_along(const RowCopy& copy, int rows, int elem) { return copy.cols && (size_t)rows * copy.cols * elem <= 16u << 20; }
 
 // dx = resid + rstd * (g - mean(g) - xhat * mean(g * xhat)),  g = dy * gain,  xhat = (x - mean) * rstd.
 // A workgroup is 8 waves; WR of them share a row (wave w takes the column slice w % WR, NC chunks
