@@ -178,7 +178,7 @@ def run_workload(P, R, synth, torch, np, name, cfg, steps, warmup, queued, want_
                 "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                 "traffic": traffic, "traffic_source": traffic_src,
                 "timing": "HIP events around every GEMM launch of traced steps in this run, on the stream of the launches "
-                          "(while traced, the W pass keeps its products on that one stream)",
+                          "(while traced, the W pass launches its products one by one on that one stream)",
                 "avg_launch_us": round(1e3 * gemm_ms / len(gemms), 2), "flop_per_launch": gemm_flop / len(gemms),
                 "algorithmic_bytes_per_launch": round(sum(gemm_bytes(r) for r in gemms) / len(gemms)),
                 "launches_per_step": len(gemms) // reps, "by_pass": gemm_by_pass}
