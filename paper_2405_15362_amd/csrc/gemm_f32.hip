@@ -446,7 +446,9 @@ int launch_fma_f32(hipStream_t st, const F32Params& p) {
 // Kernel and output tile of a product: 128 x 128, 64 x 128, 64 x 64, 32 x 64 and 32 x 32 tiles staged in LDS, 16 x 16
 // ones in the direct kernel with 16-byte loads, and, with element-wise loads, 16 x 16 ones in the direct
 // kernel or 64 x 64 ones in the FMA kernel.
-enum F32Shape { kTile128, kTile64, kTile32x64, kTile32, kDirect, kDirectElements, kFmaElements, kTile64x128, kTile32Four };
+enum F32Shape { kTile128, kTile64, kTile32x64, kTile32, kDirect, kDirectElements, kFmaElements, kTile64x128, kTile32Four, kNoTile };
+// One dimension of a launch holds fewer than 2^32 threads (one past that is not refused, it leaves workgroups out).
+bool one_launch(F32Shape shape, long tiles) { return tiles < (1LL << 32) / (shape == kTile32Four ? 256 : 512); }
 
 // With 16-byte loads: the tile with the least fitted time, us = fixed + n (tile_k k + tile) + ceil(n / per_cu) (group_k k + group)
 // + ceil(n) (round_k k + round) at n tiles per compute unit, per_cu of them side by side, and k = K / 1024.  Fitted to
@@ -474,11 +476,12 @@ F32Shape pick_tile_f32(bool tb, int M, int N, int K) {
       {kTile32Four, 32, 32, 5, {2.47, 2.24}, {0.189, 0.176}, {0.545, 0.53}, {3.27, 2.7}, {0., 0.}, {4.55, 4.5}, {0., 0.}},
       {kDirect, 16, 16, 4, {2.54, 2.21}, {0., 0.0346}, {0.373, 0.247}, {0.713, 0.508}, {0., 0.}, {2.5, 2.91}, {0.234, 0.}}};
   auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  F32Shape best = kTile128;
+  F32Shape best = kNoTile;
   double best_us = 1e300;
   for (const T& t : kTimes) {
     if (t.shape == kTile64x128 && tiles(128, 128) >= 4 * 256) continue;
     const long count = tiles(t.bm, t.bn), rounds = (count + 255) / 256, groups = (count + 256L * t.per_cu - 1) / (256L * t.per_cu);
+    if (!one_launch(t.shape, count)) continue;
     const double k = K / 1024.0, n = (double)count / 256.0;
     double us = t.fixed[tb] + n * (t.tile_k[tb] * k + t.tile[tb]) + (double)groups * (t.group_k[tb] * k + t.group[tb]) +
                 (double)rounds * (t.round_k[tb] * k + t.round[tb]);
@@ -488,9 +491,12 @@ F32Shape pick_tile_f32(bool tb, int M, int N, int K) {
       best = t.shape;
     }
   }
-  if (const int f = tuning(kTuneGemmTile); f >= 0) best = (F32Shape)f;
-  // one dimension of a launch holds fewer than 2^32 threads, 512 to a 16 x 16 tile
-  if (best == kDirect && tiles(16, 16) >= 1L << 23) best = kTile64;
+  if (const int f = tuning(kTuneGemmTile); f >= 0) {  // where the launch would not hold them, the next larger tiles from 64 x 64 on that it does
+    best = kNoTile;
+    for (F32Shape shape : {(F32Shape)f, kTile64, kTile64x128, kTile128})
+      for (const T& t : kTimes)
+        if (best == kNoTile && t.shape == shape && one_launch(shape, tiles(t.bm, t.bn))) best = shape;
+  }
   return best;
 }
 
@@ -530,8 +536,9 @@ int launch_f32(hipStream_t st, const F32Params& p, F32Shape shape) {
     case kDirect: return launch_direct_f32<TA, TB>(st, p, true);
     case kDirectElements: return launch_direct_f32<TA, TB>(st, p, false);
     case kFmaElements: return launch_fma_f32<TA, TB>(st, p);
+    case kNoTile: break;
   }
-  return fail(PMC_ERR_INVALID, "gemm_f32: unknown shape %d", (int)shape);
+  return fail(PMC_ERR_INVALID, "gemm_f32: %d x %d outputs are more than one launch holds", p.M, p.N);
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int WK, int NSTAGE>
@@ -616,7 +623,10 @@ int wgrad_batch(hipStream_t st, int dtype, const WgradBatchArgs& a, int shape) {
   return dtype == PMC_F32 ? gemm_f32_wgrad_batch(st, a, shape) : gemm_bf16_wgrad_batch(st, a, shape);
 }
 
-GemmPlan gemm_f32_plan(const GemmArgs& a) { return {kPlanF32 + (int)shape_of(a), 1, 0}; }
+GemmPlan gemm_f32_plan(const GemmArgs& a) {
+  const F32Shape shape = shape_of(a);
+  return {shape == kNoTile ? -1 : kPlanF32 + (int)shape, 1, 0};
+}
 
 // Shape and pointer checks common to both precisions, then dispatch.
 int gemm(hipStream_t st, const GemmArgs& a) {

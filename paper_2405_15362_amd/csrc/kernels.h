@@ -86,7 +86,7 @@ size_t gemm_scratch_bytes(GemmArgs a);
 
 // What gemm() launches for a product: host arithmetic only, so that the rules can be tested without a GPU.
 // kernel: in bf16 tiles of a shape (see gemm_bf16.hip), the two weight-gradient kernels, the general kernel, or partial
-// products over `splits` ranges of K (+ 2: in large tiles, + 5: in 64x64 ones); kPlanF32 + F32Shape in fp32.
+// products over `splits` ranges of K (+ 2: in large tiles, + 5: in 64x64 ones); kPlanF32 + F32Shape in fp32 (-1: refused, more tiles than a launch holds).
 enum { kPlanTile = 0, kPlanPersistent = 20, kPlanPair = 21, kPlanGeneral = 22, kPlanSplit = 30, kPlanF32 = 100 };
 struct GemmPlan {
   int kernel, splits, k_tiles_per_split;

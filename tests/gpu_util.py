@@ -114,6 +114,10 @@ def oracle_chunk(cfg, params, x, dy):
 PLAN_TILE, PLAN_PERSISTENT, PLAN_PAIR, PLAN_GENERAL, PLAN_SPLIT = 0, 20, 21, 22, 30   # PLAN_TILE / PLAN_SPLIT + tile shape
 F32_TILE128, F32_TILE64, F32_TILE32X64, F32_TILE32, F32_DIRECT, F32_DIRECT_ELEMENTS, F32_FMA_ELEMENTS = range(100, 107)
 F32_TILE64X128, F32_TILE32_FOUR = 107, 108
+F32_REFUSED = -1
+# output tile and threads of a workgroup
+F32_WORKGROUP = {F32_TILE128: (128, 128, 512), F32_TILE64: (64, 64, 512), F32_TILE32X64: (32, 64, 512), F32_TILE32: (32, 32, 512),
+                 F32_DIRECT: (16, 16, 512), F32_DIRECT_ELEMENTS: (16, 16, 512), F32_TILE64X128: (64, 128, 512), F32_TILE32_FOUR: (32, 32, 256)}
 
 
 def gemm_plan(dtype, ta, tb, M, N, K, epi=0, lda=None, ldb=None, ldc=None, offset=0, ws_bytes=0):

@@ -264,6 +264,26 @@ def test_fp32_16x16_tiles_fit_one_launch(ta, tb):
         assert U.gemm_plan("f32", ta, tb, 65536, 32768, 64)[0] == U.F32_TILE64
 
 
+@pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3, 4])
+def test_fp32_tiles_of_any_shape_fit_one_launch(tile):
+    """Picked or forced, with K from the least to the longest whose operands the tiles take: fewer than 2^32 threads, or a refusal
+    where even 128x128 tiles would need more."""
+    with U.tuned(gemm_tile=tile):
+        for M, N in ((8388608, 4096), (131072, 65536), (131072, 131072), (65536, 32768), (262144, 262144), (4096, 16777216), (524288, 131072),
+                     (524288, 262140), (524288, 262144), (1 << 20, 1 << 20), (8388608, 65536)):
+            longest = (0x7fffffff // 4 - 1) // max(M, N) // 4 * 4
+            for K in {4, 60, longest} if longest >= 60 else {4, longest}:
+                if K > longest:
+                    continue
+                for ta, tb in LAYOUTS:
+                    kernel = U.gemm_plan("f32", ta, tb, M, N, K)[0]
+                    if kernel == U.F32_REFUSED:
+                        assert -(-M // 128) * -(-N // 128) * 512 >= 1 << 32, (M, N, K)
+                        continue
+                    bm, bn, threads = U.F32_WORKGROUP[kernel]
+                    assert -(-M // bm) * -(-N // bn) * threads < 1 << 32, (M, N, K, kernel)
+
+
 # (layout, M, N, K), us in one piece and in the split that was picked there (operands from HBM; cached where the larger is below 32 MB)
 ONE_PIECE = [("W", 1088, 4352, 8464, 115, 149), ("F", 2176, 2560, 10240, 140, 175), ("F", 1432, 3744, 14976, 191, 238),
              ("W", 1408, 4224, 13440, 185, 223), ("W", 3912, 4104, 16168, 584, 655), ("W", 1024, 3072, 10816, 100, 115),
