@@ -579,7 +579,7 @@ ATTN_SHAPES = [("bf16", 1, 8, 1, 64), ("bf16", 1, 64, 3, 128), ("bf16", 1, 65, 2
 
 @pytest.mark.parametrize("case", ATTN_SHAPES, ids=lambda c: "-".join(map(str, c)))
 @pytest.mark.parametrize("causal", [True, False])
-def test_attention_launch_shapes(ctx, case, causal):
+def test_attention_picked_launch_shapes(ctx, case, causal):
     """Forward; backward apart from qkv, where few blocks run as one launch; both against the oracle, and bit for bit what the two
     launches in place give."""
     dtype, batch, seq, heads, dh = case

@@ -223,6 +223,17 @@ def test_tuning_switches():
         P.pmc_tuning_set("no_such_switch", 1)
 
 
+def test_no_test_hides_another():
+    """A second function of the same name in a module replaces the first one, whose cases then never run."""
+    import ast
+    import glob
+    for path in glob.glob(os.path.join(ROOT, "tests", "*.py")):
+        scopes = [n for n in ast.walk(ast.parse(open(path).read())) if isinstance(n, (ast.Module, ast.ClassDef))]
+        for scope in scopes:
+            names = [n.name for n in scope.body if isinstance(n, (ast.FunctionDef, ast.ClassDef))]
+            assert len(names) == len(set(names)), (os.path.basename(path), sorted(n for n in set(names) if names.count(n) > 1))
+
+
 def test_header_is_plain_c():
     """The boundary is a C ABI: the header must compile as C99 on its own (no C++ or torch types)."""
     import shutil
