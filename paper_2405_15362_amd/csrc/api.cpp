@@ -912,6 +912,12 @@ int pmc_test_gemm_plan(int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t 
   return PMC_OK;
 }
 
+// For the library's own tests (not in pmc.h): see attention_mfma_plan.
+int pmc_test_attention_plan(int32_t batch, int32_t seq, int32_t heads, int32_t head_dim, int32_t causal, int32_t* out) {
+  k::attention_mfma_plan(batch, seq, heads, head_dim, causal, out);
+  return PMC_OK;
+}
+
 // For the library's own tests (not in pmc.h): tiles of the one launch that does the W pass of `count` microbatches
 // (-1: the products go out one by one).
 int pmc_test_wgrad_shape(const pmc_chunk_cfg* cfg, int32_t count) {

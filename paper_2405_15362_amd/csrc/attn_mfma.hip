@@ -717,11 +717,11 @@ int fwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal
 // 36.7 / 38.7 / 48.6, 8 x 4096 (w 512) - / 77 / 68 / 62 / 88, 16 x 64 6.8 / 5.9 / 6.9 / 8.3 / 5.7; not causal 64 x 512 34 / 18.4 / 21.5 / 24 / 17.3;
 // heads of 64, causal 16 x 2048 (w 512) 28 / 26.5 / 22.9 / 24.2 / 34, 12 x 4096 (w 768) - / - / 46.8 / 50.5 / 63.4, 48 x 768 (w 576) - / - /
 // 13.8 / 16.9 / 17.0, 4 x 24 x 512 (w 768) - / - / 14.5 / 16.6 / 13.4; not causal 16 x 2048 42 / 33 / 29 / 32 / 35, 24 x 2048 (w 768) - / - / 43.2 / 44.4 / 45.7.
-// The attn_shape tuning switch (0|1|2) forces the third (0) or the last (1, 2), and a family of launch shapes of the backward
-// pass (tests and tuning).
+// The attn_shape tuning switch (0|1|2) forces the eight-wave one (0) or the last (1, 2), and a family of the backward pass in two launches
+// (tests and tuning).
 enum FwdShape { kFwd32, kFwd64, kFwd64Wide, kFwd64Eight, kFwd128 };
 FwdShape fwd_shape(int batch, int seq, int heads, int dh, int causal) {
-  if (const int f = tuning(kTuneAttnShape); f >= 0) return f == 0 ? kFwd64Wide : kFwd128;
+  if (const int f = tuning(kTuneAttnShape); f >= 0) return f == 0 ? kFwd64Eight : kFwd128;
   const int64_t pairs = (int64_t)heads * batch, w = (seq + 63) / 64 * pairs;
   if (seq <= 64) return kFwd128;
   if (w > 512) return dh <= 64 && w < 1024 && seq >= (causal ? 704 : 2048) ? kFwd64Wide : kFwd128;
@@ -747,6 +747,11 @@ int bwd_family(int batch, int seq, int heads, int dh, int causal) {
   if (w <= 256) return 0;
   if ((seq + 127) / 128 * pairs >= 512 || (w > 512 && (int64_t)seq * 10 < w * 13)) return 1;
   return (int64_t)seq * 64 >= (int64_t)(causal ? 384 : 768) * dh ? 0 : 1;
+}
+
+// The one-launch form of the backward pass apart from qkv (0: two launches, as in place).
+int bwd_merged(int batch, int seq, int heads, int dh, int causal) {
+  return tuning(kTuneAttnShape) >= 0 ? 0 : attention_merged(batch, seq, heads, dh, causal);
 }
 
 template <int DH, bool PAD>
@@ -806,7 +811,7 @@ int bwd_merged_launch(hipStream_t st, int batch, int seq, int heads, int dh, int
 template <int DH, bool PAD>
 int bwd_t(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, const void* o, const float* lse,
           const void* d_o, void* dqkv, void* dq, int ld_dq, float* delta) {
-  const int fam = bwd_family(batch, seq, heads, dh, causal), merged = fam == 1 || fam == 2 ? 0 : attention_merged(batch, seq, heads, dh, causal);
+  const int fam = bwd_family(batch, seq, heads, dh, causal), merged = bwd_merged(batch, seq, heads, dh, causal);
   if (dq == dqkv && merged == 1)
     return bwd_merged_launch<DH, 2, 4, 1, 2, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse, d_o, dqkv);
   if (dq == dqkv && merged == 2)
@@ -836,6 +841,12 @@ int check(const char* what, int batch, int seq, int heads, int dh, const void* q
 
 // Head sizes 64 and 128 fill the kernels' tiles; the other multiples of 8 run in the next larger
 // tile with its remaining columns held at zero.
+void attention_mfma_plan(int batch, int seq, int heads, int dh, int causal, int* out) {
+  out[0] = fwd_shape(batch, seq, heads, dh, causal);
+  out[1] = bwd_merged(batch, seq, heads, dh, causal);
+  out[2] = bwd_family(batch, seq, heads, dh, causal);
+}
+
 int attention_forward_mfma(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, void* o,
                            float* lse) {
   if (int rc = check("attention_forward", batch, seq, heads, dh, qkv)) return rc;

@@ -158,6 +158,19 @@ class tuned:
             P.pmc_tuning_set(k, -1)
 
 
+# what bf16 attention would launch: forward shape, one-launch form of the backward pass (0: two launches), family of its two launches
+ATTN_32, ATTN_64, ATTN_64_WIDE, ATTN_64_EIGHT, ATTN_128 = range(5)
+
+
+def attention_plan(batch, seq, heads, dh, causal):
+    import ctypes
+
+    import paper_2405_15362_amd as P
+    out = (ctypes.c_int32 * 3)()
+    P.lib.pmc_test_attention_plan(batch, seq, heads, dh, int(causal), out)
+    return tuple(out)
+
+
 # tiles of a W pass in one launch (-1: its products are launched one by one)
 WGRAD_256, WGRAD_PAIR, WGRAD_128, WGRAD_64X128, WGRAD_64, WGRAD_32 = range(6)
 WGRAD_F32_64, WGRAD_F32_32, WGRAD_F32_32_KSPLIT = range(3)

@@ -356,6 +356,16 @@ def test_the_workspace_of_a_pass_holds_the_plan_of_each_of_its_products():
     assert split > 100
 
 
+@pytest.mark.parametrize("causal", [True, False])
+def test_the_attention_switch_forces_what_it_names(causal):
+    """0: eight-wave workgroups of 64 rows forward and backward, 1 and 2: 128-row ones forward, the families 1 and 2 backward;
+    the backward pass in two launches, for whatever sizes."""
+    for batch, seq, heads, dh in ((1, 64, 3, 128), (8, 64, 64, 32), (1, 200, 16, 128), (16, 128, 16, 128), (1, 1000, 16, 128), (1, 4096, 40, 128)):
+        for value, want in ((0, (U.ATTN_64_EIGHT, 0, 0)), (1, (U.ATTN_128, 0, 1)), (2, (U.ATTN_128, 0, 2))):
+            with U.tuned(attn_shape=value):
+                assert U.attention_plan(batch, seq, heads, dh, causal) == want, (batch, seq, heads, dh, value)
+
+
 def test_bf16_plan_of_layouts_without_a_direct_path():
     assert U.gemm_plan("bf16", True, True, 512, 512, 512)[0] == U.PLAN_GENERAL
     assert U.gemm_plan("bf16", False, False, 512, 512, 512, P.EPI_MUL)[0] == U.PLAN_GENERAL
