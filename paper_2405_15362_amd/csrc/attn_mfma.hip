@@ -18,6 +18,7 @@
 // The launch shapes are chosen by the number of (row block, head) pairs: few pairs get small
 // row blocks and more waves per block so that all compute units have work.
 #include <cstdlib>
+#include <type_traits>
 
 #include "dev_common.h"
 #include "kernels.h"
@@ -173,12 +174,21 @@ __device__ __forceinline__ void zero_tiles(bf16_t* smem, int elems, int tid) {
 // waves on every SIMD even when there are few (query block, head) pairs, and shortens the serial
 // chain of a long row of key blocks.
 // PAD: the head size dh is smaller than the tile width DH (the columns past dh are kept at zero).
-template <int DH, int QW, int KW, int NKT, bool PAD>
+// OWN: each of the wave's first OWN 32-key tiles is summed against a reference of its own, the tile's maximum (what is summed so far is
+// rescaled to it).  Probabilities are rounded to bf16, all but the reference's, which is 1, and of up to a few hundred keys the
+// largest few are a good part of the sum of squares that the rounding error of o is made of.  Four key groups have four exact ones to
+// a query from the start; with OWN = 4 / KW the shapes of fewer groups have the same four, and they move the reference sooner
+// (SLACK), which keeps pace with four groups where scores are spread widely.  Error of o against 64 bits over that of four groups, one reference
+// to a group / OWN: 8 x 128 tokens, 16 heads of 64, no mask, two groups 1.08 / 1.00 and one 1.10 / 1.00; over 80 sizes of
+// up to 2048 tokens with q and k ~ N(0, 0.25), N(0, 1), N(0, 4) at worst 1.15 / 1.004, on average 1.03 / 1.00, 1.00, 0.97.  It costs two groups
+// 0.5 % and one 2 % of the time: the first tiles run in a loop of their own, which leaves the other loop as it is.
+template <int DH, int QW, int KW, int NKT, bool PAD, int OWN>
 __global__ __launch_bounds__(QW * KW * 64, QW * KW == 4 ? 2 : 1) void attn_fwd_mfma(int seq, int heads, int dh, int causal, const bf16_t* __restrict__ qkv,
                                                                bf16_t* __restrict__ o, float* __restrict__ lse,
                                                                float scale_log2) {
   constexpr int NT = QW * KW * 64, BQW = 32 * QW, WK = 32 * NKT, BSW = WK * KW;
   constexpr int KT = BSW * DH, VT = BSW * DH;
+  constexpr float SLACK = OWN > 0 ? 3.0f : kSlack;
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];  // [2][K tile | V tile]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hl = lane >> 5;
   const int qg = wave % QW, kg = wave / QW;
@@ -199,6 +209,7 @@ __global__ __launch_bounds__(QW * KW * 64, QW * KW == 4 ? 2 : 1) void attn_fwd_m
 #pragma unroll
   for (int dt = 0; dt < DH / 32; ++dt) zero(oacc[dt]);
   float m2 = -INFINITY, lsum = 0.f;  // softmax reference (log2 units, scale applied; see below) and sum
+  float top = -INFINITY;             // OWN: maximum of the tiles with a reference of their own
 
   const int kend = causal ? min(seq, q0 + BQW) : seq;
   const int nblk = (kend + BSW - 1) / BSW;
@@ -215,7 +226,8 @@ __global__ __launch_bounds__(QW * KW * 64, QW * KW == 4 ? 2 : 1) void attn_fwd_m
   // them inside the loop would also cover the loads that prefetch the next block.
 #pragma unroll
   for (int ks = 0; ks < DH / 16; ++ks) asm volatile("" ::"v"(qf[ks]));
-  for (int blk = 0; blk < nblk; ++blk) {
+  auto block = [&](int blk, auto own_references) {
+    constexpr bool own = decltype(own_references)::value;
     const int k0 = blk * BSW + WK * kg;  // this wave's 32 NKT keys
     const bf16_t* kt_ = smem + (blk & 1) * (KT + VT);
     const bf16_t* vt_ = kt_ + KT;
@@ -257,43 +269,71 @@ __global__ __launch_bounds__(QW * KW * 64, QW * KW == 4 ? 2 : 1) void attn_fwd_m
             if (key >= seq || (causal && key > qrow)) s[kt][r] = -INFINITY;
           }
       }
-      float mx = s[0][0];
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      // m2 is the reference the exponentials are taken against, not necessarily the exact running
-      // maximum: it moves (and what is summed so far is rescaled) only when some query's maximum
-      // has risen by more than kSlack above it, so probabilities stay below 2^kSlack and the
-      // quotient o / lsum and lse = m2 + log2(lsum) are the same as with the exact maximum.
-      const float m_new = fmaxf(m2, mx * scale_log2);
-      if (__any(m_new > m2 + kSlack)) {
-        const float alpha = __builtin_amdgcn_exp2f(m2 - ((m_new == -INFINITY) ? 0.f : m_new));
+      auto finite = [](float m) { return m == -INFINITY ? 0.f : m; };  // no key so far: exp2(-inf - 0) = 0
+      auto rescale = [&](float m) {                                    // what is summed so far, from reference m2 to m
+        const float alpha = __builtin_amdgcn_exp2f(m2 - finite(m));
         lsum *= alpha;
 #pragma unroll
         for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
           for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
-        m2 = m_new;
+        m2 = m;
+      };
+      float ref[NKT];
+      if constexpr (own) {
+        // one for each tile; it may also fall, to kSlack below the largest score so far, so that probabilities stay below 2^kSlack
+#pragma unroll
+        for (int kt = 0; kt < NKT; ++kt) {
+          float mx = s[kt][0];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
+          mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2;
+          top = fmaxf(top, mx);
+          ref[kt] = mx == -INFINITY ? (kt ? ref[0] : m2) : fmaxf(mx, top - kSlack);
+        }
+        rescale(ref[0]);
+      } else {
+        float mx = s[0][0];
+#pragma unroll
+        for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        // m2 is the reference the exponentials are taken against, not necessarily the exact running
+        // maximum: it moves (and what is summed so far is rescaled) only when some query's maximum
+        // has risen by more than SLACK above it, so probabilities stay below 2^kSlack and the
+        // quotient o / lsum and lse = m2 + log2(lsum) are the same as with the exact maximum.
+        const float m_new = fmaxf(m2, mx * scale_log2);
+        if (__any(m_new > m2 + SLACK)) rescale(m_new);
+#pragma unroll
+        for (int kt = 0; kt < NKT; ++kt) ref[kt] = m2;
       }
-      const float m_use = (m2 == -INFINITY) ? 0.f : m2;
       float rowsum = 0.f;
 #pragma unroll
-      for (int kt = 0; kt < NKT; ++kt)
+      for (int kt = 0; kt < NKT; ++kt) {
+        const float m_use = finite(ref[kt]);
+        if (own && kt > 0) {
+          lsum += rowsum + __shfl_xor(rowsum, 32, 64);
+          rowsum = 0.f;
+        }
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kt][r], scale_log2, -m_use));
           s[kt][r] = p;
           rowsum += p;
         }
+      }
       rowsum += __shfl_xor(rowsum, 32, 64);
-      lsum += rowsum;
+      if (!own || NKT == 1) lsum += rowsum;
 #pragma unroll
       for (int g = 0; g < 2 * NKT; ++g) {  // 16 keys at a time: tile g / 2, half g % 2
         if (g + 1 < 2 * NKT) {
 #pragma unroll
           for (int dt = 0; dt < DH / 32; ++dt) vf[(g + 1) & 1][dt] = frag_cols<DH>(vt_, 32 * dt, WK * kg + 16 * (g + 1), lane);
+        }
+        if (own && g == 2) {
+          rescale(ref[NKT - 1]);
+          lsum += rowsum;
         }
         const bf16x8 pb = acc_to_frag(s[g >> 1], g & 1);
 #pragma unroll
@@ -303,7 +343,11 @@ __global__ __launch_bounds__(QW * KW * 64, QW * KW == 4 ? 2 : 1) void attn_fwd_m
     }
     __builtin_amdgcn_s_waitcnt(kWaitAllLoads);  // this wave's part of the next block has landed
     __syncthreads();
-  }
+  };
+  int blk = 0;
+  if constexpr (OWN > 0)
+    for (; blk < min(nblk, OWN / NKT); ++blk) block(blk, std::true_type{});
+  for (; blk < nblk; ++blk) block(blk, std::false_type{});
   if (KW > 1) {
     // Merge the key groups of each query group: groups 1.. park (O, m, l) in LDS (the tiles are no
     // longer read), group 0 folds them in ascending order.  Slot layout: [DH/2 + 2][64 lanes] fp32.
@@ -691,13 +735,13 @@ __global__ __launch_bounds__(KG * QG * 128, KG * QG == 2 ? (KW > 0 ? 2 : 3) : 1)
   }
 }
 
-template <int DH, int QW, int KW, int NKT, bool PAD>
+template <int DH, int QW, int KW, int NKT, bool PAD, int OWN = 0>
 int fwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, void* o, float* lse) {
   constexpr size_t lds = 2 * sizeof(bf16_t) * 32 * NKT * KW * 2 * DH;
   static std::atomic<bool> done{false};
-  if (int rc = reserve_lds(attn_fwd_mfma<DH, QW, KW, NKT, PAD>, lds, done, "attention_forward")) return rc;
+  if (int rc = reserve_lds(attn_fwd_mfma<DH, QW, KW, NKT, PAD, OWN>, lds, done, "attention_forward")) return rc;
   const float scale_log2 = kLog2e / sqrtf((float)dh);
-  attn_fwd_mfma<DH, QW, KW, NKT, PAD><<<dim3(heads * batch, (seq + 32 * QW - 1) / (32 * QW)), dim3(QW * KW * 64), lds, st>>>(
+  attn_fwd_mfma<DH, QW, KW, NKT, PAD, OWN><<<dim3(heads * batch, (seq + 32 * QW - 1) / (32 * QW)), dim3(QW * KW * 64), lds, st>>>(
       seq, heads, dh, causal, (const bf16_t*)qkv, (bf16_t*)o, lse, scale_log2);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(PMC_ERR_HIP, "attention_forward launch failed: %s", hipGetErrorString(e));
@@ -719,16 +763,18 @@ int fwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal
 // 13.8 / 16.9 / 17.0, 4 x 24 x 512 (w 768) - / - / 14.5 / 16.6 / 13.4; not causal 16 x 2048 42 / 33 / 29 / 32 / 35, 24 x 2048 (w 768) - / - / 43.2 / 44.4 / 45.7.
 // The attn_shape tuning switch (0|1|2) forces the eight-wave one (0) or the last (1, 2), and a family of the backward pass in two launches
 // (tests and tuning).
-enum FwdShape { kFwd32, kFwd64, kFwd64Wide, kFwd64Eight, kFwd128 };
+enum FwdShape { kFwd32, kFwd64, kFwd64Wide, kFwd64Eight, kFwd128, kFwd128Own };
 FwdShape fwd_shape(int batch, int seq, int heads, int dh, int causal) {
   if (const int f = tuning(kTuneAttnShape); f >= 0) return f == 0 ? kFwd64Eight : kFwd128;
   const int64_t pairs = (int64_t)heads * batch, w = (seq + 63) / 64 * pairs;
-  if (seq <= 64) return kFwd128;
-  if (w > 512) return dh <= 64 && w < 1024 && seq >= (causal ? 704 : 2048) ? kFwd64Wide : kFwd128;
+  // references of their own for the first keys where they are few or the call is small: see attn_fwd_mfma
+  const FwdShape rows128 = (seq + 127) / 128 * pairs < 512 ? kFwd128Own : kFwd128;
+  if (seq <= 64) return rows128;
+  if (w > 512) return dh <= 64 && w < 1024 && seq >= (causal ? 704 : 2048) ? kFwd64Wide : rows128;
   if (seq <= 192) return kFwd64;
   if ((seq + 31) / 32 * pairs <= 256) return kFwd32;
   if (w <= 256 || dh <= 64) return kFwd64Wide;
-  if (!causal) return kFwd128;
+  if (!causal) return rows128;
   return seq < 1536 ? kFwd64 : seq < 3072 ? kFwd64Wide : kFwd64Eight;
 }
 
@@ -758,9 +804,10 @@ template <int DH, bool PAD>
 int fwd_t(hipStream_t st, int batch, int seq, int heads, int dh, int causal, const void* qkv, void* o, float* lse) {
   switch (fwd_shape(batch, seq, heads, dh, causal)) {
     case kFwd32: return fwd_launch<DH, 1, 4, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
-    case kFwd64: return fwd_launch<DH, 2, 2, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
+    case kFwd64: return fwd_launch<DH, 2, 2, 1, PAD, 2>(st, batch, seq, heads, dh, causal, qkv, o, lse);
     case kFwd64Eight: return fwd_launch<DH, 2, 4, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
-    case kFwd64Wide: return fwd_launch<DH, 2, 2, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
+    case kFwd64Wide: return fwd_launch<DH, 2, 2, 2, PAD, 2>(st, batch, seq, heads, dh, causal, qkv, o, lse);
+    case kFwd128Own: return fwd_launch<DH, 4, 1, 2, PAD, 4>(st, batch, seq, heads, dh, causal, qkv, o, lse);
     default: return fwd_launch<DH, 4, 1, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
   }
 }
