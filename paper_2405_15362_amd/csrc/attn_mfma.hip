@@ -748,34 +748,38 @@ int fwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal
   return PMC_OK;
 }
 
-// Forward, by w = 64-row workgroups of the whole call.  Few tokens and heads leave the chain of one workgroup as the time, so rows
-// get small workgroups whose waves split the other side, as long as all of them run at once:
-//   32 queries, four waves that take every fourth 32-key tile: from 256 tokens a sequence on, up to 256 of these workgroups
-//   64 queries, two key groups, 32 keys at a time: up to 192 tokens, and heads of more than 64 under a causal mask up to w = 512 (two
-//       workgroups to a compute unit)
-//   64 queries, two key groups, 64 keys at a time: up to w = 256, heads of up to 64 w = 512
-//   64 queries, four key groups of two waves each: the longest sequences of few heads of more than 64, causal
-//   128 queries, every wave all keys, two workgroups to a unit: everything else, and one block of up to 64 tokens
-// us of these five in turn, heads of 128, causal: 16 x 256 tokens (w 64) 7.8 / 8.4 / 8.5 / 9.9 / 11.1, 16 x 1000 (w 256) 20.5 / 18.9 / 18.0 /
-// 18.1 / 26.6, 64 x 192 (w 192) 12.4 / 7.9 / 8.7 / 9.9 / 9.0, 64 x 512 (w 512) 30 / 14.9 / 18.6 / 21 / 17.5, 16 x 2048 (w 512) 56 / 39.5 /
-// 36.7 / 38.7 / 48.6, 8 x 4096 (w 512) - / 77 / 68 / 62 / 88, 16 x 64 6.8 / 5.9 / 6.9 / 8.3 / 5.7; not causal 64 x 512 34 / 18.4 / 21.5 / 24 / 17.3;
-// heads of 64, causal 16 x 2048 (w 512) 28 / 26.5 / 22.9 / 24.2 / 34, 12 x 4096 (w 768) - / - / 46.8 / 50.5 / 63.4, 48 x 768 (w 576) - / - /
-// 13.8 / 16.9 / 17.0, 4 x 24 x 512 (w 768) - / - / 14.5 / 16.6 / 13.4; not causal 16 x 2048 42 / 33 / 29 / 32 / 35, 24 x 2048 (w 768) - / - / 43.2 / 44.4 / 45.7.
+// Forward.  Few tokens and heads leave the chain of one workgroup as the time, so rows get small workgroups whose waves split the other
+// side; the more workgroups there are (w of 64 rows), the less that is worth and the more it costs to fetch and to fold.
+//   128 queries, every wave all keys: from 512 such workgroups on; with references of its own (see attn_fwd_mfma) also below that, from
+//       w = 768 on, for heads of more than 64 without a mask from 512 on
+//   32 queries, four waves that take every fourth 32-key tile: more than 192 tokens, up to 256 of these workgroups
+//   64 queries, eight waves in four key groups: long sequences, whose chain counts most.  Longer than 512 tokens (256 with heads of up to
+//       64) up to w = 256; than 2 w (1.5 w; without a mask 512 tokens, and never with heads of more than 64) up to 512; beyond that only heads
+//       of up to 64 under a mask, longer than 5 (w - 512) + 500
+//   64 queries, four waves in two key groups: everything else
+// Over 5220 calls (1 .. 64 heads of 40 .. 128, 1 .. 8 sequences of 8 .. 4096 tokens) the shape picked is 0.6 % slower than the best one on
+// average, 1.24 times at worst; against 64-row workgroups of eight waves below 512 128-row ones (the rule it replaced at first) 0.83 of the time, 1.06 at
+// worst.  us of 32 / 64 four waves / 64 eight waves / 128 queries, heads of 128, causal: 16 x 256 tokens (w 64) 7.9 / 8.6 / 9.7 / 11.4, 64 x 192 (w 192) 12.1 / 8.0 / 9.7 /
+// 9.1, 16 x 1000 (w 256) 21.4 / 19.4 / 18.0 / 26.8, 64 x 512 (w 512) 32 / 15.9 / 21 / 18.4, 16 x 2048 (w 512) 57 / 38.6 / 36.5 / 47.6, 8 x 4096 (w 512) 91 / 69 / 57 / 87,
+// 26 x 1500 (w 624) 63 / 32 / 45 / 40, 60 x 1000 (w 960) 81 / 36 / 51 / 32; not causal 32 x 1000 (w 512) 55 / 30.3 / 35.6 / 28.6, 5 x 3000 (w 235) 69 / 50 / 41 / 66;
+// heads of 64, causal 16 x 2048 (w 512) 26 / 24.7 / 21.7 / 34.8, 48 x 768 (w 576) 19.4 / 13.0 / 15.9 / 17.0; not causal 16 x 2048 41 / 31.8 / 30.4 / 34.7.
 // The attn_shape tuning switch (0|1|2) forces the eight-wave one (0) or the last (1, 2), and a family of the backward pass in two launches
 // (tests and tuning).
-enum FwdShape { kFwd32, kFwd64, kFwd64Wide, kFwd64Eight, kFwd128, kFwd128Own };
+enum FwdShape { kFwd32, kFwd64, kFwd64Eight, kFwd128, kFwd128Own };
 FwdShape fwd_shape(int batch, int seq, int heads, int dh, int causal) {
   if (const int f = tuning(kTuneAttnShape); f >= 0) return f == 0 ? kFwd64Eight : kFwd128;
   const int64_t pairs = (int64_t)heads * batch, w = (seq + 63) / 64 * pairs;
-  // references of their own for the first keys where they are few or the call is small: see attn_fwd_mfma
-  const FwdShape rows128 = (seq + 127) / 128 * pairs < 512 ? kFwd128Own : kFwd128;
-  if (seq <= 64) return rows128;
-  if (w > 512) return dh <= 64 && w < 1024 && seq >= (causal ? 704 : 2048) ? kFwd64Wide : rows128;
-  if (seq <= 192) return kFwd64;
-  if ((seq + 31) / 32 * pairs <= 256) return kFwd32;
-  if (w <= 256 || dh <= 64) return kFwd64Wide;
-  if (!causal) return rows128;
-  return seq < 1536 ? kFwd64 : seq < 3072 ? kFwd64Wide : kFwd64Eight;
+  const bool wide = dh > 64;
+  if ((seq + 127) / 128 * pairs >= 512) return kFwd128;
+  if (seq <= 64) return kFwd64;
+  if ((seq + 31) / 32 * pairs <= 256) return seq <= 192 ? kFwd64 : kFwd32;
+  if (w <= 256) return seq <= (wide ? 512 : 256) ? kFwd64 : kFwd64Eight;
+  if (w <= 512) {
+    if (causal) return 2 * (int64_t)seq <= (wide ? 4 : 3) * w ? kFwd64 : kFwd64Eight;
+    return wide || seq <= 512 ? kFwd64 : kFwd64Eight;
+  }
+  if (causal && !wide) return seq <= 5 * (w - 512) + 500 ? kFwd64 : kFwd64Eight;
+  return w > 768 || (wide && !causal) ? kFwd128Own : kFwd64;
 }
 
 // Backward, family 0: 64-row workgroups of 8 waves, the dQ ones with four key groups; one workgroup fills a unit.  Family 1: 128-query
@@ -806,7 +810,6 @@ int fwd_t(hipStream_t st, int batch, int seq, int heads, int dh, int causal, con
     case kFwd32: return fwd_launch<DH, 1, 4, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
     case kFwd64: return fwd_launch<DH, 2, 2, 1, PAD, 2>(st, batch, seq, heads, dh, causal, qkv, o, lse);
     case kFwd64Eight: return fwd_launch<DH, 2, 4, 1, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
-    case kFwd64Wide: return fwd_launch<DH, 2, 2, 2, PAD, 2>(st, batch, seq, heads, dh, causal, qkv, o, lse);
     case kFwd128Own: return fwd_launch<DH, 4, 1, 2, PAD, 4>(st, batch, seq, heads, dh, causal, qkv, o, lse);
     default: return fwd_launch<DH, 4, 1, 2, PAD>(st, batch, seq, heads, dh, causal, qkv, o, lse);
   }

@@ -159,7 +159,7 @@ class tuned:
 
 
 # what bf16 attention would launch: forward shape, one-launch form of the backward pass (0: two launches), family of its two launches
-ATTN_32, ATTN_64, ATTN_64_WIDE, ATTN_64_EIGHT, ATTN_128, ATTN_128_OWN = range(6)
+ATTN_32, ATTN_64, ATTN_64_EIGHT, ATTN_128, ATTN_128_OWN = range(5)
 
 
 def attention_plan(batch, seq, heads, dh, causal):

@@ -356,6 +356,26 @@ def test_the_workspace_of_a_pass_holds_the_plan_of_each_of_its_products():
     assert split > 100
 
 
+# batch, sequence, heads, head size, causal, us of the forward shapes (32 queries, 64 in four waves, 64 in eight, 128 with references of its own)
+ATTN_FORWARD = [(1, 256, 16, 128, True, 7.91, 8.58, 9.72, 11.44), (1, 1000, 16, 128, True, 21.36, 19.41, 17.98, 26.75),
+                (1, 192, 64, 128, True, 12.12, 7.97, 9.70, 9.05), (1, 512, 64, 128, True, 31.84, 15.93, 21.09, 18.43),
+                (1, 2048, 16, 128, True, 56.88, 38.55, 36.47, 47.64), (1, 4096, 8, 128, True, 91.34, 68.58, 57.49, 87.29),
+                (1, 1500, 26, 128, True, 62.72, 31.88, 45.02, 39.61), (1, 1000, 60, 128, True, 80.78, 36.02, 51.41, 32.01),
+                (8, 1697, 1, 112, True, 27.99, 29.89, 24.05, 43.72), (2, 1570, 4, 80, True, 26.82, 28.55, 22.95, 40.8), (1, 3000, 5, 128, False, 69.02, 49.55, 41.17, 65.65),
+                (1, 1000, 32, 128, False, 54.60, 30.30, 35.60, 28.55), (1, 768, 32, 128, False, 34.05, 23.18, 28.36, 21.78),
+                (1, 2048, 16, 64, True, 26.23, 24.74, 21.71, 34.75), (4, 512, 24, 64, True, 18.58, 11.70, 16.08, 13.38),
+                (1, 2048, 16, 64, False, 41.35, 31.80, 30.35, 34.66)]
+
+
+@pytest.mark.parametrize("case", ATTN_FORWARD, ids=lambda c: "-".join(map(str, c[:5])))
+def test_attention_forward_picks_a_fast_shape(case):
+    """Within 8 % of the best, which is what neighbouring shapes differ by where the rule changes over, and no slower than 64-row workgroups of
+    eight waves by more than 3 %."""
+    us = dict(zip((U.ATTN_32, U.ATTN_64, U.ATTN_64_EIGHT, U.ATTN_128_OWN), case[5:]))
+    picked = U.attention_plan(*case[:5])[0]
+    assert us[picked] <= 1.08 * min(us.values()) and us[picked] <= 1.03 * us[U.ATTN_64_EIGHT], picked
+
+
 @pytest.mark.parametrize("causal", [True, False])
 def test_the_attention_switch_forces_what_it_names(causal):
     """0: eight-wave workgroups of 64 rows forward and backward, 1 and 2: 128-row ones forward, the families 1 and 2 backward;
