@@ -918,6 +918,11 @@ int pmc_test_attention_plan(int32_t batch, int32_t seq, int32_t heads, int32_t h
   return PMC_OK;
 }
 
+// For the library's own tests (not in pmc.h): columns of q|k|v that a pass keeps for attention's backward (0: two launches in place).
+int pmc_test_attention_kept_columns(int32_t dtype, int32_t batch, int32_t seq, int32_t heads, int32_t head_dim, int32_t causal) {
+  return k::attention_backward_kept_columns(dtype, batch, seq, heads, head_dim, causal);
+}
+
 // For the library's own tests (not in pmc.h): tiles of the one launch that does the W pass of `count` microbatches
 // (-1: the products go out one by one).
 int pmc_test_wgrad_shape(const pmc_chunk_cfg* cfg, int32_t count) {

@@ -36,25 +36,33 @@ size_t attention_backward_scratch_bytes(int dtype, int batch, int seq, int heads
 }
 
 // Where both halves of the backward pass go out as one launch, by w = 64-row workgroups of one half.
-//   1: 8 waves to a workgroup, one workgroup to a compute unit; as long as each half has at most one per unit (w <= 256).
+//   1: 8 waves to a workgroup, one workgroup to a compute unit.  Up to w = 128 the workgroups of both halves fit the units at once; up to
+//      256 they do not, and all but the causal ones, whose lengths differ, meet in two rounds that take longer than two launches.
 //   2: 4 waves, two to a unit; for one block of rows, where there is nothing to split over more waves, and for short sequences
-//      beyond w = 128, where two rounds of the larger ones meet.
-// Otherwise two launches are faster, whose workgroups need less LDS and fewer registers each.  us of 1 / 2 / two launches, without
-// the copy that in-place results need, heads of 128, causal unless said: 16 heads x 512 tokens 21.8 / 29.1 / 30; 16 x 1000 (w 256) 45 / 53 / 50;
-// 16 x 64 11.4 / 9.6 / 16; 128 x 128 (w 256) 22.9 / 15.8 / 25; 64 x 192 (w 192) 22.7 / 18.2; 128 x 192 (w 384) - / 25.9 / 29.5, not causal
-// 30.2 / 30.5; 64 x 512 (w 512) - / 43 / 51, not causal 65 / 54; 16 x 2048 (w 512) - / 122 / 106.  fp32 (16-row blocks): 8 heads of 64, 512
-// tokens 31 in one, 36 in two; 16 heads 57 and 50.
+//      beyond w = 128.
+// Otherwise two launches are faster, whose workgroups need less LDS and fewer registers each.  us of 1 / 2 / two launches in place with their copy,
+// heads of 128: causal 16 heads x 512 tokens (w 128) 22.0 / 29.6 / 36.1, 16 x 1000 (w 256) 46 / 55 / 54, 5 x 3000 (w 235) 97 / 152 / 124, 16 x 64 11.2 / 9.5 / 18.1,
+// 128 x 128 (w 256) 22.7 / 15.5 / 25.8, 64 x 192 (w 192) 22.5 / 17.7 / 27.1, 128 x 192 (w 384) 34.8 / 25.5 / 34.2, 64 x 512 (w 512) 57 / 43 / 52, 32 x 768 (w 384) 52 / 44 / 59,
+// 16 x 2048 (w 512) 141 / 123 / 108; not causal 128 x 192 35.8 / 29.9 / 35.2, 16 x 1000 78 / 83 / 66, 5 x 3000 204 / 217 / 149.  Over 5220 calls (1 .. 64 heads of
+// 40 .. 128, 1 .. 8 sequences of 8 .. 4096 tokens), with the copy of q|k|v that one launch needs in a pass: 0.59 of the time of two launches of one
+// family per size in place, the rule that came before, and nowhere more than 2 % slower.
 int attention_merged(int batch, int seq, int heads, int head_dim, int causal) {
   const int64_t w = (int64_t)((seq + 63) / 64) * heads * batch;
   if (seq <= 64) return w <= 512 ? 2 : 0;
-  if (w > 128 && w <= (causal ? 512 : 384) && seq <= (causal && w > 256 ? 512 : 256)) return 2;
-  return w <= 256 ? 1 : 0;
+  if (w <= 128) return 1;
+  if (w <= 256) return seq <= (head_dim > 64 ? 256 : 128) ? 2 : causal || seq <= 256 ? 1 : 0;
+  return (causal ? w <= 512 && seq <= 512 : w <= 384 && seq <= 256) ? 2 : 0;
 }
-bool attention_merged_f32(int batch, int seq, int heads) { return (int64_t)((seq + 15) / 16) * heads * batch <= 256; }
+// fp32, by 16-row workgroups: as kind 1.  us of one / two launches: causal 8 heads of 64 x 512 tokens (256 workgroups) 30 / 39, 16 x 512 57 / 53, 8 of 128 x 500 53 / 72;
+// not causal 4 of 64 x 1000 (252) 82 / 66, 8 of 128 x 500 86 / 74, 32 of 64 x 100 (224) 15.6 / 18.2.
+bool attention_merged_f32(int batch, int seq, int heads, int causal) {
+  const int64_t w = (int64_t)((seq + 15) / 16) * heads * batch;
+  return w <= (causal || seq <= 128 ? 256 : 128);
+}
 
 int attention_backward_kept_columns(int dtype, int batch, int seq, int heads, int head_dim, int causal) {
   const bool merged =
-      use_mfma(dtype, head_dim) ? attention_merged(batch, seq, heads, head_dim, causal) > 0 : attention_merged_f32(batch, seq, heads);
+      use_mfma(dtype, head_dim) ? attention_merged(batch, seq, heads, head_dim, causal) > 0 : attention_merged_f32(batch, seq, heads, causal);
   return merged ? 3 * heads * head_dim : 0;
 }
 

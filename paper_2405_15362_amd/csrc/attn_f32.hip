@@ -443,7 +443,7 @@ int bwd_launch(hipStream_t st, int batch, int seq, int heads, int dh, int causal
                const void* d_o, void* dqkv, void* dq, int ld_dq, float* delta) {
   static std::atomic<bool> done_dq{false}, done_dkv{false}, done_both{false};
   constexpr size_t lds = fold_bytes<DH>();
-  if (dq == dqkv && attention_merged_f32(batch, seq, heads)) {
+  if (dq == dqkv && attention_merged_f32(batch, seq, heads, causal)) {
     if (int rc = reserve_lds(attn_bwd_f32<T, DH, VEC>, lds, done_both, "attention_backward")) return rc;
     return for_row_blocks("attention_backward", batch, seq, heads, 2, [&](int block0, dim3 grid) {
       attn_bwd_f32<T, DH, VEC><<<grid, dim3(kWavesF * 64), lds, st>>>(block0, seq, heads, dh, causal, (const T*)qkv, (const T*)o, lse,

@@ -782,21 +782,27 @@ FwdShape fwd_shape(int batch, int seq, int heads, int dh, int causal) {
   return w > 768 || (wide && !causal) ? kFwd128Own : kFwd64;
 }
 
-// Backward, family 0: 64-row workgroups of 8 waves, the dQ ones with four key groups; one workgroup fills a unit.  Family 1: 128-query
-// workgroups (64-key ones in the dK/dV kernel) of 4 waves, two or three to a unit.  Family 0 as long as its workgroups fit the 256 units at
-// once; under a causal mask, where their lengths differ and the short ones fill up, also beyond, up to 512 (128-row block, head) pairs, for
-// sequences long enough that the chain counts: longer the more workgroups there are.  us of family 0 / 1, heads of 128, w = 64-row
-// workgroups: causal 60 heads x 1000 (w 960) 146 / 107, 20 x 2048 (w 640) 148 / 163, 12 x 4096 (w 768) 266 / 302; 16 x
-// 1000 (w 256) 50 / 87; 32 x 768 (w 384) 58 / 73; 128 x 256 (w 512) 52 / 42; 64 x 512 (w 512) 60 / 58; not causal 32 x 768 84 / 75,
-// 32 x 1000 115 / 117.  Where attention_merged says 2, the shapes of that one launch also do the two launches in place, so that both
-// give the same bits.
+// Backward in two launches.  Family 0: 64-row workgroups of 8 waves, the dQ ones with four key groups; one workgroup fills a unit.  Family 1:
+// 128-query workgroups (64-key ones in the dK/dV kernel) of 4 waves, two or three to a unit.  Family 3: the 64-row workgroups of 4 waves that
+// attention_merged's kind 2 has in one launch.  By w = 64-row workgroups: 0 as long as its workgroups fit the 256 units at once; 1 from 512 (128-row
+// block, head) pairs on.  Between, the chain counts for long sequences and the units for many workgroups: 0 up to w = 512 (1 where many
+// workgroups of up to 1024 tokens and wide heads fill the units without a mask), beyond that the longer the sequence the more workgroups 0
+// stays the faster for, and 3 between the two.  Where kind 2 does the one launch beyond one round of it, and for one block of rows, 3 is as fast in place and
+// gives the same bits.  us of 0 / 1 / 3 in place, heads of 128: causal 16 heads x 1000 tokens (w 256) 54 / 81 / 67, 28 x 600 (w 280) 53 / 61 / 56, 16 x 2048 (w 512) 108 / 148 / 126,
+// 20 x 2048 (w 640) 147 / 163 / 138, 26 x 1500 (w 624) 131 / 132 / 114, 12 x 4096 (w 768) 265 / 303 / 254, 60 x 1000 (w 960) 146 / 108 / 107; not causal 32 x 768 (w 384) 86 / 73 / 71, 32 x 1000 (w 512) 117 /
+// 114 / 109; heads of 64, causal 16 x 2048 70 / 106 / 94, 12 x 4096 143 / 203 / 178, 48 x 768 (w 576) 48 / 54 / 49, 4 x 24 x 512 (w 768) 51 / 44 / 41.  Over the calls that attention_merged
+// names, 0.93 of the time of 0 below 512 pairs and 1 from there on, 1.06 at worst.
 int bwd_family(int batch, int seq, int heads, int dh, int causal) {
   if (const int f = tuning(kTuneAttnShape); f >= 0) return f;
-  if (attention_merged(batch, seq, heads, dh, causal) == 2) return 3;
   const int64_t pairs = (int64_t)heads * batch, w = (seq + 63) / 64 * pairs;
+  if (attention_merged(batch, seq, heads, dh, causal) == 2 && (seq <= 64 || w > 256)) return 3;
   if (w <= 256) return 0;
-  if ((seq + 127) / 128 * pairs >= 512 || (w > 512 && (int64_t)seq * 10 < w * 13)) return 1;
-  return (int64_t)seq * 64 >= (int64_t)(causal ? 384 : 768) * dh ? 0 : 1;
+  if ((seq + 127) / 128 * pairs >= 512) return 1;
+  const bool wide = dh > 64;
+  if (w <= 512) return !causal && wide && w > 384 && seq <= 1024 ? 1 : 0;
+  if (!wide) return seq < w - (causal ? 128 : 0) ? 1 : 0;
+  if (!causal) return 1;
+  return seq < 4 * (w - 512) + 500 ? 1 : seq < 10 * (w - 512) + 900 ? 3 : 0;
 }
 
 // The one-launch form of the backward pass apart from qkv (0: two launches, as in place).

@@ -145,7 +145,7 @@ int attention_backward(hipStream_t stream, int dtype, int batch, int seq, int he
 // attention_backward from the copy: with qkv and dqkv apart few blocks run as one launch.
 int attention_backward_kept_columns(int dtype, int batch, int seq, int heads, int head_dim, int causal);
 int attention_merged(int batch, int seq, int heads, int head_dim, int causal);  // 0: two launches
-bool attention_merged_f32(int batch, int seq, int heads);
+bool attention_merged_f32(int batch, int seq, int heads, int causal);
 // What a bf16 call on the matrix cores launches (host arithmetic only): the forward shape, the one-launch form of the backward pass apart from
 // qkv (0: two launches) and the family of its two launches (see attn_mfma.hip).
 void attention_mfma_plan(int batch, int seq, int heads, int head_dim, int causal, int* out);

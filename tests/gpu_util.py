@@ -171,6 +171,11 @@ def attention_plan(batch, seq, heads, dh, causal):
     return tuple(out)
 
 
+def attention_kept_columns(dtype, batch, seq, heads, dh, causal):
+    import paper_2405_15362_amd as P
+    return P.lib.pmc_test_attention_kept_columns(P.PMC_F32 if dtype == "f32" else P.PMC_BF16, batch, seq, heads, dh, int(causal))
+
+
 # tiles of a W pass in one launch (-1: its products are launched one by one)
 WGRAD_256, WGRAD_PAIR, WGRAD_128, WGRAD_64X128, WGRAD_64, WGRAD_32 = range(6)
 WGRAD_F32_64, WGRAD_F32_32, WGRAD_F32_32_KSPLIT = range(3)

@@ -376,6 +376,55 @@ def test_attention_forward_picks_a_fast_shape(case):
     assert us[picked] <= 1.08 * min(us.values()) and us[picked] <= 1.03 * us[U.ATTN_64_EIGHT], picked
 
 
+# batch, sequence, heads, head size, causal, us of the backward pass in one launch of the kinds 1 and 2 and in two launches of the families
+# 0, 1, 3 in place
+ATTN_BACKWARD = [(1, 512, 16, 128, True, 22.04, 29.62, 36.11, 48.36, 41.07), (1, 1000, 16, 128, True, 45.99, 54.54, 54.33, 81.38, 67.17),
+                 (1, 3000, 5, 128, True, 96.68, 151.65, 123.94, 210.23, 174.84), (1, 64, 16, 128, True, 11.20, 9.53, 21.64, 18.16, 18.12),
+                 (1, 128, 128, 128, True, 22.72, 15.48, 27.46, 27.78, 25.79), (1, 192, 128, 128, True, 34.82, 25.54, 46.87, 34.17, 35.18),
+                 (1, 512, 64, 128, True, 57.35, 43.06, 59.62, 56.87, 51.62), (1, 2048, 16, 128, True, 140.52, 123.21, 108.26, 147.58, 125.93),
+                 (1, 2048, 20, 128, True, 158.69, 129.55, 147.14, 163.49, 138.16), (1, 1000, 60, 128, True, 151.87, 110.63, 146.20, 108.06, 106.84),
+                 (8, 2227, 2, 80, True, 159.97, 143.16, 128.50, 164.97, 138.12), (1, 1494, 26, 80, True, 119.37, 99.72, 121.28, 130.95, 111.53),
+                 (1, 1000, 16, 128, False, 77.57, 83.15, 66.03, 102.26, 89.84), (1, 3000, 5, 128, False, 203.82, 216.53, 148.53, 263.12, 227.65),
+                 (1, 3931, 3, 64, False, 225.56, 264.85, 154.48, 283.55, 258.28), (1, 192, 128, 128, False, 35.78, 29.88, 50.43, 35.15, 35.88),
+                 (1, 768, 32, 128, False, 80.08, 71.29, 86.38, 72.83, 71.04), (1, 1000, 32, 128, False, 132.44, 134.50, 117.19, 113.60, 108.71),
+                 (1, 212, 37, 40, False, 17.21, 18.59, 23.07, 29.11, 27.55), (1, 2048, 16, 64, True, 98.33, 80.92, 70.27, 106.44, 93.74),
+                 (1, 4096, 12, 64, True, 219.30, 165.75, 143.23, 203.44, 177.67), (4, 512, 24, 64, True, 52.60, 33.24, 50.88, 44.17, 41.39)]
+
+
+@pytest.mark.parametrize("case", ATTN_BACKWARD, ids=lambda c: "-".join(map(str, c[:5])))
+def test_attention_backward_picks_a_fast_form(case):
+    """In a pass (one launch where there is one) and in place, no slower than the rule of one family per size by more than 2 %: 64-row workgroups of
+    eight waves below 512 (128-row block, head) pairs, 128-row ones from there on."""
+    batch, seq, heads = case[:3]
+    one, two = {1: case[5], 2: case[6]}, {0: case[7], 1: case[8], 3: case[9]}
+    before = two[0 if -(-seq // 128) * heads * batch < 512 else 1]
+    _, kind, family = U.attention_plan(*case[:5])
+    assert two[family] <= 1.02 * before and (kind == 0 or one[kind] <= 0.95 * before), (kind, family)
+
+
+def test_the_attention_shape_cases_reach_every_launch_shape():
+    import test_gpu_ops as ops
+    plans = [(U.attention_plan(b, s, h, dh, causal), dh > 64, s > 64) for dtype, b, s, h, dh in ops.ATTN_SHAPES for causal in (True, False)
+             if dtype == "bf16" and dh % 8 == 0]
+    for wide in (True, False):
+        forward = {p[0] for p, w, _ in plans if w == wide}
+        assert forward == {U.ATTN_32, U.ATTN_64, U.ATTN_64_EIGHT, U.ATTN_128, U.ATTN_128_OWN}, (wide, forward)
+        # of several blocks of rows: one launch of both kinds; two launches, of the families 0 and 1
+        backward = {p[1:] for p, w, blocks in plans if w == wide and blocks}
+        assert backward >= {(1, 0), (2, 0), (2, 3), (0, 0), (0, 1)}, (wide, backward)
+    assert (0, 3) in {p[1:] for p, _, _ in plans}
+    kept = {U.attention_kept_columns(dtype, b, s, h, dh, causal) > 0 for dtype, b, s, h, dh in ops.ATTN_SHAPES for causal in (True, False) if dtype == "f32"}
+    assert kept == {True, False}
+
+
+def test_fp32_attention_backward_in_one_launch_where_that_is_faster():
+    # sequence, heads, head size, causal, us of one launch and of two in place
+    for seq, heads, dh, causal, one, two in ((512, 8, 64, True, 29.71, 38.77), (512, 16, 64, True, 56.83, 52.66), (1000, 4, 64, False, 82.21, 66.33),
+                                             (500, 8, 128, False, 86.02, 73.90), (500, 8, 128, True, 53.21, 72.15), (100, 32, 64, False, 15.64, 18.17)):
+        keeps = U.attention_kept_columns("f32", 1, seq, heads, dh, causal) > 0
+        assert keeps == (one < two), (seq, heads, dh, causal)
+
+
 @pytest.mark.parametrize("causal", [True, False])
 def test_the_attention_switch_forces_what_it_names(causal):
     """0: eight-wave workgroups of 64 rows forward and backward, 1 and 2: 128-row ones forward, the families 1 and 2 backward;
