@@ -453,8 +453,10 @@ bool one_launch(F32Shape shape, long tiles) { return tiles < (1LL << 32) / (shap
 // With 16-byte loads: the tile with the least fitted time, us = fixed + n (tile_k k + tile) + ceil(n / per_cu) (group_k k + group)
 // + ceil(n) (round_k k + round) at n tiles per compute unit, per_cu of them side by side, and k = K / 1024.  Fitted to
 // 2323 products of more than 12 us (operands of 200 MB in turn) and 4697 smaller ones (in a graph, so that the host does
-// not count), M = 16 .. 6144, N = 64 .. 5120, K = 64 .. 5120: the tile picked is 0.5 % slower than the best one on average, 1.18
-// times at worst.  All but the 32 x 32 tile of four waves have two waves to a SIMD or more, eight waves to a workgroup, with K
+// not count), M = 16 .. 6144, N = 64 .. 5120, K = 64 .. 5120: the tile picked is 0.8 % slower than the best one on average, 1.24
+// times at worst.  The fit overrates 16 x 16 tiles just past a round of 256, which is no round for four of them to a unit: with 0.94 of their
+// time none of the 7020 products loses more than 7.6 % to the choice among the same five shapes with four waves, with all of it 31 lose more than 10 % (up to
+// 18 %), with 0.88 of it 14 (up to 25 %).  In 250 steps of hidden 64 .. 768 and 16 .. 640 tokens the three are within 0.03 % on average.  All but the 32 x 32 tile of four waves have two waves to a SIMD or more, eight waves to a workgroup, with K
 // in two groups where the tile is too small for eight: with four waves to a unit nothing covered the reads from LDS.  The
 // larger products run in 0.89 and the smaller in 0.95 of the time that the same tiles with four waves take; four waves / eight:
 // 512 x 1024 x 4096 (F, 32 x 64) 49.2 / 45.3 us, 768 x 5120 x 1280 (F, 64 x 64 / 64 x 128) 97 / 88, 512 x 3072 x 1024 (F) 45 / 38,
@@ -485,7 +487,7 @@ F32Shape pick_tile_f32(bool tb, int M, int N, int K) {
     const double k = K / 1024.0, n = (double)count / 256.0;
     double us = t.fixed[tb] + n * (t.tile_k[tb] * k + t.tile[tb]) + (double)groups * (t.group_k[tb] * k + t.group[tb]) +
                 (double)rounds * (t.round_k[tb] * k + t.round[tb]);
-    if (t.shape == kDirect) us *= 0.88;  // what it gains inside a pass: 128 x 1024 x 256 (F) 4.8 us in a graph and 5.3 in a step, 32 x 32 tiles 4.75 and 5.9
+    if (t.shape == kDirect) us *= 0.94;  // see above
     if (us < best_us) {
       best_us = us;
       best = t.shape;

@@ -275,6 +275,20 @@ def test_fp32_16x16_tiles_fit_one_launch(ta, tb):
         assert U.gemm_plan("f32", ta, tb, 65536, 32768, 64)[0] == U.F32_TILE64
 
 
+# B stored [N,K], M, N, K, us of the choice before (four waves to a tile), of 32x64 tiles, 32x32 ones of eight waves and of four, 16x16 ones
+FP32_SMALL = [(True, 512, 312, 88, 3.91, 4.14, 3.52, 3.08, 4.31), (True, 1464, 176, 704, 10.86, 10.27, 10.53, 11.0, 13.15), (True, 352, 416, 104, 3.92, 4.30, 3.53, 3.36, 4.43),
+              (True, 200, 1248, 1248, 17.3, 16.7, 16.7, 17.8, 21.6), (True, 40, 4864, 1216, 16.8, 16.0, 16.0, 17.3, 20.1),
+              (False, 48, 1824, 456, 5.25, 8.57, 6.19, 6.23, 5.34), (False, 440, 160, 456, 5.44, 8.72, 6.38, 6.49, 5.39), (True, 688, 192, 768, 7.54, 10.67, 7.50, 7.80, 10.69),
+              (True, 96, 688, 2064, 13.7, 24.4, 15.3, 17.1, 13.6), (False, 128, 1024, 256, 4.88, 6.16, 4.77, 4.75, 4.80)]
+
+
+@pytest.mark.parametrize("tb,M,N,K,before,t32x64,t32,t32four,direct", FP32_SMALL)
+def test_fp32_products_of_few_tiles_pick_a_fast_shape(tb, M, N, K, before, t32x64, t32, t32four, direct):
+    us = {U.F32_TILE32X64: t32x64, U.F32_TILE32: t32, U.F32_TILE32_FOUR: t32four, U.F32_DIRECT: direct}
+    picked = U.gemm_plan("f32", False, tb, M, N, K)[0]
+    assert us[picked] <= 1.08 * before, picked
+
+
 @pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3, 4])
 def test_fp32_tiles_of_any_shape_fit_one_launch(tile):
     """Picked or forced, with K from the least to the longest whose operands the tiles take: fewer than 2^32 threads, or a refusal
