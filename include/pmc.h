@@ -20,7 +20,8 @@
  *  - Work is enqueued on the HIP stream given to pmc_create and is asynchronous unless stated.
  *    The W pass is one launch (per eight layers) that does every weight-gradient product and bias
  *    gradient of the call, except in these cases, where its products are launched one by one: at
- *    2048 tokens and more of a wide bf16 layer; for layers bound to the same gradient memory; while a
+ *    2048 tokens and more of a bf16 layer each of whose products fills whole rounds of large tiles (hidden
+ *    4096, FFN 16384); for layers bound to the same gradient memory; while a
  *    switch forces the kernel of a product; while tracing, whose records are one per operation.
  *    One by one, the bf16 W pass runs every second product and the
  *    bias-gradient column sums on a second, non-blocking stream of default priority that the

@@ -1433,25 +1433,32 @@ int launch_wgrad_batch(hipStream_t st, WgradBatchParams& p) {
 }
 }  // namespace
 
-// Tiles of the one launch; picked by fitted times (see batch_us in wgrad_batch.h) of 2061 W passes, hidden 64 .. 7168, 16 .. 8192
-// tokens, 1 .. 4 layers, FFN 1 .. 4.5 x hidden: the shape picked is 1.7 % slower than the best one on average (1.29 times at
-// worst), and 2.7 times as fast as the products launched one by one on two streams (geometric mean over the 2061).  Some of them, us one by
-// one / in one launch: 2 layers of hidden 256, 192 tokens 52 / 9; 2 of 1024, 4096 tokens 320 / 214; 2 of 2048, 1024 tokens
-// 312 / 283; 2 of 4096, 1024 tokens 1140 / 1015.
+// Tiles of the one launch; picked by fitted times (see batch_us in wgrad_batch.h) of 4030 W passes, hidden 64 .. 8192, 16 .. 65536 tokens
+// in 1 .. 8 pieces, 1 .. 4 layers, FFN 1 .. 4.5 x hidden: the shape picked is 1.1 % slower than the best one on average (1.31 times at
+// worst, at a few microseconds; 0.8 % beyond 2048 tokens and 0.2 % beyond 8192), and 1.86 times as fast as the products launched one by one on two streams (geometric mean).
+// Some of them, us one by one / in one launch: 2 layers of hidden 256, 192 tokens 52 / 9; 2 of 1024, 4096 tokens 333 / 226; 2 of 2048, 1024 tokens
+// 321 / 290; 2 of 4096, 1024 tokens 1140 / 1015; 2 of 5120, 4096 tokens 4584 / 4577; 1 of 2304 x 2776, 8 x 5488 tokens 3104 / 3087 (4178 in tiles of shape 1).
 //   0: 256x256, four 32-deep stages   1: 256x128, two workgroups per compute unit   2: 128x128, likewise
 //   3: 64x128   4: 64x64   5: 32x32 whose waves split K (few outputs over many tokens)
 enum BatchShape { kBatch256, kBatchPair, kBatch128, kBatch64x128, kBatch64, kBatch32, kBatchShapes };
 
-// The shape, or -1 where the products go out one by one: at 2048 tokens and more with twelve and more rounds of 256x256 tiles
-// over the compute units in each layer the products fill the chip by themselves, and the persistent kernel beside a
-// second stream is as fast or faster (3072 .. 9408 tiles per layer, 2048 .. 8192 tokens: one launch 0.99 of it, 0.97 .. 1.02).
+// The shape, or -1 where the products go out one by one: where each of them fills whole rounds of 256x256 tiles over the compute units, to 98 %, a launch
+// of its own leaves nothing idle, and from 2048 tokens on the persistent kernel beside a second stream is as fast.  Time of one launch over that of
+// two streams: 11 such passes of 2104 .. 6360 tokens 0.97 .. 1.04, 1.00 on average (2 layers of 4096, 2048 tokens 1683 and 1663 us); fewer tokens 0.94; rounds filled to 0.90 .. 0.98
+// 0.98 (0.86 .. 1.03), to 0.80 .. 0.90 0.96 (0.86 .. 1.03), less 0.88 (0.64 .. 1.09: 2 layers of 2048 x 6416, 6464 tokens 1102 and 1014 us, whose last round is a quarter full).
 int gemm_bf16_wgrad_batch_shape(const WgradBatchArgs& a) {
   constexpr int kBm[kBatchShapes] = {256, 256, 128, 64, 64, 32}, kBn[kBatchShapes] = {256, 128, 128, 128, 64, 32};
   static constexpr BatchTime kTimes[kBatchShapes] = {
-      {11.06, 0.86, 8.73, 26.8, 13.6, 0., 1},  {6.78, 1.87, 6.93, 11.4, 9.66, 3.07, 2}, {6.48, 1.41, 4.35, 5.60, 5.97, 1.18, 2},
-      {4.52, 2.57, 3.42, 2.40, 3.47, 2.20, 3}, {4.51, 2.71, 2.70, 1.15, 1.19, 1.82, 4}, {5.33, 1.57, 1.75, 0.65, 0.74, 1.01, 2}};
+      {11.06, 0.86, 8.73, 26.8, 13.6, 0., 1, 0.},     {6.78, 1.87, 6.93, 11.4, 9.66, 3.07, 2, 1.14},  {6.48, 1.41, 4.35, 5.60, 5.97, 1.18, 2, 1.58},
+      {4.52, 2.57, 3.42, 2.40, 3.47, 2.20, 3, 0.69}, {4.51, 2.71, 2.70, 1.15, 1.19, 1.82, 4, 0.48}, {5.33, 1.57, 1.75, 0.65, 0.74, 1.01, 2, 0.}};
   const double K = (double)a.K * a.pieces;
-  if (K >= 2048 && batch_tiles(a, 256, 256) >= 12 * 256) return -1;
+  double filled = 0., rounds = 0.;
+  for (int j = 0; j < 4; ++j) {
+    const long tiles = (long)((a.M[j] + 255) / 256) * ((a.N[j] + 255) / 256);
+    filled += (double)tiles;
+    rounds += (double)((tiles + 255) / 256);
+  }
+  if (K >= 2048 && filled >= 0.98 * 256. * rounds) return -1;
   int best = -1;
   double best_us = 1e300;
   for (int s = 0; s < kBatchShapes; ++s) {

@@ -5,6 +5,8 @@
 // tiles become affordable because their number adds up, and the workgroups that share a compute unit drift out of phase, so
 // that one's read-modify-write of C runs under another's K loop.
 #pragma once
+#include <cmath>
+
 #include "dev_common.h"
 #include "kernels.h"
 
@@ -19,13 +21,17 @@ inline long batch_tiles(const WgradBatchArgs& a, int bm, int bn) {
 }
 // us of a batch: n tiles per compute unit at K tokens take a fixed time, the chain of one tile (per 1024 of K), a share of the
 // compute unit per tile (per 1024 of K, and once), and the chain again for every round of tiles (per_cu workgroups run side by side).
+// Beyond 3072 tokens a share of K costs more the longer K is: the passes are long enough for the chip's power limit, and the smaller the tile the
+// more of its operands come from memory again (long_k, relative to the shape that costs least).
 struct BatchTime {
   double fixed, chain_k, tile_k, tile, round_k, round;
   int per_cu;
+  double long_k = 0.;
 };
 inline double batch_us(const BatchTime& t, double tiles, double K) {
   const double n = tiles / 256., k = K / 1024., rounds = (double)(long)((n + t.per_cu * 0.999999) / t.per_cu);
-  return t.fixed + t.chain_k * k + n * (t.tile_k * k + t.tile) + rounds * (t.round_k * k + t.round);
+  const double tile_k = t.tile_k + (k > 3. ? t.long_k * std::log2(k / 3.) : 0.);
+  return t.fixed + t.chain_k * k + n * (tile_k * k + t.tile) + rounds * (t.round_k * k + t.round);
 }
 
 // Column sums of 64 columns from col0 of `pieces` matrices [rows][n] (pitch lda) by 256 threads (tid): out[c] += the sum of each

@@ -181,9 +181,13 @@ WGRAD_256, WGRAD_PAIR, WGRAD_128, WGRAD_64X128, WGRAD_64, WGRAD_32 = range(6)
 WGRAD_F32_64, WGRAD_F32_32, WGRAD_F32_32_KSPLIT = range(3)
 
 
-def wgrad_shape(cfg, count=1):
+def wgrad_shape_of(cfg, count=1):
     import ctypes
 
     import paper_2405_15362_amd as P
+    return P.lib.pmc_test_wgrad_shape(ctypes.byref(cfg), count)
+
+
+def wgrad_shape(cfg, count=1):
     from paper_2405_15362_amd import runtime as R
-    return P.lib.pmc_test_wgrad_shape(ctypes.byref(R.cfg_from_synth(cfg)), count)
+    return wgrad_shape_of(R.cfg_from_synth(cfg), count)

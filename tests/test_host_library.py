@@ -337,6 +337,23 @@ def test_the_weight_gradients_of_a_layer_share_the_two_workgroup_kernel(tokens):
             assert kernels == {h > 1280 and tokens <= 1024}, (h, f, tokens)
 
 
+# layers, hidden, FFN, tokens of a microbatch, microbatches; us of the products one by one on two streams, in one launch of 256x256, 256x128, 128x128 tiles
+W_PASSES = [(2, 4096, 16384, 2048, 1, 1663, 1683, 1800, 2072), (2, 5120, 20480, 4096, 1, 4584, 4577, 4975, 6122), (1, 7168, 28672, 1024, 1, 1696, 1684, 1670, 1899),
+            (2, 2048, 8192, 1024, 1, 321, 308, 290, 320), (2, 1024, 4096, 4096, 1, 333, 230, 226, 256), (2, 2048, 8192, 4096, 1, 792, 764, 806, 956),
+            (2, 4096, 11008, 4096, 1, 2333, 2264, 2455, 2960), (1, 5504, 7696, 3584, 1, 1647, 1425, 1549, 1799), (2, 4160, 16640, 4224, 1, 3363, 3136, 3505, 4204),
+            (2, 4416, 17664, 3136, 1, 2901, 2758, 3054, 3559), (1, 3136, 8760, 8064, 3, 4462, 4546, 6191, 8427), (1, 2304, 2776, 5488, 8, 3104, 3087, 4178, 6204),
+            (3, 1600, 6040, 1264, 8, 1996, 1893, 2510, 2987), (1, 1600, 6400, 5904, 3, 1180, 1190, 1298, 1438), (1, 1856, 4464, 2568, 8, 1347, 1429, 1626, 2045)]
+
+
+@pytest.mark.parametrize("case", W_PASSES, ids=lambda c: "-".join(map(str, c[:5])))
+def test_the_w_pass_takes_a_fast_path(case):
+    layers, h, f, tokens, queued = case[:5]
+    us = dict(zip((-1, U.WGRAD_256, U.WGRAD_PAIR, U.WGRAD_128), case[5:]))
+    cfg = P.make_cfg(layers, h, max(1, h // 64), f, tokens // (8 if tokens >= 2048 else 1), 8 if tokens >= 2048 else 1)
+    picked = U.wgrad_shape_of(cfg, queued)
+    assert us[picked] <= 1.065 * min(us.values()), picked   # the fit's error on the passes it was made from, at worst
+
+
 def test_the_workspace_of_a_pass_holds_the_plan_of_each_of_its_products():
     """Every product of a pass gets, with the scratch that the pass's workspace has, the plan it gets with unlimited
     scratch, whatever the sizes (token counts that are no multiple of 64, ranges of unequal length), and the scratch is
