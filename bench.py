@@ -111,11 +111,27 @@ def run_workload(P, R, synth, torch, np, name, cfg, steps, warmup, queued, want_
     for r in recs:
         by_op.setdefault(r["op"], []).append(r["ms"])
     op_ms_per_step = {op: round(sum(v) / reps, 4) for op, v in by_op.items()}
-    gemms = [r for r in recs if r["op"] == "gemm"]
-    gemm_flop = sum(2.0 * r["m"] * r["n"] * r["k"] for r in gemms)
+    # the products; a W pass in one launch ("wgrad": m tokens, n layers, k microbatches) is one record with its bias sums
+    gemms = [r for r in recs if r["op"] in ("gemm", "wgrad")]
+
+    def flop_of(r):
+        return r["n"] * r["k"] * 2.0 * r["m"] * h * (4 * h + 2 * f) if r["op"] == "wgrad" else 2.0 * r["m"] * r["n"] * r["k"]
+
+    gemm_flop = sum(flop_of(r) for r in gemms)
     gemm_ms = sum(r["ms"] for r in gemms)
+    # the table of single products, and the bias column sums: those of a W pass in one launch from traced steps that
+    # launch them one by one
+    single = recs
+    if any(r["op"] == "wgrad" for r in recs):
+        forced = P.pmc_tuning_get("w_streams")
+        P.pmc_tuning_set("w_streams", 1)
+        P.pmc_trace_begin(ctx.ctx, 8192)
+        for _ in range(reps):
+            step()
+        single = P.pmc_trace_end(ctx.ctx, 8192)
+        P.pmc_tuning_set("w_streams", forced)
     shapes = {}
-    for r in gemms:
+    for r in (r for r in single if r["op"] == "gemm"):
         shapes.setdefault((r["pass_"], r["m"], r["n"], r["k"]), []).append(r["ms"])
     gemm_table = [{"pass": k[0], "m": k[1], "n": k[2], "k": k[3], "us": round(1e3 * float(np.mean(v)), 1),
                    "tflops": round(2.0 * k[1] * k[2] * k[3] / (float(np.mean(v)) * 1e-3) / 1e12, 1)}
@@ -125,15 +141,15 @@ def run_workload(P, R, synth, torch, np, name, cfg, steps, warmup, queued, want_
     for k in "FBW":
         sel = [r for r in gemms if r["pass_"] == k]
         if sel:
-            tf = sum(2.0 * r["m"] * r["n"] * r["k"] for r in sel) / (sum(r["ms"] for r in sel) * 1e-3) / 1e12
+            tf = sum(flop_of(r) for r in sel) / (sum(r["ms"] for r in sel) * 1e-3) / 1e12
             gemm_by_pass[k] = {"tflops": round(tf, 1), "frac": round(tf / PEAK_BF16_TFLOPS, 4)}
 
     # HBM-bound row kernels: algorithmic bytes (read + written) per launch over its traced time
     e = 2 if cfg.dtype == "bf16" else 4
     T = cfg.tokens
 
-    def rate(sel, nbytes):
-        ms = [r["ms"] for r in recs if sel(r)]
+    def rate(sel, nbytes, of=recs):
+        ms = [r["ms"] for r in of if sel(r)]
         if not ms:
             return None
         t = float(np.median(ms))
@@ -144,7 +160,7 @@ def run_workload(P, R, synth, torch, np, name, cfg, steps, warmup, queued, want_
     elementwise = {
         "ln_fwd": rate(lambda r: r["op"] == "ln_fwd", 2 * T * h * e),                          # x in, y out
         "ln_bwd": rate(lambda r: r["op"] == "ln_bwd" and not r["trans_a"], 4 * T * h * e),      # dy, x, resid in, dx out
-        "colsum": rate(lambda r: r["op"] == "colsum", T * (5 * h + f) * e),                     # the four dY of a layer
+        "colsum": rate(lambda r: r["op"] == "colsum", T * (5 * h + f) * e, single),             # the four dY of a layer
         "copy": rate(lambda r: r["op"] == "copy", 2 * T * h * e),
     }
     att_f = [r["ms"] for r in recs if r["op"] == "attn_fwd"]
@@ -165,6 +181,8 @@ def run_workload(P, R, synth, torch, np, name, cfg, steps, warmup, queued, want_
         read-modify-write), plus the tensor its epilogue reads or writes besides (residual, GeLU
         output, GeLU input)."""
         m, n, k = r["m"], r["n"], r["k"]
+        if r["op"] == "wgrad":
+            return n * (k * 2 * m * (8 * h + 2 * f) + 8 * h * (4 * h + 2 * f))
         if r["pass_"] == "W":
             return 2 * (m * k + k * n) + 8 * m * n
         extra = 2 * m * n if (n == f or (r["pass_"] == "F" and n == h)) else 0
@@ -172,13 +190,14 @@ def run_workload(P, R, synth, torch, np, name, cfg, steps, warmup, queued, want_
 
     traffic, traffic_src = stored_traffic(name)
     roofline = {"bound": "mfma",
-                "kernel": "gemm_bf16_dma_kernel / gemm_bf16_wgrad_persistent_kernel / gemm_bf16_wgrad_pair_kernel, with "
-                          "splitk_reduce_kernel where K is split (every product of a step: 4 projections x F,B,W x layers)",
+                "kernel": "gemm_bf16_dma_kernel, with splitk_reduce_kernel where K is split, for F and B; "
+                          + ("gemm_bf16_wgrad_batch_kernel, one launch with the bias sums, for W" if single is not recs else
+                             "gemm_bf16_wgrad_persistent_kernel for W") + " (every product of a step: 4 projections x F,B,W x layers)",
                 "achieved": round(achieved, 1), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                 "traffic": traffic, "traffic_source": traffic_src,
                 "timing": "HIP events around every GEMM launch of traced steps in this run, on the stream of the launches "
-                          "(while traced, the W pass launches its products one by one on that one stream)",
+                          "(a W pass that is not one launch keeps its products on that one stream while traced)",
                 "avg_launch_us": round(1e3 * gemm_ms / len(gemms), 2), "flop_per_launch": gemm_flop / len(gemms),
                 "algorithmic_bytes_per_launch": round(sum(gemm_bytes(r) for r in gemms) / len(gemms)),
                 "launches_per_step": len(gemms) // reps, "by_pass": gemm_by_pass}
@@ -217,9 +236,9 @@ def main() -> int:
     ap.add_argument("--profile", action="store_true",
                     help="for profiler runs: the headline workload only (no other workloads, replay, queued W or cpu baseline)")
     ap.add_argument("--w-streams", type=int, default=0, choices=(0, 1, 2),
-                    help="streams of the W pass (library switch w_streams): 1 keeps every kernel on one stream, which is "
-                         "how the traced steps behind `roofline` run; a kernel trace of such a run shows un-overlapped "
-                         "kernel durations.  0: the library's default (2)")
+                    help="launch the products of the W pass one by one (library switch w_streams), on one stream or alternating "
+                         "between two; a kernel trace of a run on one stream shows un-overlapped kernel durations.  "
+                         "0: the library's default (one launch, or two streams)")
     ap.add_argument("--microbatch-study", action="store_true",
                     help="instead of the benchmark line: the single-pass table over microbatch sizes (Appendix D.2) and "
                          "V-Half at twice the microbatch size against 1F1B (Section 4.3), as one JSON object")

@@ -21,8 +21,8 @@
  *    The W pass is one launch (per eight layers) that does every weight-gradient product and bias
  *    gradient of the call, except in these cases, where its products are launched one by one: at
  *    2048 tokens and more of a bf16 layer each of whose products fills whole rounds of large tiles (hidden
- *    4096, FFN 16384); for layers bound to the same gradient memory; while a
- *    switch forces the kernel of a product; while tracing, whose records are one per operation.
+ *    4096, FFN 16384); for layers bound to the same gradient memory; while one of the switches gemm_tile,
+ *    gemm_group, gemm_wgrad and w_streams is set, to whatever value.
  *    One by one, the bf16 W pass runs every second product and the
  *    bias-gradient column sums on a second, non-blocking stream of default priority that the
  *    context owns (created at first use).  The pass forks it from the context's stream with an
@@ -30,8 +30,9 @@
  *    everything the caller enqueues on the context's stream before or after the call is ordered
  *    against all of the pass's work; nothing is ever left running on the second stream between
  *    calls.  pmc_tuning_set("w_streams", 1) keeps the whole pass on the context's stream, and so
- *    does tracing (pmc_trace_begin), whose per-operation events assume one stream: traced W times
- *    are therefore those of the one-stream configuration.
+ *    does tracing (pmc_trace_begin), whose per-operation events assume one stream: where the products are launched one
+ *    by one, traced W times are those of the one-stream configuration.  (To have the operations of a
+ *    W pass that is one launch timed one by one, set w_streams while tracing.)
  *  - Tensors are row-major.  Activations are [tokens, hidden] with tokens = microbatch * seq
  *    (sequences of one microbatch stored back to back).  Storage type is float (PMC_F32) or
  *    bfloat16 (PMC_BF16; all accumulation in fp32).  Gradients of parameters are always fp32.
@@ -284,13 +285,15 @@ int schedule_replay(pmc_ctx* ctx, const pmc_schedule* s, pmc_chunk* const* chunk
 
 typedef enum pmc_trace_op {
   PMC_OP_GEMM = 0, PMC_OP_LN_FWD = 1, PMC_OP_LN_BWD = 2, PMC_OP_ATTN_FWD = 3, PMC_OP_ATTN_BWD = 4,
-  PMC_OP_COLSUM = 5, PMC_OP_COPY = 6
+  PMC_OP_COLSUM = 5, PMC_OP_COPY = 6,
+  PMC_OP_WGRAD = 7 /* a W pass in one launch: every weight-gradient product and bias gradient of up to eight layers */
 } pmc_trace_op;
 
 typedef struct pmc_trace_rec {
   int32_t op;        /* pmc_trace_op                                                          */
   int32_t pass;      /* pmc_op of the pass that launched it                                    */
-  int32_t m, n, k;   /* GEMM: problem size; attention: tokens, heads, head size; else rows, cols, 0 */
+  int32_t m, n, k;   /* GEMM: problem size; attention: tokens, heads, head size; WGRAD: tokens of a
+                        microbatch, layers, microbatches; else rows, cols, 0                    */
   int32_t variant;   /* GEMM: trans_a | trans_b << 1 | epilogue << 2; else 0                   */
   float ms;          /* elapsed time between HIP events recorded around the operation          */
 } pmc_trace_rec;

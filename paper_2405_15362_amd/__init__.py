@@ -365,7 +365,7 @@ def schedule_replay(ctx, s, chunks, x, dy_last, y_last=None, dx_first=None, flag
 
 # ---- tracing ---------------------------------------------------------------------------------
 
-TRACE_OPS = ("gemm", "ln_fwd", "ln_bwd", "attn_fwd", "attn_bwd", "colsum", "copy")
+TRACE_OPS = ("gemm", "ln_fwd", "ln_bwd", "attn_fwd", "attn_bwd", "colsum", "copy", "wgrad")
 
 
 def pmc_trace_begin(ctx, capacity: int = 4096) -> None:

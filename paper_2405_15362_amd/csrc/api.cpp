@@ -421,7 +421,7 @@ int chunk_backward_input(pmc_chunk* ch, int32_t mb, const void* dy, void* dx) {
 // tail of one fills with the head of the next, and the memory-bound bias-gradient sums run under a
 // product (measured on the W pass: -5 % at hidden 2048 / 1024 tokens, -6 % at 4096 / 2048, -5 % at
 // 5120 / 4096; a third and fourth stream gain nothing more).  The w_streams tuning switch forces the choice.
-// Off while tracing, whose per-operation events assume one stream.
+// One stream while tracing, whose per-operation events assume it.
 int w_pass_streams(const pmc_chunk* ch) {
   if (ch->ctx->tracing || ch->cfg.dtype != PMC_BF16) return 1;
   if (const int f = tuning(kTuneWStreams); f >= 0) return f;
@@ -472,10 +472,8 @@ k::WgradBatchArgs wgrad_batch_args(const pmc_chunk_cfg& c, char* const* slab, in
 // be done product by product (rc is then untouched); nothing has been launched.
 bool weights_in_one_launch(pmc_chunk* ch, char* const* slab, int count, int* rc) {
   if (!ch->grads_apart) return false;  // products into one gradient have to follow one another
-  if (ch->ctx->tracing) return false;  // its records are one per product
   const int L = ch->cfg.layers, per = k::WgradBatchArgs::kMaxLayers;
-  std::vector<std::pair<k::WgradBatchArgs, int>> launches;
-  for (int top = L - 1; top >= 0; top -= per) {
+  auto args_from = [&](int top) {  // of the layers top, top - 1, ...
     k::WgradBatchArgs a = wgrad_batch_args(ch->cfg, slab, count);
     for (int l = top; l >= 0 && l > top - per; --l) {
       const LayerOffsets& o = ch->off[l];
@@ -489,14 +487,20 @@ bool weights_in_one_launch(pmc_chunk* ch, char* const* slab, int count, int* rc)
         to.bias[j] = G(ch, l, bias[j]);
       }
     }
-    const int shape = k::wgrad_batch_shape(ch->cfg.dtype, a);
-    if (shape < 0) return false;
-    launches.emplace_back(a, shape);
+    return a;
+  };
+  k::WgradBatchArgs a = args_from(L - 1);
+  int shape = k::wgrad_batch_shape(ch->cfg.dtype, a);
+  if (shape < 0) return false;
+  for (int top = L - 1 - per; top >= 0; top -= per)
+    if (k::wgrad_batch_shape(ch->cfg.dtype, args_from(top)) < 0) return false;
+  for (int top = L - 1;;) {
+    *rc = traced(ch->ctx, PMC_OP_WGRAD, PMC_W, a.K, a.layers, a.pieces, 0, [&] { return k::wgrad_batch(ch->ctx->stream, ch->cfg.dtype, a, shape); });
+    top -= per;
+    if (top < 0 || *rc != PMC_OK) return true;
+    a = args_from(top);
+    shape = k::wgrad_batch_shape(ch->cfg.dtype, a);
   }
-  *rc = PMC_OK;
-  for (auto& l : launches)
-    if (*rc == PMC_OK) *rc = k::wgrad_batch(ch->ctx->stream, ch->cfg.dtype, l.first, l.second);
-  return true;
 }
 
 int chunk_backward_weight_one(pmc_chunk* ch, int32_t mb, bool release) {

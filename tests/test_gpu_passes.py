@@ -23,7 +23,7 @@ CASES = {
     # head size 112 (the paper's hidden 7168 over 64 heads): attention tiles 128 wide, 16 columns held at zero
     "dh112_bf16": synth.ChunkCfg(layers=2, hidden=336, heads=3, ffn=512, seq=136, dtype="bf16"),
     # the workload bench.py times, at full size and in the launch configuration it runs in (large GEMM
-    # tiles, 64x128 tiles, split K, short-sequence attention shapes, W pass on two streams): every
+    # tiles, 64x128 tiles, split K, short-sequence attention shapes, W pass in one launch): every
     # output and gradient element against the oracle (a few seconds of fp64 numpy)
     "c2_full_bf16": synth.CONFIGS["C2"],
     # one layer of the hidden-4096, 2048-token shape: the many-block attention shapes and GEMMs that are
@@ -470,8 +470,9 @@ def test_replay_config5_full_size():
 W_NAMES = [k for k in R.PARAM_NAMES if not k.startswith("ln")]  # what W adds into
 
 
-def _w_pass(cfg, pieces, same_gradients=False):
-    """F and B of `pieces` microbatches, then one W call into gradients that start at 0.25; every gradient."""
+def _w_pass(cfg, pieces, same_gradients=False, trace=None):
+    """F and B of `pieces` microbatches, then one W call into gradients that start at 0.25; every gradient.  trace: a list for the records
+    of the W call."""
     params = synth.chunk_params(cfg, "one_launch")
     ctx = R.Context(R.cfg_from_synth(cfg), slabs=pieces)
     ch = ctx.add_chunk(params, cfg.dtype)
@@ -488,7 +489,11 @@ def _w_pass(cfg, pieces, same_gradients=False):
         P.stage_forward(ch.handle, j, x, y)
         P.stage_backward_input(ch.handle, j, dy, dx)
         keep += [x, dy, y, dx]
+    if trace is not None:
+        P.pmc_trace_begin(ctx.ctx)
     P.stage_backward_weight(ch.handle, list(range(pieces)))
+    if trace is not None:
+        trace += P.pmc_trace_end(ctx.ctx)
     torch.cuda.synchronize()
     got = [{k: host(v) for k, v in g.items()} for g in ch.grads]
     ctx.close()
@@ -522,6 +527,23 @@ def test_w_pass_in_one_launch_against_products_one_by_one(case):
     for l in range(layers):
         for k in R.PARAM_NAMES:
             assert np.isfinite(got[l][k]).all() and rel_l2(got[l][k], want[l][k]) <= 1e-5, (l, k)
+
+
+@pytest.mark.parametrize("dtype,layers,queued", [("bf16", 2, 1), ("bf16", 9, 3), ("f32", 2, 2)])
+def test_a_traced_w_pass_is_the_untraced_one(dtype, layers, queued):
+    """Tracing keeps the one launch: one record per eight layers (and per microbatch in fp32), and the same bits."""
+    cfg = synth.ChunkCfg(layers=layers, hidden=192, heads=3, ffn=328, seq=104, dtype=dtype)
+    assert U.wgrad_shape(cfg, queued if dtype == "bf16" else 1) >= 0
+    recs = []
+    plain, traced = _w_pass(cfg, queued), _w_pass(cfg, queued, trace=recs)
+    for l in range(layers):
+        for k in R.PARAM_NAMES:
+            assert np.array_equal(plain[l][k], traced[l][k]), (l, k)
+    w = [r for r in recs if r["pass_"] == "W"]
+    per_call = [min(8, layers - i) for i in range(0, layers, 8)]
+    assert [(r["op"], r["m"], r["n"], r["k"]) for r in w] == [("wgrad", 104, n, queued if dtype == "bf16" else 1) for n in per_call] * (
+        1 if dtype == "bf16" else queued)
+    assert all(r["ms"] > 0 for r in w)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
