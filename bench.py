@@ -159,9 +159,10 @@ def run_workload(P, R, synth, torch, np, name, cfg, steps, warmup, queued, want_
 
     elementwise = {
         "ln_fwd": rate(lambda r: r["op"] == "ln_fwd", 2 * T * h * e),                          # x in, y out
-        "ln_bwd": rate(lambda r: r["op"] == "ln_bwd" and not r["trans_a"], 4 * T * h * e),      # dy, x, resid in, dx out
+        # dy, x, resid in, dx out; without the calls in whose launch a copy of q|k|v rides along
+        "ln_bwd": rate(lambda r: r["op"] == "ln_bwd" and not r["trans_a"] and not r["k"], 4 * T * h * e),
         "colsum": rate(lambda r: r["op"] == "colsum", T * (5 * h + f) * e, single),             # the four dY of a layer
-        "copy": rate(lambda r: r["op"] == "copy", 2 * T * h * e),
+        "copy": rate(lambda r: r["op"] == "copy" and r["n"] == h, 2 * T * h * e),               # dY, where it does not ride along
     }
     att_f = [r["ms"] for r in recs if r["op"] == "attn_fwd"]
     att_b = [r["ms"] for r in recs if r["op"] == "attn_bwd"]

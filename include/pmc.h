@@ -293,8 +293,11 @@ typedef struct pmc_trace_rec {
   int32_t op;        /* pmc_trace_op                                                          */
   int32_t pass;      /* pmc_op of the pass that launched it                                    */
   int32_t m, n, k;   /* GEMM: problem size; attention: tokens, heads, head size; WGRAD: tokens of a
-                        microbatch, layers, microbatches; else rows, cols, 0                    */
-  int32_t variant;   /* GEMM: trans_a | trans_b << 1 | epilogue << 2; else 0                   */
+                        microbatch, layers, microbatches; LN_BWD: rows, cols, columns of a copy of
+                        `tokens` rows that rides along (0: none; larger than 16 MB it is a COPY of its
+                        own); else rows, cols, 0                                                 */
+  int32_t variant;   /* GEMM: trans_a | trans_b << 1 | epilogue << 2; LN_BWD: 1 for the sums over
+                        the workgroups of m calls; else 0                                       */
   float ms;          /* elapsed time between HIP events recorded around the operation          */
 } pmc_trace_rec;
 

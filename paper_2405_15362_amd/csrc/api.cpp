@@ -371,9 +371,16 @@ int chunk_backward_input(pmc_chunk* ch, int32_t mb, const void* dy, void* dx) {
   // one launch adds them all up (when the regions run out, and at the end of the pass)
   k::LnPartialJobs ln_jobs;
   auto next_partial = [&]() { return (float*)(ws + ch->wsl.partial + (size_t)ln_jobs.count * ch->wsl.partial_stride); };
+  // a copy beside LayerNorm's work: in its launch where it rides along, here otherwise (copy is then emptied)
+  auto copy_apart = [&](k::RowCopy& copy) {
+    if (!copy.cols || k::copy_rides_along(c.dtype, T, copy.cols)) return (int)PMC_OK;
+    const int cols = copy.cols;
+    copy.cols = 0;
+    return traced(ch->ctx, PMC_OP_COPY, PMC_B, T, cols, 0, 0, [&] { return k::copy_rows(st, c.dtype, T, cols, copy.src, copy.ld_src, copy.dst, copy.ld_dst); });
+  };
   auto flush_ln = [&](bool force, k::RowCopy copy = {}) {
     if (ln_jobs.count == 0 || (!force && ln_jobs.count < k::LnPartialJobs::kMax)) return (int)PMC_OK;
-    const int rc = traced(ch->ctx, PMC_OP_LN_BWD, PMC_B, ln_jobs.count, 2 * h, 0, 1, [&] { return k::layernorm_backward_reduce(st, h, ln_jobs, c.dtype, T, copy); });
+    const int rc = traced(ch->ctx, PMC_OP_LN_BWD, PMC_B, ln_jobs.count, 2 * h, copy.cols, 1, [&] { return k::layernorm_backward_reduce(st, h, ln_jobs, c.dtype, T, copy); });
     ln_jobs.count = 0;
     return rc;
   };
@@ -387,8 +394,10 @@ int chunk_backward_input(pmc_chunk* ch, int32_t mb, const void* dy, void* dx) {
     // dC = dU . W1^T
     PMC_TRY(t_gemm(ch->ctx, PMC_B, gemm_args(ch, false, true, T, h, f, s + o.u, f, P(ch, l, W_1), f, t_h, h, PMC_EPI_NONE), ch->wsl));
     // dX_mid = dY + LN2 input-gradient(dC), written over X_mid; LN2 gain/bias gradients
-    PMC_TRY(traced(ch->ctx, PMC_OP_LN_BWD, PMC_B, T, h, 0, 0, [&] { return k::layernorm_backward(st, c.dtype, T, h, t_h, s + o.xmid, P(ch, l, LN2_G), (const float*)(s + o.mean2),
-                                  (const float*)(s + o.rstd2), dyl, s + o.xmid, G(ch, l, LN2_G), G(ch, l, LN2_B), next_partial(), &ln_jobs, keep); }));
+    k::RowCopy riding = keep;
+    PMC_TRY(copy_apart(riding));
+    PMC_TRY(traced(ch->ctx, PMC_OP_LN_BWD, PMC_B, T, h, riding.cols, 0, [&] { return k::layernorm_backward(st, c.dtype, T, h, t_h, s + o.xmid, P(ch, l, LN2_G), (const float*)(s + o.mean2),
+                                  (const float*)(s + o.rstd2), dyl, s + o.xmid, G(ch, l, LN2_G), G(ch, l, LN2_B), next_partial(), &ln_jobs, riding); }));
     PMC_TRY(flush_ln(false));
     // dO = dX_mid . Wo^T
     PMC_TRY(t_gemm(ch->ctx, PMC_B, gemm_args(ch, false, true, T, h, h, s + o.xmid, h, P(ch, l, W_O), h, t_h, h, PMC_EPI_NONE), ch->wsl));
@@ -409,6 +418,7 @@ int chunk_backward_input(pmc_chunk* ch, int32_t mb, const void* dy, void* dx) {
   keep_dy.src = dy;
   keep_dy.dst = s + ch->off[0].x;
   keep_dy.ld_src = keep_dy.ld_dst = keep_dy.cols = h;
+  PMC_TRY(copy_apart(keep_dy));
   PMC_TRY(flush_ln(true, keep_dy));
   m.state = kBackwardDone;
   ch->ctx->pool.shrink(m.device, (int64_t)ch->stats_bytes);

@@ -122,6 +122,7 @@ struct RowCopy {
   void* dst = nullptr;
   int ld_dst = 0, cols = 0;
 };
+bool copy_rides_along(int dtype, int rows, int cols);  // else it is better off as a launch of its own (copy_rows)
 int layernorm_backward(hipStream_t stream, int dtype, int rows, int h, const void* dy, const void* x,
                        const void* gain, const float* mean, const float* rstd, const void* resid, void* dx,
                        float* dgain, float* dbias, float* partial, LnPartialJobs* defer = nullptr, RowCopy copy = {});

@@ -113,9 +113,6 @@ int copy_blocks(const RowCopy& copy, int rows, int threads) {
   const int down = std::max(1, threads / (copy.cols / Vec<T>::N));
   return std::min((rows + down - 1) / down, 1024);
 }
-// Larger copies stay launches of their own: their workgroups would wait for those that they share the launch with, and move their
-// bytes no faster.  12.6 MB (q|k|v of 1024 tokens of hidden 2048) by themselves 6.1 us, riding along 1.8 (a step of two layers 1140 -> 1132).
-bool rides_along(const RowCopy& copy, int rows, int elem) { return copy.cols && (size_t)rows * copy.cols * elem <= 16u << 20; }
 
 // dx = resid + rstd * (g - mean(g) - xhat * mean(g * xhat)),  g = dy * gain,  xhat = (x - mean) * rstd.
 // A workgroup is 8 waves; WR of them share a row (wave w takes the column slice w % WR, NC chunks
@@ -432,6 +429,10 @@ size_t layernorm_backward_scratch_floats(int rows, int h) {
   return (size_t)ln_bwd_blocks(rows, 1) * 2 * h;
 }
 
+// Larger copies are launches of their own: their workgroups would wait for those that they share the launch with, and move their
+// bytes no faster.  12.6 MB (q|k|v of 1024 tokens of hidden 2048) by themselves 6.1 us, riding along 1.8 (a step of two layers 1140 -> 1132).
+bool copy_rides_along(int dtype, int rows, int cols) { return (size_t)rows * cols * (dtype == PMC_F32 ? 4 : 2) <= 16u << 20; }
+
 int check_copy(int dtype, const RowCopy& copy) {
   const int vec = dtype == PMC_F32 ? 4 : 8;
   if (copy.cols && (copy.cols < 0 || !copy.src || !copy.dst || !aligned16(copy.src) || !aligned16(copy.dst) || copy.cols % vec || copy.ld_src % vec ||
@@ -444,10 +445,6 @@ int check_copy(int dtype, const RowCopy& copy) {
 int layernorm_backward_reduce(hipStream_t st, int h, const LnPartialJobs& jobs, int dtype, int rows, RowCopy copy) {
   if (jobs.count < 1 || jobs.count > LnPartialJobs::kMax) return fail(PMC_ERR_INVALID, "layernorm_backward_reduce: %d jobs", jobs.count);
   const bool f32 = dtype == PMC_F32;
-  if (copy.cols && !rides_along(copy, rows, f32 ? 4 : 2)) {
-    if (int rc = copy_rows(st, dtype, rows, copy.cols, copy.src, copy.ld_src, copy.dst, copy.ld_dst)) return rc;
-    copy.cols = 0;
-  }
   if (int rc = check_copy(dtype, copy)) return rc;
   const int copying = f32 ? copy_blocks<float>(copy, rows, kSumWaves * 64) : copy_blocks<bf16_t>(copy, rows, kSumWaves * 64);
   sum_partials_kernel<<<dim3((2 * h + 63) / 64 * jobs.count + copying), dim3(kSumWaves * 64), 0, st>>>(jobs, 2 * h, h, (size_t)2 * h, rows, f32, copy);
@@ -465,10 +462,6 @@ int layernorm_backward(hipStream_t st, int dtype, int rows, int h, const void* d
     return fail(PMC_ERR_INVALID, "layernorm_backward: NULL pointer");
   if (!aligned16(dy) || !aligned16(x) || !aligned16(gain) || !aligned16(dx) || (resid && !aligned16(resid)))
     return fail(PMC_ERR_INVALID, "layernorm_backward: pointers must be 16-byte aligned");
-  if (copy.cols && !rides_along(copy, rows, dtype == PMC_F32 ? 4 : 2)) {
-    if (int rc = copy_rows(st, dtype, rows, copy.cols, copy.src, copy.ld_src, copy.dst, copy.ld_dst)) return rc;
-    copy.cols = 0;
-  }
   if (int rc = check_copy(dtype, copy)) return rc;
   if (dtype == PMC_F32) return ln_bwd_t<float>(st, rows, h, dy, x, gain, mean, rstd, resid, dx, dgain, dbias, partial, defer, copy);
   if (dtype == PMC_BF16) return ln_bwd_t<bf16_t>(st, rows, h, dy, x, gain, mean, rstd, resid, dx, dgain, dbias, partial, defer, copy);

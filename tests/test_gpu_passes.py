@@ -529,6 +529,43 @@ def test_w_pass_in_one_launch_against_products_one_by_one(case):
             assert np.isfinite(got[l][k]).all() and rel_l2(got[l][k], want[l][k]) <= 1e-5, (l, k)
 
 
+# two layers; rows that ride along with LayerNorm's backward and its sums, q|k|v and dY in turn (columns, 0: a copy of its own or none)
+COPIES = [("bf16", 256, 2, 256, 2, 768, 256),      # small: both
+          ("bf16", 2048, 16, 256, 8, 0, 2048),     # 25 MB of q|k|v, 8.4 MB of dY
+          ("bf16", 1152, 9, 1024, 8, 0, 0),        # two launches in attention's backward: nothing to keep; 19 MB of dY
+          ("f32", 256, 4, 120, 1, 768, 256)]
+
+
+@pytest.mark.parametrize("dtype,h,heads,seq,mb,kept,dy_cols", COPIES)
+def test_copies_beside_layernorm_have_records(dtype, h, heads, seq, mb, kept, dy_cols):
+    """A copy that is a launch of its own is a record of its own; gradients against the oracle either way."""
+    print("copies", dtype, h, heads, seq, mb, flush=True)
+    cfg = synth.ChunkCfg(layers=2, hidden=h, heads=heads, ffn=64, seq=seq, microbatch=mb, dtype=dtype)
+    params = synth.chunk_params(cfg, "copies")
+    x, dy = synth.chunk_input(cfg, "copies"), synth.upstream_grad(cfg, "copies")
+    ctx = R.Context(R.cfg_from_synth(cfg), slabs=1)
+    ch = ctx.add_chunk(params, cfg.dtype)
+    xd, dyd = dev(x, dtype), dev(dy, dtype)
+    y, dx = torch.empty_like(xd), torch.empty_like(xd)
+    P.stage_forward(ch.handle, 0, xd, y)
+    P.pmc_trace_begin(ctx.ctx)
+    P.stage_backward_input(ch.handle, 0, dyd, dx)
+    recs = P.pmc_trace_end(ctx.ctx)
+    P.stage_backward_weight(ch.handle, [0])
+    torch.cuda.synchronize()
+    T, keeps = cfg.tokens, U.attention_kept_columns(dtype, mb, seq, heads, h // heads, True) > 0
+    copies = [(r["m"], r["n"]) for r in recs if r["op"] == "copy"]
+    ln = [(r["m"], r["n"], r["k"]) for r in recs if r["op"] == "ln_bwd"]
+    assert ln == [(T, h, kept), (T, h, 0)] * 2 + [(4, 2 * h, dy_cols)]
+    assert copies == [(T, 3 * h)] * (2 if keeps and not kept else 0) + [(T, h)] * (0 if dy_cols else 1)
+    _, dx_ref, ln_ref, w_ref = oracle_chunk(cfg, params, x, dy)
+    assert_close(host(dx), dx_ref, dtype, "dx")
+    for l in range(2):
+        for k, v in {**ln_ref[l], **w_ref[l]}.items():
+            assert_close(host(ch.grads[l][k]), v, dtype, f"L{l}.{k}")
+    ctx.close()
+
+
 @pytest.mark.parametrize("dtype,layers,queued", [("bf16", 2, 1), ("bf16", 9, 3), ("f32", 2, 2)])
 def test_a_traced_w_pass_is_the_untraced_one(dtype, layers, queued):
     """Tracing keeps the one launch: one record per eight layers (and per microbatch in fp32), and the same bits."""
