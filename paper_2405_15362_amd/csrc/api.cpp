@@ -179,10 +179,12 @@ WorkspaceLayout workspace_of(const pmc_chunk_cfg& c) {
   size_t at = 0;
   w.t_h = at;
   at += align256((size_t)t * c.hidden * e);
+  // with q|k|v kept for it, attention's backward is not in place
+  const int kept = k::attention_backward_kept_columns(c.dtype, c.microbatch, c.seq, c.heads, c.hidden / c.heads, c.causal);
   w.attn = at;
-  at += k::attention_backward_scratch_bytes(c.dtype, c.microbatch, c.seq, c.heads, c.hidden / c.heads);
+  at += k::attention_backward_scratch_bytes(c.dtype, c.microbatch, c.seq, c.heads, c.hidden / c.heads, kept == 0);
   w.kept = at;
-  at += align256((size_t)t * k::attention_backward_kept_columns(c.dtype, c.microbatch, c.seq, c.heads, c.hidden / c.heads, c.causal) * e);
+  at += align256((size_t)t * kept * e);
   w.partial = at;
   // one region per LayerNorm of the backward pass (their reductions are run together at its end)
   const size_t pf = k::layernorm_backward_scratch_floats(t, c.hidden);

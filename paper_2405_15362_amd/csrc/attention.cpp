@@ -30,9 +30,9 @@ int attention_forward(hipStream_t st, int dtype, int batch, int seq, int heads, 
   return attention_forward_f32(st, dtype, batch, seq, heads, head_dim, causal, qkv, o, lse);
 }
 
-size_t attention_backward_scratch_bytes(int dtype, int batch, int seq, int heads, int head_dim) {
+size_t attention_backward_scratch_bytes(int dtype, int batch, int seq, int heads, int head_dim, bool in_place) {
   const size_t tokens = (size_t)batch * seq;
-  return align256(tokens * heads * head_dim * elem(dtype)) + align256(tokens * heads * sizeof(float));
+  return align256(tokens * heads * sizeof(float)) + (in_place ? align256(tokens * heads * head_dim * elem(dtype)) : 0);
 }
 
 // Where both halves of the backward pass go out as one launch, by w = 64-row workgroups of one half.
@@ -83,8 +83,8 @@ int attention_backward(hipStream_t st, int dtype, int batch, int seq, int heads,
   const int h = heads * head_dim;
   const int vec = dtype == PMC_F32 ? 4 : 8;
   if (h % vec) return fail(PMC_ERR_INVALID, "attention_backward: hidden %d must be a multiple of %d", h, vec);
-  char* dq_stage = (char*)scratch;
-  float* delta = (float*)(dq_stage + align256(tokens * h * elem(dtype)));
+  float* delta = (float*)scratch;
+  char* dq_stage = (char*)scratch + align256(tokens * heads * sizeof(float));
   const size_t bytes = tokens * 3 * h * elem(dtype);
   if ((const char*)qkv + bytes <= (const char*)dqkv || (const char*)dqkv + bytes <= (const char*)qkv)
     return backward(st, dtype, batch, seq, heads, head_dim, causal, qkv, o, lse, d_o, dqkv, dqkv, 3 * h, delta);

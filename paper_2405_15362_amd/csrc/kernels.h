@@ -137,8 +137,9 @@ int layernorm_backward_static(hipStream_t stream, int dtype, int rows, int h, co
 
 int attention_forward(hipStream_t stream, int dtype, int batch, int seq, int heads, int head_dim, int causal,
                       const void* qkv, void* o, float* lse);
-// scratch: dq staging [batch*seq, heads*head_dim] in the storage type, then delta fp32 [batch, heads, seq].
-size_t attention_backward_scratch_bytes(int dtype, int batch, int seq, int heads, int head_dim);
+// scratch: delta fp32 [batch, heads, seq], then, where dqkv overlaps qkv (in_place), dq staging [batch*seq, heads*head_dim] in
+// the storage type.
+size_t attention_backward_scratch_bytes(int dtype, int batch, int seq, int heads, int head_dim, bool in_place = true);
 int attention_backward(hipStream_t stream, int dtype, int batch, int seq, int heads, int head_dim, int causal,
                        const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv,
                        void* scratch);

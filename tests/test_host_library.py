@@ -354,6 +354,17 @@ def test_the_w_pass_takes_a_fast_path(case):
     assert us[picked] <= 1.065 * min(us.values()), picked   # the fit's error on the passes it was made from, at worst
 
 
+@pytest.mark.parametrize("dtype,hidden,heads,seq,mb", [("bf16", 512, 8, 512, 8), ("bf16", 256, 4, 384, 12), ("f32", 512, 8, 512, 1)])
+def test_the_workspace_of_a_pass_has_no_dq_staging_beside_a_copy_of_qkv(dtype, hidden, heads, seq, mb):
+    """Attention's backward reads q|k|v from a copy in the workspace or stages dQ there, never both: with a causal mask these
+    shapes take the copy (3 hidden columns), without one the staging buffer (hidden columns)."""
+    size = 4 if dtype == "f32" else 2
+    assert U.attention_kept_columns(dtype, mb, seq, heads, hidden // heads, True) == 3 * hidden
+    assert U.attention_kept_columns(dtype, mb, seq, heads, hidden // heads, False) == 0
+    copy, staging = (P.pmc_pass_workspace_bytes(P.make_cfg(1, hidden, heads, 4 * hidden, seq, mb, dtype, causal)) for causal in (True, False))
+    assert copy - staging == 2 * hidden * seq * mb * size
+
+
 def test_the_workspace_of_a_pass_holds_the_plan_of_each_of_its_products():
     """Every product of a pass gets, with the scratch that the pass's workspace has, the plan it gets with unlimited
     scratch, whatever the sizes (token counts that are no multiple of 64, ranges of unequal length), and the scratch is
