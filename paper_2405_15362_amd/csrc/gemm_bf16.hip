@@ -997,7 +997,7 @@ int launch_tile(hipStream_t st, const GemmParams& p, int epi) {
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KMAJ, bool B_KMAJ, int NSTAGE, int EPI, bool SEG = false, int BK = 64,
           bool CUT = false, bool KSPLIT = false, int KG = 1>
 int launch_dma(hipStream_t st, GemmParams p) {
-  if constexpr ((A_KMAJ || B_KMAJ) && !CUT)
+  if constexpr ((A_KMAJ || B_KMAJ) && !CUT && KG == 1)
     if (p.K & 63) return launch_dma<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, true, KSPLIT, KG>(st, p);
   constexpr int NT = WAVES_M * WAVES_N * KG * 64;
   constexpr size_t lds = (size_t)NSTAGE * (BM + BN) * BK * sizeof(bf16_t);
@@ -1027,7 +1027,7 @@ constexpr Layout layout_of(bool a_kmaj, bool b_kmaj) { return !a_kmaj ? kLayoutW
 //   2: 128x128, 4 waves: 4 stages as long as a compute unit gets one tile at most, otherwise 2 stages, so that
 //      two workgroups fit a unit.  With one workgroup per unit nothing else covers the latency of a tile's
 //      loads: 4096 x 1024 x 4096, F / B / W layout, 2 stages 52.1 / 47.2 / 52.8 us, 4 stages 39.8 / 36.4 / 43.0.  In the F and
-//      B layouts such a workgroup has eight waves in two groups that share the K of every tile (see dma_tile)
+//      B layouts such a workgroup has eight waves in two groups that share the K of every tile where gemm_bf16_k_groups says so
 //   3: 64x128, 4 waves, 3 stages (skinny outputs; only where A is contraction-contiguous)
 //   4: 256x320, 8 waves, 2 stages (not with the fp32 read-modify-write epilogue: registers)
 //   5: 64x64, 5 stages   6: 32x64, 6 stages   7: 32x32, 8 stages; 4 waves that split K (see dma_tile)
@@ -1079,6 +1079,18 @@ int pick_tile(Layout layout, int M, int N, long K, bool wide_ok, double* us = nu
 // top it would spill registers, so weight-gradient products do not use it
 constexpr bool wide_ok(int epi) { return epi != PMC_EPI_ACCUM_F32; }
 
+}  // namespace
+
+// 128x128 tiles of the F and B layouts, one at most to a compute unit: eight waves in two K groups (see dma_tile) or four.  Time of eight
+// over that of four, over 6982 such products of layers of hidden 64 .. 8192 with 16 .. 8192 tokens, operands in the memory-side cache / from HBM
+// (geometric means of F, B): here 0.89, 0.88 / 1.00, 1.00, nowhere more than 1.02 in the mean of the two.  Where the last K tile is partial 1.01, 1.03 / 1.04, 1.09
+// (four / eight waves: 400 x 4952 x 14856 in B 157 / 179 us); whole K below 1024 1.03, 1.01 / 1.07, 1.06, as adding the groups up takes longer than what they cover; one row
+// of tiles, or operands beyond the 256 MB of that cache, 0.98, 0.98 / 1.02, 1.00 and up to 1.10, as they come at the rate of HBM either way (128 x 31744 x 7936 in F 97 / 106 us).
+bool gemm_bf16_k_groups(int M, int N, int K) {
+  return tiles_of(2, M, N) <= 256 && K % 64 == 0 && K >= 1024 && M > 128 && ((size_t)M + N) * K * sizeof(bf16_t) <= 256u << 20;
+}
+
+namespace {
 template <bool A_KMAJ, bool B_KMAJ, int EPI, bool SEG = false>
 int launch_dma_tile(hipStream_t st, const GemmParams& p, int shape) {
   switch (shape) {
@@ -1102,7 +1114,9 @@ int launch_dma_tile(hipStream_t st, const GemmParams& p, int shape) {
       else break;
     default: break;
   }
-  if (tiles_of(2, p.M, p.N) <= 256) return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 4, EPI, SEG, 64, false, false, A_KMAJ ? 2 : 1>(st, p);
+  if constexpr (A_KMAJ)
+    if (gemm_bf16_k_groups(p.M, p.N, p.K)) return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 4, EPI, SEG, 64, false, false, 2>(st, p);
+  if (tiles_of(2, p.M, p.N) <= 256) return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 4, EPI, SEG>(st, p);
   return launch_dma<128, 128, 2, 2, A_KMAJ, B_KMAJ, 2, EPI, SEG>(st, p);
 }
 

@@ -109,11 +109,13 @@ def test_gemm_f32_tiles_that_no_switch_forces(ctx, M, N, K, shape):
 
 @pytest.mark.parametrize("tb,epis", [(False, (P.EPI_BIAS_RESID, P.EPI_BIAS_GELU_GRAD)), (True, (P.EPI_NONE, P.EPI_MUL))])
 def test_gemm_bf16_128_tiles_in_two_k_groups(ctx, tune, tb, epis):
-    """128x128 tiles of at most one round: K of less than one group's half tile, of half a tile, of whole ones, ragged."""
+    """128x128 tiles of at most one round: eight waves in two K groups, with ragged output tiles; and four waves where K is of less than half a
+    tile, of half a tile, of whole ones but short, ragged, or where there is one row of tiles."""
     tune(gemm_tile=2)
-    for K in (8, 32, 40, 64, 72, 128, 200, 328):
+    for M, K in [(136, K) for K in (8, 32, 40, 64, 72, 128, 200, 328, 960, 1024, 1032, 1088, 4160)] + [(128, 1024)]:
+        assert P.lib.pmc_test_gemm_k_groups(M, 264, K) == (M > 128 and K >= 1024 and K % 64 == 0)
         for epi in epis:
-            _gemm_case(ctx, "bf16", False, tb, 136, 264, K, epi)
+            _gemm_case(ctx, "bf16", False, tb, M, 264, K, epi)
 
 
 @pytest.mark.parametrize("ta", [False, True])

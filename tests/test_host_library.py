@@ -326,6 +326,31 @@ def test_bf16_products_are_split_along_k_where_that_is_faster(layout, M, N, K, w
     assert (plan[1] > 1) == (split_us < whole_us), plan
 
 
+# layout, M, N, K; us of 128x128 tiles with four waves and with eight in two K groups, operands in the memory-side cache and from HBM
+K_GROUPS = [("F", 128, 20520, 6840, 83.5, 91.5, 99.5, 104.5), ("F", 128, 22680, 7560, 96.0, 99.3, 113.2, 113.0),
+            ("F", 128, 23016, 7672, 97.2, 108.6, 117.6, 118.8), ("F", 8192, 384, 128, 5.6, 5.6, 6.4, 6.3),
+            ("F", 3616, 568, 128, 5.4, 5.5, 6.1, 6.3), ("F", 128, 31744, 7936, 98.1, 96.6, 108.8, 106.2),
+            ("F", 120, 31744, 7936, 97.7, 96.0, 105.3, 104.8), ("F", 952, 4096, 16384, 144.9, 151.2, 119.7, 135.3),
+            ("F", 656, 4352, 17408, 138.1, 148.7, 107.7, 144.0), ("F", 560, 5376, 21504, 170.9, 184.8, 135.8, 176.9),
+            ("F", 8192, 352, 1024, 11.5, 14.2, 10.9, 14.9), ("F", 704, 4096, 1024, 11.6, 12.9, 11.1, 13.4),
+            ("F", 512, 6656, 26624, 240.7, 242.0, 244.1, 247.4), ("B", 280, 7800, 23400, 252.2, 255.7, 321.8, 323.5),
+            ("B", 296, 8168, 24504, 260.0, 262.2, 315.7, 314.1), ("B", 288, 8184, 8184, 63.0, 86.9, 77.1, 102.9),
+            ("B", 8192, 504, 128, 5.8, 5.8, 6.5, 6.5), ("B", 7504, 472, 128, 5.9, 5.9, 6.5, 6.6),
+            ("B", 72, 25600, 6400, 65.8, 68.3, 68.6, 70.3), ("B", 104, 30720, 7680, 97.1, 96.5, 99.5, 98.8),
+            ("B", 680, 5280, 21120, 173.1, 188.6, 144.9, 155.6), ("B", 1200, 2720, 10880, 86.9, 91.2, 72.9, 79.6),
+            ("B", 520, 4792, 16000, 115.1, 123.7, 91.5, 114.2), ("B", 7448, 272, 1088, 11.9, 12.6, 11.5, 12.8),
+            ("B", 3632, 1024, 1024, 12.4, 13.9, 12.1, 14.3), ("B", 488, 6144, 24576, 208.4, 208.4, 220.0, 220.6)]
+
+
+@pytest.mark.parametrize("case", K_GROUPS, ids=lambda c: "-".join(map(str, c[:4])))
+def test_two_k_groups_of_waves_where_they_are_faster(case):
+    """By the geometric mean of the time in the cache and from HBM, within 3 %."""
+    layout, M, N, K, four_cached, four_hbm, eight_cached, eight_hbm = case
+    assert U.gemm_plan("bf16", False, layout == "B", M, N, K, ws_bytes=1 << 40) == (U.PLAN_TILE + 2, 1, 0)
+    four, eight = (four_cached * four_hbm) ** 0.5, (eight_cached * eight_hbm) ** 0.5
+    assert (eight if P.lib.pmc_test_gemm_k_groups(M, N, K) else four) <= 1.03 * min(four, eight)
+
+
 @pytest.mark.parametrize("tokens", [8, 256, 512, 1000, 1024, 1032, 4096])
 def test_the_weight_gradients_of_a_layer_share_the_two_workgroup_kernel(tokens):
     """All four products of a layer run as two 256x128 workgroups per compute unit or none does (mixed, a step of hidden
