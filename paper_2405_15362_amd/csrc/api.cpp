@@ -942,6 +942,11 @@ int pmc_test_attention_kept_columns(int32_t dtype, int32_t batch, int32_t seq, i
 // For the library's own tests (not in pmc.h): whether 128x128 tiles of a product without a transposed A have two K groups.
 int pmc_test_gemm_k_groups(int32_t M, int32_t N, int32_t K) { return k::gemm_bf16_k_groups(M, N, K); }
 
+// For the library's own tests (not in pmc.h): whether the ranges of K of a split product have XCDs of their own.
+int pmc_test_gemm_split_own_xcds(int32_t trans_b, int32_t tiles_m, int32_t M, int32_t N, int32_t K, int32_t splits) {
+  return k::gemm_bf16_split_own_xcds(trans_b != 0, tiles_m, M, N, K, splits);
+}
+
 // For the library's own tests (not in pmc.h): tiles of the one launch that does the W pass of `count` microbatches
 // (-1: the products go out one by one).
 int pmc_test_wgrad_shape(const pmc_chunk_cfg* cfg, int32_t count) {

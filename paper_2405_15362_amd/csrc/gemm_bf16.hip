@@ -52,6 +52,7 @@ struct GemmParams {
   int tiles_m, tiles_n;
   int group_m;            // height, in tiles, of the column groups the tiles are walked in (see tile_of_pid)
   int splits, k_tiles_per_split;  // fast path: 64-wide K tiles of each range (all of K when not split)
+  bool own_xcds;                  // partial products: a range of K has XCDs of its own (see split_of_block)
   // Segmented contraction (weight gradients of several queued microbatches in one product): the K
   // axis is the concatenation of nseg pieces of seg_k rows each (every piece fills whole K tiles of its
   // own, the last one with zeros), piece i living at (Aseg[i], Bseg[i]) with the pitches lda, ldb.
@@ -464,19 +465,29 @@ __device__ __forceinline__ void tile_of_pid(const GemmParams& p, int pid, int& t
 // Partial product: workgroup -> (range of K, tile).  2, 4 or 8 ranges go to XCDs of their own, 4, 2 or 1 to a range, each a
 // contiguous run of tiles: an XCD then fetches a share of K only, over a block of tiles that much larger, and an operand crosses the
 // fabric 2 to 4 times less often (1024 x 2048 x 8192 in 4 ranges of 128x128 tiles: 67 MB instead of 168).  The grid is
-// 8 x tiles per XCD; false: nothing to do.  Other counts (7 ranges of a K that is not divisible) deal the ranges out one after the other.
+// 8 x tiles per XCD; false: nothing to do.  Other counts (7 ranges of a K that is not divisible) deal the ranges out one after the other, and so
+// does a single row of tiles, which shares no panel of B, with much to fetch: with B stored [K][N] from 64 MB of operands on (time with XCDs of their own over
+// that in turn, 309 products, 0.99 in the memory-side cache and 1.01 from HBM, up to 1.14: 40 x 19968 x 6656 in 4 ranges, in turn / of their own, 52 / 57 and 63 / 70 us; below
+// 0.97 and 0.99), with B stored [N][K] beyond the 256 MB of that cache (142: 1.00 and 1.01, up to 1.09: 112 x 8192 x 24576 in 8 ranges 98 / 106 us; below 0.99 and 1.01).
 __host__ __device__ inline int tiles_per_xcd(int tiles, int splits) { return (tiles * splits + 7) / 8; }
-__device__ __forceinline__ bool split_of_block(const GemmParams& p, int& split, int& tile) {
+}  // namespace
+bool gemm_bf16_split_own_xcds(bool tb, int tiles_m, int M, int N, int K, int splits) {
+  return 8 % splits == 0 && (tiles_m > 1 || ((size_t)M + N) * K * sizeof(bf16_t) < (tb ? 256u : 64u) << 20);
+}
+namespace {
+__device__ __forceinline__ bool split_of_block(const GemmParams& p, int& split, int& tile_m, int& tile_n) {
   const int ntiles = p.tiles_m * p.tiles_n, id = blockIdx.x;
-  if (8 % p.splits == 0) {
-    const int xcd = id & 7, local = id >> 3, per = tiles_per_xcd(ntiles, p.splits);
+  if (p.own_xcds) {
+    const int xcd = id & 7, local = id >> 3, per = tiles_per_xcd(ntiles, p.splits), tile = (xcd / p.splits) * per + local;
     split = xcd % p.splits;
-    tile = (xcd / p.splits) * per + local;
-    return tile < ntiles && local < per;
+    if (tile >= ntiles || local >= per) return false;
+    walk_tiles(p, tile, tile_m, tile_n);
+    return true;
   }
   split = id / ntiles;
-  tile = id - split * ntiles;
-  return split < p.splits;
+  if (split >= p.splits) return false;
+  tile_of_pid(p, id - split * ntiles, tile_m, tile_n);
+  return true;
 }
 __device__ __forceinline__ void tile_of_block(const GemmParams& p, int& tile_m, int& tile_n) {
   tile_of_pid(p, blockIdx.x, tile_m, tile_n);
@@ -786,9 +797,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KG * 64) void gemm_bf16_dma_ker
   int tile_m, tile_n;
   const int per = p.k_tiles_per_split * (64 / BK);
   if constexpr (EPI == kEpiPartial) {
-    int split, tile;
-    if (!split_of_block(p, split, tile)) return;
-    walk_tiles(p, tile, tile_m, tile_n);
+    int split;
+    if (!split_of_block(p, split, tile_m, tile_n)) return;
     GemmParams part = p;
     part.C = reinterpret_cast<float*>(p.C) + (size_t)split * p.M * p.N;
     dma_tile<BM, BN, WAVES_M, WAVES_N, A_KMAJ, B_KMAJ, NSTAGE, EPI, SEG, BK, CUT, KSPLIT, KG>(part, smem, tile_m, tile_n, split * per,
@@ -1012,7 +1022,8 @@ int launch_dma(hipStream_t st, GemmParams p) {
     p.group_m = forced > 0 ? forced : (BM >= 256 ? 4 : 8);
   }
   const int tiles = p.tiles_m * p.tiles_n;
-  kern<<<dim3(EPI == kEpiPartial ? 8 * tiles_per_xcd(tiles, p.splits) : tiles), dim3(NT), lds, st>>>(p);
+  p.own_xcds = EPI == kEpiPartial && gemm_bf16_split_own_xcds(B_KMAJ, p.tiles_m, p.M, p.N, p.K, p.splits);
+  kern<<<dim3(p.own_xcds ? 8 * tiles_per_xcd(tiles, p.splits) : EPI == kEpiPartial ? tiles * p.splits : tiles), dim3(NT), lds, st>>>(p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(PMC_ERR_HIP, "gemm_bf16 launch failed: %s", hipGetErrorString(e));
   return PMC_OK;

@@ -93,6 +93,7 @@ struct GemmPlan {
 };
 GemmPlan gemm_f32_plan(const GemmArgs& a);
 GemmPlan gemm_bf16_plan(const GemmArgs& a);
+bool gemm_bf16_split_own_xcds(bool tb, int tiles_m, int M, int N, int K, int splits);  // partial products: a range of K has XCDs of its own
 bool gemm_bf16_k_groups(int M, int N, int K);  // 128x128 tiles of the F and B layouts: eight waves in two K groups (else four)
 
 int gemm(hipStream_t stream, const GemmArgs& a);

@@ -247,6 +247,16 @@ def test_gemm_bf16_split_k_ranges_on_xcds_of_their_own(ctx, ta, tb, M, N, K, ran
     _gemm_case(ctx, "bf16", ta, tb, M, N, K, epi)
 
 
+@pytest.mark.parametrize("tb,M,N,K,shape,ranges", [(False, 40, 4104, 8200, 5, 2), (False, 56, 1032, 32840, 5, 8), (False, 40, 3080, 11000, 5, 4),
+                                                    (False, 104, 4104, 8200, 2, 8), (True, 104, 6152, 22536, 2, 8)])
+def test_gemm_bf16_split_k_of_one_row_of_tiles_dealt_in_turn(ctx, tb, M, N, K, shape, ranges):
+    """One row of tiles and operands of 64 MB and more, 256 MB with B stored [N][K]; also numbers of tiles that do not divide over the XCDs, ranges of unequal length."""
+    epi = P.EPI_MUL if tb else P.EPI_BIAS_RESID
+    assert U.gemm_plan("bf16", False, tb, M, N, K, epi, ws_bytes=256 << 20)[:2] == (U.PLAN_SPLIT + shape, ranges)
+    assert not P.lib.pmc_test_gemm_split_own_xcds(tb, 1, M, N, K, ranges)
+    _gemm_case(ctx, "bf16", False, tb, M, N, K, epi)
+
+
 def test_gemm_bf16_weight_gradient_persistent(ctx, tune):
     """The persistent W-pass kernel (fp32 C += A^T B; one workgroup per compute unit walks its
     256x256 tiles, its first tile cut in two along K to put the workgroups out of phase): fewer tiles

@@ -351,6 +351,29 @@ def test_two_k_groups_of_waves_where_they_are_faster(case):
     assert (eight if P.lib.pmc_test_gemm_k_groups(M, N, K) else four) <= 1.03 * min(four, eight)
 
 
+# layout, M, N, K; us of a split product whose ranges of K are dealt out in turn and with XCDs of their own, operands in the memory-side cache and from HBM
+SPLIT_DEALS = [("F", 48, 21504, 7168, 69.6, 73.1, 75.5, 83.7), ("F", 40, 19968, 6656, 51.8, 62.9, 57.1, 70.2),
+               ("F", 16, 2000, 8000, 13.0, 14.3, 10.9, 14.0), ("F", 80, 3840, 15360, 31.7, 41.3, 27.3, 40.6),
+               ("F", 88, 3328, 13312, 28.0, 35.9, 23.8, 35.8), ("B", 16, 5520, 16560, 39.5, 52.1, 38.4, 46.9),
+               ("B", 48, 5504, 16512, 45.5, 54.5, 42.9, 51.8), ("B", 40, 2048, 8192, 13.0, 13.7, 11.1, 14.1),
+               ("B", 96, 2032, 8128, 16.5, 17.8, 14.1, 17.1), ("B", 144, 4864, 19456, 65.3, 79.2, 57.3, 77.6),
+               ("F", 96, 4320, 18744, 43.2, 60.5, 47.7, 62.6), ("F", 104, 4408, 13032, 35.6, 48.0, 38.4, 50.8),
+               ("F", 512, 4048, 16192, 79.2, 95.2, 72.7, 78.7), ("F", 512, 4096, 16384, 77.6, 92.9, 72.5, 75.5),
+               ("B", 112, 8192, 24576, 97.4, 98.0, 106.4, 106.0), ("B", 96, 8192, 24576, 94.0, 93.7, 100.6, 101.0),
+               ("B", 512, 3456, 13824, 61.6, 78.8, 56.6, 63.8), ("B", 448, 4008, 12024, 71.3, 84.1, 61.9, 72.3)]
+
+
+@pytest.mark.parametrize("case", SPLIT_DEALS, ids=lambda c: "-".join(map(str, c[:4])))
+def test_ranges_of_k_have_xcds_of_their_own_where_that_is_faster(case):
+    """By the geometric mean of the time in the cache and from HBM, within 3 %."""
+    layout, M, N, K, turn_cached, turn_hbm, own_cached, own_hbm = case
+    kernel, ranges, _ = U.gemm_plan("bf16", False, layout == "B", M, N, K, ws_bytes=1 << 40)
+    assert ranges > 1
+    rows = -(-M // (64 if kernel == U.PLAN_SPLIT + 5 else 128))
+    turn, own = (turn_cached * turn_hbm) ** 0.5, (own_cached * own_hbm) ** 0.5
+    assert (own if P.lib.pmc_test_gemm_split_own_xcds(layout == "B", rows, M, N, K, ranges) else turn) <= 1.03 * min(turn, own)
+
+
 @pytest.mark.parametrize("tokens", [8, 256, 512, 1000, 1024, 1032, 4096])
 def test_the_weight_gradients_of_a_layer_share_the_two_workgroup_kernel(tokens):
     """All four products of a layer run as two 256x128 workgroups per compute unit or none does (mixed, a step of hidden
