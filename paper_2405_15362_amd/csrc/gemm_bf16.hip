@@ -1178,7 +1178,7 @@ int launch_wgrad_persistent(hipStream_t st, GemmParams p) {
   return PMC_OK;
 }
 
-// The two-workgroup kernel pays 1.5x the operand traffic of 256x256 tiles and a barrier every 16 matrix
+// The two-workgroup kernel, for W products launched one by one (layers that share gradients, one stream or two forced), pays 1.5x the operand traffic of 256x256 tiles and a barrier every 16 matrix
 // instructions; it wins where the K loop is short, so that a tile's ring fill and read-modify-write
 // epilogue weigh as much as its K loop (measured on whole steps: -5 % of the W pass at 1024 tokens,
 // +6 % at 2048, +26 % at 4096).  It does not win alone (2048 x 2048 at K = 1024 takes 27.4 us, 18.3 in 128x128
