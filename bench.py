@@ -356,7 +356,7 @@ def main() -> int:
 
 
 def stored_traffic(name):
-    """HBM-side bytes per product (fetch + write) from the profiler's FETCH_SIZE and WRITE_SIZE
+    """HBM-side bytes per launch of products (fetch + write; a W pass in one launch is one) from the profiler's FETCH_SIZE and WRITE_SIZE
     counters on this workload.  Counters cannot be read from inside this process: the figure comes
     from the committed summary of two profiler runs of `bench.py --profile --config <name>`, named
     in the second return value.  (None, None) if there is no summary for this workload."""
